@@ -809,9 +809,40 @@ __device__ __forceinline__ void loss_mean_block(const float *__restrict__ loss_b
   if (threadIdx.x == 0) loss[0] = part[0] / (float)B;
 }
 
-__global__ __launch_bounds__(256) void loss_mean_kernel(const float *__restrict__ loss_b, float *__restrict__ loss, int B) {
+// host (optional): pinned memory that receives the error word and the loss.
+__global__ __launch_bounds__(256) void loss_mean_kernel(const float *__restrict__ loss_b, float *__restrict__ loss, int B,
+                                                        const int *__restrict__ err, int *__restrict__ host) {
   __shared__ float part[256];
   loss_mean_block(loss_b, loss, B, part);
+  if (host && threadIdx.x == 0) {
+    host[0] = *err;
+    host[1] = __float_as_int(part[0] / (float)B);
+  }
+}
+
+// Elements [first, first + count) of a rows x cols tensor with row pitch ld, to contiguous memory that
+// the host reads (ESZ bytes per element, 4-byte stores; hi/lo words become fp32), and the error word.
+template <int ESZ, bool HL>
+__global__ __launch_bounds__(256) void pack_rows_kernel(const void *__restrict__ src, void *__restrict__ dst, long long first,
+                                                        int count, int cols, int ld, const int *__restrict__ err,
+                                                        int *__restrict__ host) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i == 0) host[0] = *err;
+  if constexpr (ESZ == 4) {
+    if (i >= count) return;
+    const long long e = first + i, r = e / cols;
+    uint32_t v = ((const uint32_t *)src)[r * ld + (e - r * cols)];
+    if (HL) v = __float_as_uint(bf16_value(v & 0xFFFFu) + bf16_value(v >> 16));
+    ((uint32_t *)dst)[i] = v;
+  } else {
+    if (4 * i >= count) return;
+    uint32_t v = 0;
+    for (int k = 0; k < 4 && 4 * i + k < count; ++k) {
+      const long long e = first + 4 * i + k, r = e / cols;
+      v |= (uint32_t)((const uint8_t *)src)[r * ld + (e - r * cols)] << (8 * k);
+    }
+    ((uint32_t *)dst)[i] = v;
+  }
 }
 
 // One workgroup beyond the last job (only launched when loss_b != NULL) takes the mean loss.

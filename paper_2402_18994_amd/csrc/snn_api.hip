@@ -34,6 +34,9 @@ namespace {
 
 inline size_t rup(size_t x, size_t m) { return (x + m - 1) / m * m; }
 
+// Read-back space of a context: word 0 the error word, word 1 the loss, then two chunks.
+constexpr size_t SNN_PIN_HEAD = 256, SNN_PIN_CHUNK = 512 << 10;
+
 struct Layer {
   int K = 0, N = 0;        // fan-in, fan-out
   int ld = 0;              // padded fan-out of the activation tensors (multiple of 8)
@@ -108,6 +111,8 @@ struct snn_ctx {
   ReduceJobs pending;             // partial sums of the last backward pass that have not been added yet
   bool reduce_pending = false;
   int opt[SNN_OPT_COUNT] = {4, 1, 1, 1, 1, 0, 128, 1024, 128, 1, 0, 0, 1, 1, 18, 0};   // snn_option values, in the enum's order
+  char *pin = nullptr;            // pinned host memory the read-back kernels write: SNN_PIN_HEAD bytes, then two chunks
+  hipEvent_t pin_ev[2] = {nullptr, nullptr};
   uint32_t *hand = nullptr;       // hand-over space of the forward launches that give a sample to two workgroups
   int hand_parts = 1;             // hand-over regions per sample (one per column block of a layer)
   int fwd_epoch = 0;              // number of such launches so far (their flags count from epoch * 1024)
@@ -612,7 +617,7 @@ int launch_reduce(snn_ctx *c, const ReduceJobs &jobs, bool with_loss) {
 
 int ensure_loss(snn_ctx *c) {
   if (c->loss_ready) return SNN_OK;
-  hipLaunchKernelGGL(loss_mean_kernel, dim3(1), dim3(256), 0, c->stream, c->loss_b, c->loss, c->B);
+  hipLaunchKernelGGL(loss_mean_kernel, dim3(1), dim3(256), 0, c->stream, c->loss_b, c->loss, c->B, nullptr, nullptr);
   HIPCHK(c, hipGetLastError());
   c->loss_ready = true;
   return SNN_OK;
@@ -1092,7 +1097,7 @@ int launch_readout_forward(snn_ctx *c, const int32_t *labels) {
   hipLaunchKernelGGL(cross_entropy_kernel, dim3((c->B + 3) / 4), dim3(256), 0, c->stream, c->z, labels, c->loss_b,
                      c->dz, c->B, c->C, c->ldC, c->err_flag);
   HIPCHK(c, hipGetLastError());
-  hipLaunchKernelGGL(loss_mean_kernel, dim3(1), dim3(256), 0, c->stream, c->loss_b, c->loss, c->B);
+  hipLaunchKernelGGL(loss_mean_kernel, dim3(1), dim3(256), 0, c->stream, c->loss_b, c->loss, c->B, nullptr, nullptr);
   HIPCHK(c, hipGetLastError());
   return SNN_OK;
 }
@@ -1168,10 +1173,9 @@ int reduce_and_update(snn_ctx *c, float lr) {
   return SNN_OK;
 }
 
-int check_err_flag(snn_ctx *c) {
-  int flag = 0;
-  HIPCHK(c, hipMemcpyAsync(&flag, c->err_flag, sizeof(int), hipMemcpyDeviceToHost, c->stream));
-  HIPCHK(c, hipStreamSynchronize(c->stream));
+// The stream has finished and the error word is in the read-back space.
+int check_err_word(snn_ctx *c) {
+  const int flag = *(volatile int *)c->pin;
   if (flag) {
     HIPCHK(c, fill_zero(c->stream, c->err_flag, 256));
     if (flag & 2) return fail(c, SNN_ERR_HIP, "a forward launch gave up waiting for another workgroup");
@@ -1183,6 +1187,47 @@ int check_err_flag(snn_ctx *c) {
 // Describes where a tensor lives: rows x cols elements, leading dimension, element size;
 // `hl`: held on the device in hi/lo form, fp32 on the host side.
 struct TensorView { void *p; size_t rows, cols, ld, esz; bool hl; };
+
+// Copies a tensor to `dst` without its padding columns and waits for it; the error word comes along.
+// Small tensors and rows with padding go through pinned memory that a kernel writes (one launch and
+// one wait; hi/lo words become fp32 on the way), chunk by chunk, the host copying one chunk out while
+// the next is written; long tensors that lie as the caller wants them are a plain copy.  (A strided
+// copy into pageable memory costs microseconds per ROW: 1.75 ms for the 256 x 20 logits of
+// 700-128-128-20, which take 0.02 ms this way.)
+int read_back(snn_ctx *c, const TensorView &v, void *dst) {
+  const size_t n = v.rows * v.cols, per = SNN_PIN_CHUNK / v.esz;       // elements: all, per chunk
+  char *out = (char *)dst;
+  if (v.ld == v.cols && !v.hl && n * v.esz > 2 * SNN_PIN_CHUNK) {
+    HIPCHK(c, hipMemcpyAsync(dst, v.p, n * v.esz, hipMemcpyDeviceToHost, c->stream));
+    HIPCHK(c, hipMemcpyAsync(c->pin, c->err_flag, sizeof(int), hipMemcpyDeviceToHost, c->stream));
+    HIPCHK(c, hipStreamSynchronize(c->stream));
+    return SNN_OK;
+  }
+  const size_t chunks = (n + per - 1) / per;
+  for (size_t i = 0; i <= chunks; ++i) {
+    if (i < chunks) {
+      const size_t cnt = std::min(per, n - i * per);
+      char *to = c->pin + SNN_PIN_HEAD + (i & 1) * SNN_PIN_CHUNK;
+      const size_t words = v.esz == 4 ? cnt : (cnt + 3) / 4;
+      const dim3 grid((unsigned)((words + 255) / 256)), block(256);
+      if (v.esz == 1)
+        hipLaunchKernelGGL((pack_rows_kernel<1, false>), grid, block, 0, c->stream, v.p, to, (long long)(i * per), (int)cnt, (int)v.cols, (int)v.ld, c->err_flag, (int *)c->pin);
+      else if (v.hl)
+        hipLaunchKernelGGL((pack_rows_kernel<4, true>), grid, block, 0, c->stream, v.p, to, (long long)(i * per), (int)cnt, (int)v.cols, (int)v.ld, c->err_flag, (int *)c->pin);
+      else
+        hipLaunchKernelGGL((pack_rows_kernel<4, false>), grid, block, 0, c->stream, v.p, to, (long long)(i * per), (int)cnt, (int)v.cols, (int)v.ld, c->err_flag, (int *)c->pin);
+      HIPCHK(c, hipGetLastError());
+      if (chunks > 1) HIPCHK(c, hipEventRecord(c->pin_ev[i & 1], c->stream));
+    }
+    if (i > 0) {
+      if (chunks > 1) HIPCHK(c, hipEventSynchronize(c->pin_ev[(i - 1) & 1]));
+      else HIPCHK(c, hipStreamSynchronize(c->stream));
+      memcpy(out + (i - 1) * per * v.esz, c->pin + SNN_PIN_HEAD + ((i - 1) & 1) * SNN_PIN_CHUNK,
+             std::min(per, n - (i - 1) * per) * v.esz);
+    }
+  }
+  return SNN_OK;
+}
 
 int view_of(snn_ctx *c, int tensor, int layer, TensorView *v, bool for_set) {
   const size_t M = (size_t)c->M;
@@ -1254,7 +1299,14 @@ int view_of(snn_ctx *c, int tensor, int layer, TensorView *v, bool for_set) {
   return SNN_OK;
 }
 
-// Host-side twin of the device's hi/lo form (used only to move tensors in and out).
+// What snn_init allocates on the host side.
+void free_host(snn_ctx *c) {
+  if (c->pin) (void)hipHostFree(c->pin);
+  for (hipEvent_t ev : c->pin_ev)
+    if (ev) (void)hipEventDestroy(ev);
+}
+
+// Host-side twin of the device's hi/lo form (used only to move tensors in).
 inline uint16_t host_bf16(float x) {
   uint32_t u;
   memcpy(&u, &x, 4);
@@ -1309,6 +1361,7 @@ int32_t snn_init(const snn_config *cfg, void *workspace_dev, size_t workspace_by
   c->stream = (hipStream_t)hip_stream;
   auto bail = [&](hipError_t e, const char *what) {
     fail(nullptr, SNN_ERR_HIP, "%s failed: %s", what, hipGetErrorString(e));
+    free_host(c);
     delete c;
     return (int32_t)SNN_ERR_HIP;
   };
@@ -1329,6 +1382,9 @@ int32_t snn_init(const snn_config *cfg, void *workspace_dev, size_t workspace_by
     void *unused = nullptr;                              // set-up of snn_weight_grad_static on this device
     if ((e = static_scratch(&unused)) != hipSuccess) return bail(e, "hipGetSymbolAddress(scratch)");
   }
+  if ((e = hipHostMalloc((void **)&c->pin, SNN_PIN_HEAD + 2 * SNN_PIN_CHUNK, hipHostMallocDefault)) != hipSuccess) return bail(e, "hipHostMalloc");
+  for (hipEvent_t &ev : c->pin_ev)
+    if ((e = hipEventCreateWithFlags(&ev, hipEventDisableTiming)) != hipSuccess) return bail(e, "hipEventCreate");
   if ((e = hipMemsetAsync(c->ws, 0, c->ws_bytes, c->stream)) != hipSuccess) return bail(e, "hipMemsetAsync(workspace)");
   std::vector<std::vector<float>> beta_host(c->L);        // alive until the synchronisation below
   for (int l = 0; l < c->L; ++l) {
@@ -1343,7 +1399,7 @@ int32_t snn_init(const snn_config *cfg, void *workspace_dev, size_t workspace_by
       return bail(e, "hipMemcpyAsync(R)");
   }
   if ((e = hipStreamSynchronize(c->stream)) != hipSuccess) return bail(e, "hipStreamSynchronize");
-  if (update_layers(c, 0, c->L, false, 0.f) != SNN_OK) { g_err = c->err; delete c; return SNN_ERR_HIP; }
+  if (update_layers(c, 0, c->L, false, 0.f) != SNN_OK) { g_err = c->err; free_host(c); delete c; return SNN_ERR_HIP; }
   if ((e = hipStreamSynchronize(c->stream)) != hipSuccess) return bail(e, "hipStreamSynchronize");
   *out = c;
   return SNN_OK;
@@ -1386,9 +1442,13 @@ static int32_t forward_layers(snn_ctx *c, const int32_t *labels_dev, float *loss
   }
   c->state = 1;
   if (loss_host) {
-    if ((rc = ensure_loss(c))) return rc;
-    HIPCHK(c, hipMemcpyAsync(loss_host, c->loss, sizeof(float), hipMemcpyDeviceToHost, c->stream));
-    if ((rc = check_err_flag(c))) return rc;
+    // the loss and the error word go straight to pinned memory: one launch, one wait
+    hipLaunchKernelGGL(loss_mean_kernel, dim3(1), dim3(256), 0, c->stream, c->loss_b, c->loss, c->B, c->err_flag, (int *)c->pin);
+    HIPCHK(c, hipGetLastError());
+    c->loss_ready = true;
+    HIPCHK(c, hipStreamSynchronize(c->stream));
+    *loss_host = ((volatile float *)c->pin)[1];
+    if ((rc = check_err_word(c))) return rc;
   }
   return SNN_OK;
 }
@@ -1505,16 +1565,8 @@ int32_t snn_get_tensor(snn_ctx *c, int32_t tensor, int32_t layer, void *dst, siz
     if ((rc = launch_input_grad(c, layer))) return rc;   // formed on the fly in snn_backward: materialise it now
     c->layers[layer - 1].ds_ready = true;
   }
-  HIPCHK(c, hipMemcpy2DAsync(dst, v.cols * v.esz, v.p, v.ld * v.esz, v.cols * v.esz, v.rows, hipMemcpyDeviceToHost,
-                             c->stream));
-  HIPCHK(c, hipStreamSynchronize(c->stream));
-  if (v.hl) {                                   // hi + lo -> fp32, in place
-    uint32_t *w = (uint32_t *)dst;
-    float *f = (float *)dst;
-    for (size_t i = 0; i < v.rows * v.cols; ++i)
-      f[i] = host_bf16_value((uint16_t)(w[i] & 0xFFFFu)) + host_bf16_value((uint16_t)(w[i] >> 16));
-  }
-  return check_err_flag(c);
+  if ((rc = read_back(c, v, dst))) return rc;
+  return check_err_word(c);
 }
 
 int32_t snn_set_tensor(snn_ctx *c, int32_t tensor, int32_t layer, const void *src, size_t bytes) {
@@ -1541,8 +1593,9 @@ int32_t snn_set_tensor(snn_ctx *c, int32_t tensor, int32_t layer, const void *sr
     }
     src = tmp.data();
   }
-  HIPCHK(c, hipMemcpy2DAsync(v.p, v.ld * v.esz, src, v.cols * v.esz, v.cols * v.esz, v.rows, hipMemcpyHostToDevice,
-                             c->stream));
+  if (v.ld == v.cols) HIPCHK(c, hipMemcpyAsync(v.p, src, v.rows * v.cols * v.esz, hipMemcpyHostToDevice, c->stream));
+  else HIPCHK(c, hipMemcpy2DAsync(v.p, v.ld * v.esz, src, v.cols * v.esz, v.cols * v.esz, v.rows, hipMemcpyHostToDevice,
+                                  c->stream));
   HIPCHK(c, hipStreamSynchronize(c->stream));
   if (tensor == SNN_T_D_LOGITS || tensor == SNN_T_ARGMAX_T) c->dj_ready = false;   // dJ must be recomputed
   if (tensor == SNN_T_CURRENT) c->layers[layer - 1].i_ready = true;     // what the caller imposed is what a reader gets
@@ -1722,6 +1775,7 @@ int32_t snn_destroy(snn_ctx *c) {
   if (!c) return SNN_OK;
   (void)hipStreamSynchronize(c->stream);
   for (hipEvent_t e : c->prof.ev) (void)hipEventDestroy(e);
+  free_host(c);
   delete c;
   return SNN_OK;
 }

@@ -875,6 +875,26 @@ def test_repeatable_bit_for_bit():
         assert np.array_equal(a, b)
 
 
+@pytest.mark.parametrize("precision", ["fp32", "bf16"])
+@pytest.mark.parametrize("T,B,N", [(1, 1, 1), (3, 5, 13), (64, 128, 16), (8, 129, 127), (64, 129, 35)],
+                         ids=["one-element", "padded", "exactly-one-chunk", "one-chunk-and-a-rest", "three-chunks"])
+def test_tensors_read_back_as_set(precision, T, B, N):
+    """snn_get_tensor returns what snn_set_tensor wrote, bit for bit: rows with and without padding
+    columns, byte tensors of a length that is no multiple of 4, words in hi/lo form (values that two
+    bfloat16 hold exactly), and lengths around the 512 KiB chunks of the read-back."""
+    from paper_2402_18994_amd.binding import SNN
+    rng = np.random.default_rng(T * 1000 + N)
+    snn = SNN(T, B, (8, N, 3), (False,), (0.9, 0.9), 1.0, "arctan", 2.0, precision,
+              [rng.standard_normal((8, N)), rng.standard_normal((N, 3))])
+    for name, layer, dtype in (("membrane", 1, np.float32), ("spikes", 1, np.uint8), ("d_current", 1, np.float32),
+                               ("readout_current", 0, np.float32), ("argmax_t", 0, np.int32)):
+        shape, _ = snn._shape(name, layer)
+        v = rng.integers(0, 2, shape) if dtype == np.uint8 else rng.integers(-30000, 30000, shape)
+        snn.set_tensor(name, layer, v.astype(dtype))
+        assert np.array_equal(snn.get_tensor(name, layer), v.astype(dtype)), name
+    snn.destroy()
+
+
 def test_error_paths():
     from paper_2402_18994_amd.binding import SnnError
     wl = workloads.CONFIGS["tiny_ff"]
