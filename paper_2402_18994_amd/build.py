@@ -1,21 +1,25 @@
 """Compile the HIP library for gfx950 in-tree (hipcc cross-compiles without a GPU)."""
+import concurrent.futures
 import os
 import subprocess
 import sys
+import tempfile
 
 HERE = os.path.dirname(os.path.abspath(__file__))
-SRC = os.path.join(HERE, "csrc", "snn_api.hip")
+CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libsnn_hip.so")
 
-FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
+FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
          # keep the compiler from forming packed fp32 VALU instructions
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-Wall", "-Wno-unused-function"]
+# translation unit -> flags of its own
+UNITS = {"snn_api.hip": [],
+         # results of MFMAs in ordinary vector registers (the time loops read them at once)
+         "rlif_tile.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
 
 
-def build(verbose: bool = False) -> str:
-    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-    cmd = [hipcc] + FLAGS + os.environ.get("SNN_EXTRA_FLAGS", "").split() + ["-o", OUT, SRC]
+def _run(cmd, verbose: bool) -> None:
     if verbose:
         print(" ".join(cmd), flush=True)
     res = subprocess.run(cmd, capture_output=True, text=True)
@@ -25,6 +29,18 @@ def build(verbose: bool = False) -> str:
         raise RuntimeError("hipcc failed:\n" + err)
     if verbose and err.strip():
         print(err, file=sys.stderr)
+
+
+def build(verbose: bool = False) -> str:
+    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+    extra = os.environ.get("SNN_EXTRA_FLAGS", "").split()
+    with tempfile.TemporaryDirectory() as tmp, concurrent.futures.ThreadPoolExecutor(4) as pool:
+        objs = {u: os.path.join(tmp, u + ".o") for u in UNITS}
+        jobs = [pool.submit(_run, [hipcc] + FLAGS + UNITS[u] + extra + ["-c", "-o", objs[u], os.path.join(CSRC, u)], verbose)
+                for u in UNITS]
+        for j in jobs:
+            j.result()
+        _run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", OUT] + list(objs.values()), verbose)
     return OUT
 
 

@@ -1,12 +1,13 @@
 // Recurrent LIF layers: V_{t+1} = beta V_t + I_t + S_t R - theta S_t, with S_t the spikes
 // just emitted from V_t (R is [from][to]).  Every step needs all N spikes of a sample from
-// the step before.  Layers of up to 128 neurons run their whole time loop in one kernel (a
-// workgroup owns a batch tile and all neurons).  Wider layers walk time on the host side of
+// the step before.  Layers of up to 256 neurons run their whole time loop in one kernel
+// (rlif_tile.hpp).  Wider layers walk time on the host side of
 // the stream: one launch per step, each a [B x N] x [N x N] MFMA product whose epilogue
 // applies the LIF update (forward) or the surrogate-gradient recursion (reverse); stream
 // order is the inter-step barrier.
 #pragma once
 #include "gemm.hpp"
+#include "rlif_tile.hpp"
 #include "scan.hpp"
 
 namespace snn {
@@ -18,419 +19,10 @@ static hipError_t fill_zero(hipStream_t st, void *p, size_t bytes) {
   return hipGetLastError();
 }
 
-// ---------------------------------------------------------------- narrow layers: one launch
-// For N <= 128 a workgroup can own a batch tile of 32 samples with ALL neurons of the layer:
-// the recurrence then never leaves the workgroup and the whole time loop runs inside one
-// kernel.  The product is taken transposed, (S_t R)^T = R^T S_t^T: the MFMA's row operand is a
-// 32-neuron slab of R^T (or of R for the reverse pass), loaded once and kept in registers for
-// all T steps; the column operand is the 32 x 128 tile of the samples' current spikes (or of
-// the planes of g), exchanged between the four wavefronts through LDS, double-buffered, one
-// barrier per step.  In the 32x32 accumulator a lane holds sample (lane & 31) and sixteen
-// neurons in four groups of four adjacent ones, so state, loads and stores are per-lane
-// 16-byte vectors and the LIF update needs no shuffles.  Wavefront w owns neurons
-// [32w, 32w+32).  Rows of I (or dS and V) are fetched PF steps ahead of their use.
-// These 32-sample kernels are followed by the ones in use by default, which tile the batch by
-// 16 samples (16x16x32 MFMAs, eight wavefronts of 16 neurons): the step is a dependent chain -
-// spikes or planes of g into LDS, barrier, fragments, products, update - and its length is the
-// number of values a lane carries: 16 here, 4 there (0.97 -> 0.43 us per forward step,
-// 1.64 -> 0.64 per reverse step at 128 neurons).
-constexpr int RL_PITCH = 272;                 // bytes per sample row of an exchange tile (128 bf16 + pad)
-
-// The sixteen-byte fragment of a weight plane [row][k] (k contiguous, pitch ldq) for MFMA step ks.
-__device__ __forceinline__ bf16x8 rl_weight_frag(rsrc_t r, int row, int ldq, int ks, int lane) {
-  const int k = 16 * ks + 8 * (lane >> 5);
-  const u32x4 v = ld_b128(r, k < ldq ? (row * ldq + k) * 2 : OOB, 0);
-  return __builtin_bit_cast(bf16x8, v);
-}
-
-// Row pitches of the LDS stage through which the 16-sample kernel below stores V_t and S_t as
-// whole rows.  (This 32-sample kernel stores straight from the accumulator layout, 32 sample rows
-// of 32 bytes per instruction, and serves rows that are no multiple of 16 neurons.)
-constexpr int RL_VP = 132;                    // floats per sample row of the V stage (128 + pad)
-constexpr int RL_SP = 144;                    // bytes per sample row of the S stage (128 + pad)
-template <int NP>   // NP weight planes: 1 (bfloat16 weights) or 3 (fp32 as hi + mid + lo)
-__global__ __launch_bounds__(256) void rlif_forward_fused_kernel(const float *__restrict__ I, float *__restrict__ V,
-                                                                 uint8_t *__restrict__ S,
-                                                                 const uint16_t *__restrict__ QRf, int ldqr,
-                                                                 long long qr_plane, int T, int B, int N, int ld,
-                                                                 const float *__restrict__ beta_v, float theta) {
-  constexpr int PF = 4;
-  __shared__ __align__(16) char xs[2][32 * RL_PITCH];
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int b = blockIdx.x * 32 + (lane & 31);
-  const int row4 = B * ld * 4;
-  const unsigned bytes = (unsigned)T * B * ld * 4u;
-  const rsrc_t rI = make_rsrc(I, bytes), rV = make_rsrc(V, bytes), rS = make_rsrc(S, bytes / 4);
-  const rsrc_t rQ = make_rsrc(QRf, (unsigned)(NP * qr_plane * 2));
-
-  bf16x8 wf[NP][8];                             // R^T[32w + (lane&31)][:], all planes, all k steps
-#pragma unroll
-  for (int p = 0; p < NP; ++p)
-#pragma unroll
-    for (int ks = 0; ks < 8; ++ks)
-      wf[p][ks] = rl_weight_frag(rQ, (int)(p * (qr_plane / ldqr)) + 32 * w + (lane & 31), ldqr, ks, lane);
-
-  int vo4[4], vo1[4], xo[4];                    // per group of four neurons
-#pragma unroll
-  for (int g = 0; g < 4; ++g) {
-    const int n = 32 * w + 8 * g + 4 * (lane >> 5);
-    const bool ok = b < B && n < ld;
-    vo4[g] = ok ? (b * ld + n) * 4 : OOB;
-    vo1[g] = ok ? b * ld + n : OOB;
-    xo[g] = (lane & 31) * RL_PITCH + n * 2;
-  }
-  float v[16], beta[16];
-#pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    v[i] = 0.f;                                  // V_0 = 0
-    const int n = 32 * w + 8 * (i >> 2) + 4 * (lane >> 5) + (i & 3);
-    beta[i] = n < ld ? beta_v[n] : 0.f;          // one decay per neuron
-  }
-  u32x4 cur[PF][4];
-#pragma unroll
-  for (int d = 0; d < PF; ++d)
-#pragma unroll
-    for (int g = 0; g < 4; ++g) cur[d][g] = ld_b128(rI, vo4[g], min(d, T - 1) * row4);
-
-  // One step.  The chain that bounds it is serial - spikes into LDS, barrier, fragment reads, the
-  // MFMAs, the state update - so everything that does not depend on the product is issued
-  // while the MFMAs run: the stores of V_t and S_t sit between the MFMAs and the update, and
-  // the eight products of a step go to two accumulators (even and odd k steps) so that only
-  // four of them depend on each other.
-  auto step = [&](u32x4 (&in)[4], int t) {
-    uint32_t sp[16];
-#pragma unroll
-    for (int i = 0; i < 16; ++i) sp[i] = v[i] > theta ? 1u : 0u;
-    char *x = xs[t & 1];
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      u32x2 sx;                                  // four spikes as bfloat16 0.0 / 1.0
-      sx[0] = (sp[4 * g] | (sp[4 * g + 1] << 16)) * 0x3F80u;
-      sx[1] = (sp[4 * g + 2] | (sp[4 * g + 3] << 16)) * 0x3F80u;
-      *(u32x2 *)(x + xo[g]) = sx;
-    }
-    f32x16 acc, acc1;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) acc[r] = acc1[r] = 0.f;
-    lds_barrier();
-    if (t + 1 < T) {                             // the last state is not used
-#pragma unroll
-      for (int ks = 0; ks < 8; ++ks) {
-        const bf16x8 sf = *(const bf16x8 *)(x + (lane & 31) * RL_PITCH + (16 * ks + 8 * (lane >> 5)) * 2);
-#pragma unroll
-        for (int p = NP - 1; p >= 0; --p) {
-          if (ks & 1) acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[p][ks], sf, acc1, 0, 0, 0);
-          else acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[p][ks], sf, acc, 0, 0, 0);
-        }
-      }
-    }
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      u32x4 vv;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) vv[i] = __float_as_uint(v[4 * g + i]);
-      st_b128(rV, vo4[g], t * row4, vv);
-      st_b32(rS, vo1[g], t * (row4 >> 2), sp[4 * g] | (sp[4 * g + 1] << 8) | (sp[4 * g + 2] << 16) | (sp[4 * g + 3] << 24));
-    }
-    // accumulator register r: neuron 32w + 8*(r/4) + 4*(lane/32) + r%4, i.e. group r/4, element r%4
-#pragma unroll
-    for (int i = 0; i < 16; ++i)
-      v[i] = beta[i] * v[i] + __uint_as_float(in[i >> 2][i & 3]) + (acc[i] + acc1[i]) - (sp[i] ? theta : 0.f);
-#pragma unroll
-    for (int g = 0; g < 4; ++g) in[g] = ld_b128(rI, vo4[g], min(t + PF, T - 1) * row4);
-  };
-  int t = 0;
-  for (; t + PF <= T; t += PF) {
-#pragma unroll
-    for (int d = 0; d < PF; ++d) step(cur[d], t + d);
-  }
-#pragma unroll
-  for (int d = 0; d < PF; ++d)
-    if (t + d < T) step(cur[d], t + d);
-}
-
-// The same forward pass on tiles of 16 samples (16x16x32 MFMAs): a lane then carries 8 neurons
-// of one sample instead of 16 - half the compares, packs, updates, loads and LDS traffic in the
-// step's dependent chain - and a batch fills twice as many compute units.  Wavefront w still
-// owns neurons [32w, 32w+32), as two row tiles of 16; in a tile's accumulator the lane holds
-// sample (lane & 15) and the four adjacent neurons 4 (lane / 16) .. +3.  Rows of a multiple of 16
-// neurons only: V_t and S_t always leave through the LDS stage (rows 2 (NWV k + w) + lane/32 of
-// the tile for V instruction k; the first two wavefronts store S, rows 8w + lane/8).
-// NTW: row tiles per wavefront.  2: four wavefronts; 1: eight wavefronts of 16 neurons each, a
-// lane then carries 4 neurons (half the dependent chain again, two wavefronts per SIMD).
-template <int NP, int NTW>
-__global__ __launch_bounds__(512 / NTW) void rlif_forward_fused16_kernel(const float *__restrict__ I, float *__restrict__ V,
-                                                                   uint8_t *__restrict__ S,
-                                                                   const uint16_t *__restrict__ QRf, int ldqr,
-                                                                   long long qr_plane, int T, int B, int N, int ld,
-                                                                   const float *__restrict__ beta_v, float theta) {
-  constexpr int PF = 8;                         // steps of I in flight (8: 108 us for the two layers of 700-128-128-20, 4: 111)
-  __shared__ __align__(16) char xs[2][16 * RL_PITCH];
-  __shared__ __align__(16) float vstage[2][16 * RL_VP];
-  __shared__ __align__(16) uint8_t sstage[2][16 * RL_SP];
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int bl = lane & 15, q = lane >> 4;       // sample of the tile, group of four neurons / of eight k
-  const int b = blockIdx.x * 16 + bl;
-  const int row4 = B * ld * 4;
-  const unsigned bytes = (unsigned)T * B * ld * 4u;
-  const rsrc_t rI = make_rsrc(I, bytes), rV = make_rsrc(V, bytes), rS = make_rsrc(S, bytes / 4);
-  const rsrc_t rQ = make_rsrc(QRf, (unsigned)(NP * qr_plane * 2));
-
-  // R^T[16 (NTW w + i) + (lane & 15)][32 ks + 8 q .. +7], all planes: resident
-  constexpr int NWV = 8 / NTW;                   // wavefronts
-  bf16x8 wf[NP][NTW][4];
-#pragma unroll
-  for (int p = 0; p < NP; ++p)
-#pragma unroll
-    for (int i = 0; i < NTW; ++i)
-#pragma unroll
-      for (int ks = 0; ks < 4; ++ks) {
-        const int row = (int)(p * (qr_plane / ldqr)) + 16 * (NTW * w + i) + bl, k = 32 * ks + 8 * q;
-        wf[p][i][ks] = __builtin_bit_cast(bf16x8, ld_b128(rQ, k < ldqr ? (row * ldqr + k) * 2 : OOB, 0));
-      }
-
-  int vo4[NTW], xo[NTW], nn[NTW];
-#pragma unroll
-  for (int i = 0; i < NTW; ++i) {
-    nn[i] = 16 * (NTW * w + i) + 4 * q;
-    vo4[i] = b < B && nn[i] < ld ? (b * ld + nn[i]) * 4 : OOB;
-    xo[i] = bl * RL_PITCH + nn[i] * 2;
-  }
-  int vro[NTW], vlo[NTW], sro, slo;
-#pragma unroll
-  for (int k = 0; k < NTW; ++k) {
-    const int r = 2 * (NWV * k + w) + (lane >> 5), c = (lane & 31) * 4, bb = blockIdx.x * 16 + r;
-    vro[k] = bb < B && c < ld ? (bb * ld + c) * 4 : OOB;
-    vlo[k] = r * RL_VP + c;
-  }
-  {
-    const int r = 8 * (w & 1) + (lane >> 3), c = (lane & 7) * 16, bb = blockIdx.x * 16 + r;
-    sro = w < 2 && bb < B && c < ld ? bb * ld + c : OOB;
-    slo = r * RL_SP + c;
-  }
-  float v[4 * NTW], beta[4 * NTW];
-#pragma unroll
-  for (int e = 0; e < 4 * NTW; ++e) {
-    v[e] = 0.f;                                  // V_0 = 0
-    const int n = nn[e >> 2] + (e & 3);
-    beta[e] = n < ld ? beta_v[n] : 0.f;
-  }
-  u32x4 cur[PF][NTW];
-#pragma unroll
-  for (int d = 0; d < PF; ++d)
-#pragma unroll
-    for (int i = 0; i < NTW; ++i) cur[d][i] = ld_b128(rI, vo4[i], min(d, T - 1) * row4);
-
-  auto step = [&](u32x4 (&in)[NTW], int t) {
-    uint32_t sp[4 * NTW];
-#pragma unroll
-    for (int e = 0; e < 4 * NTW; ++e) sp[e] = v[e] > theta ? 1u : 0u;
-    char *x = xs[t & 1];
-#pragma unroll
-    for (int i = 0; i < NTW; ++i) {
-      u32x2 sx;                                  // four spikes as bfloat16 0.0 / 1.0
-      sx[0] = (sp[4 * i] | (sp[4 * i + 1] << 16)) * 0x3F80u;
-      sx[1] = (sp[4 * i + 2] | (sp[4 * i + 3] << 16)) * 0x3F80u;
-      *(u32x2 *)(x + xo[i]) = sx;
-      f32x4 vv = {v[4 * i], v[4 * i + 1], v[4 * i + 2], v[4 * i + 3]};
-      *(f32x4 *)&vstage[t & 1][bl * RL_VP + nn[i]] = vv;
-      *(uint32_t *)&sstage[t & 1][bl * RL_SP + nn[i]] =
-          sp[4 * i] | (sp[4 * i + 1] << 8) | (sp[4 * i + 2] << 16) | (sp[4 * i + 3] << 24);
-    }
-    f32x4 acc[NTW][2];                             // [tile][even / odd k step]
-#pragma unroll
-    for (int i = 0; i < NTW; ++i)
-#pragma unroll
-      for (int o = 0; o < 2; ++o) acc[i][o] = f32x4{0.f, 0.f, 0.f, 0.f};
-    lds_barrier();
-    if (t + 1 < T) {                             // the last state is not used
-#pragma unroll
-      for (int ks = 0; ks < 4; ++ks) {
-        const bf16x8 sf = *(const bf16x8 *)(x + bl * RL_PITCH + (32 * ks + 8 * q) * 2);
-#pragma unroll
-        for (int p = NP - 1; p >= 0; --p)
-#pragma unroll
-          for (int i = 0; i < NTW; ++i)
-            acc[i][ks & 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[p][i][ks], sf, acc[i][ks & 1], 0, 0, 0);
-      }
-    }
-#pragma unroll
-    for (int k = 0; k < NTW; ++k) st_b128(rV, vro[k], t * row4, *(const u32x4 *)&vstage[t & 1][vlo[k]]);
-    st_b128(rS, sro, t * (row4 >> 2), *(const u32x4 *)&sstage[t & 1][slo]);
-#pragma unroll
-    for (int e = 0; e < 4 * NTW; ++e)
-      v[e] = beta[e] * v[e] + __uint_as_float(in[e >> 2][e & 3]) + (acc[e >> 2][0][e & 3] + acc[e >> 2][1][e & 3]) -
-             (sp[e] ? theta : 0.f);
-#pragma unroll
-    for (int i = 0; i < NTW; ++i) in[i] = ld_b128(rI, vo4[i], min(t + PF, T - 1) * row4);
-  };
-  int t = 0;
-  for (; t + PF <= T; t += PF) {
-#pragma unroll
-    for (int d = 0; d < PF; ++d) step(cur[d], t + d);
-  }
-#pragma unroll
-  for (int d = 0; d < PF; ++d)
-    if (t + d < T) step(cur[d], t + d);
-}
-
-// Reverse pass of these layers: g <- beta g + surr(V_t - theta) (dS_t - theta g + g R^T), dI_t = g
-// before the update.  g is real-valued, so it enters the product as bfloat16 planes (hi + lo
-// with bfloat16 weights, hi + mid + lo with fp32 weights); (g R^T)^T = R g^T with R[from][to]
-// as the row operand.
-// The reverse pass on tiles of 16 samples, as rlif_forward_fused16_kernel: a lane carries 8
-// neurons of one sample, wavefront w two row tiles of 16 neurons of R (NTW = 2), or 4 and one
-// on eight wavefronts (NTW = 1).
-template <int NP, int SURR, int NTW>
-__global__ __launch_bounds__(512 / NTW) void rlif_reverse_fused16_kernel(const float *__restrict__ dS,
-                                                                   const float *__restrict__ V,
-                                                                   uint32_t *__restrict__ dI,
-                                                                   const uint16_t *__restrict__ QRb, int ldqr,
-                                                                   long long qr_plane, int T, int B, int N, int ld,
-                                                                   const float *__restrict__ beta_v, float theta, float slope,
-                                                                   float *__restrict__ db_part) {
-  constexpr int PF = 3;                         // steps of dS and V in flight (3: 154 us for the two layers of 700-128-128-20, 2: 166, 4: 178)
-  constexpr int GP = NP == 1 ? 2 : 3;           // planes of g
-  constexpr bool HL = NP == 1;                  // dI is stored in hi/lo form with bfloat16 weights
-  __shared__ __align__(16) char xs[2][GP][16 * RL_PITCH];
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int bl = lane & 15, q4 = lane >> 4;
-  const int b = blockIdx.x * 16 + bl;
-  const int row4 = B * ld * 4;
-  const unsigned bytes = (unsigned)T * B * ld * 4u;
-  const rsrc_t rdS = make_rsrc(dS, bytes), rV = make_rsrc(V, bytes), rdI = make_rsrc(dI, bytes);
-  const rsrc_t rQ = make_rsrc(QRb, (unsigned)(NP * qr_plane * 2));
-
-  bf16x8 wf[NP][NTW][4];                        // R[16 (NTW w + i) + (lane & 15)][32 ks + 8 (lane / 16) .. +7]
-#pragma unroll
-  for (int p = 0; p < NP; ++p)
-#pragma unroll
-    for (int i = 0; i < NTW; ++i)
-#pragma unroll
-      for (int ks = 0; ks < 4; ++ks) {
-        const int row = (int)(p * (qr_plane / ldqr)) + 16 * (NTW * w + i) + bl, k = 32 * ks + 8 * q4;
-        wf[p][i][ks] = __builtin_bit_cast(bf16x8, ld_b128(rQ, k < ldqr ? (row * ldqr + k) * 2 : OOB, 0));
-      }
-
-  int vo4[NTW], xo[NTW], nn[NTW];
-#pragma unroll
-  for (int i = 0; i < NTW; ++i) {
-    nn[i] = 16 * (NTW * w + i) + 4 * q4;
-    vo4[i] = b < B && nn[i] < ld ? (b * ld + nn[i]) * 4 : OOB;
-    xo[i] = bl * RL_PITCH + nn[i] * 2;
-  }
-  float gv[4 * NTW], beta[4 * NTW], db[4 * NTW];
-#pragma unroll
-  for (int e = 0; e < 4 * NTW; ++e) {
-    gv[e] = 0.f;                                 // g_T = 0
-    db[e] = 0.f;                                 // sum over t of g_{t+1} V_t
-    const int n = nn[e >> 2] + (e & 3);
-    beta[e] = n < ld ? beta_v[n] : 0.f;
-  }
-  u32x4 cds[PF][NTW], cv[PF][NTW];
-#pragma unroll
-  for (int d = 0; d < PF; ++d)
-#pragma unroll
-    for (int i = 0; i < NTW; ++i) {
-      const int so = max(T - 1 - d, 0) * row4;
-      cds[d][i] = ld_b128(rdS, vo4[i], so);
-      cv[d][i] = ld_b128(rV, vo4[i], so);
-    }
-
-  auto step = [&](u32x4 (&ds)[NTW], u32x4 (&vv)[NTW], int t) {
-    char *x = (char *)xs[t & 1];
-    u32x4 o[NTW];
-#pragma unroll
-    for (int i = 0; i < NTW; ++i) {
-      uint32_t pl[GP][4];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const float gg = gv[4 * i + j];
-        if (HL) {
-          const uint32_t hl = pack_hl(gg);
-          o[i][j] = hl;
-          pl[0][j] = hl & 0xFFFFu;
-          pl[1][j] = hl >> 16;
-        } else {
-          o[i][j] = __float_as_uint(gg);
-#pragma unroll
-          for (int q = 0; q < GP; ++q) pl[q][j] = bf16_piece(gg, q);
-        }
-      }
-#pragma unroll
-      for (int q = 0; q < GP; ++q) {
-        u32x2 px;
-        px[0] = pl[q][0] | (pl[q][1] << 16);
-        px[1] = pl[q][2] | (pl[q][3] << 16);
-        *(u32x2 *)(x + q * 16 * RL_PITCH + xo[i]) = px;
-      }
-    }
-    f32x4 acc[NTW][2];                             // [tile][even / odd k step]
-#pragma unroll
-    for (int i = 0; i < NTW; ++i)
-#pragma unroll
-      for (int o2 = 0; o2 < 2; ++o2) acc[i][o2] = f32x4{0.f, 0.f, 0.f, 0.f};
-    lds_barrier();
-    if (t > 0) {                                 // the g leaving step 0 is not used
-#pragma unroll
-      for (int ks = 0; ks < 4; ++ks) {
-        bf16x8 gf[GP];
-#pragma unroll
-        for (int q = 0; q < GP; ++q)
-          gf[q] = *(const bf16x8 *)(x + q * 16 * RL_PITCH + bl * RL_PITCH + (32 * ks + 8 * q4) * 2);
-        // smallest products first
-#pragma unroll
-        for (int sum = NP + GP - 2; sum >= 0; --sum)
-#pragma unroll
-          for (int p = 0; p < NP; ++p) {
-            const int q = sum - p;
-            if (q >= 0 && q < GP && (NP == 1 || p + q < 3)) {
-#pragma unroll
-              for (int i = 0; i < NTW; ++i)
-                acc[i][ks & 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[p][i][ks], gf[q], acc[i][ks & 1], 0, 0, 0);
-            }
-          }
-      }
-    }
-#pragma unroll
-    for (int i = 0; i < NTW; ++i) st_b128(rdI, vo4[i], t * row4, o[i]);
-    float sg[4 * NTW];
-#pragma unroll
-    for (int e = 0; e < 4 * NTW; ++e) sg[e] = surr_rcp<SURR>(slope, __uint_as_float(vv[e >> 2][e & 3]) - theta);
-#pragma unroll
-    for (int e = 0; e < 4 * NTW; ++e) {
-      const float qq = __uint_as_float(ds[e >> 2][e & 3]) - theta * gv[e] + (acc[e >> 2][0][e & 3] + acc[e >> 2][1][e & 3]);
-      const float vt = __uint_as_float(vv[e >> 2][e & 3]);
-      db[e] += gv[e] * vt;
-      gv[e] = beta[e] * gv[e] + sg[e] * qq;
-    }
-#pragma unroll
-    for (int i = 0; i < NTW; ++i) {
-      const int so = max(t - PF, 0) * row4;
-      ds[i] = ld_b128(rdS, vo4[i], so);
-      vv[i] = ld_b128(rV, vo4[i], so);
-    }
-  };
-  int t = T - 1;
-  for (; t - PF + 1 >= 0; t -= PF) {
-#pragma unroll
-    for (int d = 0; d < PF; ++d) step(cds[d], cv[d], t - d);
-  }
-#pragma unroll
-  for (int d = 0; d < PF; ++d)
-    if (t - d >= 0) step(cds[d], cv[d], t - d);
-  if (db_part) {                                 // per sample; summed over the batch by the reduction launch
-#pragma unroll
-    for (int i = 0; i < NTW; ++i)
-      if (b < B && nn[i] < ld)
-        *(float4 *)(db_part + (size_t)b * ld + nn[i]) = make_float4(db[4 * i], db[4 * i + 1], db[4 * i + 2], db[4 * i + 3]);
-  }
-}
-
 // ---------------------------------------------------------------- wide layers: one launch per step
 // Wider layers do not fit a workgroup, so time is walked on the host side of the stream and
-// stream order is the inter-step barrier.  One step is the transposed product of the fused
-// kernels above, tiled 32 neurons x 32 samples per workgroup; the four wavefronts split the
+// stream order is the inter-step barrier.  One step is the transposed product (S_t R)^T = R^T S_t^T,
+// tiled 32 neurons x 32 samples per workgroup; the four wavefronts split the
 // contraction and add their accumulators through LDS, after which wavefront w applies the
 // LIF update (or the surrogate recursion) to neuron group w of the tile.  Each wavefront
 // walks its share of the contraction in 64-wide tiles of its own: rows are fetched with
@@ -713,29 +305,7 @@ __global__ __launch_bounds__(256) void rlif_step_reverse_kernel(const uint32_t *
 static hipError_t rlif_forward(hipStream_t st, bool fp32, int T, int B, int N, int ld, const float *I, float *V,
                                uint8_t *S, const uint16_t *QRf, int ldqr, long long qr_plane, const float *beta,
                                float theta) {
-  if (ld <= 128) {                              // the whole time loop in one launch
-    // Rows of a multiple of 16 neurons: tiles of 16 samples, eight wavefronts of 16 neurons, V_t
-    // and S_t stored as whole rows.  Other widths: tiles of 32 samples, stores straight from the
-    // accumulator layout.
-    if (ld % 16 == 0) {
-      const dim3 grid16((B + 15) / 16);
-      if (fp32)
-        hipLaunchKernelGGL((rlif_forward_fused16_kernel<3, 1>), grid16, dim3(512), 0, st, I, V, S, QRf, ldqr, qr_plane, T,
-                           B, N, ld, beta, theta);
-      else
-        hipLaunchKernelGGL((rlif_forward_fused16_kernel<1, 1>), grid16, dim3(512), 0, st, I, V, S, QRf, ldqr, qr_plane, T,
-                           B, N, ld, beta, theta);
-      return hipGetLastError();
-    }
-    const dim3 grid((B + 31) / 32), block(256);
-    if (fp32)
-      hipLaunchKernelGGL((rlif_forward_fused_kernel<3>), grid, block, 0, st, I, V, S, QRf, ldqr, qr_plane, T, B, N,
-                         ld, beta, theta);
-    else
-      hipLaunchKernelGGL((rlif_forward_fused_kernel<1>), grid, block, 0, st, I, V, S, QRf, ldqr, qr_plane, T, B, N,
-                         ld, beta, theta);
-    return hipGetLastError();
-  }
+  if (rlif_tile_fits(ld)) return rlif_tile_forward(st, fp32, T, B, ld, I, V, S, QRf, ldqr, qr_plane, beta, theta);
   const size_t stride = (size_t)B * ld;
   hipError_t e;
   if ((e = fill_zero(st, V, stride * 4)) != hipSuccess) return e;     // V_0 = 0
@@ -762,23 +332,7 @@ static hipError_t rlif_forward(hipStream_t st, bool fp32, int T, int B, int N, i
 static hipError_t rlif_reverse(hipStream_t st, bool fp32, int T, int B, int N, int ld, const float *dS, const float *V,
                                uint32_t *dI, float *g0, float *g1, const uint16_t *QRb, int ldqr,
                                long long qr_plane, const float *beta, float theta, int surrogate, float slope, float *db_part) {
-  if (ld <= 128) {
-    const dim3 grid((B + 15) / 16);
-#define SNN_RLR(NP, SU)                                                                                         \
-  hipLaunchKernelGGL((rlif_reverse_fused16_kernel<NP, SU, 1>), grid, dim3(512), 0, st, dS, V, dI, QRb, ldqr, qr_plane, \
-                     T, B, N, ld, beta, theta, slope, db_part)
-    if (fp32) {
-      switch (surrogate) { case 0: SNN_RLR(3, 0); break; case 1: SNN_RLR(3, 1); break;
-                           case 2: SNN_RLR(3, 2); break; case 3: SNN_RLR(3, 3); break;
-                           case 4: SNN_RLR(3, 4); break; default: SNN_RLR(3, 5); break; }
-    } else {
-      switch (surrogate) { case 0: SNN_RLR(1, 0); break; case 1: SNN_RLR(1, 1); break;
-                           case 2: SNN_RLR(1, 2); break; case 3: SNN_RLR(1, 3); break;
-                           case 4: SNN_RLR(1, 4); break; default: SNN_RLR(1, 5); break; }
-    }
-#undef SNN_RLR
-    return hipGetLastError();
-  }
+  if (rlif_tile_fits(ld)) return rlif_tile_reverse(st, fp32, T, B, ld, dS, V, dI, QRb, ldqr, qr_plane, beta, theta, surrogate, slope, db_part);
   const size_t stride = (size_t)B * ld;
   hipError_t e;
   if ((e = fill_zero(st, g0, stride * 4)) != hipSuccess) return e;                              // g_T = 0

@@ -6,6 +6,7 @@
 // previous block is being integrated.
 #pragma once
 #include "common.hpp"
+#include "surrogate.hpp"
 
 namespace snn {
 
@@ -118,26 +119,6 @@ __global__ __launch_bounds__(256) void lif_forward_kernel(const float *__restric
 // surrogate at V_t - theta_t with respect to V_t and its negative with respect to A_t, so
 // ga <- gamma ga - S_t g - surr q (S_t = [V_t > theta_t], the reset's factor) and
 // g <- beta g + surr q.
-template <int SURR> __device__ __forceinline__ float surr(float k, float x) {
-  if (SURR == 0) { float d = 1.0f + k * fabsf(x); return 1.0f / (d * d); }
-  if (SURR == 1) { float u = 1.5707963267948966f * k * x; return (0.5f * k) / (1.0f + u * u); }
-  if (SURR == 2) { float s = 1.0f / (1.0f + __expf(-k * x)); return k * s * (1.0f - s); }
-  if (SURR == 3) return fmaxf(0.0f, 1.0f - fabsf(k * x));
-  if (SURR == 4) return fabsf(k * x) <= 1.0f ? 0.5f : 0.0f;      // boxcar
-  return 1.0f;                                                   // straight-through
-}
-
-// The surrogates with the hardware reciprocal (1 ulp) instead of an IEEE division: for the
-// kernels where the surrogate's arithmetic, not memory, is what a step waits for (the one-launch
-// layer reverse: the division alone took 1.6 us per block of 64 steps; the recurrent reverse
-// kernel: sixteen divisions per lane and step).
-template <int SURR> __device__ __forceinline__ float surr_rcp(float k, float x) {
-  if (SURR == 0) { const float d = 1.0f + k * fabsf(x); return __builtin_amdgcn_rcpf(d * d); }
-  if (SURR == 1) { const float u = 1.5707963267948966f * k * x; return (0.5f * k) * __builtin_amdgcn_rcpf(1.0f + u * u); }
-  if (SURR == 2) { const float s = __builtin_amdgcn_rcpf(1.0f + __expf(-k * x)); return k * s * (1.0f - s); }
-  return surr<SURR>(k, x);
-}
-
 template <int VEC, int U, int SURR, bool HL, int POL, bool ADAPT>
 __global__ __launch_bounds__(256) void lif_reverse_kernel(const float *__restrict__ dS, const float *__restrict__ V,
                                                           uint32_t *__restrict__ dI, int T, int stride,

@@ -707,8 +707,9 @@ int launch_lif_forward(snn_ctx *c, int l) {
   if (y.recurrent) {
     Bracket br(c, SNN_K_RLIF_FORWARD, l + 1);
     // a wide layer on rounded weights whose grid fits the compute units at one workgroup each: the whole
-    // time loop in one launch (SNN_OPT_RLIF_PERSIST), else a launch per step
-    if (c->opt[SNN_OPT_RLIF_PERSIST] && y.rp_space && c->T >= 2 && rlif_persist_fits(c->B, y.ld, y.ldqr, c->cus)) {
+    // time loop in one launch (SNN_OPT_RLIF_PERSIST), else a launch per step; layers that fit a workgroup
+    // have nothing to exchange and take this path only where a test asks for its waits to fail
+    if (c->opt[SNN_OPT_RLIF_PERSIST] && (!rlif_tile_fits(y.ld) || c->opt[SNN_OPT_WAIT_FAULT]) && y.rp_space && c->T >= 2 && rlif_persist_fits(c->B, y.ld, y.ldqr, c->cus)) {
       HIPCHK(c, rlif_persist_forward(c->stream, c->T, c->B, y.ld, y.I, y.V, y.S, y.QRf, y.ldqr, y.beta_v, c->theta,
                                      y.rp_space, c->err_flag, 1 << c->opt[SNN_OPT_WAIT_LIMIT_LOG2], c->opt[SNN_OPT_WAIT_FAULT] != 0));
       return SNN_OK;

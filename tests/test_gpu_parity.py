@@ -742,6 +742,21 @@ def test_recurrent_both_sample_tilings(precision):
 
 
 @pytest.mark.parametrize("precision", ["fp32", "bf16"])
+@pytest.mark.parametrize("T,B,widths", [(9, 5, (8, 32)), (3, 4, (33, 64)), (13, 1, (65, 128)), (7, 3, (136, 192)),
+                                        (8, 6, (193, 256))], ids=lambda v: "-".join(map(str, v)) if isinstance(v, tuple) else str(v))
+def test_recurrent_layers_on_a_workgroup_of_four_samples(precision, T, B, widths):
+    """Recurrent layers of up to 256 neurons: widths at both ends of every number of contraction steps
+    the kernels are compiled for (two, four, six, eight steps of 32), the last wavefront full and nearly
+    empty, batches that leave samples of a workgroup unused, fewer steps than are in flight and a
+    remainder of them."""
+    wl = workloads.Workload(name="rec_four", index=29, T=T, B=B, sizes=(60,) + widths + (10,), recurrent=(True, True),
+                            beta=(0.9, 0.92, 0.95), theta=1.0, surrogate="arctan", slope=2.0,
+                            precision=precision, rate_lo=0.1, rate_hi=0.3, rec_gain=1.0)
+    rep = full_step_parity(wl, w_gain=1.5)
+    assert rep["spike_rate"][0] > 0
+
+
+@pytest.mark.parametrize("precision", ["fp32", "bf16"])
 def test_recurrent_small(precision):
     wl = workloads.Workload(name="rec_small", index=13, T=31, B=40, sizes=(50, 40, 24, 5), recurrent=(True, True),
                             beta=(0.9, 0.9, 0.9), theta=1.0, surrogate="superspike", slope=25.0,
