@@ -742,7 +742,7 @@ def test_recurrent_both_sample_tilings(precision):
 
 
 @pytest.mark.parametrize("precision", ["fp32", "bf16"])
-@pytest.mark.parametrize("T,B,widths", [(9, 5, (8, 32)), (3, 4, (33, 64)), (13, 1, (65, 128)), (7, 3, (136, 192)),
+@pytest.mark.parametrize("T,B,widths", [(9, 5, (8, 32)), (3, 4, (33, 64)), (13, 2, (65, 128)), (7, 3, (136, 192)),
                                         (8, 6, (193, 256))], ids=lambda v: "-".join(map(str, v)) if isinstance(v, tuple) else str(v))
 def test_recurrent_layers_on_a_workgroup_of_four_samples(precision, T, B, widths):
     """Recurrent layers of up to 256 neurons: widths at both ends of every number of contraction steps
