@@ -228,20 +228,21 @@ typedef enum {
  *                     the kernel that brings both operand tiles into LDS as they lie in memory and
  *                     reads the MFMA fragments through the transposing LDS reads; 0: the general
  *                     product kernel, which transposes in registers
- *   RLIF_PERSIST      1 (default): the forward time loop of a recurrent layer wider than 128 neurons on rounded
- *                     weights runs as ONE launch when its grid of 32 x 32 tiles fits the compute units at a
- *                     workgroup each and its padded width is a multiple of 256 up to 2048 (weights resident
- *                     in LDS, spikes exchanged as bits through memory, a counter per sample tile; a wait that
- *                     times out after about a second is reported as SNN_ERR_HIP); 0: a launch per step
+ *   RLIF_PERSIST      1 (default): the time loops of a recurrent layer of 257 to 2048 neurons on rounded
+ *                     weights run as ONE launch each, groups of workgroups exchanging spikes and gradients
+ *                     through memory (launches of this kind are ordered one behind the other on a device,
+ *                     whatever streams they are on; a wait that times out after about a second is
+ *                     reported as SNN_ERR_HIP); 0: a launch per step, the same bits
  *                     (LAYER_TIME_SPLIT = 1 and LAYER_PAIR = 2 tell one launch from the next by a count that the
  *                     host passes as a kernel argument: do not replay calls made under them from a captured
  *                     graph.  Everything else enqueues kernels only - no host read-back unless a loss pointer
  *                     is given, no allocation, fill kernels instead of memsets - and can be captured.)
- *   WAIT_LIMIT_LOG2   a workgroup of that launch polls at most 2^value times for another one's words:
+ *   WAIT_LIMIT_LOG2   a workgroup of such a launch polls at most 2^value times for another one's words:
  *                     4..20 (default 18, about a second)
  *   WAIT_FAULT        0 (default); 1: every such wait expects words that nobody writes, so it times out and
  *                     the launch ends the way it would if a workgroup were missing (the grid drains, the next
- *                     call that reads the error word returns SNN_ERR_HIP).  For tests of that path. */
+ *                     call that reads the error word returns SNN_ERR_HIP).  For tests of that path (layers of
+ *                     193 to 256 neurons take it too then). */
 typedef enum {
   SNN_OPT_LAYER_FORWARD = 0,
   SNN_OPT_LAYER_PAIR = 1,

@@ -15,6 +15,7 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
          "-Wall", "-Wno-unused-function"]
 # translation unit -> flags of its own
 UNITS = {"snn_api.hip": [],
+         "rlif_wide.hip": [],
          # results of MFMAs in ordinary vector registers (the time loops read them at once)
          "rlif_tile.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
 

@@ -20,7 +20,7 @@
 #include "scan.hpp"
 #include "layer_reverse.hpp"
 #include "rlif.hpp"
-#include "rlif_persist.hpp"
+#include "rlif_wide.hpp"
 
 using namespace snn;
 
@@ -324,8 +324,7 @@ void carve(snn_ctx &c, Carver &cv) {
       y.QRb = cv.take<uint16_t>((size_t)np * y.qr_plane);
       y.g[0] = cv.take<float>((size_t)c.B * y.ld);
       y.g[1] = cv.take<float>((size_t)c.B * y.ld);
-      if (c.precision != SNN_PREC_FP32 && rlif_persist_fits(c.B, y.ld, y.ldqr, 1 << 30))
-        y.rp_space = cv.take<char>(rlif_persist_bytes(c.B, y.ldqr));
+      if (c.precision != SNN_PREC_FP32 && rlif_wide_layer(y.ld)) y.rp_space = cv.take<char>(RlifWide::BYTES);
       y.splits_r = choose_splits(c.M, wg_tiles, wg_weights, wg_row_bytes, &y.per_r, wg_tr);
       if (y.splits_r > 1) y.part_r = cv.take<float>((size_t)y.splits_r * N * N);
     }
@@ -702,16 +701,32 @@ hipError_t lif_fwd_launch(snn_ctx *c, Layer &y) {
   return hipGetLastError();
 }
 
+// A recurrent layer on rounded weights that is too wide for one workgroup and not wider than 2048 neurons
+// runs on groups of workgroups (rlif_wide.hpp), all steps in a launch (SNN_OPT_RLIF_PERSIST = 0: one).
+// Layers that fit a workgroup have nothing to exchange and take this path only where a test asks for
+// its waits to fail.
+bool rlif_wide(const snn_ctx *c, const Layer &y) {
+  return y.rp_space && (!rlif_tile_fits(y.ld) || c->opt[SNN_OPT_WAIT_FAULT]);
+}
+RlifWideArgs rlif_wide_args(snn_ctx *c, Layer &y) {
+  RlifWideArgs a;
+  memset(&a, 0, sizeof a);
+  a.ldr = y.ldqr; a.T = c->T; a.B = c->B; a.ld = y.ld;
+  a.beta_v = y.beta_v; a.theta = c->theta; a.slope = c->slope; a.surrogate = c->surrogate;
+  a.space = (char *)y.rp_space; a.err = c->err_flag;
+  a.max_polls = 1 << c->opt[SNN_OPT_WAIT_LIMIT_LOG2];
+  a.tag_bias = c->opt[SNN_OPT_WAIT_FAULT] ? 0x40000000u : 0u;
+  return a;
+}
+
 int launch_lif_forward(snn_ctx *c, int l) {
   Layer &y = c->layers[l];
   if (y.recurrent) {
     Bracket br(c, SNN_K_RLIF_FORWARD, l + 1);
-    // a wide layer on rounded weights whose grid fits the compute units at one workgroup each: the whole
-    // time loop in one launch (SNN_OPT_RLIF_PERSIST), else a launch per step; layers that fit a workgroup
-    // have nothing to exchange and take this path only where a test asks for its waits to fail
-    if (c->opt[SNN_OPT_RLIF_PERSIST] && (!rlif_tile_fits(y.ld) || c->opt[SNN_OPT_WAIT_FAULT]) && y.rp_space && c->T >= 2 && rlif_persist_fits(c->B, y.ld, y.ldqr, c->cus)) {
-      HIPCHK(c, rlif_persist_forward(c->stream, c->T, c->B, y.ld, y.I, y.V, y.S, y.QRf, y.ldqr, y.beta_v, c->theta,
-                                     y.rp_space, c->err_flag, 1 << c->opt[SNN_OPT_WAIT_LIMIT_LOG2], c->opt[SNN_OPT_WAIT_FAULT] != 0));
+    if (rlif_wide(c, y)) {
+      RlifWideArgs a = rlif_wide_args(c, y);
+      a.X = y.I; a.V = y.V; a.S = y.S; a.R = y.QRf;
+      HIPCHK(c, rlif_wide_forward(c->stream, a, c->cus, c->opt[SNN_OPT_RLIF_PERSIST] != 0));
       return SNN_OK;
     }
     HIPCHK(c, rlif_forward(c->stream, c->precision == SNN_PREC_FP32, c->T, c->B, y.N, y.ld, y.I, y.V, y.S, y.QRf,
@@ -764,6 +779,12 @@ int launch_lif_reverse(snn_ctx *c, int l) {
   Layer &y = c->layers[l];
   if (y.recurrent) {
     Bracket br(c, SNN_K_RLIF_REVERSE, l + 1);
+    if (rlif_wide(c, y)) {
+      RlifWideArgs a = rlif_wide_args(c, y);
+      a.X = y.dS; a.V = y.V; a.dI = y.dI; a.gs = y.g[0]; a.R = y.QRb; a.db_part = y.part_b;
+      HIPCHK(c, rlif_wide_reverse(c->stream, a, c->cus, c->opt[SNN_OPT_RLIF_PERSIST] != 0));
+      return SNN_OK;
+    }
     HIPCHK(c, rlif_reverse(c->stream, c->precision == SNN_PREC_FP32, c->T, c->B, y.N, y.ld, y.dS, y.V, y.dI,
                            y.g[0], y.g[1], y.QRb, y.ldqr, y.qr_plane, y.beta_v, c->theta, c->surrogate, c->slope,
                            y.part_b));
@@ -1179,7 +1200,7 @@ int check_err_word(snn_ctx *c) {
   const int flag = *(volatile int *)c->pin;
   if (flag) {
     HIPCHK(c, fill_zero(c->stream, c->err_flag, 256));
-    if (flag & 2) return fail(c, SNN_ERR_HIP, "a forward launch gave up waiting for another workgroup");
+    if (flag & 2) return fail(c, SNN_ERR_HIP, "a launch gave up waiting for another workgroup");
     return fail(c, SNN_ERR_ARG, "a label was outside [0, C)");
   }
   return SNN_OK;

@@ -338,6 +338,63 @@ def test_wide_recurrent_forward_in_one_launch(T, B, sizes, rec):
             assert np.array_equal(a, b)
 
 
+@pytest.mark.parametrize("T,B,sizes,surrogate", [(9, 17, (40, 257, 10), "superspike"), (7, 16, (30, 512, 520, 6), "sigmoid"),
+                                                  (2, 3, (30, 300, 5), "arctan"), (1, 4, (30, 300, 5), "arctan"),
+                                                  (5, 140, (20, 1100, 5), "triangular"), (6, 20, (20, 2048, 5), "boxcar")])
+def test_wide_recurrent_loops_on_groups_of_workgroups(T, B, sizes, surrogate):
+    """Both time loops of recurrent layers of more than 256 neurons, in one launch and with a launch per
+    step, bit for bit, and the step against the oracle with the decays trained: a member with one
+    neuron, members of two widths, one and two steps, more tiles of 16 samples than groups fit at once
+    (1100 neurons: 18 members, eight groups, nine tiles), the widest layer."""
+    L = len(sizes) - 1
+    wl = workloads.Workload(name="rlif-wide", index=31, T=T, B=B, sizes=sizes, recurrent=(True,) * (L - 1),
+                            beta=(0.9, 0.93, 0.95)[:L], theta=1.0, surrogate=surrogate, slope=1.0 if surrogate in ("triangular", "boxcar") else 4.0,
+                            precision="bf16", rate_lo=0.1, rate_hi=0.3, loss="integral")
+    beta_step_parity(wl, w_gain=1.5)
+    inp = workloads.generate(wl, w_gain=1.5)
+    outs = []
+    for knob in (1, 0, 1):
+        snn = make(wl, inp, {"rlif_persist": knob})
+        snn.forward(inp.X, inp.labels)
+        snn.backward()
+        outs.append([snn.get_tensor(n, l) for l in range(1, L) for n in ("membrane", "spikes", "d_current", "grad_r")])
+        snn.destroy()
+    for o in outs[1:]:
+        for a, b in zip(o, outs[0]):
+            assert np.array_equal(a, b)
+
+
+def test_wide_recurrent_training_on_two_streams():
+    """Two networks of a wide recurrent layer, stepped on two streams without waiting in between: grids that
+    wait for their own workgroups run one behind the other, and both end where one alone does."""
+    import torch
+    wl = workloads.Workload(name="rlif-streams", index=32, T=12, B=128, sizes=(40, 2048, 5), recurrent=(True,),
+                            beta=(0.9, 0.93), theta=1.0, surrogate="arctan", slope=2.0, precision="bf16",
+                            rate_lo=0.05, rate_hi=0.2, loss="max")
+    inp = workloads.generate(wl, w_gain=1.5)
+    x, y = torch.from_numpy(inp.X).cuda(), torch.from_numpy(inp.labels.astype(np.int32)).cuda()
+    torch.cuda.synchronize()
+    nets = []
+    for _ in range(3):
+        with torch.cuda.stream(torch.cuda.Stream()):
+            nets.append(make(wl, inp))
+    for _ in range(4):
+        for snn in nets[:2]:
+            snn.forward(x, y, want_loss=False)
+            snn.backward()
+            snn.sgd_step(1e-3)
+    for _ in range(4):
+        nets[2].forward(x, y, want_loss=False)
+        nets[2].backward()
+        nets[2].sgd_step(1e-3)
+    got = [[snn.get_tensor("weight", 1), snn.get_tensor("rweight", 1)] for snn in nets]
+    for snn in nets:
+        snn.destroy()
+    for g in got[:2]:
+        for a, b in zip(g, got[2]):
+            assert np.array_equal(a, b)
+
+
 def test_wide_recurrent_forward_wait_times_out():
     """The bounded wait of the one-launch recurrent loop, forced from the host: with
     SNN_OPT_WAIT_FAULT every wait expects words that nobody writes, so each workgroup gives up after
