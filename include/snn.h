@@ -224,10 +224,9 @@ typedef enum {
  *                     while this one is scanned; the state is handed over through memory).  Measured
  *                     no faster at 700-128-128-20, T = 128, B = 256 (each workgroup still loads all of
  *                     W per block, and the loads are what bounds the product): on request only
- *   WGRAD_TR          1 (default): weight-gradient products wider than 64 columns on rounded weights use
- *                     the kernel that brings both operand tiles into LDS as they lie in memory and
- *                     reads the MFMA fragments through the transposing LDS reads; 0: the general
- *                     product kernel, which transposes in registers
+ *   WGRAD_TR          1 (default): weight-gradient products use the kernel that brings both operand tiles
+ *                     into LDS as they lie in memory and reads the MFMA fragments from there
+ *                     transposed; 0: the general product kernel, which transposes in registers
  *   RLIF_PERSIST      1 (default): the time loops of a recurrent layer of 257 to 2048 neurons on rounded
  *                     weights run as ONE launch each, groups of workgroups exchanging spikes and gradients
  *                     through memory (launches of this kind are ordered one behind the other on a device,

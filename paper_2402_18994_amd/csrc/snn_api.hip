@@ -219,7 +219,11 @@ hipError_t static_scratch(void **out) {
 int choose_splits(long long M, int tiles, long long weights, long long row_bytes, long long *per_split, bool one_per_cu) {
   const long long target = 512;                          // workgroups resident at once
   if (tiles < 1) tiles = 1;
-  const long long max_by_len = M / 256;                  // at least four 64-row tiles per workgroup
+  long long max_by_len = M / 256;                        // at least four 64-row tiles per workgroup
+  // A short contraction on few tiles leaves the chip empty either way: shorter splits then, as long as a
+  // workgroup per tile and split still fits the chip at once (100-64-10 in fp32, T*B = 512: 8 splits of 64 rows
+  // instead of 2 of 256, step 51.6 -> 36.2 us together with one launch for both layers)
+  if (max_by_len < 8 && tiles <= 32) max_by_len = M / 64;
   long long want = target / tiles;
   if (want > max_by_len) want = max_by_len;
   if (want < 1) want = 1;
@@ -285,12 +289,7 @@ void carve(snn_ctx &c, Carver &cv) {
   };
   c.wg_tall = c.precision != SNN_PREC_FP32 && count_tiles(false) >= 32;
   // (the splits are laid out here, for the kernel that SNN_OPT_WGRAD_TR selects at this point)
-  bool wg_tr = c.opt[SNN_OPT_WGRAD_TR] && c.precision != SNN_PREC_FP32;
-  {
-    bool any_wide = false;
-    for (int l = 0; l < c.L; ++l) any_wide = any_wide || c.layers[l].N > 64;
-    wg_tr = wg_tr && any_wide;
-  }
+  const bool wg_tr = c.opt[SNN_OPT_WGRAD_TR] != 0;
   const int wg_tiles = count_tiles(c.wg_tall && !wg_tr);
   long long wg_weights = 0, wg_row_bytes = 0;             // what the merged launch writes per split / reads per row
   for (int l = 0; l < c.L; ++l) {
@@ -538,9 +537,10 @@ struct WgradJobs {
   GemmJobs narrow, mid, wide;        // cols <= 32, <= 64, wider
 };
 
-// The wide products on rounded weights go through the kernel built on transposing LDS reads
-// (SNN_OPT_WGRAD_TR, 128 x 128 tiles), else through the general one (256 x 128 tiles when there are many).
-static bool wgrad_tr(const snn_ctx *c) { return c->opt[SNN_OPT_WGRAD_TR] && c->precision != SNN_PREC_FP32; }
+// All of them go through the kernel built on transposing LDS reads (SNN_OPT_WGRAD_TR, 128 x 128 tiles:
+// also those of narrower layers, in the same launch), else through the general one (256 x 128 tiles when
+// there are many wide ones).
+static bool wgrad_tr(const snn_ctx *c) { return c->opt[SNN_OPT_WGRAD_TR] != 0; }
 static bool wgrad_tall(const snn_ctx *c) { return c->wg_tall && !wgrad_tr(c); }
 
 int flush_tn(snn_ctx *c, WgradJobs &w, int which) {
@@ -555,8 +555,8 @@ int flush_tn(snn_ctx *c, WgradJobs &w, int which) {
             : gemm_jobs_launch<P_T_U8, Q_T_HL, EPI_STORE, 2, 2, 2, 1, 2, 1>(w.mid, c->stream);
     memset(&w.mid, 0, sizeof w.mid);
   } else if (which == 2 && w.wide.njobs) {
-    e = f32 ? gemm_jobs_launch<P_T_U8, Q_T_F32S, EPI_STORE, 2, 2, 2, 2, 3, 1>(w.wide, c->stream)
-            : wgrad_tr(c) ? wgrad_tr_jobs_launch(w.wide, c->stream)
+    e = wgrad_tr(c) ? wgrad_tr_jobs_launch(w.wide, f32, c->stream)
+            : f32 ? gemm_jobs_launch<P_T_U8, Q_T_F32S, EPI_STORE, 2, 2, 2, 2, 3, 1>(w.wide, c->stream)
             : c->wg_tall ? gemm_jobs_launch<P_T_U8, Q_T_HL, EPI_STORE, 2, 2, 4, 2, 2, 1>(w.wide, c->stream)
                            : gemm_jobs_launch<P_T_U8, Q_T_HL, EPI_STORE, 2, 2, 2, 2, 2, 1>(w.wide, c->stream);
     memset(&w.wide, 0, sizeof w.wide);
@@ -579,7 +579,7 @@ int queue_tn(snn_ctx *c, WgradJobs &w, SpikeSrc s, int rows, const void *G, int 
   a.kc_per_split = (int)per;
   a.c_split_stride = (long long)rows * cols;
   a.C = splits > 1 ? part : out;
-  const int which = cols <= 32 ? 0 : cols <= 64 ? 1 : 2;
+  const int which = wgrad_tr(c) || cols > 64 ? 2 : cols <= 32 ? 0 : 1;
   GemmJobs &list = which == 0 ? w.narrow : which == 1 ? w.mid : w.wide;
   if (list.njobs == SNN_GEMM_MAX_JOBS) {
     int rc = flush_tn(c, w, which);
@@ -1689,7 +1689,7 @@ int32_t snn_weight_grad_static(const uint8_t *S_dev, const float *G_dev, float *
   // reads it, so nothing has to be cleared between calls.
   const long long weights = (long long)K * N;
   long long per = 0;
-  int splits = choose_splits(M, wgrad_tiles(K, N, false), weights, K + 4ll * N, &per, false);
+  int splits = choose_splits(M, wgrad_tiles(K, N, false), weights, K + 4ll * N, &per, true);
   const long long fit = (long long)SNN_STATIC_SCRATCH_BYTES / (weights * 4);
   if (splits > fit) {
     per = (long long)rup((size_t)((M + fit - 1) / fit), 64);
@@ -1705,16 +1705,8 @@ int32_t snn_weight_grad_static(const uint8_t *S_dev, const float *G_dev, float *
   a.C = splits > 1 ? (float *)scr : dW_dev;
   GemmJobs jobs;
   memset(&jobs, 0, sizeof jobs);
-  if (N <= 32) {
-    gemm_jobs_add<4, 1, 1, 1>(jobs, a, splits);
-    e = gemm_jobs_launch<P_T_U8, Q_T_F32S, EPI_STORE, 4, 1, 1, 1, 3, 1>(jobs, st);
-  } else if (N <= 64) {
-    gemm_jobs_add<2, 2, 2, 1>(jobs, a, splits);
-    e = gemm_jobs_launch<P_T_U8, Q_T_F32S, EPI_STORE, 2, 2, 2, 1, 3, 1>(jobs, st);
-  } else {
-    gemm_jobs_add<2, 2, 2, 2>(jobs, a, splits);
-    e = gemm_jobs_launch<P_T_U8, Q_T_F32S, EPI_STORE, 2, 2, 2, 2, 3, 1>(jobs, st);
-  }
+  gemm_jobs_add<2, 2, 2, 2>(jobs, a, splits);
+  e = wgrad_tr_jobs_launch(jobs, true, st);
   if (e != hipSuccess) return fail(nullptr, SNN_ERR_HIP, "weight-gradient launch failed: %s", hipGetErrorString(e));
   if (splits > 1) {
     ReduceJobs red;

@@ -47,13 +47,154 @@ struct WgradTr {
   static constexpr int LDS_BYTES = NS * ST;
 };
 
+// The multiplying half of wgrad_tr_body for fp32 words (see F32 there).
+template <bool PK, int NS, typename FIssue, typename FPrep, typename FLoad, typename FConv>
+__device__ __forceinline__ void wgrad_tr_f32_multiply(const GemmArgs &a, char *lds, const int lane, const int wave, const int row0,
+                                                      const int col0, const int split, const int nk, FIssue &issue, FPrep &issue_prepare,
+                                                      FLoad &issue_load, FConv &convert) {
+  typedef WgradTr<NS> G;
+  constexpr int SP = G::SP, ST = G::ST, NL = G::NL;
+  typedef const __attribute__((address_space(3))) uint32_t *lds_u32_ptr;
+  // A (tr_b8), step s, row tile i: as for HL words, row tiles 0..3 at bytes 32 i of a stage row.
+  // B, step s: stage rows 16 s + 8 (lane / 32) + e, e = 0..7, word 32 wave + lane % 32; the place of a
+  // row's 16-byte units depends on e % 4 only (rows 4 apart: + 2048 bytes).
+  const int g = lane >> 4, j = lane & 15;
+  lds_char_ptr fa[4], fb[4];
+  {
+    lds_char_ptr base = (lds_char_ptr)lds;
+    const int ra = 8 * (g >> 1) + (j >> 1);
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      fa[i] = PK ? base + (lane >> 5) * 128 + 32 * i + (lane & 31)
+                 : base + ra * 128 + (((2 * i + (g & 1)) ^ (ra & 7)) << 4) + 8 * (j & 1);
+    const int col = 32 * wave + (lane & 31);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) fb[e] = base + SP + (8 * (lane >> 5) + e) * 512 + (((col >> 2) ^ (4 * e)) << 4) + 4 * (col & 3);
+  }
+  f32x16 acc[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[i][r] = 0.f;
+
+  struct Pending {
+    bf16x8 af[4];
+    u32x4 q[3];                                        // hi, mid, lo
+  };
+  auto read_a = [&](auto U, auto S, int i, v2i32_t &ar) {
+    constexpr int off = decltype(U)::value * ST + decltype(S)::value * (PK ? 256 : 2048);
+    if constexpr (PK) {
+      ar.x = *(const __attribute__((address_space(3))) unsigned char *)(fa[i] + off);
+      ar.y = 0;
+    } else {
+      ar = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i32_ptr)(fa[i] + off));
+    }
+  };
+  auto read_b = [&](auto U, auto S, int e, uint32_t (&x)[8]) {
+    constexpr int off = decltype(U)::value * ST + decltype(S)::value * 8192;
+    x[e] = *(lds_u32_ptr)(fb[e & 3] + (off + (e >> 2) * 2048));
+  };
+  // Rows 2p and 2p + 1 of the fragment: hi and mid by cutting off the lower 16 bits, both remainders
+  // exact in fp32, the last one of at most 8 bits.
+  auto split3 = [&](const uint32_t (&x)[8], int p, Pending &d) {
+    const uint32_t x0 = x[2 * p], x1 = x[2 * p + 1];
+    const float r0 = __uint_as_float(x0) - __uint_as_float(x0 & 0xFFFF0000u), r1 = __uint_as_float(x1) - __uint_as_float(x1 & 0xFFFF0000u);
+    const uint32_t m0 = __float_as_uint(r0), m1 = __float_as_uint(r1);
+    const float l0 = r0 - __uint_as_float(m0 & 0xFFFF0000u), l1 = r1 - __uint_as_float(m1 & 0xFFFF0000u);
+    d.q[0][p] = __builtin_amdgcn_perm(x1, x0, 0x07060302u);
+    d.q[1][p] = __builtin_amdgcn_perm(m1, m0, 0x07060302u);
+    d.q[2][p] = __builtin_amdgcn_perm(__float_as_uint(l1), __float_as_uint(l0), 0x07060302u);
+  };
+  // MFMA n of a step: smallest pieces first, four independent sums in turn
+  auto mfma = [&](const Pending &x, auto N) {
+    constexpr int n = decltype(N)::value, i = n & 3, q = 2 - (n >> 2);
+    acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x.af[i], __builtin_bit_cast(bf16x8, x.q[q]), acc[i], 0, 0, 0);
+  };
+  // A stage as in the HL kernel: the MFMAs of its second step are carried over the next barrier, one slot
+  // per MFMA; slots 0..3 of a step read what the next step needs, 4..11 convert it.
+  auto half = [&](auto U, auto S, const Pending &x, Pending &next, auto fetch) {
+    v2i32_t ar[4];
+    uint32_t xr[8];
+    static_for<12>([&](auto N) {
+      constexpr int n = decltype(N)::value;
+      mfma(x, N);
+      if constexpr (n < 4) {
+        read_b(U, S, 2 * n, xr);
+        read_b(U, S, 2 * n + 1, xr);
+        read_a(U, S, n, ar[n]);
+      } else if constexpr (n % 2 == 0) {
+        split3(xr, (n - 4) / 2, next);
+      } else {
+        next.af[(n - 5) / 2] = convert(ar[(n - 5) / 2]);
+      }
+      fetch(N);
+      __builtin_amdgcn_sched_barrier(0);
+    });
+  };
+  auto stage = [&](auto U, int kt, Pending &pend) {
+    constexpr int u = decltype(U)::value;
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NS - 2) * NL) : "memory");
+    lds_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    Pending now;
+    const auto ld = issue_prepare(kt + NS - 1, (u + NS - 1) % NS);
+    half(U, std::integral_constant<int, 0>(), pend, now, [&](auto N) {
+      if constexpr (decltype(N)::value >= 1 && decltype(N)::value <= NL) issue_load(ld, std::integral_constant<int, decltype(N)::value - 1>());
+    });
+    half(U, std::integral_constant<int, 1>(), now, pend, [](auto) {});
+  };
+#pragma unroll
+  for (int t = 0; t < NS - 1; ++t) issue(t, t);
+  Pending pend;                                         // zeros in front of the first stage
+  {
+    const u32x4 z = {0u, 0u, 0u, 0u};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) pend.af[i] = __builtin_bit_cast(bf16x8, z);
+#pragma unroll
+    for (int q = 0; q < 3; ++q) pend.q[q] = z;
+  }
+  int kt = 0;
+  for (; kt + NS <= nk; kt += NS) {
+    static_for<NS>([&](auto U) { stage(U, kt + decltype(U)::value, pend); });
+  }
+  static_for<NS - 1>([&](auto U) {
+    if (kt + decltype(U)::value < nk) stage(U, kt + decltype(U)::value, pend);
+  });
+  static_for<12>([&](auto N) { mfma(pend, N); });
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+
+  // Lane holds column (lane & 31) of the 32 x 32 tiles, register r row 8 (r / 4) + 4 (lane / 32) + (r % 4).
+  float *C = a.C + (size_t)split * a.c_split_stride;
+  const int col = col0 + 32 * wave + (lane & 31);
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const float v = 0.5f * acc[i][r];
+      const int row = row0 + 32 * i + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+      if (row < a.rows && col < a.cols) {
+        const size_t o = (size_t)row * a.ldc + col;
+        if (a.nt_store) __builtin_nontemporal_store(v, &C[o]);
+        else C[o] = v;
+      }
+    }
+}
+
 // PK: S is the raster packed along time (eight steps of a channel and sample in a byte, first step in
 // the most significant bit), and the contraction runs in packed order: element m = 64 q + 8 mg + r is
 // sample 8 bg + mg at step 8 tp + r for q = tp (B / 8) + bg.  The eight elements a lane feeds to an
 // MFMA are then the eight bits of one byte: the S part of a stage is 4 samples x 128 bytes, read
 // bytewise and expanded in registers; the rows of G are gathered in that order by the loads' per-lane
 // offsets, so its tile in LDS and its fragment reads are those of the plain order.
-template <bool PK, int NS>
+// F32: the words of G are plain fp32 (the products of the unrounded weights) and each enters as three
+// bfloat16 pieces x = hi + mid + lo, all 24 bits of it, so a term of the sum is exact.  The fragments are
+// read with ordinary 4-byte LDS reads (32 lanes = 32 consecutive neurons of a row) and split in registers,
+// 44 instructions for 8 rows: the four wavefronts stand side by side, 128 rows k x 32 columns n each, so
+// that no word of G is split twice.  A stage is then 24 MFMAs (768 cycles) with 84 x 2 instructions of
+// conversion between them (general kernel: every word split by rounding in software, about 40 instructions
+// per word pair, behind register transposes).  700-128, T*B = 32768, with
+// the reduction: 47.6 -> 25.6 us.
+template <bool PK, bool F32, int NS>
 __device__ __forceinline__ void wgrad_tr_body(const GemmArgs &a, const int block, char *lds) {
   typedef WgradTr<NS> G;
   constexpr int BM = G::BM, BN = G::BN, MT = G::MT;
@@ -151,6 +292,38 @@ __device__ __forceinline__ void wgrad_tr_body(const GemmArgs &a, const int block
     static_for<NL>([&](auto N) { issue_load(r, N); });
   };
 
+  auto convert = [&](v2i32_t x) {                      // eight 0/1 bytes (PK: the eight bits of x.x) -> eight bfloat16 of value 2 x spike
+    u32x4 d;
+    if constexpr (PK) {
+      // z holds the byte at bits 0..7 and again at bits 17..24: shifted left by 7 + 2 j, bit 14 is step
+      // 2 j and bit 30 is step 2 j + 1
+      const uint32_t z = (uint32_t)x.x | ((uint32_t)x.x << 17);
+      d.x = (z << 7) & 0x40004000u;
+      d.y = (z << 9) & 0x40004000u;
+      d.z = (z << 11) & 0x40004000u;
+      d.w = (z << 13) & 0x40004000u;
+      return __builtin_bit_cast(bf16x8, d);
+    }
+    // (F32: also the caller's own bytes, of which bit 0 counts)
+    const uint32_t t0 = ((uint32_t)x.x << 6) & (F32 ? 0x40404040u : ~0u), t1 = ((uint32_t)x.y << 6) & (F32 ? 0x40404040u : ~0u);
+    d.x = __builtin_amdgcn_perm(0u, t0, 0x010C000Cu);
+    d.y = __builtin_amdgcn_perm(0u, t0, 0x030C020Cu);
+    d.z = __builtin_amdgcn_perm(0u, t1, 0x010C000Cu);
+    d.w = __builtin_amdgcn_perm(0u, t1, 0x030C020Cu);
+    return __builtin_bit_cast(bf16x8, d);
+  };
+  typedef std::integral_constant<int, 0> I0;
+  typedef std::integral_constant<int, 1> I1;
+  typedef std::integral_constant<int, 2> I2;
+  typedef std::integral_constant<int, 3> I3;
+  typedef std::integral_constant<int, 4> I4;
+#define SNN_SLOT_END __builtin_amdgcn_sched_barrier(0)
+
+  if constexpr (F32) {
+    wgrad_tr_f32_multiply<PK, NS>(a, lds, lane, wave, row0, col0, split, nk, issue, issue_prepare, issue_load, convert);
+    return;
+  }
+
   // LDS side.  A lane belongs to group g = lane / 16 with index j in it.
   // A (tr_b8), MFMA step s, row tile i: the lane points at stage row 16 s + 8 (g / 2) + j / 2 of S, bytes
   // 64 wm + 32 i + 16 (g % 2) + 8 (j % 2) .. + 7.
@@ -179,26 +352,6 @@ __device__ __forceinline__ void wgrad_tr_body(const GemmArgs &a, const int block
     for (int t = 0; t < 4; ++t)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][t][r] = 0.f;
-
-  auto convert = [&](v2i32_t x) {                      // eight 0/1 bytes (PK: the eight bits of x.x) -> eight bfloat16 of value 2 x spike
-    u32x4 d;
-    if constexpr (PK) {
-      // z holds the byte at bits 0..7 and again at bits 17..24: shifted left by 7 + 2 j, bit 14 is step
-      // 2 j and bit 30 is step 2 j + 1
-      const uint32_t z = (uint32_t)x.x | ((uint32_t)x.x << 17);
-      d.x = (z << 7) & 0x40004000u;
-      d.y = (z << 9) & 0x40004000u;
-      d.z = (z << 11) & 0x40004000u;
-      d.w = (z << 13) & 0x40004000u;
-      return __builtin_bit_cast(bf16x8, d);
-    }
-    const uint32_t t0 = (uint32_t)x.x << 6, t1 = (uint32_t)x.y << 6;
-    d.x = __builtin_amdgcn_perm(0u, t0, 0x010C000Cu);
-    d.y = __builtin_amdgcn_perm(0u, t0, 0x030C020Cu);
-    d.z = __builtin_amdgcn_perm(0u, t1, 0x010C000Cu);
-    d.w = __builtin_amdgcn_perm(0u, t1, 0x030C020Cu);
-    return __builtin_bit_cast(bf16x8, d);
-  };
 
   // One stage in buffer u.  At its barrier every wavefront has seen its own loads of the stage land
   // and has left stage kt - 1, whose buffer takes the loads of stage kt + NS - 1.
@@ -242,12 +395,6 @@ __device__ __forceinline__ void wgrad_tr_body(const GemmArgs &a, const int block
 #pragma unroll
       for (int i = 0; i < 2; ++i) mfma(x, t, i);
   };
-  typedef std::integral_constant<int, 0> I0;
-  typedef std::integral_constant<int, 1> I1;
-  typedef std::integral_constant<int, 2> I2;
-  typedef std::integral_constant<int, 3> I3;
-  typedef std::integral_constant<int, 4> I4;
-#define SNN_SLOT_END __builtin_amdgcn_sched_barrier(0)
   auto stage = [&](auto U, int kt, Pending &pend) {
     constexpr int u = decltype(U)::value;
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NS - 2) * NL) : "memory");
@@ -320,24 +467,25 @@ __device__ __forceinline__ void wgrad_tr_body(const GemmArgs &a, const int block
       }
 }
 
-// The weight-gradient jobs of wide layers (rounded weights); a job's S may be the raster packed along time.
+// The weight-gradient jobs; a job's S may be the raster packed along time.
 // NS: stages in flight.  3 (60 KiB) lets two workgroups share a compute unit.  More do not help, not even
 // a launch of one workgroup per compute unit (700-128-128-20, T*B = 32768, 256 workgroups: 18.1 us with
 // 3, 18.3 with 4, 19.6 with 6): the latency of the loads is covered.
-template <int NS>
+template <bool F32, int NS>
 __global__ __launch_bounds__(256, 2) void wgrad_tr_jobs_kernel(const GemmJobs jobs) {
   static_assert(WgradTr<NS>::LDS_BYTES <= 163840, "LDS of a compute unit");
   __shared__ __attribute__((aligned(16))) char lds[WgradTr<NS>::LDS_BYTES];
   int j = 0;
   while (j + 1 < jobs.njobs && (int)blockIdx.x >= jobs.first_block[j + 1]) ++j;
-  if (jobs.job[j].packed) wgrad_tr_body<true, NS>(jobs.job[j], blockIdx.x - jobs.first_block[j], lds);
-  else wgrad_tr_body<false, NS>(jobs.job[j], blockIdx.x - jobs.first_block[j], lds);
+  if (jobs.job[j].packed) wgrad_tr_body<true, F32, NS>(jobs.job[j], blockIdx.x - jobs.first_block[j], lds);
+  else wgrad_tr_body<false, F32, NS>(jobs.job[j], blockIdx.x - jobs.first_block[j], lds);
 }
 
-static hipError_t wgrad_tr_jobs_launch(const GemmJobs &jobs, hipStream_t st) {
+static hipError_t wgrad_tr_jobs_launch(const GemmJobs &jobs, bool f32, hipStream_t st) {
   if (jobs.njobs == 0) return hipSuccess;
   dim3 grid(jobs.first_block[jobs.njobs], 1, 1);
-  hipLaunchKernelGGL(wgrad_tr_jobs_kernel<3>, grid, dim3(256), 0, st, jobs);
+  if (f32) hipLaunchKernelGGL((wgrad_tr_jobs_kernel<true, 3>), grid, dim3(256), 0, st, jobs);
+  else hipLaunchKernelGGL((wgrad_tr_jobs_kernel<false, 3>), grid, dim3(256), 0, st, jobs);
   return hipGetLastError();
 }
 

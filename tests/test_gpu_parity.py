@@ -306,6 +306,44 @@ def test_weight_gradients_through_transposing_reads(T, B, sizes, rec, packed):
         assert np.abs(a - b).max() <= 1e-5 * np.abs(b).max() + 1e-30
 
 
+@pytest.mark.parametrize("T,B,sizes,precision,packed", [(32, 16, (100, 64, 10), "fp32", False),
+                                                          (5, 3, (12, 40, 3), "fp32", False),
+                                                          (33, 5, (203, 130, 70, 11), "fp32", False),
+                                                          (50, 24, (300, 257, 20), "fp32", True),
+                                                          (50, 24, (140, 48, 10), "bf16", True),
+                                                          (70, 31, (36, 60, 33, 10), "bf16", False)],
+                         ids=["short-splits", "less-than-a-stage", "ragged", "packed", "narrow-packed-bf16", "narrow-bf16"])
+def test_weight_gradients_of_fp32_and_narrow_layers_through_transposing_reads(T, B, sizes, precision, packed):
+    """The same kernel on fp32 current gradients (split in three bfloat16 pieces as they leave LDS) and
+    on layers of at most 64 columns, against the general kernel on the same current gradients."""
+    L = len(sizes) - 1
+    wl = workloads.Workload(name="wgrad-tr-32", index=22, T=T, B=B, sizes=sizes, recurrent=(False,) * (L - 1),
+                            beta=(0.9, 0.93, 0.95)[:L], theta=1.0, surrogate="superspike", slope=10.0, precision=precision,
+                            rate_lo=0.05, rate_hi=0.15, loss="max")
+    inp = workloads.generate(wl, w_gain=3.0)
+    grads = []
+    for knob in (1, 0):
+        snn = make(wl, inp, {"wgrad_tr": knob})
+        if packed:
+            snn.forward_packed(np.packbits(inp.X, axis=0), inp.labels)
+        else:
+            snn.forward(inp.X, inp.labels)
+        snn.backward()
+        grads.append([snn.get_tensor("grad_w", l + 1) for l in range(L)])
+        if knob:
+            G = snn.get_tensor("d_current", 1).reshape(T * B, -1).astype(np.float64)
+        snn.destroy()
+    for a, b in zip(*grads):
+        # exact products of the same operands; only the order of the fp32 additions differs: at most
+        # M 2^-24 of the sum of the terms' sizes, in a column of which the largest sum is no small part
+        assert np.abs(a - b).max() <= 1e-5 * np.abs(b).max() + 1e-30
+    assert np.abs(grads[0][0]).max() > 0
+    ref = inp.X.reshape(T * B, -1).astype(np.float64).T @ G
+    mag = inp.X.reshape(T * B, -1).astype(np.float64).T @ np.abs(G)
+    # (a term is exact; T B additions; rounded weights: G read back is hi + lo itself)
+    assert (np.abs(grads[0][0] - ref) <= T * B * 2.0 ** -24 * mag + 1e-30).all()
+
+
 @pytest.mark.parametrize("T,B,sizes,rec", [(37, 40, (50, 256, 10), (True,)),
                                             (20, 33, (64, 512, 250, 10), (True, True)),
                                             (2, 5, (30, 256, 10), (True,)),
