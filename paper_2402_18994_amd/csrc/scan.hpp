@@ -683,23 +683,35 @@ __global__ __launch_bounds__(256) void readout_reverse_kernel(const float *__res
 
 // Gradient of the readout decays, per chain: y_t = beta y_{t-1} + J_t gives
 // dL/dbeta = sum_{t >= 1} h_t y_{t-1} with h_t = dJ_t.  Summed over the batch by the reduction
-// launch.  Only run when the decays are trained.
+// launch.  Only run when the decays are trained.  There are few chains and each is a string of memory
+// round trips: a workgroup takes 32 of them, their steps cut in eight (700-256-256-20, T = B = 128: one
+// thread per chain 13.6 us, 4.6 us).
 template <bool HL>
 __global__ __launch_bounds__(256) void readout_beta_grad_kernel(const uint32_t *__restrict__ dJ, const float *__restrict__ Y,
                                                                 float *__restrict__ db_part, int T, int stride) {
-  const int p = blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= stride) return;
+  __shared__ float part[8][32];
+  const int p = blockIdx.x * 32 + (threadIdx.x & 31), seg = threadIdx.x >> 5;
+  const int len = (T + 7) / 8, t0 = max(1, seg * len), t1 = min(T, (seg + 1) * len);
   float acc = 0.f;
-#pragma unroll 4
-  for (int t = 1; t < T; ++t) {
-    const uint32_t w = dJ[(size_t)t * stride + p];
-    const float h = HL ? bf16_value(w & 0xFFFFu) + bf16_value(w >> 16) : __uint_as_float(w);
-    acc += h * Y[(size_t)(t - 1) * stride + p];
+  if (p < stride) {
+#pragma unroll 8
+    for (int t = t0; t < t1; ++t) {
+      const uint32_t w = dJ[(size_t)t * stride + p];
+      const float h = HL ? bf16_value(w & 0xFFFFu) + bf16_value(w >> 16) : __uint_as_float(w);
+      acc += h * Y[(size_t)(t - 1) * stride + p];
+    }
   }
-  db_part[p] = acc;
+  part[seg][threadIdx.x & 31] = acc;
+  __syncthreads();
+  if (seg == 0 && p < stride) {
+#pragma unroll
+    for (int v = 1; v < 8; ++v) acc += part[v][threadIdx.x];
+    db_part[p] = acc;
+  }
 }
 
 #define SNN_MAX_JOBS 24
+#define SNN_MAX_BETA_JOBS 12
 // beta <- clip(beta - lr dbeta, 0, 1) for several layers in one launch (the clip of the LIF listing).
 struct BetaJobs {
   int njobs;
@@ -963,18 +975,55 @@ struct ReduceUpdateJobs {
   long long qf_plane[SNN_MAX_JOBS], qb_plane[SNN_MAX_JOBS];
 };
 
-__global__ __launch_bounds__(256) void reduce_update_kernel(const ReduceUpdateJobs jobs, float lr, int nplanes,
-                                                            const float *__restrict__ loss_b, float *__restrict__ loss,
-                                                            int B) {
+// Trained decays ride along: dbeta = sum over the samples of their parts, in the same order, and
+// beta <- clip(beta - lr dbeta, 0, 1); a workgroup per 64 neurons.  (A reduction and two update launches
+// took 16 us of the 170 us step of 700-256-256-20, T = B = 128, this launch 7.5.)
+struct BetaReduceJobs {
+  int njobs;
+  int first_block[SNN_MAX_BETA_JOBS + 1];
+  const float *part[SNN_MAX_BETA_JOBS];
+  float *beta[SNN_MAX_BETA_JOBS], *dbeta[SNN_MAX_BETA_JOBS];
+  int N[SNN_MAX_BETA_JOBS], ld[SNN_MAX_BETA_JOBS];
+};
+__device__ __forceinline__ void beta_reduce_block(const BetaReduceJobs &jobs, int block, float lr, int B, float *sm) {
+  int j = 0;
+  while (j + 1 < jobs.njobs && block >= jobs.first_block[j + 1]) ++j;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, ld = jobs.ld[j];
+  const int n = (block - jobs.first_block[j]) * 64 + lane;
+  const float *__restrict__ part = jobs.part[j] + n;
+  float acc = 0.f;
+  if (n < ld) {
+    int s = w;
+    for (; s + 60 < B; s += 64) {
+      float v[16];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) v[u] = part[(size_t)(s + 4 * u) * ld];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) acc += v[u];
+    }
+    for (; s < B; s += 4) acc += part[(size_t)s * ld];
+  }
+  sm[threadIdx.x] = acc;
+  __syncthreads();
+  if (w == 0 && n < ld) {
+    const float g = ((sm[lane] + sm[64 + lane]) + sm[128 + lane]) + sm[192 + lane];
+    jobs.dbeta[j][n] = g;
+    if (n < jobs.N[j]) jobs.beta[j][n] = fminf(1.f, fmaxf(0.f, jobs.beta[j][n] - lr * g));
+  }
+}
+
+// `block`: of the workgroups that do not belong to the decays.
+__device__ __forceinline__ void reduce_update_body(const ReduceUpdateJobs &jobs, const int block, float lr, int nplanes,
+                                                   const float *__restrict__ loss_b, float *__restrict__ loss, int B,
+                                                   float *lsum) {
   __shared__ __attribute__((aligned(16))) uint16_t tile[3][32][8];
-  __shared__ float lsum[256];
-  if ((int)blockIdx.x >= jobs.first_block[jobs.njobs]) {
+  if (block >= jobs.first_block[jobs.njobs]) {
     loss_mean_block(loss_b, loss, B, lsum);
     return;
   }
   int j = 0;
-  while (j + 1 < jobs.njobs && (int)blockIdx.x >= jobs.first_block[j + 1]) ++j;
-  const int blk = blockIdx.x - jobs.first_block[j];
+  while (j + 1 < jobs.njobs && block >= jobs.first_block[j + 1]) ++j;
+  const int blk = block - jobs.first_block[j];
   float *__restrict__ W = jobs.W[j];
   float *__restrict__ dW = jobs.dW[j];
   const float *__restrict__ part = jobs.part[j];
@@ -1028,6 +1077,23 @@ __global__ __launch_bounds__(256) void reduce_update_kernel(const ReduceUpdateJo
     const int p = threadIdx.x >> 5, nn = n0 + tx;
     if (nn < N) *(uint4 *)&Qf[(size_t)p * jobs.qf_plane[j] + (size_t)nn * jobs.ldqf[j] + k0] = *(const uint4 *)&tile[p][tx][0];
   }
+}
+
+__global__ __launch_bounds__(256) void reduce_update_kernel(const ReduceUpdateJobs jobs, float lr, int nplanes,
+                                                            const float *__restrict__ loss_b, float *__restrict__ loss,
+                                                            int B) {
+  __shared__ float lsum[256];
+  reduce_update_body(jobs, blockIdx.x, lr, nplanes, loss_b, loss, B, lsum);
+}
+
+// (The workgroups of the decays, few and with a long chain of loads, come first in the grid.)
+__global__ __launch_bounds__(256) void reduce_update_betas_kernel(const ReduceUpdateJobs jobs, const BetaReduceJobs betas,
+                                                                  float lr, int nplanes, const float *__restrict__ loss_b,
+                                                                  float *__restrict__ loss, int B) {
+  __shared__ float lsum[256];
+  const int block = (int)blockIdx.x - betas.first_block[betas.njobs];
+  if (block < 0) beta_reduce_block(betas, blockIdx.x, lr, B, lsum);
+  else reduce_update_body(jobs, block, lr, nplanes, loss_b, loss, B, lsum);
 }
 
 }  // namespace snn

@@ -594,6 +594,7 @@ int queue_tn(snn_ctx *c, WgradJobs &w, SpikeSrc s, int rows, const void *G, int 
 
 static_assert(SNN_MAX_REDUCE_JOBS >= 3 * SNN_MAX_LAYERS, "dW, dR and dbeta of every layer");
 static_assert(SNN_MAX_JOBS >= 2 * SNN_MAX_LAYERS, "W and R of every layer");
+static_assert(SNN_MAX_BETA_JOBS >= SNN_MAX_LAYERS, "the decays of every layer");
 bool add_reduce_job(ReduceJobs &jobs, const float *part, float *out, int splits, long long n, bool always = false) {
   if (splits <= 1 && !always) return true;  // a single split was written straight to `out`
   if (jobs.njobs >= SNN_MAX_REDUCE_JOBS) return false;
@@ -1186,9 +1187,22 @@ int reduce_and_update(snn_ctx *c, float lr) {
     add(y.Wm, y.dW, y.K, y.N, y.Qf, y.ldqf, y.qf_plane, y.Qb, y.ldqb, y.qb_plane);
     if (y.recurrent) add(y.Rm, y.dR, y.N, y.N, y.QRf, y.ldqr, y.qr_plane, y.QRb, y.ldqr, y.qr_plane);
   }
+  BetaReduceJobs betas;
+  memset(&betas, 0, sizeof betas);
+  for (int l = 0; c->learn_beta && l < c->L; ++l) {
+    Layer &y = c->layers[l];
+    const int j = betas.njobs++;
+    betas.part[j] = y.part_b; betas.beta[j] = y.beta_v; betas.dbeta[j] = y.dbeta; betas.N[j] = y.N; betas.ld[j] = y.ld;
+    betas.first_block[j + 1] = betas.first_block[j] + (y.ld + 63) / 64;
+  }
   const bool with_loss = !c->loss_ready;
-  hipLaunchKernelGGL(reduce_update_kernel, dim3(jobs.first_block[jobs.njobs] + (with_loss ? 1 : 0)), dim3(256), 0,
-                     c->stream, jobs, lr, c->nplanes, with_loss ? c->loss_b : nullptr, c->loss, c->B);
+  const dim3 grid(betas.first_block[betas.njobs] + jobs.first_block[jobs.njobs] + (with_loss ? 1 : 0)), block(256);
+  if (betas.njobs)
+    hipLaunchKernelGGL(reduce_update_betas_kernel, grid, block, 0, c->stream, jobs, betas, lr, c->nplanes,
+                       with_loss ? c->loss_b : nullptr, c->loss, c->B);
+  else
+    hipLaunchKernelGGL(reduce_update_kernel, grid, block, 0, c->stream, jobs, lr, c->nplanes,
+                       with_loss ? c->loss_b : nullptr, c->loss, c->B);
   HIPCHK(c, hipGetLastError());
   if (with_loss) c->loss_ready = true;
   c->reduce_pending = false;
@@ -1531,19 +1545,19 @@ int32_t snn_backward(snn_ctx *c) {
     Layer &ro = c->layers[c->L - 1];
     const int stride = c->B * c->ldC;
     if (c->hl)
-      hipLaunchKernelGGL(readout_beta_grad_kernel<true>, dim3((stride + 255) / 256), dim3(256), 0, c->stream, ro.dI,
+      hipLaunchKernelGGL(readout_beta_grad_kernel<true>, dim3((stride + 31) / 32), dim3(256), 0, c->stream, ro.dI,
                          ro.V, ro.part_b, c->T, stride);
     else
-      hipLaunchKernelGGL(readout_beta_grad_kernel<false>, dim3((stride + 255) / 256), dim3(256), 0, c->stream, ro.dI,
+      hipLaunchKernelGGL(readout_beta_grad_kernel<false>, dim3((stride + 31) / 32), dim3(256), 0, c->stream, ro.dI,
                          ro.V, ro.part_b, c->T, stride);
     HIPCHK(c, hipGetLastError());
     for (int l = 0; l < c->L; ++l)
       if (!add_reduce_job(jobs, c->layers[l].part_b, c->layers[l].dbeta, c->B, c->layers[l].ld, true))
         return fail(c, SNN_ERR_UNSUPPORTED, "more than %d gradient reductions in one backward pass", SNN_MAX_REDUCE_JOBS);
   }
-  // Without trained decays the reduction of the partial sums waits for snn_sgd_step, which does
-  // it in the launch that updates the parameters (SNN_OPT_DEFER_REDUCE = 0: reduce here).
-  const bool defer = !c->learn_beta && c->opt[SNN_OPT_DEFER_REDUCE];
+  // The reduction of the partial sums waits for snn_sgd_step, which does it in the launch that updates
+  // the parameters (SNN_OPT_DEFER_REDUCE = 0: reduce here).
+  const bool defer = c->opt[SNN_OPT_DEFER_REDUCE] != 0;
   if ((rc = launch_weight_grads(c, wj, jobs, !c->loss_ready, defer))) return rc;
   c->state = 2;
   return SNN_OK;
@@ -1553,9 +1567,10 @@ int32_t snn_sgd_step(snn_ctx *c, float lr) {
   if (!c) return fail(nullptr, SNN_ERR_NULL, "context is NULL");
   if (c->state < 2) return fail(c, SNN_ERR_STATE, "snn_sgd_step needs a preceding snn_backward");
   Bracket br(c, SNN_K_SGD, 0);
-  int rc = c->reduce_pending ? reduce_and_update(c, lr) : update_layers(c, 0, c->L, true, lr);
+  const bool pending = c->reduce_pending;
+  int rc = pending ? reduce_and_update(c, lr) : update_layers(c, 0, c->L, true, lr);
   if (rc) return rc;
-  if (c->learn_beta) {
+  if (c->learn_beta && !pending) {
     BetaJobs bj;
     memset(&bj, 0, sizeof bj);
     for (int l = 0; l < c->L; ++l) {

@@ -689,6 +689,42 @@ def test_sgd_step_straight_after_backward(sizes, recurrent, precision):
     assert all(np.abs(g).max() > 0 for g in out[0][2::2][:L])
 
 
+@pytest.mark.parametrize("T,B,sizes,recurrent,precision", [(9, 1, (20, 64, 5), (False,), "bf16"),
+                                                            (1, 67, (20, 70, 24, 70), (False, False), "fp32"),
+                                                            (2, 130, (30, 128, 128, 20), (False, False), "bf16"),
+                                                            (33, 64, (30, 40, 33), (True,), "fp32")])
+def test_sgd_step_straight_after_backward_with_trained_decays(T, B, sizes, recurrent, precision):
+    """The same with trained decays, whose gradients and update ride in that launch: one sample and
+    several rounds of sixteen, widths that are no multiple of its 64 columns, one step and two."""
+    from paper_2402_18994_amd.binding import from_workload
+    L = len(sizes) - 1
+    wl = workloads.Workload(name="sgd-fused-beta", index=27, T=T, B=B, sizes=sizes, recurrent=recurrent,
+                            beta=(0.9, 0.93, 0.95)[:L], theta=1.0, surrogate="superspike", slope=10.0, precision=precision,
+                            rate_lo=0.1, rate_hi=0.3, rec_gain=1.0)
+    inp = workloads.generate(wl, w_gain=3.0)
+    out = []
+    for mode in ("straight", "read-first", "off"):
+        snn = from_workload(wl, inp, learn_beta=True, options={"defer_reduce": 0 if mode == "off" else 1})
+        snn.forward(inp.X, inp.labels)
+        snn.backward()
+        if mode == "read-first":
+            snn.get_tensor("grad_beta", 1)
+        snn.sgd_step(0.05)
+        res = []
+        for l in range(1, L + 1):
+            res += [snn.get_tensor(n, l) for n in ("beta", "grad_beta", "weight")]
+        if mode == "straight":
+            dJ, Y = (snn.get_tensor(n).astype(np.float64) for n in ("d_readout_current", "readout_trace"))
+        out.append(res)
+        snn.destroy()
+    for got in out[:2]:
+        for a, b in zip(got, out[2]):
+            assert np.array_equal(a, b)
+    terms = dJ[1:] * Y[:-1]                             # dL/dbeta of the readout
+    bound = (T * B + 8) * 2.0 ** -24 * np.abs(terms).sum(axis=(0, 1)) + 1e-30
+    assert (np.abs(out[0][3 * L - 2] - terms.sum(axis=(0, 1))) <= bound).all()
+
+
 def test_sgd_step_straight_after_backward_headline_shape():
     """The training loop bench.py times (forward, backward, step, nothing read in between) at the
     full headline shape: weights after two steps, their gradients and the loss must have the
