@@ -14,7 +14,9 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-Wall", "-Wno-unused-function"]
 # translation unit -> flags of its own
-UNITS = {"snn_api.hip": [],
+# (kernels on page boundaries: their speed does not depend on which others are compiled in front of them; the
+# same instructions of the 700-128-128-20 step take 79.8 us where the linker puts them, 79.4 us so)
+UNITS = {"snn_api.hip": ["-Xarch_device", "-falign-functions=4096"],
          "rlif_wide.hip": [],
          # results of MFMAs in ordinary vector registers (the time loops read them at once)
          "rlif_tile.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
