@@ -17,6 +17,9 @@
  *     on the stream.
  *   - All kernels are enqueued on the HIP stream given to snn_init.  Calls
  *     return after enqueueing unless stated otherwise.
+ *   - Threads may call snn_get_tensor on one context at the same time, also beside
+ *     a call that brings a loss to the host; they take turns.  All other calls on
+ *     one context are the caller's to order.
  *   - Every function returns an snn_status; nothing throws or exits.  After
  *     a non-zero status snn_last_error(ctx) describes it.
  *   - There is no CPU fallback: without a usable HIP device snn_init fails

@@ -113,6 +113,7 @@ struct snn_ctx {
   int opt[SNN_OPT_COUNT] = {4, 1, 1, 1, 1, 0, 128, 1024, 128, 1, 0, 0, 1, 1, 18, 0};   // snn_option values, in the enum's order
   char *pin = nullptr;            // pinned host memory the read-back kernels write: SNN_PIN_HEAD bytes, then two chunks
   hipEvent_t pin_ev[2] = {nullptr, nullptr};
+  std::mutex pin_mutex;           // held from a read-back's launch until the host has taken the values out
   uint32_t *hand = nullptr;       // hand-over space of the forward launches that give a sample to two workgroups
   int hand_parts = 1;             // hand-over regions per sample (one per column block of a layer)
   int fwd_epoch = 0;              // number of such launches so far (their flags count from epoch * 1024)
@@ -1479,6 +1480,7 @@ static int32_t forward_layers(snn_ctx *c, const int32_t *labels_dev, float *loss
   c->state = 1;
   if (loss_host) {
     // the loss and the error word go straight to pinned memory: one launch, one wait
+    std::lock_guard<std::mutex> lock(c->pin_mutex);
     hipLaunchKernelGGL(loss_mean_kernel, dim3(1), dim3(256), 0, c->stream, c->loss_b, c->loss, c->B, c->err_flag, (int *)c->pin);
     HIPCHK(c, hipGetLastError());
     c->loss_ready = true;
@@ -1593,6 +1595,7 @@ int32_t snn_get_tensor(snn_ctx *c, int32_t tensor, int32_t layer, void *dst, siz
   if (rc) return rc;
   if (bytes != v.rows * v.cols * v.esz)
     return fail(c, SNN_ERR_SHAPE, "tensor %d needs %zu bytes, got %zu", tensor, v.rows * v.cols * v.esz, bytes);
+  std::lock_guard<std::mutex> lock(c->pin_mutex);
   if ((rc = flush_reduce(c))) return rc;
   if (tensor == SNN_T_LOSS && (rc = ensure_loss(c))) return rc;
   if (tensor == SNN_T_CURRENT && layer >= 1 && layer <= c->L - 1 && !c->layers[layer - 1].i_ready) {

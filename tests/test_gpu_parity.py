@@ -1041,6 +1041,40 @@ def test_tensors_read_back_as_set(precision, T, B, N):
     snn.destroy()
 
 
+def test_several_threads_read_one_context():
+    """Threads that read different tensors of one context at once (ctypes releases the interpreter lock)
+    each get their own tensor: tensors of the same size, of several chunks of the read-back space, and
+    the loss of a forward pass."""
+    import threading
+    T, B, N = 32, 130, 129
+    rng = np.random.default_rng(3)
+    W = [rng.standard_normal(s).astype(np.float32) for s in ((N, N), (N, N), (N, 7))]
+    from paper_2402_18994_amd.binding import SNN
+    snn = SNN(T, B, (N, N, N, 7), (False, False), (0.9, 0.9, 0.9), 1.0, "arctan", 2.0, "bf16", W)
+    x = (rng.random((T, B, N)) < 0.1).astype(np.uint8)
+    labels = rng.integers(0, 7, B).astype(np.int32)
+    snn.forward(x, labels, want_loss=False)
+    names = [("weight", 1), ("weight", 2), ("membrane", 1), ("membrane", 2), ("logits", 0), ("loss", 0)]
+    want = {k: snn.get_tensor(*k) for k in names}
+    assert not np.array_equal(want["weight", 1], want["weight", 2])
+    wrong, start = [], threading.Barrier(len(names))
+
+    def read(key):
+        start.wait()
+        for _ in range(60 if key[0] == "membrane" else 300):
+            if not np.array_equal(snn.get_tensor(*key), want[key]):
+                wrong.append(key)
+                return
+
+    threads = [threading.Thread(target=read, args=(k,)) for k in names]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    snn.destroy()
+    assert not wrong
+
+
 def test_error_paths():
     from paper_2402_18994_amd.binding import SnnError
     wl = workloads.CONFIGS["tiny_ff"]
