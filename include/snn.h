@@ -233,8 +233,9 @@ typedef enum {
  *   RLIF_PERSIST      1 (default): the time loops of a recurrent layer of 257 to 2048 neurons on rounded
  *                     weights run as ONE launch each, groups of workgroups exchanging spikes and gradients
  *                     through memory (launches of this kind are ordered one behind the other on a device,
- *                     whatever streams they are on; a wait that times out after about a second is
- *                     reported as SNN_ERR_HIP); 0: a launch per step, the same bits
+ *                     whatever streams of the process they are on; a wait that times out after about a
+ *                     second is reported as SNN_ERR_HIP); 0, and on a stream that is being captured,
+ *                     where they could not be ordered: a launch per step, the same bits
  *                     (LAYER_TIME_SPLIT = 1 and LAYER_PAIR = 2 tell one launch from the next by a count that the
  *                     host passes as a kernel argument: do not replay calls made under them from a captured
  *                     graph.  Everything else enqueues kernels only - no host read-back unless a loss pointer

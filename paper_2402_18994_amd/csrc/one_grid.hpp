@@ -1,0 +1,46 @@
+// Order between launches whose workgroups wait for each other.
+//
+// Two such grids must not share the compute units half and half: each would hold what the other's missing
+// workgroups need.  They are therefore ordered one behind the other on a device, whatever streams of this
+// process they are on, by an event per device.  A stream that is being captured cannot be ordered: its launches
+// run whenever the graph is replayed, beside whatever else runs then.  `ordered()` says whether a launch may
+// wait for its own workgroups; if not, it must be one that waits for nothing.
+#pragma once
+#include <hip/hip_runtime_api.h>
+
+#include <mutex>
+
+namespace snn {
+
+class OneGridAtATime {
+ public:
+  // `wanted`: false leaves the streams alone (ordered() is false then).
+  OneGridAtATime(hipStream_t st, bool wanted) : st_(st) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    int dev = 0;
+    if (!wanted || hipStreamIsCapturing(st, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone ||
+        hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= MAX_DEVICES)
+      return;
+    mutex().lock();
+    ev_ = &events()[dev];
+    if (*ev_) (void)hipStreamWaitEvent(st, *ev_, 0);
+    else if (hipEventCreateWithFlags(ev_, hipEventDisableTiming) != hipSuccess) *ev_ = nullptr;
+  }
+  ~OneGridAtATime() {
+    if (!ev_) return;
+    if (*ev_) (void)hipEventRecord(*ev_, st_);
+    mutex().unlock();
+  }
+  OneGridAtATime(const OneGridAtATime &) = delete;
+  OneGridAtATime &operator=(const OneGridAtATime &) = delete;
+  bool ordered() const { return ev_ != nullptr; }
+
+ private:
+  static constexpr int MAX_DEVICES = 64;
+  static std::mutex &mutex() { static std::mutex m; return m; }
+  static hipEvent_t *events() { static hipEvent_t e[MAX_DEVICES] = {}; return e; }
+  hipStream_t st_;
+  hipEvent_t *ev_ = nullptr;
+};
+
+}  // namespace snn

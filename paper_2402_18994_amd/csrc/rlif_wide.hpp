@@ -22,8 +22,9 @@
 // update and publication), reverse loop 6.08 -> 2.46 ms (4.8 us: 1.3 until the flags are up, 1.8 loads of
 // g and products, 0.8 sum, 0.8 publication and its acknowledgement); a launch per step was the reverse loop.
 //
-// Every workgroup that waits must be resident with those it waits for: the launch covers all steps only
-// if the grid fits the compute units at a workgroup each, and otherwise (or with SNN_OPT_RLIF_PERSIST = 0)
+// Every workgroup that waits must be resident with those it waits for: a launch covers all steps only
+// if the grid fits the compute units at a workgroup each and is ordered behind the other grids of this kind
+// (one_grid.hpp; not on a stream that is being captured).  Otherwise (or with SNN_OPT_RLIF_PERSIST = 0)
 // one launch covers one step, the state passing through V and gs: the same arithmetic, the same bits.
 // A wait polls at most 2^18 times (SNN_OPT_WAIT_LIMIT_LOG2); on a time-out the workgroup sets bit 1 of the
 // error word and a flag that ends all waiting everywhere, so the grid drains and the host reports it.

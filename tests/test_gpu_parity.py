@@ -433,6 +433,61 @@ def test_wide_recurrent_training_on_two_streams():
             assert np.array_equal(a, b)
 
 
+def graph_nodes(graph):
+    """Number of nodes of a captured torch.cuda.CUDAGraph(keep_graph=True)."""
+    import ctypes
+    path = next(line.split()[-1] for line in open("/proc/self/maps") if "libamdhip64" in line)
+    n = ctypes.c_size_t(0)
+    assert ctypes.CDLL(path).hipGraphGetNodes(ctypes.c_void_p(graph.raw_cuda_graph()), None, ctypes.byref(n)) == 0
+    return n.value
+
+
+def test_captured_wide_recurrent_steps_wait_for_nothing():
+    """Training steps of two networks with a wide recurrent layer, captured on two streams and replayed
+    together beside the eager steps of a third one: replays cannot be ordered, so a captured time loop
+    is a launch per step in each direction, and all three end where one network alone does."""
+    import torch
+    T = 12
+    wl = workloads.Workload(name="rlif-captured", index=36, T=T, B=128, sizes=(40, 2048, 5), recurrent=(True,),
+                            beta=(0.9, 0.93), theta=1.0, surrogate="arctan", slope=2.0, precision="bf16",
+                            rate_lo=0.05, rate_hi=0.2, loss="max")
+    inp = workloads.generate(wl, w_gain=1.5)
+    x, y = torch.from_numpy(inp.X).cuda(), torch.from_numpy(inp.labels.astype(np.int32)).cuda()
+    torch.cuda.synchronize()
+
+    def step(snn):
+        snn.forward(x, y, want_loss=False)
+        snn.backward()
+        snn.sgd_step(1e-3)
+
+    streams, nets, graphs = [torch.cuda.Stream() for _ in range(4)], [], []
+    for st in streams:
+        with torch.cuda.stream(st):
+            nets.append(make(wl, inp))
+    for st, snn in zip(streams[:2], nets):
+        graphs.append(torch.cuda.CUDAGraph(keep_graph=True))
+        with torch.cuda.graph(graphs[-1], stream=st):
+            step(snn)
+        assert graph_nodes(graphs[-1]) >= 2 * T
+        graphs[-1].instantiate()
+    for _ in range(4):
+        for st, g in zip(streams, graphs):
+            with torch.cuda.stream(st):
+                g.replay()
+        step(nets[2])
+    torch.cuda.synchronize()
+    for _ in range(4):
+        step(nets[3])
+    got = [[snn.get_tensor("weight", 1), snn.get_tensor("rweight", 1)] for snn in nets]
+    del graphs
+    for snn in nets:
+        snn.destroy()
+    assert not np.array_equal(got[3][1], inp.R[0])
+    for g in got[:3]:
+        for a, b in zip(g, got[3]):
+            assert np.array_equal(a, b)
+
+
 def test_wide_recurrent_forward_wait_times_out():
     """The bounded wait of the one-launch recurrent loop, forced from the host: with
     SNN_OPT_WAIT_FAULT every wait expects words that nobody writes, so each workgroup gives up after
@@ -459,7 +514,7 @@ def test_wide_recurrent_forward_wait_times_out():
 
 
 @pytest.mark.parametrize("name,T,B", [("shd_ff128", 128, 32), ("shd_rec128", 40, 32), ("wide-rec", 24, 64)],
-                         ids=["one-launch-layers", "narrow-recurrent", "one-launch-recurrent-loop"])
+                         ids=["one-launch-layers", "narrow-recurrent", "wide-recurrent-loop"])
 def test_training_step_in_a_hip_graph(name, T, B):
     """snn_forward + snn_backward + snn_sgd_step captured on the context's stream and replayed: the calls
     enqueue kernels only (no host read-back without a loss pointer, no allocation, fill kernels instead
@@ -468,7 +523,7 @@ def test_training_step_in_a_hip_graph(name, T, B):
     same number of eager steps."""
     import torch
     if name == "wide-rec":
-        wl = workloads.Workload(name="graph-wide-rec", index=26, T=T, B=B, sizes=(50, 256, 10), recurrent=(True,),
+        wl = workloads.Workload(name="graph-wide-rec", index=26, T=T, B=B, sizes=(50, 300, 10), recurrent=(True,),
                                 beta=(0.9, 0.93), theta=1.0, surrogate="superspike", slope=10.0, precision="bf16",
                                 rate_lo=0.03, rate_hi=0.12, loss="max")
     else:
