@@ -1113,15 +1113,13 @@ int launch_readout_forward(snn_ctx *c, const int32_t *labels) {
     return SNN_OK;
   }
   c->dj_ready = false;
-  c->loss_ready = true;
+  c->loss_ready = false;
   const int stride = c->B * c->ldC;
   hipLaunchKernelGGL(readout_forward_kernel, dim3((stride + 255) / 256), dim3(256), 0, c->stream, y.I, y.V, c->z,
                      c->tstar, c->T, stride, y.beta_v, c->ldC, c->integral ? 1 : 0);
   HIPCHK(c, hipGetLastError());
   hipLaunchKernelGGL(cross_entropy_kernel, dim3((c->B + 3) / 4), dim3(256), 0, c->stream, c->z, labels, c->loss_b,
                      c->dz, c->B, c->C, c->ldC, c->err_flag);
-  HIPCHK(c, hipGetLastError());
-  hipLaunchKernelGGL(loss_mean_kernel, dim3(1), dim3(256), 0, c->stream, c->loss_b, c->loss, c->B, nullptr, nullptr);
   HIPCHK(c, hipGetLastError());
   return SNN_OK;
 }

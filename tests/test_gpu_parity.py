@@ -898,6 +898,36 @@ def test_more_than_64_classes(precision):
     assert rep["spike_rate"][0] > 0.01
 
 
+def test_more_than_64_classes_mean_loss_is_taken_once():
+    """The mean loss of a wide readout waits for whoever wants it, as that of a narrow one: a captured
+    readout step is the scan and the cross-entropy.  The loss is the same from the forward pass, from a reader and after the step that also takes it."""
+    import torch
+    from paper_2402_18994_amd.binding import SNN
+    rng = np.random.default_rng(5)
+    T, B = 9, 6
+    x = torch.from_numpy((rng.random((T, B, 40)) < 0.2).astype(np.uint8)).cuda()
+    y = torch.from_numpy(rng.integers(0, 70, B).astype(np.int32)).cuda()
+    W = [rng.standard_normal(s).astype(np.float32) for s in ((40, 16), (16, 70))]
+    stream = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(stream):
+        snn = SNN(T, B, (40, 16, 70), (False,), (0.9, 0.9), 1.0, "superspike", 25.0, "fp32", W)
+        loss = snn.forward(x, y)
+        assert abs(loss - snn.get_tensor("loss_per_sample").astype(np.float64).mean()) <= 1e-6 * abs(loss)
+        snn.forward(x, y, want_loss=False)
+        assert snn.get_tensor("loss")[0] == loss
+        snn.forward(x, y, want_loss=False)
+        snn.backward()
+        snn.sgd_step(0.0)
+        assert snn.get_tensor("loss")[0] == loss
+        graph = torch.cuda.CUDAGraph(keep_graph=True)
+        with torch.cuda.graph(graph, stream=stream):
+            snn.run_step("readout_forward", 2, labels=y)
+        assert graph_nodes(graph) == 2
+        del graph
+        snn.destroy()
+
+
 # ---------------------------------------------------------------- headline configuration, full size
 @pytest.mark.parametrize("gain", [1.0, 3.0])
 def test_shd_ff128_full_size(gain):
