@@ -22,10 +22,13 @@
 // update and publication), reverse loop 6.08 -> 2.46 ms (4.8 us: 1.3 until the flags are up, 1.8 loads of
 // g and products, 0.8 sum, 0.8 publication and its acknowledgement); a launch per step was the reverse loop.
 //
-// Every workgroup that waits must be resident with those it waits for: a launch covers all steps only
+// Every workgroup that waits must be resident with those it waits for: these launches are made only
 // if the grid fits the compute units at a workgroup each and is ordered behind the other grids of this kind
-// (one_grid.hpp; not on a stream that is being captured).  Otherwise (or with SNN_OPT_RLIF_PERSIST = 0)
-// one launch covers one step, the state passing through V and gs: the same arithmetic, the same bits.
+// (one_grid.hpp; not on a stream that is being captured).  Otherwise (or with SNN_OPT_RLIF_PERSIST = 0) kernels of
+// one step are launched T times, which exchange through S and dI and wait for nobody: the same sums in the
+// same order, the same bits.  (100-2048(rec)-20, T = 64, B = 128: 576 us forward and 821 reverse, 161 and
+// 279 in one launch; 512 neurons: 238 and 267, 99 and 145.  The kernels of the one launch cut to a
+// step, exchange and waits included, took 867 and 1348, 323 and 488.)
 // A wait polls at most 2^18 times (SNN_OPT_WAIT_LIMIT_LOG2); on a time-out the workgroup sets bit 1 of the
 // error word and a flag that ends all waiting everywhere, so the grid drains and the host reports it.
 #pragma once
@@ -52,7 +55,7 @@ struct RlifWideArgs {
   float *V;                                               // written (forward), read (reverse)
   uint8_t *S;
   uint32_t *dI;
-  float *gs;                                              // [B][ld] g between launches of one step each
+  float *gs;                                              // [B][ld] g between launches of a step each
   const uint16_t *R;                                      // R^T [to][from] (forward), R [from][to] (reverse)
   int ldr, T, B, ld, P, groups;                           // P: members of a group
   const float *beta_v;
@@ -65,7 +68,7 @@ struct RlifWideArgs {
   uint32_t tag_bias;                                      // 0, or (tests) what makes every wait expect a step nobody publishes
   int tile0;                                              // first tile of this launch (group g takes tile0 + g)
   uint32_t tag0;                                          // what step t publishes under is tag0 + t
-  int step0, steps;                                       // this launch takes steps step0 .. step0 + steps - 1 of T
+  int step;                                               // the step of a launch of one
 };
 
 static bool rlif_wide_layer(int ld) { return ld > 192 && ld <= RlifWide::MAXN; }

@@ -378,12 +378,14 @@ def test_wide_recurrent_forward_in_one_launch(T, B, sizes, rec):
 
 @pytest.mark.parametrize("T,B,sizes,surrogate", [(9, 17, (40, 257, 10), "superspike"), (7, 16, (30, 512, 520, 6), "sigmoid"),
                                                   (2, 3, (30, 300, 5), "arctan"), (1, 4, (30, 300, 5), "arctan"),
-                                                  (5, 140, (20, 1100, 5), "triangular"), (6, 20, (20, 2048, 5), "boxcar")])
+                                                  (5, 140, (20, 1100, 5), "triangular"), (6, 20, (20, 2048, 5), "boxcar"),
+                                                  (4, 131, (20, 1960, 5), "ste")])
 def test_wide_recurrent_loops_on_groups_of_workgroups(T, B, sizes, surrogate):
     """Both time loops of recurrent layers of more than 256 neurons, in one launch and with a launch per
     step, bit for bit, and the step against the oracle with the decays trained: a member with one
     neuron, members of two widths, one and two steps, more tiles of 16 samples than groups fit at once
-    (1100 neurons: 18 members, eight groups, nine tiles), the widest layer."""
+    (1100 neurons: 18 members, eight groups, nine tiles; 1960: a launch of one step whose workgroups take
+    a second tile with the rows they hold), the widest layer."""
     L = len(sizes) - 1
     wl = workloads.Workload(name="rlif-wide", index=31, T=T, B=B, sizes=sizes, recurrent=(True,) * (L - 1),
                             beta=(0.9, 0.93, 0.95)[:L], theta=1.0, surrogate=surrogate, slope=1.0 if surrogate in ("triangular", "boxcar") else 4.0,
