@@ -21,6 +21,7 @@
 #include "layer_reverse.hpp"
 #include "rlif.hpp"
 #include "rlif_wide.hpp"
+#include "splits.hpp"
 
 using namespace snn;
 
@@ -195,59 +196,6 @@ hipError_t static_scratch(void **out) {
   }
   *out = g_scratch_ptr[dev];
   return hipSuccess;
-}
-
-// Contraction splits of the weight-gradient products, which share one launch with `tiles`
-// output tiles in total over M rows each.  `weights`: elements of all gradient matrices (a
-// split writes that many partial sums); `row_bytes`: operand bytes the products read per row
-// of the contraction.  Measured facts behind the rule:
-//   * the splits of a tile are dealt round-robin to the 8 XCDs (see gemm_body), so a count
-//     that is not a multiple of 8 leaves some XCDs with a split more than others and the
-//     launch lasts as long as the fullest (700-512-512-20, T*B = 65536: 21 splits 253 us,
-//     24 splits 225 us, 32 splits 180 us);
-//   * 512 workgroups run at once (two per compute unit).  Slightly more than that (24 splits
-//     x 22 tiles = 528) is the worst case: the stragglers run a whole workgroup's work alone.
-//     Either everything fits at once, or there are at least 1.3 rounds of shorter workgroups;
-//   * every split writes and the reduction re-reads all partial sums: with large matrices
-//     (2048 wide: 56 MB per split) more splits cost more than they gain (64 splits: 10.2 ms
-//     against 3.3 ms with 8), and 16 splits never beat 8 at 1024 wide.
-//   * the kernel on transposing LDS reads (wgrad_tr.hpp) multiplies as fast with one workgroup per
-//     compute unit as with two (its MFMAs are fed by the wavefront's own instruction stream), so for
-//     it (`one_per_cu`) half as many splits cover the chip at the same product time and half the
-//     partial sums (700-128-128-20, T*B = 32768: 32 splits 19.1 us + 4.4 us for the update against
-//     64 splits 20.7 + 6.5);
-//   * 2..7 splits would leave whole XCDs without work (a split lives on one XCD): 8 then.
-int choose_splits(long long M, int tiles, long long weights, long long row_bytes, long long *per_split, bool one_per_cu) {
-  const long long target = 512;                          // workgroups resident at once
-  if (tiles < 1) tiles = 1;
-  long long max_by_len = M / 256;                        // at least four 64-row tiles per workgroup
-  // A short contraction on few tiles leaves the chip empty either way: shorter splits then, as long as a
-  // workgroup per tile and split still fits the chip at once (100-64-10 in fp32, T*B = 512: 8 splits of 64 rows
-  // instead of 2 of 256, step 51.6 -> 36.2 us together with one launch for both layers)
-  if (max_by_len < 8 && tiles <= 32) max_by_len = M / 64;
-  long long want = target / tiles;
-  if (want > max_by_len) want = max_by_len;
-  if (want < 1) want = 1;
-  if (want > 1 && want < 8 && max_by_len >= 8) want = 8;
-  if (want >= 8) {
-    want = want / 8 * 8;                                 // all at once, balanced over the XCDs
-    // when that leaves more than 15 % of the chip idle: more, shorter workgroups, as long as
-    // each keeps 16 tiles of the contraction and the partial sums stay below a quarter of the
-    // operand bytes
-    const long long more = ((target * 13 / 10 + tiles - 1) / tiles + 7) / 8 * 8;
-    if (want * tiles * 100 < target * 85 && M / more >= 1024 && more * weights * 4 * 4 <= M * row_bytes) want = more;
-    const long long half = (target / 2 / tiles) / 8 * 8; // one workgroup per compute unit
-    if (one_per_cu && half >= 8 && half < want && half * tiles * 100 >= target / 2 * 85) want = half;
-  }
-  long long per = (long long)rup((size_t)((M + want - 1) / want), 64);
-  *per_split = per;
-  return (int)((M + per - 1) / per);
-}
-
-int wgrad_tiles(int rows, int cols, bool tall) {
-  int bn = cols <= 32 ? 32 : (cols <= 64 ? 64 : 128);
-  const int bm = tall && cols > 64 ? 256 : 128;
-  return ((rows + bm - 1) / bm) * ((cols + bn - 1) / bn);
 }
 
 // Rows of C per workgroup for the products over all T*B rows whose output is wider than 64
@@ -1706,6 +1654,7 @@ int32_t snn_weight_grad_static(const uint8_t *S_dev, const float *G_dev, float *
   const long long weights = (long long)K * N;
   long long per = 0;
   int splits = choose_splits(M, wgrad_tiles(K, N, false), weights, K + 4ll * N, &per, true);
+  if (M <= 384) { splits = 1; per = round_up(M, 64); }   // (the reduction is a launch of its own: 256 rows 8.9 us instead of 11.2)
   const long long fit = (long long)SNN_STATIC_SCRATCH_BYTES / (weights * 4);
   if (splits > fit) {
     per = (long long)rup((size_t)((M + fit - 1) / fit), 64);

@@ -1,0 +1,74 @@
+// How the contraction of the weight-gradient products is split over workgroups (host arithmetic only).
+#pragma once
+
+namespace snn {
+
+inline long long round_up(long long x, long long m) { return (x + m - 1) / m * m; }
+
+constexpr long long SHORT_ROWS = 8192, SHORT_TILES = 32;  // a short contraction on few tiles: see below
+
+// Contraction splits of the weight-gradient products, which share one launch with `tiles`
+// output tiles in total over M rows each.  `weights`: elements of all gradient matrices (a
+// split writes that many partial sums); `row_bytes`: operand bytes the products read per row
+// of the contraction.  Measured facts behind the rule:
+//   * the splits of a tile are dealt round-robin to the 8 XCDs (see gemm_body), so a count
+//     that is not a multiple of 8 leaves some XCDs with a split more than others and the
+//     launch lasts as long as the fullest (700-512-512-20, T*B = 65536: 21 splits 253 us,
+//     24 splits 225 us, 32 splits 180 us);
+//   * 512 workgroups run at once (two per compute unit).  Slightly more than that (24 splits
+//     x 22 tiles = 528) is the worst case: the stragglers run a whole workgroup's work alone.
+//     Either everything fits at once, or there are at least 1.3 rounds of shorter workgroups;
+//   * every split writes and the reduction re-reads all partial sums: with large matrices
+//     (2048 wide: 56 MB per split) more splits cost more than they gain (64 splits: 10.2 ms
+//     against 3.3 ms with 8), and 16 splits never beat 8 at 1024 wide.
+//   * the kernel on transposing LDS reads (wgrad_tr.hpp) multiplies as fast with one workgroup per
+//     compute unit as with two (its MFMAs are fed by the wavefront's own instruction stream), so for
+//     it (`one_per_cu`) half as many splits cover the chip at the same product time and half the
+//     partial sums (700-128-128-20, T*B = 32768: 32 splits 19.1 us + 4.4 us for the update against
+//     64 splits 20.7 + 6.5);
+//   * 2..7 splits would leave whole XCDs without work (a split lives on one XCD): 8 then;
+//   * a short contraction on few tiles leaves most of the chip empty, and its time is that of one split
+//     plus that of the partial sums: 8 to 13 ns a row of a split and 1.25 ps a partial sum (written and read).
+//     Splits are doubled as long as that shortens the sum of both, a workgroup per compute
+//     unit at most; beyond 64 the launch itself is the longer part.  us, 64 / 128 / 256 / 512 rows a split, * the
+//     rule's: steps of 700-128-128-20, T*B = 1536: 49.5 48.5 48.4 50.1 (192 rows: 47.4*), 4096: 54.3 53.4 51.8* 52.3,
+//     8192: 66.2 57.8 54.7* 55.5; of 100-64-10 in fp32, 512: 35.4* 37.0 38.7 42.2, 2048: 37.2* 38.5 40.2 45.0, 8192:
+//     44.3 43.8* 45.0 49.4; of 700-256-256-20, 1024: 65.5 61.6* 62.2 64.1, 4096: 83.8 74.6 69.9 69.0*.  With M / 64 splits
+//     below 2048 rows and M / 256 from there on the count fell from 16 to 8 at 2048 rows (100-64-10: 33.8 us), and
+//     large matrices paid for partial sums (700-128-128-20, 1536: 49.5 us).
+inline int choose_splits(long long M, int tiles, long long weights, long long row_bytes, long long *per_split, bool one_per_cu) {
+  const long long target = 512;                          // workgroups resident at once
+  if (tiles < 1) tiles = 1;
+  if (one_per_cu && M <= SHORT_ROWS && tiles <= SHORT_TILES) {
+    long long want = 1;
+    while (want < 64 && 2 * want * tiles <= target / 2 && 128 * want <= M && 2 * want * want * weights < 8000 * M) want *= 2;
+    *per_split = round_up((M + want - 1) / want, 64);
+    return (int)((M + *per_split - 1) / *per_split);
+  }
+  const long long max_by_len = M / 256;                  // at least four 64-row tiles per workgroup
+  long long want = target / tiles;
+  if (want > max_by_len) want = max_by_len;
+  if (want < 1) want = 1;
+  if (want > 1 && want < 8 && max_by_len >= 8) want = 8;
+  if (want >= 8) {
+    want = want / 8 * 8;                                 // all at once, balanced over the XCDs
+    // when that leaves more than 15 % of the chip idle: more, shorter workgroups, as long as
+    // each keeps 16 tiles of the contraction and the partial sums stay below a quarter of the
+    // operand bytes
+    const long long more = ((target * 13 / 10 + tiles - 1) / tiles + 7) / 8 * 8;
+    if (want * tiles * 100 < target * 85 && M / more >= 1024 && more * weights * 4 * 4 <= M * row_bytes) want = more;
+    const long long half = (target / 2 / tiles) / 8 * 8; // one workgroup per compute unit
+    if (one_per_cu && half >= 8 && half < want && half * tiles * 100 >= target / 2 * 85) want = half;
+  }
+  long long per = round_up((M + want - 1) / want, 64);
+  *per_split = per;
+  return (int)((M + per - 1) / per);
+}
+
+inline int wgrad_tiles(int rows, int cols, bool tall) {
+  int bn = cols <= 32 ? 32 : (cols <= 64 ? 64 : 128);
+  const int bm = tall && cols > 64 ? 256 : 128;
+  return ((rows + bm - 1) / bm) * ((cols + bn - 1) / bn);
+}
+
+}  // namespace snn

@@ -56,6 +56,23 @@ def test_static_scratch_weight_gradient_matches_the_context_step(shapes):
         assert torch.equal(dW, dW2)
 
 
+@pytest.mark.parametrize("M,K,N", [(1, 4, 4), (63, 132, 20), (384, 36, 36), (385, 100, 16), (2049, 700, 8)])
+def test_static_scratch_weight_gradient_at_the_edges_of_its_routes(M, K, N):
+    """One split and no reduction up to 384 rows, several from there on: against the fp64 contraction, twice with the same bits."""
+    import torch
+    from paper_2402_18994_amd import binding
+    rng = np.random.default_rng(M)
+    X = (rng.random((M, K)) < 0.08).astype(np.uint8)
+    G = (rng.standard_normal((M, N)) * 10.0 ** rng.integers(-4, 1, size=(M, 1))).astype(np.float32)
+    Xd, Gd = torch.from_numpy(X).cuda(), torch.from_numpy(G).cuda()
+    out = [torch.full((K, N), float("nan"), dtype=torch.float32, device="cuda") for _ in range(2)]
+    for dW in out:
+        binding.weight_grad_static(Xd, Gd, dW)
+    torch.cuda.synchronize()
+    assert torch.equal(out[0], out[1])
+    parity.close_grad("dW static vs definition", out[0].cpu().numpy(), X.astype(np.float64).T @ G.astype(np.float64))
+
+
 def test_static_scratch_entry_point_refuses_what_it_cannot_hold():
     import torch
     from paper_2402_18994_amd import binding
