@@ -225,13 +225,14 @@ struct Carver {
 void carve(snn_ctx &c, Carver &cv) {
   const size_t M = (size_t)c.M;
   const int np = c.nplanes;
-  // Output tiles of all weight-gradient products (they share one launch).  With many tiles
+  // Output tiles of the weight-gradient products that share one launch.  With many tiles
   // the products are large enough for 256 x 128 tiles, which move 1.7 times fewer operand
   // bytes per flop (measured 2.8 times faster at 1024-wide layers, slower at 128-wide ones).
+  auto narrow = [&](const Layer &y) { return narrow_tiles(c.M, y.K, y.N, c.precision == SNN_PREC_FP32); };
   auto count_tiles = [&](bool tall) {
     int n = 0;
     for (int l = 0; l < c.L; ++l) {
-      n += wgrad_tiles(c.layers[l].K, c.layers[l].N, tall);
+      if (!narrow(c.layers[l])) n += wgrad_tiles(c.layers[l].K, c.layers[l].N, tall);
       if (c.layers[l].recurrent) n += wgrad_tiles(c.layers[l].N, c.layers[l].N, tall);
     }
     return n;
@@ -243,8 +244,14 @@ void carve(snn_ctx &c, Carver &cv) {
   long long wg_weights = 0, wg_row_bytes = 0;             // what the merged launch writes per split / reads per row
   for (int l = 0; l < c.L; ++l) {
     const Layer &y = c.layers[l];
-    wg_weights += (long long)y.K * y.N + (y.recurrent ? (long long)y.N * y.N : 0);
-    wg_row_bytes += y.K + 4ll * y.N + (y.recurrent ? y.N : 0);   // spike bytes below, 4-byte current gradients
+    if (!narrow(y)) {
+      wg_weights += (long long)y.K * y.N;
+      wg_row_bytes += y.K + 4ll * y.N;                           // spike bytes below, 4-byte current gradients
+    }
+    if (y.recurrent) {
+      wg_weights += (long long)y.N * y.N;
+      wg_row_bytes += y.N + (narrow(y) ? 4ll * y.N : 0);
+    }
   }
   for (int l = 0; l < c.L; ++l) {
     Layer &y = c.layers[l];
@@ -261,7 +268,9 @@ void carve(snn_ctx &c, Carver &cv) {
     }
     // (layer 1: from the length of the contraction in packed order, T rounded up to whole bytes of
     // eight steps, so that the same splits serve a raster packed along time)
-    y.splits_w = choose_splits(l == 0 ? (long long)((c.T + 7) / 8 * 8) * c.B : c.M, wg_tiles, wg_weights, wg_row_bytes, &y.per_w, wg_tr);
+    const long long rows_w = l == 0 ? (long long)((c.T + 7) / 8 * 8) * c.B : c.M;
+    y.splits_w = narrow(y) ? choose_splits(rows_w, wgrad_tiles(y.K, y.N, false), (long long)K * N, K + 4ll * N, &y.per_w, false)
+                           : choose_splits(rows_w, wg_tiles, wg_weights, wg_row_bytes, &y.per_w, wg_tr);
     if (y.splits_w > 1) y.part_w = cv.take<float>((size_t)y.splits_w * K * N);
     if (y.recurrent) {
       y.Rm = cv.take<float>(N * N);
@@ -486,9 +495,9 @@ struct WgradJobs {
   GemmJobs narrow, mid, wide;        // cols <= 32, <= 64, wider
 };
 
-// All of them go through the kernel built on transposing LDS reads (SNN_OPT_WGRAD_TR, 128 x 128 tiles:
-// also those of narrower layers, in the same launch), else through the general one (256 x 128 tiles when
-// there are many wide ones).
+// They go through the kernel built on transposing LDS reads (SNN_OPT_WGRAD_TR, 128 x 128 tiles: also those of
+// narrower layers, in the same launch, except long ones of at most 32 columns, see narrow_tiles), else through
+// the general one (256 x 128 tiles when there are many wide ones).
 static bool wgrad_tr(const snn_ctx *c) { return c->opt[SNN_OPT_WGRAD_TR] != 0; }
 static bool wgrad_tall(const snn_ctx *c) { return c->wg_tall && !wgrad_tr(c); }
 
@@ -528,7 +537,8 @@ int queue_tn(snn_ctx *c, WgradJobs &w, SpikeSrc s, int rows, const void *G, int 
   a.kc_per_split = (int)per;
   a.c_split_stride = (long long)rows * cols;
   a.C = splits > 1 ? part : out;
-  const int which = wgrad_tr(c) || cols > 64 ? 2 : cols <= 32 ? 0 : 1;
+  const bool tr = wgrad_tr(c) && !narrow_tiles(c->M, rows, cols, c->precision == SNN_PREC_FP32);
+  const int which = tr || cols > 64 ? 2 : cols <= 32 ? 0 : 1;
   GemmJobs &list = which == 0 ? w.narrow : which == 1 ? w.mid : w.wide;
   if (list.njobs == SNN_GEMM_MAX_JOBS) {
     int rc = flush_tn(c, w, which);
@@ -1653,8 +1663,9 @@ int32_t snn_weight_grad_static(const uint8_t *S_dev, const float *G_dev, float *
   // reads it, so nothing has to be cleared between calls.
   const long long weights = (long long)K * N;
   long long per = 0;
-  int splits = choose_splits(M, wgrad_tiles(K, N, false), weights, K + 4ll * N, &per, true);
-  if (M <= 384) { splits = 1; per = round_up(M, 64); }   // (the reduction is a launch of its own: 256 rows 8.9 us instead of 11.2)
+  const bool narrow = narrow_tiles(M, K, N, true);
+  int splits = choose_splits(M, wgrad_tiles(K, N, false), weights, K + 4ll * N, &per, !narrow);
+  if (M <= 384) { splits = 1; per = round_up(M, 64); }             // (the reduction is a launch of its own: 256 rows 8.9 us instead of 11.2)
   const long long fit = (long long)SNN_STATIC_SCRATCH_BYTES / (weights * 4);
   if (splits > fit) {
     per = (long long)rup((size_t)((M + fit - 1) / fit), 64);
@@ -1670,8 +1681,13 @@ int32_t snn_weight_grad_static(const uint8_t *S_dev, const float *G_dev, float *
   a.C = splits > 1 ? (float *)scr : dW_dev;
   GemmJobs jobs;
   memset(&jobs, 0, sizeof jobs);
-  gemm_jobs_add<2, 2, 2, 2>(jobs, a, splits);
-  e = wgrad_tr_jobs_launch(jobs, true, st);
+  if (narrow) {
+    gemm_jobs_add<4, 1, 1, 1>(jobs, a, splits);
+    e = gemm_jobs_launch<P_T_U8, Q_T_F32S, EPI_STORE, 4, 1, 1, 1, 3, 1>(jobs, st);
+  } else {
+    gemm_jobs_add<2, 2, 2, 2>(jobs, a, splits);
+    e = wgrad_tr_jobs_launch(jobs, true, st);
+  }
   if (e != hipSuccess) return fail(nullptr, SNN_ERR_HIP, "weight-gradient launch failed: %s", hipGetErrorString(e));
   if (splits > 1) {
     ReduceJobs red;

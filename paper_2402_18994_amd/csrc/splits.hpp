@@ -71,4 +71,14 @@ inline int wgrad_tiles(int rows, int cols, bool tall) {
   return ((rows + bm - 1) / bm) * ((cols + bn - 1) / bn);
 }
 
+// A product of at most 32 columns: three of the four wavefronts of a 128-column tile multiply nothing, which shows
+// once it takes longer than a launch.  Tiles of 128 x 32 of the general kernel then, in a launch of their own.  One
+// product alone, fp32, 512 x 16: T*B = 16384 13.4 us with the wide tile and 14.4 with the narrow one, 32768 18.4 and
+// 16.8, 262144 84.3 and 71.1; 100 x 16, one tile: 29.3 and 29.3 at 262144.  Rounded weights take two pieces instead
+// of three: the step of 700-32-20 at 131072 126.6 us and 124.8, 700-32-10 at 262144 257 and 239.
+inline bool narrow_tiles(long long M, int rows, int cols, bool fp32) {
+  const long long t = (rows + 127) / 128;
+  return cols <= 32 && t >= 2 && t * M >= (fp32 ? 1 << 17 : 1 << 20);
+}
+
 }  // namespace snn

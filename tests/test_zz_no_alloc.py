@@ -56,9 +56,11 @@ def test_static_scratch_weight_gradient_matches_the_context_step(shapes):
         assert torch.equal(dW, dW2)
 
 
-@pytest.mark.parametrize("M,K,N", [(1, 4, 4), (63, 132, 20), (384, 36, 36), (385, 100, 16), (2049, 700, 8)])
+@pytest.mark.parametrize("M,K,N", [(1, 4, 4), (63, 132, 20), (384, 36, 36), (385, 100, 16), (2049, 700, 8),
+                                   (32773, 512, 16), (65536, 256, 32), (65533, 132, 4)])
 def test_static_scratch_weight_gradient_at_the_edges_of_its_routes(M, K, N):
-    """One split and no reduction up to 384 rows, several from there on: against the fp64 contraction, twice with the same bits."""
+    """One split and no reduction up to 384 rows, several from there on, and for long products of at most
+    32 columns the narrow tiles: against the fp64 contraction, twice with the same bits."""
     import torch
     from paper_2402_18994_amd import binding
     rng = np.random.default_rng(M)
