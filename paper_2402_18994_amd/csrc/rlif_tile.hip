@@ -3,11 +3,31 @@
 
 namespace snn {
 
+// Sixteen samples a workgroup instead of four once the four-sample grid is more than two workgroups a compute unit (256
+// of them) and their wavefronts share the SIMDs: us at T = 32, rounded weights, forward / reverse, four and
+// sixteen samples: 128 neurons, B = 2048: 18.2 / 23.7 and 19.5 / 23.8, 2304: 25.4 / 32.6 and 19.7 / 23.4, 8192: 77.5 /
+// 88.6 and 52.3 / 81.6; 64 neurons, 2048: 10.7 / 14.1 and 12.5 / 13.5, 8192: 31.5 / 39.8 and 23.4 / 32.0; 32 neurons,
+// 4096: 9.9 / 13.0 and 9.5 / 13.2, 8192: 16.9 / 21.1 and 13.2 / 17.4.  (fp32, 128 neurons, 2304: 32.6 / 39.7 and 21.0 / 36.4;
+// 64, 3072: 15.7 / 19.0 and 13.8 / 22.2, 4608: 24.4 / 28.7 and 17.5 / 27.1: three planes of g times three
+// of R share the columns of four samples.)
+static bool sixteen(int B, int ld, bool three_planes_of_g = false) {
+  return ld <= 128 && B > 2048 && (long long)B * ((ld + 31) / 32) >= (three_planes_of_g ? 9216 : 6144);
+}
+
 // Steps of 32 neurons of the contraction, rounded up to the sizes the kernels are compiled for.
 static int tile_steps(int ld) { return ld <= 64 ? 2 : ld <= 128 ? 4 : ld <= 192 ? 6 : 8; }
 
 hipError_t rlif_tile_forward(hipStream_t st, bool fp32, int T, int B, int ld, const float *I, float *V, uint8_t *S,
                              const uint16_t *QRf, int ldqr, long long qr_plane, const float *beta, float theta) {
+  if (sixteen(B, ld)) {
+    const dim3 grid((B + 15) / 16), block(64 * ((ld + 15) / 16));
+#define SNN_RTF(NP, KS) hipLaunchKernelGGL((rlif_tile16_forward_kernel<NP, KS>), grid, block, 0, st, I, V, S, QRf, ldqr, qr_plane, T, B, ld, beta, theta)
+    if (ld <= 64) { if (fp32) SNN_RTF(3, 2); else SNN_RTF(1, 2); }
+    else if (fp32) SNN_RTF(3, 4);
+    else SNN_RTF(1, 4);
+#undef SNN_RTF
+    return hipGetLastError();
+  }
   const dim3 grid((B + 3) / 4), block(64 * ((ld + 31) / 32));
 #define SNN_RTF(KS)                                                                                                    \
   do {                                                                                                                 \
@@ -22,6 +42,14 @@ hipError_t rlif_tile_forward(hipStream_t st, bool fp32, int T, int B, int ld, co
 template <int NP, int SURR>
 static hipError_t reverse(hipStream_t st, int T, int B, int ld, const float *dS, const float *V, uint32_t *dI, const uint16_t *QRb,
                           int ldqr, long long qr_plane, const float *beta, float theta, float slope, float *db_part) {
+  if (sixteen(B, ld, NP == 3)) {
+    const dim3 grid((B + 15) / 16), block(64 * ((ld + 15) / 16));
+#define SNN_RTR(KS)                                                                                                    \
+  hipLaunchKernelGGL((rlif_tile16_reverse_kernel<NP, SURR, KS>), grid, block, 0, st, dS, V, dI, QRb, ldqr, qr_plane, T, B, ld, beta, theta, slope, db_part)
+    if (ld <= 64) SNN_RTR(2); else SNN_RTR(4);
+#undef SNN_RTR
+    return hipGetLastError();
+  }
   const dim3 grid((B + 3) / 4), block(64 * ((ld + 31) / 32));
 #define SNN_RTR(KS)                                                                                                    \
   hipLaunchKernelGGL((rlif_tile_reverse_kernel<NP, SURR, KS>), grid, block, 0, st, dS, V, dI, QRb, ldqr, qr_plane, T, B, ld, beta, theta, slope, db_part)

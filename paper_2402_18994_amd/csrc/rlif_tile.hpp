@@ -43,19 +43,19 @@ template <int KS> struct RlifTile {
   static constexpr int XP = KS * 64 + 16;                 // bytes between the samples of an exchange tile
 };
 
-// The two row tiles of a wavefront of the weight planes [row][k]: lane (c, q) holds row c, k 8q .. 8q+7.
-template <int NP, int KS> struct RlifWeights {
-  bf16x8 f[NP][2][KS];
+// The row tiles of a wavefront (two, or one) of the weight planes [row][k]: lane (c, q) holds row c, k 8q .. 8q+7.
+template <int NP, int KS, int RT = 2> struct RlifWeights {
+  bf16x8 f[NP][RT][KS];
   __device__ __forceinline__ void load(const uint16_t *Q, int ldq, long long plane, int w, int c, int q) {
     const rsrc_t r = make_rsrc(Q, (unsigned)(NP * plane * 2));
     const int rows = (int)(plane / ldq);
 #pragma unroll
     for (int p = 0; p < NP; ++p)
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
+      for (int i = 0; i < RT; ++i)
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
-          const int row = 16 * (2 * w + i) + c, k = 32 * ks + 8 * q;
+          const int row = 16 * (RT * w + i) + c, k = 32 * ks + 8 * q;
           f[p][i][ks] = __builtin_bit_cast(bf16x8, ld_b128(r, k < ldq && row < rows ? (int)(p * plane + (long long)row * ldq + k) * 2 : OOB, 0));
         }
   }
@@ -228,6 +228,160 @@ __global__ __launch_bounds__(KS * 64) void rlif_tile_reverse_kernel(const float 
   for (int d = 0; d < PF; ++d)
     if (t - d >= 0) step(cds[d], cv[d], t - d);
   if (db_part && ok) *(u32x2 *)(db_part + (size_t)b * ld + L.n) = u32x2{__float_as_uint(db[0]), __float_as_uint(db[1])};
+}
+
+// ---------------------------------------------------------------- sixteen samples
+// Batches of many more tiles than compute units: a step's chain is hidden behind other workgroups then, and
+// what counts is the instructions of all of them.  Sixteen samples fill the MFMA's columns, a wavefront holds 16
+// neurons, a lane four of them: the fragments, the barrier and the bookkeeping of a step serve four
+// times the samples.  (Figures at the rule in rlif_tile.hip.)
+template <int NP, int KS>
+__global__ __launch_bounds__(KS * 128) void rlif_tile16_forward_kernel(const float *__restrict__ I, float *__restrict__ V,
+                                                                       uint8_t *__restrict__ S, const uint16_t *__restrict__ QRf,
+                                                                       int ldqr, long long qr_plane, int T, int B, int ld,
+                                                                       const float *__restrict__ beta_v, float theta) {
+  constexpr int XP = RlifTile<KS>::XP, PF = 4;
+  constexpr int VP = KS * 32 + 4, SP = KS * 32 + 16;      // V and S leave as the tile lies in memory, one block, through LDS:
+  __shared__ __align__(16) char xs[2][16 * XP];           // rows of 64 bytes per sample and wavefront took 80 us instead of 52
+  __shared__ __align__(16) float vs[2][16 * VP];          // (128 neurons, B = 8192, T = 32)
+  __shared__ __align__(16) uint8_t ss[2][16 * SP];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, c = lane & 15, q = lane >> 4, n = 16 * w + 4 * q;
+  const int b = blockIdx.x * 16 + c, row4 = B * ld * 4;
+  const unsigned bytes = (unsigned)T * B * ld * 4u;
+  const rsrc_t rI = make_rsrc(I, bytes), rV = make_rsrc(V, bytes), rS = make_rsrc(S, bytes / 4);
+  RlifWeights<NP, KS, 1> W;
+  W.load(QRf, ldqr, qr_plane, w, c, q);
+  const bool ok = b < B && n < ld;
+  const int vo4 = ok ? (b * ld + n) * 4 : OOB;
+  const int xo = c * XP + n * 2, fo = c * XP + 16 * q;
+  // piece i of the block: four potentials, or eight spikes, of a sample
+  const int vi = 4 * threadIdx.x, vr = vi / ld, si = 8 * threadIdx.x, sr = si / ld, b0 = blockIdx.x * 16;
+  const int vso = vr < 16 && b0 + vr < B ? (b0 * ld + vi) * 4 : OOB, sso = sr < 16 && b0 + sr < B ? b0 * ld + si : OOB;
+  const int vsl = min(vr, 15) * VP + vi - vr * ld, ssl = min(sr, 15) * SP + si - sr * ld;
+  float v[4] = {0.f, 0.f, 0.f, 0.f}, beta[4];             // V_0 = 0
+#pragma unroll
+  for (int e = 0; e < 4; ++e) beta[e] = n + e < ld ? beta_v[n + e] : 0.f;
+  u32x4 cur[PF];
+#pragma unroll
+  for (int d = 0; d < PF; ++d) cur[d] = ld_b128(rI, vo4, min(d, T - 1) * row4);
+  for (int i = threadIdx.x; i < 2 * 16 * XP / 4; i += blockDim.x) ((uint32_t *)xs)[i] = 0u;   // neurons beyond the last wavefront
+  __syncthreads();
+
+  auto step = [&](u32x4 &in, int t) {
+    char *x = xs[t & 1];
+    uint32_t s[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) s[e] = v[e] > theta ? 1u : 0u;
+    *(u32x2 *)(x + xo) = u32x2{(s[0] | (s[1] << 16)) * 0x3F80u, (s[2] | (s[3] << 16)) * 0x3F80u};
+    *(f32x4 *)(vs[t & 1] + c * VP + n) = f32x4{v[0], v[1], v[2], v[3]};
+    *(uint32_t *)(ss[t & 1] + c * SP + n) = s[0] | (s[1] << 8) | (s[2] << 16) | (s[3] << 24);
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    lds_barrier();
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      const bf16x8 sf = *(const bf16x8 *)(x + fo + 64 * ks);
+#pragma unroll
+      for (int p = NP - 1; p >= 0; --p) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(W.f[p][0][ks], sf, acc, 0, 0, 0);
+    }
+    st_b128(rV, vso, t * row4, *(const u32x4 *)(vs[t & 1] + vsl));
+    st_b64(rS, sso, t * (row4 >> 2), *(const u32x2 *)(ss[t & 1] + ssl));
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = beta[e] * v[e] + __uint_as_float(in[e]) + acc[e] - (s[e] ? theta : 0.f);
+    in = ld_b128(rI, vo4, min(t + PF, T - 1) * row4);
+  };
+  int t = 0;
+  for (; t + PF <= T; t += PF) {
+#pragma unroll
+    for (int d = 0; d < PF; ++d) step(cur[d], t + d);
+  }
+#pragma unroll
+  for (int d = 0; d < PF; ++d)
+    if (t + d < T) step(cur[d], t + d);
+}
+
+template <int NP, int SURR, int KS>
+__global__ __launch_bounds__(KS * 128) void rlif_tile16_reverse_kernel(const float *__restrict__ dS, const float *__restrict__ V,
+                                                                       uint32_t *__restrict__ dI, const uint16_t *__restrict__ QRb,
+                                                                       int ldqr, long long qr_plane, int T, int B, int ld,
+                                                                       const float *__restrict__ beta_v, float theta, float slope,
+                                                                       float *__restrict__ db_part) {
+  constexpr int XP = RlifTile<KS>::XP, PF = 3;
+  constexpr int GP = NP == 1 ? 2 : 3, XB = 16 * XP;
+  __shared__ __align__(16) char xs[2][GP][XB];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, c = lane & 15, q = lane >> 4, n = 16 * w + 4 * q;
+  const int b = blockIdx.x * 16 + c, row4 = B * ld * 4;
+  const unsigned bytes = (unsigned)T * B * ld * 4u;
+  const rsrc_t rdS = make_rsrc(dS, bytes), rV = make_rsrc(V, bytes), rdI = make_rsrc(dI, bytes);
+  RlifWeights<NP, KS, 1> W;
+  W.load(QRb, ldqr, qr_plane, w, c, q);
+  const bool ok = b < B && n < ld;
+  const int vo4 = ok ? (b * ld + n) * 4 : OOB;
+  const int xo = c * XP + n * 2, fo = c * XP + 16 * q;
+  float gv[4] = {0.f, 0.f, 0.f, 0.f}, db[4] = {0.f, 0.f, 0.f, 0.f}, beta[4];   // g_T = 0
+#pragma unroll
+  for (int e = 0; e < 4; ++e) beta[e] = n + e < ld ? beta_v[n + e] : 0.f;
+  u32x4 cds[PF], cv[PF];
+#pragma unroll
+  for (int d = 0; d < PF; ++d) {
+    cds[d] = ld_b128(rdS, vo4, max(T - 1 - d, 0) * row4);
+    cv[d] = ld_b128(rV, vo4, max(T - 1 - d, 0) * row4);
+  }
+  for (int i = threadIdx.x; i < 2 * GP * XB / 4; i += blockDim.x) ((uint32_t *)xs)[i] = 0u;
+  __syncthreads();
+
+  auto step = [&](u32x4 &ds, u32x4 &vv, int t) {
+    char *x = (char *)xs[t & 1];
+    u32x4 o;
+    if (NP == 1) {
+      u32x2 hi, lo;
+#pragma unroll
+      for (int p = 0; p < 2; ++p) {
+        hi[p] = pk_bf16(gv[2 * p], gv[2 * p + 1]);
+        lo[p] = pk_bf16(gv[2 * p] - __uint_as_float(hi[p] << 16), gv[2 * p + 1] - __uint_as_float(hi[p] & 0xFFFF0000u));
+        o[2 * p] = __builtin_amdgcn_perm(lo[p], hi[p], 0x05040100u);
+        o[2 * p + 1] = __builtin_amdgcn_perm(lo[p], hi[p], 0x07060302u);
+      }
+      *(u32x2 *)(x + xo) = hi;
+      *(u32x2 *)(x + XB + xo) = lo;
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o[e] = __float_as_uint(gv[e]);
+#pragma unroll
+      for (int k = 0; k < GP; ++k)
+        *(u32x2 *)(x + k * XB + xo) = u32x2{bf16_piece(gv[0], k) | (bf16_piece(gv[1], k) << 16), bf16_piece(gv[2], k) | (bf16_piece(gv[3], k) << 16)};
+    }
+    f32x4 acc[GP] = {};                                   // a sum per plane of g
+    lds_barrier();
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+      for (int k = 0; k < GP; ++k) {
+        const bf16x8 gf = *(const bf16x8 *)(x + k * XB + fo + 64 * ks);
+#pragma unroll
+        for (int p = NP - 1; p >= 0; --p) acc[k] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(W.f[p][0][ks], gf, acc[k], 0, 0, 0);
+      }
+    st_b128(rdI, vo4, t * row4, o);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float vt = __uint_as_float(vv[e]);
+      const float sg = surr_rcp<SURR>(slope, vt - theta), u = __uint_as_float(ds[e]) - theta * gv[e];
+      const float sum = NP == 1 ? acc[0][e] + acc[1][e] : (acc[0][e] + acc[GP - 1][e]) + acc[1][e];
+      db[e] += gv[e] * vt;
+      gv[e] = beta[e] * gv[e] + sg * (u + sum);
+    }
+    ds = ld_b128(rdS, vo4, max(t - PF, 0) * row4);
+    vv = ld_b128(rV, vo4, max(t - PF, 0) * row4);
+  };
+  int t = T - 1;
+  for (; t - PF + 1 >= 0; t -= PF) {
+#pragma unroll
+    for (int d = 0; d < PF; ++d) step(cds[d], cv[d], t - d);
+  }
+#pragma unroll
+  for (int d = 0; d < PF; ++d)
+    if (t - d >= 0) step(cds[d], cv[d], t - d);
+  if (db_part && ok)
+    *(u32x4 *)(db_part + (size_t)b * ld + n) = u32x4{__float_as_uint(db[0]), __float_as_uint(db[1]), __float_as_uint(db[2]), __float_as_uint(db[3])};
 }
 
 // Whether a recurrent layer's rows fit a workgroup of these kernels.

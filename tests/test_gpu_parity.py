@@ -980,6 +980,18 @@ def test_recurrent_layers_on_a_workgroup_of_four_samples(precision, T, B, widths
 
 
 @pytest.mark.parametrize("precision", ["fp32", "bf16"])
+@pytest.mark.parametrize("T,B,width,surrogate", [(6, 2309, 121, "superspike"), (3, 2049, 72, "boxcar"), (2, 4610, 64, "arctan"),
+                                                  (9, 6145, 20, "sigmoid"), (1, 2051, 128, "ste")])
+def test_recurrent_layers_on_a_workgroup_of_sixteen_samples(precision, T, B, width, surrogate):
+    """Batches of many more tiles than compute units: sixteen samples a workgroup, the last one with one to
+    five, layers that do and do not fill the wavefronts or the steps of 32 neurons, decays trained."""
+    wl = workloads.Workload(name="rec_sixteen", index=37, T=T, B=B, sizes=(30, width, 5), recurrent=(True,),
+                            beta=(0.9, 0.93), theta=1.0, surrogate=surrogate, slope=1.0 if surrogate == "boxcar" else 4.0,
+                            precision=precision, rate_lo=0.1, rate_hi=0.3, loss="integral")
+    beta_step_parity(wl, w_gain=1.5)
+
+
+@pytest.mark.parametrize("precision", ["fp32", "bf16"])
 def test_recurrent_small(precision):
     wl = workloads.Workload(name="rec_small", index=13, T=31, B=40, sizes=(50, 40, 24, 5), recurrent=(True, True),
                             beta=(0.9, 0.9, 0.9), theta=1.0, surrogate="superspike", slope=25.0,
