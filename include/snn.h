@@ -244,8 +244,7 @@ typedef enum {
  *                     4..20 (default 18, about a second)
  *   WAIT_FAULT        0 (default); 1: every such wait expects words that nobody writes, so it times out and
  *                     the launch ends the way it would if a workgroup were missing (the grid drains, the next
- *                     call that reads the error word returns SNN_ERR_HIP).  For tests of that path (layers of
- *                     193 to 256 neurons take it too then). */
+ *                     call that reads the error word returns SNN_ERR_HIP).  For tests of that path. */
 typedef enum {
   SNN_OPT_LAYER_FORWARD = 0,
   SNN_OPT_LAYER_PAIR = 1,

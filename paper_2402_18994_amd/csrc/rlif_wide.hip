@@ -132,7 +132,7 @@ __device__ __forceinline__ void add_words(const bf16x8 (&wf)[RT][NKS], int ks, c
 }
 
 // ---------------------------------------------------------------- all steps in a launch
-// NKS: steps of 32 neurons of the contraction per wavefront (the layer has at most 256 NKS).
+// NKS: steps of 32 neurons of the contraction per wavefront (the layer has at most 256 NKS, and more than 256).
 template <int NKS>
 __global__ __launch_bounds__(512) void rlif_wide_forward_kernel(const RlifWideArgs a) {
   constexpr int BP = NKS | 1;                             // dwords between the samples' bits of a wavefront in LDS
@@ -580,7 +580,7 @@ static hipError_t run(hipStream_t st, RlifWideArgs a, int cus, bool persist, siz
   if (order.ordered()) {
     if ((e = clear(st, a.space, cleared)) != hipSuccess) return e;
     if (words && (e = clear(st, a.space + G::WORDS, G::WORD_BYTES)) != hipSuccess) return e;
-    a.groups = std::min({tiles, 8 * (G::SLOTS / a.P), (int)G::GROUPS});
+    a.groups = std::min(tiles, 8 * (G::SLOTS / a.P));
     const dim3 grid((unsigned)(8 * a.P * ((a.groups + 7) / 8)));
     int chunk = 0;
     for (a.tile0 = 0; a.tile0 < tiles; a.tile0 += a.groups, ++chunk) {
@@ -605,7 +605,6 @@ static hipError_t run(hipStream_t st, RlifWideArgs a, int cus, bool persist, siz
   return run(st, a, cus, persist, __VA_ARGS__, rlif_wide_##dir##_kernel<n>, rlif_wide_##dir##_step_kernel<n, 1>, rlif_wide_##dir##_step_kernel<n, 2>)
 #define SNN_WIDE(dir, ...)                                                                   \
   switch ((a.ld + 255) / 256) {                                                              \
-    case 1: SNN_WIDE_CASE(dir, 1, __VA_ARGS__);                                              \
     case 2: SNN_WIDE_CASE(dir, 2, __VA_ARGS__);                                              \
     case 3: SNN_WIDE_CASE(dir, 3, __VA_ARGS__);                                              \
     case 4: SNN_WIDE_CASE(dir, 4, __VA_ARGS__);                                              \

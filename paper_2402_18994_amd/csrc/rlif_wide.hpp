@@ -40,7 +40,7 @@ struct RlifWide {
   static constexpr int NB = 64, SB = 16;                  // neurons and samples of a workgroup
   static constexpr int MAXN = 2048;                       // widest layer
   static constexpr int SLOTS = 32;                        // workgroups per XCD
-  static constexpr int GROUPS = 64;                       // most groups (layers of more than 192 neurons)
+  static constexpr int GROUPS = 8 * (SLOTS / 5);          // most groups (layers of 257 neurons have five members)
   // exchange space: abort flag, member flags [group][32] (reverse), words [parity][group][sample][2 members]
   // (forward), g [parity][group][member][sample][64] (reverse)
   static constexpr size_t FLAGS = 256, FLAG_BYTES = GROUPS * SLOTS * 4;
@@ -71,7 +71,7 @@ struct RlifWideArgs {
   int step;                                               // the step of a launch of one
 };
 
-static bool rlif_wide_layer(int ld) { return ld > 192 && ld <= RlifWide::MAXN; }
+static bool rlif_wide_layer(int ld) { return ld > 256 && ld <= RlifWide::MAXN; }
 hipError_t rlif_wide_forward(hipStream_t st, RlifWideArgs a, int cus, bool persist);
 hipError_t rlif_wide_reverse(hipStream_t st, RlifWideArgs a, int cus, bool persist);
 

@@ -662,12 +662,8 @@ hipError_t lif_fwd_launch(snn_ctx *c, Layer &y) {
 }
 
 // A recurrent layer on rounded weights that is too wide for one workgroup and not wider than 2048 neurons
-// runs on groups of workgroups (rlif_wide.hpp), all steps in a launch (SNN_OPT_RLIF_PERSIST = 0: one).
-// Layers that fit a workgroup have nothing to exchange and take this path only where a test asks for
-// its waits to fail.
-bool rlif_wide(const snn_ctx *c, const Layer &y) {
-  return y.rp_space && (!rlif_tile_fits(y.ld) || c->opt[SNN_OPT_WAIT_FAULT]);
-}
+// has exchange space and runs on groups of workgroups (rlif_wide.hpp), all steps in a launch (SNN_OPT_RLIF_PERSIST = 0:
+// one).
 RlifWideArgs rlif_wide_args(snn_ctx *c, Layer &y) {
   RlifWideArgs a;
   memset(&a, 0, sizeof a);
@@ -683,7 +679,7 @@ int launch_lif_forward(snn_ctx *c, int l) {
   Layer &y = c->layers[l];
   if (y.recurrent) {
     Bracket br(c, SNN_K_RLIF_FORWARD, l + 1);
-    if (rlif_wide(c, y)) {
+    if (y.rp_space) {
       RlifWideArgs a = rlif_wide_args(c, y);
       a.X = y.I; a.V = y.V; a.S = y.S; a.R = y.QRf;
       HIPCHK(c, rlif_wide_forward(c->stream, a, c->cus, c->opt[SNN_OPT_RLIF_PERSIST] != 0));
@@ -739,7 +735,7 @@ int launch_lif_reverse(snn_ctx *c, int l) {
   Layer &y = c->layers[l];
   if (y.recurrent) {
     Bracket br(c, SNN_K_RLIF_REVERSE, l + 1);
-    if (rlif_wide(c, y)) {
+    if (y.rp_space) {
       RlifWideArgs a = rlif_wide_args(c, y);
       a.X = y.dS; a.V = y.V; a.dI = y.dI; a.gs = y.g[0]; a.R = y.QRb; a.db_part = y.part_b;
       HIPCHK(c, rlif_wide_reverse(c->stream, a, c->cus, c->opt[SNN_OPT_RLIF_PERSIST] != 0));

@@ -349,18 +349,18 @@ def test_weight_gradients_of_fp32_and_narrow_layers_through_transposing_reads(T,
     assert (np.abs(grads[0][0] - ref) <= T * B * 2.0 ** -24 * mag + 1e-30).all()
 
 
-@pytest.mark.parametrize("T,B,sizes,rec", [(37, 40, (50, 256, 10), (True,)),
+@pytest.mark.parametrize("T,B,sizes,rec", [(37, 40, (50, 320, 10), (True,)),
                                             (20, 33, (64, 512, 250, 10), (True, True)),
-                                            (2, 5, (30, 256, 10), (True,)),
+                                            (2, 5, (30, 264, 10), (True,)),
                                             (64, 32, (90, 768, 20), (True,)),
-                                            (30, 20, (40, 200, 10), (True,))],
-                         ids=["two-sample-tiles", "two-layers-one-narrower", "single-step", "three-quarters-of-a-thousand",
+                                            (30, 20, (40, 300, 10), (True,))],
+                         ids=["three-sample-tiles", "two-layers-one-narrower", "single-step", "three-quarters-of-a-thousand",
                               "fewer-publishers-than-words"])
 def test_wide_recurrent_forward_in_one_launch(T, B, sizes, rec):
-    """The forward time loop of a recurrent layer wider than 128 neurons as one launch (weights resident
-    in LDS, spikes exchanged as bits through memory, a counter per sample tile; SNN_OPT_RLIF_PERSIST = 1)
+    """The forward time loop of a recurrent layer of more than 256 neurons as one launch (rows of R in registers,
+    spikes exchanged as bits through memory, in words that carry their step; SNN_OPT_RLIF_PERSIST = 1)
     against the oracle, and bit for bit against the launch per step (0): sample tiles with a ragged
-    tail, several neuron tiles per sample tile, a second recurrent layer whose width does not qualify,
+    tail, several members per sample tile, a second recurrent layer that fits a workgroup,
     the shortest raster, run twice on one context."""
     L = len(sizes) - 1
     wl = workloads.Workload(name="rlif-persist", index=23, T=T, B=B, sizes=sizes, recurrent=rec,
@@ -501,7 +501,7 @@ def test_wide_recurrent_forward_wait_times_out():
     2^4 polls, the grid drains, and the call that reads the error word reports SNN_ERR_HIP; the
     context works again afterwards."""
     from paper_2402_18994_amd.binding import SnnError
-    wl = workloads.Workload(name="rlif-persist-fault", index=24, T=12, B=40, sizes=(50, 256, 10), recurrent=(True,),
+    wl = workloads.Workload(name="rlif-persist-fault", index=24, T=12, B=40, sizes=(50, 300, 10), recurrent=(True,),
                             beta=(0.9, 0.93), theta=1.0, surrogate="superspike", slope=10.0, precision="bf16",
                             rate_lo=0.03, rate_hi=0.12, loss="max")
     inp = workloads.generate(wl, w_gain=2.0)
@@ -518,6 +518,36 @@ def test_wide_recurrent_forward_wait_times_out():
     loss0 = snn.forward(inp.X, inp.labels)
     assert np.array_equal(snn.get_tensor("spikes", 1), good[0]) and loss0 == good[1]
     snn.destroy()
+
+
+def test_wide_recurrent_reverse_wait_times_out():
+    """The same for the flags that the reverse loop waits for: the backward pass is enqueued, its grid drains, the
+    next call that reads the error word reports SNN_ERR_HIP, and the step after that is a good one."""
+    from paper_2402_18994_amd.binding import SnnError
+    wl = workloads.Workload(name="rlif-reverse-fault", index=24, T=12, B=40, sizes=(50, 300, 10), recurrent=(True,),
+                            beta=(0.9, 0.93), theta=1.0, surrogate="superspike", slope=10.0, precision="bf16",
+                            rate_lo=0.03, rate_hi=0.12, loss="max")
+    inp = workloads.generate(wl, w_gain=2.0)
+    grads = []
+    for knob in (1, 0):
+        snn = make(wl, inp, {"rlif_persist": knob})
+        if knob:
+            snn.forward(inp.X, inp.labels)
+            snn.set_option("wait_fault", 1)
+            snn.set_option("wait_limit_log2", 4)
+            snn.backward()
+            with pytest.raises(SnnError) as e:
+                snn.get_tensor("d_current", 1)
+            assert e.value.status == 6 and "waiting" in str(e.value)
+            snn.set_option("wait_fault", 0)
+            snn.set_option("wait_limit_log2", 18)
+        snn.forward(inp.X, inp.labels)
+        snn.backward()
+        grads.append([snn.get_tensor("d_current", 1), snn.get_tensor("grad_r", 1)])
+        snn.destroy()
+    assert np.abs(grads[0][0]).max() > 0
+    for a, b in zip(*grads):
+        assert np.array_equal(a, b)
 
 
 @pytest.mark.parametrize("name,T,B", [("shd_ff128", 128, 32), ("shd_rec128", 40, 32), ("wide-rec", 24, 64)],
