@@ -981,13 +981,11 @@ def test_shd_ff128_fp32_products():
 # ---------------------------------------------------------------- recurrent layers
 @pytest.mark.parametrize("precision", ["fp32", "bf16"])
 def test_recurrent_both_sample_tilings(precision):
-    """Narrow recurrent layers whose rows are a multiple of 16 neurons run on tiles of 16 samples
-    (eight wavefronts of 16 neurons, V_t and S_t stored as whole rows through LDS); other widths
-    run the forward pass on tiles of 32 samples with stores from the accumulator layout.  Layers
-    of 96 and 128 neurons, then 72 and 40; a batch of 45 (tails of 13 samples in either tiling),
-    37 steps (both buffers of the stage, odd tail)."""
-    for sizes in ((60, 96, 128, 10), (60, 72, 40, 10)):
-        wl = workloads.Workload(name="rec_tiles", index=28, T=37, B=45, sizes=sizes, recurrent=(True, True),
+    """Narrow recurrent layers on tiles of four samples, and of sixteen where the batch is large, a tail of one
+    and of five samples.  Layers of 96 and 128 neurons, then 72 and 40; 37 steps (both buffers of the
+    exchange, more than the steps in flight, an odd tail), 11 in the large batch."""
+    for sizes, T, B in (((60, 96, 128, 10), 37, 45), ((60, 72, 40, 10), 37, 45), ((60, 96, 72, 10), 11, 2053)):
+        wl = workloads.Workload(name="rec_tiles", index=28, T=T, B=B, sizes=sizes, recurrent=(True, True),
                                 beta=(0.9, 0.92, 0.95), theta=1.0, surrogate="superspike", slope=25.0,
                                 precision=precision, rate_lo=0.05, rate_hi=0.2, rec_gain=1.0)
         rep = full_step_parity(wl, w_gain=2.0)
@@ -1032,22 +1030,39 @@ def test_recurrent_small(precision):
 
 @pytest.mark.parametrize("surrogate", ["boxcar", "ste"])
 def test_recurrent_other_surrogates(surrogate):
-    """The surrogates that the other recurrent cases do not use, on both recurrent code paths."""
-    for sizes, T, B in (((50, 40, 5), 30, 10), ((60, 168, 5), 21, 11)):
+    """The surrogates that the other recurrent cases do not use, on a workgroup with one and with more than
+    four wavefronts, and on groups of workgroups."""
+    for sizes, T, B in (((50, 40, 5), 30, 10), ((60, 168, 5), 21, 11), ((60, 300, 5), 21, 11)):
         wl = workloads.Workload(name="rec_surr", index=23, T=T, B=B, sizes=sizes, recurrent=(True,),
                                 beta=(0.9, 0.9), theta=1.0, surrogate=surrogate, slope=1.0,
                                 precision="bf16", rate_lo=0.05, rate_hi=0.2, rec_gain=1.0)
         full_step_parity(wl, w_gain=2.5, check_sgd=False)
 
 
+@pytest.mark.parametrize("width", [168, 300])
 @pytest.mark.parametrize("precision", ["fp32", "bf16"])
-def test_recurrent_wider_than_one_workgroup(precision):
-    """A recurrent layer of more than 128 neurons walks time with one launch per step; an odd
-    number of steps and a partial batch tile on the side."""
-    wl = workloads.Workload(name="rec_wide", index=15, T=21, B=11, sizes=(60, 168, 5), recurrent=(True,),
+def test_recurrent_wider_than_one_workgroup(precision, width):
+    """A recurrent layer of more than 256 neurons does not fit a workgroup: groups of them with rounded weights,
+    one launch per step in fp32 (and 168 neurons, which do fit); an odd number of steps and a partial
+    batch tile on the side."""
+    wl = workloads.Workload(name="rec_wide", index=15, T=21, B=11, sizes=(60, width, 5), recurrent=(True,),
                             beta=(0.9, 0.9), theta=1.0, surrogate="arctan", slope=2.0,
                             precision=precision, rate_lo=0.05, rate_hi=0.2, rec_gain=1.0)
     rep = full_step_parity(wl, w_gain=2.5)
+    assert rep["spike_rate"][0] > 0.01
+
+
+@pytest.mark.parametrize("surrogate", ["superspike", "arctan", "sigmoid", "triangular", "boxcar", "ste"])
+@pytest.mark.parametrize("precision,T,B,width", [("fp32", 6, 35, 258), ("bf16", 4, 5, 2056)])
+def test_recurrent_layers_of_a_launch_per_step(precision, T, B, width, surrogate):
+    """Layers too wide for a workgroup in fp32, and for the groups of workgroups (2048 neurons) with rounded weights: a
+    launch per step in each direction, whose every surrogate no other case reaches, with the decays
+    trained; two tiles of 32 samples, and a last block of 32 neurons that holds two or eight."""
+    wl = workloads.Workload(name="rec_step", index=38, T=T, B=B, sizes=(40, width, 5), recurrent=(True,),
+                            beta=(0.9, 0.93), theta=1.0, surrogate=surrogate,
+                            slope=1.0 if surrogate in ("triangular", "boxcar", "ste") else 4.0, precision=precision,
+                            rate_lo=0.1, rate_hi=0.3, loss="integral")
+    rep = beta_step_parity(wl, w_gain=1.5)[0]
     assert rep["spike_rate"][0] > 0.01
 
 
@@ -1528,8 +1543,9 @@ def test_trainable_beta_feedforward_and_wide_readout(precision):
 
 @pytest.mark.parametrize("precision", ["fp32", "bf16"])
 def test_trainable_beta_recurrent_narrow_and_wide(precision):
-    """Both recurrent code paths: the single-kernel one (N <= 128) and one launch per step."""
-    for sizes, T, B in (((50, 40, 24, 5), 31, 40), ((60, 168, 5), 21, 11)):
+    """All recurrent code paths: on one workgroup (N <= 256), on groups of them with rounded weights, and one launch
+    per step."""
+    for sizes, T, B in (((50, 40, 24, 5), 31, 40), ((60, 168, 5), 21, 11), ((60, 300, 5), 21, 11)):
         wl = workloads.Workload(name="beta_rec", index=20, T=T, B=B, sizes=sizes, recurrent=(True,) * (len(sizes) - 2),
                                 beta=(0.9,) * (len(sizes) - 1), theta=1.0, surrogate="arctan", slope=2.0,
                                 precision=precision, rate_lo=0.05, rate_hi=0.2, rec_gain=1.0)
