@@ -14,9 +14,10 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-Wall", "-Wno-unused-function"]
 # translation unit -> flags of its own
-# (kernels on page boundaries: their speed does not depend on which others are compiled in front of them; the
-# same instructions of the 700-128-128-20 step take 79.8 us where the linker puts them, 79.4 us so)
-UNITS = {"snn_api.hip": ["-Xarch_device", "-falign-functions=4096"],
+# (The speed of the short launches depends on where their code lies: the feed-forward step runs the same instructions
+# in, us at T = B = 128 / T = 128, B = 256 of 700-128-128-20: 65.1 / 76.9 where the linker puts them, 63.5 / 76.4 at
+# multiples of 1 KiB, 64.1 / 77.2 of 4 KiB, 64.0 / 77.1 of 64 KiB.)
+UNITS = {"snn_api.hip": ["-Xarch_device", "-falign-functions=1024"],
          "rlif_wide.hip": [],
          # results of MFMAs in ordinary vector registers (the time loops read them at once)
          "rlif_tile.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
