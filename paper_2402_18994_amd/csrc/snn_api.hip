@@ -99,6 +99,7 @@ struct snn_ctx {
   int wall_khz = 100000;          // rate of the device's constant clock
   int cus = 0;                    // compute units of the device
   bool wg_tall = false;           // weight-gradient products use 256 x 128 tiles
+  bool wg_narrow = false;         // weight gradients: no product of more than 32 columns, and a long one
   bool integral = false;          // integral cross-entropy instead of max over time
   bool learn_beta = false;        // decays are trained: dbeta in snn_backward, clipped update in snn_sgd_step
   const uint8_t *x_eff = nullptr;  // raster the products read: the caller's, or x_buf
@@ -228,7 +229,14 @@ void carve(snn_ctx &c, Carver &cv) {
   // Output tiles of the weight-gradient products that share one launch.  With many tiles
   // the products are large enough for 256 x 128 tiles, which move 1.7 times fewer operand
   // bytes per flop (measured 2.8 times faster at 1024-wide layers, slower at 128-wide ones).
-  auto narrow = [&](const Layer &y) { return narrow_tiles(c.M, y.K, y.N, c.precision == SNN_PREC_FP32); };
+  // (long products of few columns in the company of wider ones have splits of their own: see long_and_narrow)
+  bool any_long = false, all_narrow = true;
+  for (int l = 0; l < c.L; ++l) {
+    any_long = any_long || long_and_narrow(c.M, c.layers[l].K, c.layers[l].N, c.precision == SNN_PREC_FP32);
+    all_narrow = all_narrow && c.layers[l].N <= 32;
+  }
+  c.wg_narrow = any_long && all_narrow;
+  auto narrow = [&](const Layer &y) { return !all_narrow && long_and_narrow(c.M, y.K, y.N, c.precision == SNN_PREC_FP32); };
   auto count_tiles = [&](bool tall) {
     int n = 0;
     for (int l = 0; l < c.L; ++l) {
@@ -239,7 +247,7 @@ void carve(snn_ctx &c, Carver &cv) {
   };
   c.wg_tall = c.precision != SNN_PREC_FP32 && count_tiles(false) >= 32;
   // (the splits are laid out here, for the kernel that SNN_OPT_WGRAD_TR selects at this point)
-  const bool wg_tr = c.opt[SNN_OPT_WGRAD_TR] != 0;
+  const bool wg_tr = c.opt[SNN_OPT_WGRAD_TR] != 0 && !c.wg_narrow;
   const int wg_tiles = count_tiles(c.wg_tall && !wg_tr);
   long long wg_weights = 0, wg_row_bytes = 0;             // what the merged launch writes per split / reads per row
   for (int l = 0; l < c.L; ++l) {
@@ -495,10 +503,10 @@ struct WgradJobs {
   GemmJobs narrow, mid, wide;        // cols <= 32, <= 64, wider
 };
 
-// They go through the kernel built on transposing LDS reads (SNN_OPT_WGRAD_TR, 128 x 128 tiles: also those of
-// narrower layers, in the same launch, except long ones of at most 32 columns, see narrow_tiles), else through
-// the general one (256 x 128 tiles when there are many wide ones).
-static bool wgrad_tr(const snn_ctx *c) { return c->opt[SNN_OPT_WGRAD_TR] != 0; }
+// All of them go through the kernel built on transposing LDS reads (SNN_OPT_WGRAD_TR, 128 x 128 tiles: also
+// those of narrower layers, in the same launch; not where all are narrow and one of them is long, see
+// long_and_narrow), else through the general one (256 x 128 tiles when there are many wide ones).
+static bool wgrad_tr(const snn_ctx *c) { return c->opt[SNN_OPT_WGRAD_TR] != 0 && !c->wg_narrow; }
 static bool wgrad_tall(const snn_ctx *c) { return c->wg_tall && !wgrad_tr(c); }
 
 int flush_tn(snn_ctx *c, WgradJobs &w, int which) {
@@ -537,8 +545,7 @@ int queue_tn(snn_ctx *c, WgradJobs &w, SpikeSrc s, int rows, const void *G, int 
   a.kc_per_split = (int)per;
   a.c_split_stride = (long long)rows * cols;
   a.C = splits > 1 ? part : out;
-  const bool tr = wgrad_tr(c) && !narrow_tiles(c->M, rows, cols, c->precision == SNN_PREC_FP32);
-  const int which = tr || cols > 64 ? 2 : cols <= 32 ? 0 : 1;
+  const int which = wgrad_tr(c) || cols > 64 ? 2 : cols <= 32 ? 0 : 1;
   GemmJobs &list = which == 0 ? w.narrow : which == 1 ? w.mid : w.wide;
   if (list.njobs == SNN_GEMM_MAX_JOBS) {
     int rc = flush_tn(c, w, which);
@@ -1659,7 +1666,7 @@ int32_t snn_weight_grad_static(const uint8_t *S_dev, const float *G_dev, float *
   // reads it, so nothing has to be cleared between calls.
   const long long weights = (long long)K * N;
   long long per = 0;
-  const bool narrow = narrow_tiles(M, K, N, true);
+  const bool narrow = long_and_narrow(M, K, N, true);
   int splits = choose_splits(M, wgrad_tiles(K, N, false), weights, K + 4ll * N, &per, !narrow);
   if (M <= 384) { splits = 1; per = round_up(M, 64); }             // (the reduction is a launch of its own: 256 rows 8.9 us instead of 11.2)
   const long long fit = (long long)SNN_STATIC_SCRATCH_BYTES / (weights * 4);

@@ -72,13 +72,16 @@ inline int wgrad_tiles(int rows, int cols, bool tall) {
 }
 
 // A product of at most 32 columns: three of the four wavefronts of a 128-column tile multiply nothing, which shows
-// once it takes longer than a launch.  Tiles of 128 x 32 of the general kernel then, in a launch of their own.  One
-// product alone, fp32, 512 x 16: T*B = 16384 13.4 us with the wide tile and 14.4 with the narrow one, 32768 18.4 and
-// 16.8, 262144 84.3 and 71.1; 100 x 16, one tile: 29.3 and 29.3 at 262144.  Rounded weights take two pieces instead
-// of three: the step of 700-32-20 at 131072 126.6 us and 124.8, 700-32-10 at 262144 257 and 239.
-inline bool narrow_tiles(long long M, int rows, int cols, bool fp32) {
+// once it takes longer than a launch.  Alone it takes tiles of 128 x 32 of the general kernel then: fp32, 512 x 16:
+// T*B = 16384 13.4 us with the wide tile and 14.4 with the narrow one, 32768 18.4 and 16.8, 262144 84.3 and 71.1; 100 x 16,
+// one tile: 29.3 and 29.3 at 262144; the step of 700-32-10 on rounded weights (two pieces a word instead of
+// three) at 262144 254 us and 239, at 131072 (700-32-20) 126.7 and 124.3.  Beside wider products it stays in their launch, but
+// with splits as if alone, for two workgroups a compute unit: steps of 700-512-20 in fp32 at 131072 938 us with
+// the launch's splits, 904 with its own, 917 in a launch of its own; 700-2048-20 on rounded weights at 65536 1185,
+// 1153 and 1180.
+inline bool long_and_narrow(long long M, int rows, int cols, bool fp32) {
   const long long t = (rows + 127) / 128;
-  return cols <= 32 && t >= 2 && t * M >= (fp32 ? 1 << 17 : 1 << 20);
+  return cols <= 32 && t >= 2 && t * M >= (fp32 ? 1 << 17 : 3 << 18);
 }
 
 }  // namespace snn

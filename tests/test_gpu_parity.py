@@ -313,14 +313,15 @@ def test_weight_gradients_through_transposing_reads(T, B, sizes, rec, packed):
                                                           (50, 24, (140, 48, 10), "bf16", True),
                                                           (70, 31, (36, 60, 33, 10), "bf16", False),
                                                           (31, 2120, (132, 8, 4), "fp32", False),
+                                                          (31, 2120, (132, 8, 40), "fp32", False),
                                                           (62, 8464, (132, 7, 4), "bf16", True)],
                          ids=["short-splits", "less-than-a-stage", "ragged", "packed", "narrow-packed-bf16", "narrow-bf16",
-                              "long-narrow", "long-narrow-packed-bf16"])
+                              "long-narrow", "long-narrow-beside-wide", "long-narrow-packed-bf16"])
 def test_weight_gradients_of_fp32_and_narrow_layers_through_transposing_reads(T, B, sizes, precision, packed):
     """The same kernel on fp32 current gradients (split in three bfloat16 pieces as they leave LDS) and
-    on layers of at most 64 columns, against the general kernel on the same current gradients; products
-    of at most 32 columns that are long enough for the general kernel's narrow tiles by default (both runs
-    then take them: the definition below is the check)."""
+    on layers of at most 64 columns, against the general kernel on the same current gradients; long products of
+    at most 32 columns, which take the general kernel's narrow tiles by default (both runs then: the
+    definition below is the check), or beside a wider one splits of their own."""
     L = len(sizes) - 1
     wl = workloads.Workload(name="wgrad-tr-32", index=22, T=T, B=B, sizes=sizes, recurrent=(False,) * (L - 1),
                             beta=(0.9, 0.93, 0.95)[:L], theta=1.0, surrogate="superspike", slope=10.0, precision=precision,
