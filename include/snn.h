@@ -231,8 +231,10 @@ typedef enum {
  *                     into LDS as they lie in memory and reads the MFMA fragments from there
  *                     transposed; 0: the general product kernel, which transposes in registers
  *   RLIF_PERSIST      1 (default): the time loops of a recurrent layer of 257 to 2048 neurons on rounded
- *                     weights run as ONE launch each, groups of workgroups exchanging spikes and gradients
- *                     through memory (launches of this kind are ordered one behind the other on a device,
+ *                     weights take all steps in a launch, groups of workgroups exchanging spikes and gradients
+ *                     through memory: one launch for as many tiles of 16 samples as the chip holds groups
+ *                     (128 samples at 2048 neurons, 768 at 320), the next one behind it (launches of this
+ *                     kind are ordered one behind the other on a device,
  *                     whatever streams of the process they are on; a wait that times out after about a
  *                     second is reported as SNN_ERR_HIP); 0, and on a stream that is being captured,
  *                     where they could not be ordered: a launch per step, the same bits

@@ -1,10 +1,10 @@
 // Recurrent LIF layers: V_{t+1} = beta V_t + I_t + S_t R - theta S_t, with S_t the spikes
 // just emitted from V_t (R is [from][to]).  Every step needs all N spikes of a sample from
 // the step before.  Layers of up to 256 neurons run their whole time loop in one kernel
-// (rlif_tile.hpp).  Wider layers walk time on the host side of
-// the stream: one launch per step, each a [B x N] x [N x N] MFMA product whose epilogue
-// applies the LIF update (forward) or the surrogate-gradient recursion (reverse); stream
-// order is the inter-step barrier.
+// (rlif_tile.hpp), those of up to 2048 on rounded weights on groups of workgroups (rlif_wide.hpp).  The others walk
+// time on the host side of the stream: one launch per step, each a [B x N] x [N x N] MFMA product
+// whose epilogue applies the LIF update (forward) or the surrogate-gradient recursion (reverse);
+// stream order is the inter-step barrier.
 #pragma once
 #include "gemm.hpp"
 #include "rlif_tile.hpp"
@@ -19,8 +19,8 @@ static hipError_t fill_zero(hipStream_t st, void *p, size_t bytes) {
   return hipGetLastError();
 }
 
-// ---------------------------------------------------------------- wide layers: one launch per step
-// Wider layers do not fit a workgroup, so time is walked on the host side of the stream and
+// ---------------------------------------------------------------- the widest, and fp32 above 256: one launch per step
+// These layers do not fit a workgroup, so time is walked on the host side of the stream and
 // stream order is the inter-step barrier.  One step is the transposed product (S_t R)^T = R^T S_t^T,
 // tiled 32 neurons x 32 samples per workgroup; the four wavefronts split the
 // contraction and add their accumulators through LDS, after which wavefront w applies the

@@ -1,5 +1,6 @@
 // Time loops of recurrent layers too wide for one workgroup, on rounded weights (up to 2048 neurons):
-// V_{t+1} = beta V_t + I_t + S_t R - theta S_t, and the reverse recursion, each in ONE launch.
+// V_{t+1} = beta V_t + I_t + S_t R - theta S_t, and the reverse recursion, all steps in a launch (one for every
+// 8 * (32 / members of a group) tiles of the batch).
 //
 // A tile of 16 samples belongs to a group of workgroups on ONE XCD: member m owns neurons 64 m .. 64 m + 63,
 // keeps their rows of R in registers for all steps (eight wavefronts, each an eighth of the
@@ -41,8 +42,8 @@ struct RlifWide {
   static constexpr int MAXN = 2048;                       // widest layer
   static constexpr int SLOTS = 32;                        // workgroups per XCD
   static constexpr int GROUPS = 8 * (SLOTS / 5);          // most groups (layers of 257 neurons have five members)
-  // exchange space: abort flag, member flags [group][32] (reverse), words [parity][group][sample][2 members]
-  // (forward), g [parity][group][member][sample][64] (reverse)
+  // exchange space: abort flag, member flags [group][32] (reverse), words [parity][group][member][sample][2]
+  // (forward), g [parity][group][member][half of the neurons][16-neuron piece][4-neuron group][sample][4] (reverse)
   static constexpr size_t FLAGS = 256, FLAG_BYTES = GROUPS * SLOTS * 4;
   static constexpr size_t WORDS = FLAGS + FLAG_BYTES, WORD_BYTES = 2ull * 256 * SB * 2 * 8;
   static constexpr size_t G = WORDS + WORD_BYTES, G_BYTES = 2ull * 256 * SB * NB * 4;

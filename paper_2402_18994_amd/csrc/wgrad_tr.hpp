@@ -1,7 +1,7 @@
-// Weight gradients dW = S^T dI on rounded-weight products, with the transposing LDS reads of
-// gfx950: C[k][n] = sum_m S[m][k] G[m][n], contraction over the T*B rows m, the slow axis of both
-// operands (S: 0/1 spike bytes [m][K]; G: current gradients, one dword per element holding a
-// bfloat16 hi (low half) and lo (high half)).
+// Weight gradients dW = S^T dI with the transposing LDS reads of gfx950: C[k][n] = sum_m S[m][k] G[m][n],
+// contraction over the T*B rows m, the slow axis of both operands (S: 0/1 spike bytes [m][K]; G: current
+// gradients, one dword per element holding a bfloat16 hi (low half) and lo (high half), as rounded-weight products
+// leave them, or plain fp32, see F32 at wgrad_tr_body).
 //
 // The general kernel (gemm.hpp) transposes 8 x 4 byte blocks and 8 x 2 word blocks in registers on
 // their way to LDS: about 110 ALU instructions and 16 LDS writes per wavefront and 64 rows between its
