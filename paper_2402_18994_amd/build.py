@@ -18,6 +18,7 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
 # in, us at T = B = 128 / T = 128, B = 256 of 700-128-128-20: 65.1 / 76.9 where the linker puts them, 63.5 / 76.4 at
 # multiples of 1 KiB, 64.1 / 77.2 of 4 KiB, 64.0 / 77.1 of 64 KiB.)
 UNITS = {"snn_api.hip": ["-Xarch_device", "-falign-functions=1024"],
+         "layer_forward.hip": ["-Xarch_device", "-falign-functions=1024"],
          "rlif_wide.hip": [],
          # results of MFMAs in ordinary vector registers (the time loops read them at once)
          "rlif_tile.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}

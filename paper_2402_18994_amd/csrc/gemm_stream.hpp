@@ -113,7 +113,10 @@ struct SpikeTile {
   // in LDS for all stages, ahead of the stages, which then hold Q alone.  A row pitch of 1088 bytes
   // puts the four packed rows a fragment read touches on different banks.
   static constexpr int PKP = 1088, PKB = ((BM / 8) * PKP + 1023) / 1024 * 1024;   // (the stages behind it start on a KiB)
-  static constexpr int lds_bytes(bool pk) { return pk ? PKB + NS * QT : NS * ST; }
+  // (three planes of Q, run_planes: three buffers of Q, two of P)
+  static constexpr int lds_bytes(bool pk, int planes = 1) {
+    return planes == 3 ? (pk ? PKB : 2 * PT) + 3 * QT : pk ? PKB + NS * QT : NS * ST;
+  }
 
   // Where a row's 16-byte pieces sit inside the row in LDS: piece c of row r at slot c ^ swz(r), so
   // that the fragment reads (32 consecutive rows, the same piece) touch every bank equally: the LDS
@@ -361,6 +364,180 @@ struct SpikeTile {
       acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, pend.q[j]), pend.af[i], acc[i][j], 0, 0, 0);
     });
     // The loads beyond the range wrote zeros: they too are over before the buffers are reused.
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    lds_barrier();
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[i][j][r] *= 0.5f;
+  }
+
+  // The same product with Q in three bfloat16 planes (fp32 weights; plane p starts p * plane bytes
+  // into the buffer).  A stage is one plane of 64 contraction elements: the stages of a round are
+  // the three planes of the same elements, so P is loaded, read and converted once per round (its
+  // fragments stay in registers, 8 TM dwords per MFMA step) and has two buffers by parity of the
+  // round, and every stage finds its plane in the Q buffer of the same number.
+  // What bounds it is the ingest of the planes: 56 KB per 64 contraction elements where one plane
+  // takes 24.
+  template <bool PK = false>
+  static __device__ __forceinline__ void run_planes(char *lds, const u32x4 rp, const u32x4 rq, const int (&pv)[PI],
+                                                    const int (&qv)[QI], const unsigned plane, const int nk,
+                                                    const int wave, const int lane, f32x16 (&acc)[TM][TN],
+                                                    const PackedRows *pk = nullptr) {
+    static_assert(NS == 3 && KS == 64, "a stage per plane");
+    const int wm = wave / WN, wn = wave % WN;
+    constexpr int PIK = PK ? 0 : PI;
+    constexpr int M = TM * TN, SLOTS = 4 * M;       // MFMAs per step, per stage
+    char *const qbuf = lds + (PK ? PKB : 0), *const pbuf = qbuf + 3 * QT;
+    const unsigned q0 = (unsigned)(uintptr_t)(lds_ptr_t)qbuf, p0 = (unsigned)(uintptr_t)(lds_ptr_t)pbuf;
+    constexpr int PKN = BM / 32;
+    u32x4 pkx[PKN];
+    if (PK) {
+      const int tid = 64 * wave + lane;
+#pragma unroll
+      for (int j = 0; j < PKN; ++j) {
+        const int piece = tid + 256 * j, r = piece >> 6, c = (piece & 63) * 16;
+        pkx[j] = ld_b128(pk->rsrc, r < pk->rows && c < pk->kbytes ? r * pk->row_stride + c : OOB, pk->base);
+      }
+    }
+    // Load n of plane pl of round kt (P first, with plane 0).  Beyond the last round the descriptors get
+    // size 0: the waits count on every instruction.
+    struct IssueRegs { u32x4 p, q; unsigned pd, qd; int ko, qo; };
+    auto prepare = [&](int kt_any, int pl) {
+      IssueRegs r;
+      const int kt = __builtin_amdgcn_readfirstlane(kt_any);
+      r.p = rp; r.q = rq;
+      if (kt >= nk) r.p.z = r.q.z = 0;
+      r.pd = __builtin_amdgcn_readfirstlane(p0 + (kt & 1) * PT + 1024 * wave);
+      r.qd = __builtin_amdgcn_readfirstlane(q0 + pl * QT + 1024 * wave);
+      r.ko = kt * KS;
+      r.qo = __builtin_amdgcn_readfirstlane((int)(kt * 2 * KS + pl * plane));
+      return r;
+    };
+    auto load = [&](const IssueRegs &r, int np, int n) {      // np: P loads among them
+      if (n < np) load_to_lds_b128(r.p, r.pd + 4096 * n, pv[n < PI ? n : 0], r.ko);
+      else if (n - np < QI) load_to_lds_b128(r.q, r.qd + 4096 * (n - np), qv[n - np < QI ? n - np : 0], r.qo);
+    };
+    auto issue = [&](int kt, int pl) {
+      const IssueRegs r = prepare(kt, pl);
+      const int np = pl == 0 ? PIK : 0;
+#pragma unroll
+      for (int n = 0; n < PI + QI; ++n) load(r, np, n);
+    };
+
+    const int h = lane >> 5;
+    int fa[UPL], fb[SPS];
+    {
+      const int ra = wm * TM * 32 + (lane & 31), rb = wn * TN * 32 + (lane & 31);
+#pragma unroll
+      for (int e = 0; e < UPL; ++e)
+        fa[e] = PK ? (ra >> 3) * PKP + (KS / 2) * h + 16 * e : ra * KS + (((UPL * h + e) ^ swz_p(ra)) << 4);
+#pragma unroll
+      for (int st = 0; st < SPS; ++st) fb[st] = rb * 2 * KS + (((SPS * h + st) ^ swz_q(rb)) << 4);
+    }
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+
+    const unsigned pk_rot = (unsigned)(1 - (lane & 7)) & 31u;
+    bf16x8 af[SPS][TM];                             // the round's spikes, doubled (see run)
+    frag_t pend[TN];                                // Q of the stage before's last step
+#pragma unroll
+    for (int sp = 0; sp < SPS; ++sp)
+#pragma unroll
+      for (int i = 0; i < TM; ++i) af[sp][i] = __builtin_bit_cast(bf16x8, frag_t{0u, 0u, 0u, 0u});
+#pragma unroll
+    for (int j = 0; j < TN; ++j) pend[j] = frag_t{0u, 0u, 0u, 0u};
+
+    // The stage of plane pl (buffer pl): MFMA slot k is the last step of the stage before, then steps 0 to
+    // 2; its own last step is left to the next stage.
+    auto stage = [&](auto PL, int kt) {
+      constexpr int pl = decltype(PL)::value;
+      // the loads of the next stage may still be in flight
+      asm volatile("s_waitcnt vmcnt(%0)" ::"n"(QI + (pl == 2 ? PIK : 0)) : "memory");
+      lds_barrier();
+      const char *const qs = qbuf + pl * QT, *const ps = pbuf + (kt & 1) * PT;
+      frag_t q[2][TN], pa[TM][UPL];
+      auto read_q = [&](int sp) {
+#pragma unroll
+        for (int j = 0; j < TN; ++j) q[sp & 1][j] = *(const frag_t *)(qs + fb[sp] + j * 64 * KS);
+      };
+      auto conv = [&](int sp, int i) {
+        const frag_t w = pa[i][sp >> 1];
+        uint32_t t0 = w[2 * (sp & 1)], t1 = w[2 * (sp & 1) + 1];
+        if (PK) {
+          t0 = __builtin_amdgcn_alignbit(t0, t0, pk_rot) & 0x40404040u;
+          t1 = __builtin_amdgcn_alignbit(t1, t1, pk_rot) & 0x40404040u;
+        } else {
+          t0 <<= 6;
+          t1 <<= 6;
+        }
+        u32x4 d;
+        d.x = __builtin_amdgcn_perm(0u, t0, 0x010C000Cu);
+        d.y = __builtin_amdgcn_perm(0u, t0, 0x030C020Cu);
+        d.z = __builtin_amdgcn_perm(0u, t1, 0x010C000Cu);
+        d.w = __builtin_amdgcn_perm(0u, t1, 0x030C020Cu);
+        asm volatile("" : "+v"(d));
+        af[sp][i] = __builtin_bit_cast(bf16x8, d);
+      };
+      // what the next stage but one needs: plane pl + 2 of this round, or of the next
+      constexpr int npl = (pl + 2) % 3, np = npl == 0 ? PIK : 0, nl = np + QI;
+      IssueRegs ir;
+      static_for<SLOTS>([&](auto K) {
+        constexpr int k = decltype(K)::value, step = k / M, i = (k % M) / TN, j = k % TN;
+        if constexpr (step == 0) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, pend[j]), af[SPS - 1][i], acc[i][j], 0, 0, 0);
+        else acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, q[(step - 1) & 1][j]), af[step - 1][i], acc[i][j], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (k == 0) {
+          if constexpr (pl == 0) {
+#pragma unroll
+            for (int x = 0; x < TM; ++x)
+#pragma unroll
+              for (int e = 0; e < UPL; ++e)
+                pa[x][e] = PK ? *(const frag_t *)(lds + fa[e] + x * 4 * PKP + kt * KS) : *(const frag_t *)(ps + fa[e] + x * 32 * KS);
+          }
+          read_q(0);
+          ir = prepare(kt + (pl == 0 ? 0 : 1), npl);
+        }
+        if constexpr (k >= 1 && k < 1 + (nl + 1) / 2) { load(ir, np, 2 * (k - 1)); if constexpr (2 * (k - 1) + 1 < nl) load(ir, np, 2 * (k - 1) + 1); }
+        // the spikes of step s are formed in the step's place in the MFMA order, one row tile per slot
+        if constexpr (pl == 0 && step < 4 && k % M >= M - TM) {
+          if constexpr (step == 0) conv(0, k % M - (M - TM));
+          else conv(step, k % M - (M - TM));
+        }
+        if constexpr (k == M - 1 + 1) read_q(1);
+        if constexpr (k == 2 * M) read_q(2);
+        if constexpr (k == 3 * M) read_q(3);
+        __builtin_amdgcn_sched_barrier(0);
+      });
+#pragma unroll
+      for (int j = 0; j < TN; ++j) pend[j] = q[(SPS - 1) & 1][j];
+    };
+
+    issue(0, 0);
+    issue(0, 1);
+    if (PK) {
+      const int tid = 64 * wave + lane;
+#pragma unroll
+      for (int j = 0; j < PKN; ++j) {
+        const int piece = tid + 256 * j;
+        *(u32x4 *)(lds + (piece >> 6) * PKP + (piece & 63) * 16) = pkx[j];
+      }
+    }
+    for (int kt = 0; kt < nk; ++kt) {
+      stage(std::integral_constant<int, 0>(), kt);
+      stage(std::integral_constant<int, 1>(), kt);
+      stage(std::integral_constant<int, 2>(), kt);
+    }
+    static_for<M>([&](auto X) {
+      constexpr int x = decltype(X)::value, i = x / TN, j = x % TN;
+      acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, pend[j]), af[SPS - 1][i], acc[i][j], 0, 0, 0);
+    });
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     lds_barrier();
 #pragma unroll

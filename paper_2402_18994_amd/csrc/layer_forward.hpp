@@ -60,27 +60,28 @@ struct LayerForwardOp {
   unsigned p_bytes;
   const uint16_t *Q;       // rounded W^T [ld or more][ldq] bfloat16, zero beyond the fan-in and fan-out
   int ldq;
-  unsigned q_bytes;
+  unsigned q_bytes, q_plane;   // all planes; bytes between planes (fp32 products: three)
+  int ld;                  // padded neurons of the layer, a multiple of 8
   float *V;                // [T*B][ld]
   uint8_t *S;              // [T*B][ld]
   const float *beta_v;     // [ld]
 };
 
 struct LayerForwardArgs {
-  // The layers of the launch, bottom up.  More than one (kernel variants NL > 1, layers of
-  // exactly 128 padded neurons): op[i + 1].P is op[i].S, and a workgroup takes its sample
+  // The layers of the launch, bottom up.  More than one (kernel variants NL > 1, layers of at
+  // most 128 padded neurons): op[i + 1].P is op[i].S, and a workgroup takes its sample
   // through all of them block by block, reading back the spikes it has just stored.
   LayerForwardOp op[2];
   float theta;             // in [2^-60, 2^26]
-  int T, B, ld;            // ld: a multiple of the workgroup's 64 or 128 neurons
+  int T, B, parts;         // parts: column blocks of 64 or 128 neurons a layer is cut in
   int nt_store;            // V and S stream past the caches
   // Readout currents J = S W_out, formed from the block's spikes while they are in LDS (only
-  // the kernel variant for a last spiking layer of exactly 128 padded neurons uses these):
+  // the kernel variant for a last spiking layer of at most 128 padded neurons uses these):
   float *J;                // [T*B][ldj], ldj a multiple of 8, at most 32
   int ldj;
-  const uint16_t *Qr;      // rounded W_out^T [32 or more rows: class][ldqr: neuron] bfloat16, zero beyond the classes
+  const uint16_t *Qr;      // W_out^T [32 or more rows: class][ldqr: neuron] bfloat16 planes, zero beyond the classes
   int ldqr;
-  unsigned qr_bytes;
+  unsigned qr_bytes, qr_plane;
   // ... and the whole readout (variants READOUT >= 2): LI scan, max over time or integral,
   // softmax cross-entropy and the readout's current gradients, as readout_loss_kernel computes them
   float *Y;                // [T*B][ldj] readout trace
@@ -90,7 +91,7 @@ struct LayerForwardArgs {
   float *loss_b;           // [B] per-sample loss
   float *dz;               // [B][ldj]
   int *err;                // flag: bit 0 = label out of range
-  uint32_t *dJ;            // [T*B][ldj] hi/lo words
+  uint32_t *dJ;            // [T*B][ldj] hi/lo words (fp32 products: fp32)
   const float *beta_r;     // [ldj] decays of the readout
   int C;                   // classes
   // Time-split variants (TS = 2): per sample SNN_HAND_BYTES of hand-over space.  Dwords 0..15:
@@ -101,6 +102,17 @@ struct LayerForwardArgs {
   uint32_t *hand;
   int epoch;
 };
+// Which variant of the kernel a launch is (layer_forward.hip).
+struct LayerForwardVariant {
+  int neurons;             // per workgroup: 64 or 128
+  int layers;              // in the launch: 1 or 2
+  int readout;             // 0, 1, 2 or 3 (see lif_layer_forward_body)
+  int planes;              // of the weights: 1 or 3
+  bool full;               // every layer fills its column blocks
+  bool packed, time_split, layer_split;
+};
+hipError_t layer_forward(hipStream_t st, const LayerForwardArgs &a, const LayerForwardVariant &v);
+
 #define SNN_HAND_BYTES 12288
 constexpr int HAND_V = 16, HAND_R = 16 + 2 * 2 * 128;      // dword offsets of the potential slots and the readout slots
 
@@ -120,6 +132,8 @@ __device__ __forceinline__ void hand_wait(const uint32_t *flag, uint32_t want, i
   }
 }
 
+// NP: planes of the weights, 1 (rounded) or 3 (fp32 products).  FULL: the launch's layers fill its column
+// blocks; else the columns past a layer's ld are computed on zero weights and not stored.
 // READOUT: 0 none; 1 the launch also forms the readout's currents J; 2 and the LI scan, the
 // maximum over time, the loss and dJ; 3 the same with the integral loss.
 //
@@ -128,7 +142,7 @@ __device__ __forceinline__ void hand_wait(const uint32_t *flag, uint32_t want, i
 // TS = 2, on the one that takes the sample's other blocks); 1 it runs the lower layer of a pair and
 // tells the workgroup of the upper layer how many 64-step chunks of its spikes have reached memory;
 // 2 it runs the upper layer and waits for the chunk of each of its blocks (see the kernel below).
-template <int TN, int NS, int READOUT, int NL, bool PACKED, int TS, int TM, int LI0, int ROLE>
+template <int TN, int NS, int READOUT, int NL, bool PACKED, int TS, int TM, int LI0, int ROLE, int NP, bool FULL>
 __device__ __forceinline__ void lif_layer_forward_body(const LayerForwardArgs &a, char *lds, float (*x_e)[8][32],
                                                        float (*x_best)[32], int (*x_tb)[32], const int b,
                                                        const int part, const int parts, const int half) {
@@ -151,7 +165,7 @@ __device__ __forceinline__ void lif_layer_forward_body(const LayerForwardArgs &a
   float beta[NL], v[NL];                              // decay and potential of neuron n0 + tid % BN, per layer
 #pragma unroll
   for (int li = 0; li < NL; ++li) {
-    beta[li] = a.op[li + LI0].beta_v[n0 + tid % BN];
+    beta[li] = FULL || n0 + tid % BN < a.op[li + LI0].ld ? a.op[li + LI0].beta_v[n0 + tid % BN] : 0.f;
     v[li] = 0.f;
   }
   const float theta = a.theta;
@@ -174,7 +188,8 @@ __device__ __forceinline__ void lif_layer_forward_body(const LayerForwardArgs &a
     const LayerForwardOp &op = a.op[li + LI0];
     const int nk = (op.kc + KS - 1) / KS;
     const u32x4 rp = raw_rsrc(op.P, op.p_bytes), rq = raw_rsrc(op.Q, op.q_bytes);
-    const rsrc_t rV = make_rsrc(op.V, (unsigned)a.T * a.B * a.ld * 4u), rS = make_rsrc(op.S, (unsigned)a.T * a.B * a.ld);
+    const int ld = FULL ? a.parts * BN : op.ld;
+    const rsrc_t rV = make_rsrc(op.V, (unsigned)a.T * a.B * ld * 4u), rS = make_rsrc(op.S, (unsigned)a.T * a.B * ld);
     int qv[QI];
 #pragma unroll
     for (int q = 0; q < QI; ++q) {
@@ -200,9 +215,11 @@ __device__ __forceinline__ void lif_layer_forward_body(const LayerForwardArgs &a
       pk.row_stride = a.B * op.ldp;
       pk.rows = ((a.T + 7) >> 3) - (t0 >> 3);
       pk.kbytes = op.ldp;
-      Tile::template run<true>(lds, rp, rq, pv, qv, nk, wave, lane, acc, &pk);
+      if constexpr (NP == 3) Tile::template run_planes<true>(lds, rp, rq, pv, qv, op.q_plane, nk, wave, lane, acc, &pk);
+      else Tile::template run<true>(lds, rp, rq, pv, qv, nk, wave, lane, acc, &pk);
     } else {
-      Tile::run(lds, rp, rq, pv, qv, nk, wave, lane, acc);
+      if constexpr (NP == 3) Tile::run_planes(lds, rp, rq, pv, qv, op.q_plane, nk, wave, lane, acc);
+      else Tile::run(lds, rp, rq, pv, qv, nk, wave, lane, acc);
     }
 
     // 2. The MFMAs take Q as their first operand, so a tile comes out transposed: the lane
@@ -227,12 +244,16 @@ __device__ __forceinline__ void lif_layer_forward_body(const LayerForwardArgs &a
     // Readout variant: W_out^T as the first MFMA operand, lane -> class (lane & 31), neurons
     // 16 kk + 8 h .. +7.  Asked for here, once per block, so that the fragments arrive under the scan
     // and do not occupy 32 registers during the products.
-    bf16x8 wr[READOUT && last ? 8 : 1];
+    bf16x8 wr[NP][READOUT && last ? BN / 16 : 1];
     if constexpr (READOUT && last) {
       const rsrc_t rQ = make_rsrc(a.Qr, a.qr_bytes);
 #pragma unroll
-      for (int kk = 0; kk < 8; ++kk)
-        wr[kk] = __builtin_bit_cast(bf16x8, ld_b128(rQ, ((lane & 31) * a.ldqr + 16 * kk + 8 * h) * 2, 0));
+      for (int pl = 0; pl < NP; ++pl)
+#pragma unroll
+        for (int kk = 0; kk < BN / 16; ++kk) {
+          const int n = 16 * kk + 8 * h;
+          wr[pl][kk] = __builtin_bit_cast(bf16x8, ld_b128(rQ, FULL || n < a.ldqr ? ((lane & 31) * a.ldqr + n) * 2 : OOB, pl * (int)a.qr_plane));
+        }
     }
 
     // 3. scan and store.  The wavefronts that hold no neuron (256 - BN threads) store what the scan
@@ -286,7 +307,7 @@ __device__ __forceinline__ void lif_layer_forward_body(const LayerForwardArgs &a
           const int p = p0 + st, row = s0 + p / VL, col = (p % VL) * 4;
           if (U * VL % NT_ == 0 || p < U * VL) {
             const u32x4 x = *(const u32x4 *)(lds + row * CP + col * 4);
-            const int vo = t0 + row < a.T ? (((t0 + row) * a.B + b) * a.ld + n0 + col) * 4 : OOB;
+            const int vo = t0 + row < a.T && (FULL || n0 + col < ld) ? (((t0 + row) * a.B + b) * ld + n0 + col) * 4 : OOB;
             if (a.nt_store) __builtin_amdgcn_raw_buffer_store_b128(x, rV, vo, 0, NT);
             else __builtin_amdgcn_raw_buffer_store_b128(x, rV, vo, 0, 0);
           }
@@ -302,9 +323,15 @@ __device__ __forceinline__ void lif_layer_forward_body(const LayerForwardArgs &a
               x[q] = (f[0] > theta ? 1u : 0u) | (f[1] > theta ? 0x100u : 0u) | (f[2] > theta ? 0x10000u : 0u) |
                      (f[3] > theta ? 0x1000000u : 0u);
             }
-            const int so = t0 + row < a.T ? ((t0 + row) * a.B + b) * a.ld + n0 + col : OOB;
+            const bool live = t0 + row < a.T;
+            const int at = ((t0 + row) * a.B + b) * ld + n0 + col;
+            const int so = live && (FULL || n0 + col + 16 <= ld) ? at : OOB;
             if (a.nt_store) __builtin_amdgcn_raw_buffer_store_b128(x, rS, so, 0, NT);
             else __builtin_amdgcn_raw_buffer_store_b128(x, rS, so, 0, 0);
+            if (!FULL && (ld & 8)) {                  // the row's last eight neurons are half a piece
+              const u32x2 x8 = {x.x, x.y};
+              st_b64(rS, live && n0 + col + 8 == ld ? at : OOB, 0, x8);
+            }
           }
         }
         if (ROLE == 1 && (s0 + U) % 64 == 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // a chunk's spikes are in the L2
@@ -326,7 +353,7 @@ __device__ __forceinline__ void lif_layer_forward_body(const LayerForwardArgs &a
       const int row = 32 * wave + (lane & 31);          // (blocks of 64 steps: the first two wavefronts)
       if (row < BM) {
 #pragma unroll
-      for (int kk = 0; kk < 8; ++kk) {
+      for (int kk = 0; kk < BN / 16; ++kk) {
         const f32x4 p0 = *(const f32x4 *)(lds + row * CP + (16 * kk + 8 * h) * 4);
         const f32x4 p1 = *(const f32x4 *)(lds + row * CP + (16 * kk + 8 * h + 4) * 4);
         u32x4 sp;
@@ -334,7 +361,9 @@ __device__ __forceinline__ void lif_layer_forward_body(const LayerForwardArgs &a
         sp.y = (p0[2] > theta ? 0x3F80u : 0u) | (p0[3] > theta ? 0x3F800000u : 0u);
         sp.z = (p1[0] > theta ? 0x3F80u : 0u) | (p1[1] > theta ? 0x3F800000u : 0u);
         sp.w = (p1[2] > theta ? 0x3F80u : 0u) | (p1[3] > theta ? 0x3F800000u : 0u);
-        jt = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wr[kk], __builtin_bit_cast(bf16x8, sp), jt, 0, 0, 0);
+#pragma unroll
+        for (int pl = NP - 1; pl >= 0; --pl)
+          jt = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wr[pl][kk], __builtin_bit_cast(bf16x8, sp), jt, 0, 0, 0);
       }
       const rsrc_t rJ = make_rsrc(a.J, (unsigned)a.T * a.B * a.ldj * 4u);
 #pragma unroll
@@ -476,7 +505,7 @@ __device__ __forceinline__ void lif_layer_forward_body(const LayerForwardArgs &a
 #pragma unroll
       for (int k = 15; k >= 0; --k) {
         hh = beta_r * hh + ((INTEGRAL ? ts0 + k < a.T : ts0 + k == tb) ? d : 0.f);
-        Ht[(16 * g + k) * JP + c] = pack_hl(hh);
+        Ht[(16 * g + k) * JP + c] = NP == 1 ? pack_hl(hh) : __float_as_uint(hh);
       }
       __syncthreads();
 #pragma unroll
@@ -497,16 +526,16 @@ __device__ __forceinline__ void lif_layer_forward_body(const LayerForwardArgs &a
 // before each block's product, which reads those spikes.  The upper layer's product, scan and
 // stores thereby run while the lower layer is still being scanned.  Only the second workgroup
 // waits, and the first has the lower id, so it is never dispatched after the one waiting for it.
-template <int TN, int NS = 3, int READOUT = 0, int NL = 1, bool PACKED = false, int TS = 1, int LS = 1>
+template <int TN, int NS = 3, int READOUT = 0, int NL = 1, bool PACKED = false, int TS = 1, int LS = 1, int NP = 1, bool FULL = true>
 __global__ __launch_bounds__(256, 2) void lif_layer_forward_kernel(const LayerForwardArgs a) {
-  static_assert(!READOUT || TN == 2, "the readout variants hold the whole layer");
-  static_assert(NL == 1 || (NL == 2 && TN == 2), "a chain of layers: whole layers of 128 neurons");
+  static_assert(NP == 1 || (NP == 3 && TS == 1 && LS == 1), "one plane of weights, or three");
+  static_assert(NL == 1 || NL == 2, "a chain of layers: whole layers");
   static_assert(TS == 1 || (TS == 2 && TN == 2), "two workgroups per sample: whole layers of 128 neurons");
   static_assert(LS == 1 || (LS == 2 && NL == 2 && TS == 1), "a pair of layers on two workgroups");
   constexpr int TM = TS == 2 ? 1 : 2;                 // blocks of 64 steps when two workgroups share a sample's blocks
   typedef SpikeTile<2, 2, TM, TN, NS> Tile;
   constexpr int BN = Tile::BN, CP = BN * 4 + 16, TILE = Tile::BM * CP;
-  constexpr int STAGES = Tile::lds_bytes(false) > Tile::lds_bytes(PACKED) ? Tile::lds_bytes(false) : Tile::lds_bytes(PACKED);
+  constexpr int STAGES = Tile::lds_bytes(false, NP) > Tile::lds_bytes(PACKED, NP) ? Tile::lds_bytes(false, NP) : Tile::lds_bytes(PACKED, NP);
   constexpr int LDS_BYTES = STAGES > TILE ? STAGES : TILE;                 // the stages share the tile's space
   static_assert(LDS_BYTES <= 80 * 1024, "two workgroups per compute unit");
   __shared__ __attribute__((aligned(16))) char lds[LDS_BYTES];
@@ -517,16 +546,16 @@ __global__ __launch_bounds__(256, 2) void lif_layer_forward_kernel(const LayerFo
   // The two workgroups of a sample part (TS = 2 or LS = 2) take ids 8 x parts apart, the one that
   // never waits for the other first.
   constexpr int WGS = TS * LS;
-  const int parts = a.ld / BN;
+  const int parts = a.parts;
   const int part = (blockIdx.x >> 3) % parts;
   const int half = WGS == 1 ? 0 : ((blockIdx.x >> 3) / parts) % WGS;
   const int b = (blockIdx.x >> 3) / (parts * WGS) * 8 + (blockIdx.x & 7);
   if (b >= a.B) return;
   if constexpr (LS == 2) {
-    if (half == 0) lif_layer_forward_body<TN, NS, 0, 1, PACKED, 1, 2, 0, 1>(a, lds, x_e, x_best, x_tb, b, part, parts, 0);
-    else lif_layer_forward_body<TN, NS, READOUT, 1, false, 1, 1, 1, 2>(a, lds, x_e, x_best, x_tb, b, part, parts, 0);
+    if (half == 0) lif_layer_forward_body<TN, NS, 0, 1, PACKED, 1, 2, 0, 1, NP, FULL>(a, lds, x_e, x_best, x_tb, b, part, parts, 0);
+    else lif_layer_forward_body<TN, NS, READOUT, 1, false, 1, 1, 1, 2, NP, FULL>(a, lds, x_e, x_best, x_tb, b, part, parts, 0);
   } else {
-    lif_layer_forward_body<TN, NS, READOUT, NL, PACKED, TS, TM, 0, 0>(a, lds, x_e, x_best, x_tb, b, part, parts, half);
+    lif_layer_forward_body<TN, NS, READOUT, NL, PACKED, TS, TM, 0, 0, NP, FULL>(a, lds, x_e, x_best, x_tb, b, part, parts, half);
   }
 }
 

@@ -312,7 +312,7 @@ void carve(snn_ctx &c, Carver &cv) {
   c.dz = cv.take<float>((size_t)c.B * c.ldC);
   c.tstar = cv.take<int>((size_t)c.B * c.ldC);
   c.hand_parts = 1;                                    // column blocks of the widest layer (64 neurons at least each)
-  for (const Layer &y : c.layers) c.hand_parts = std::max(c.hand_parts, y.ld / 64);
+  for (const Layer &y : c.layers) c.hand_parts = std::max(c.hand_parts, (y.ld + 63) / 64);
   c.hand = cv.take<uint32_t>(rup(c.B, 8) * c.hand_parts * (SNN_HAND_BYTES / 4));
   c.loss_b = cv.take<float>((size_t)c.B);
   c.loss = cv.take<float>(64);
@@ -937,17 +937,16 @@ int launch_lif_reverse_fused(snn_ctx *c, int l) {
   return SNN_OK;
 }
 
-// A feed-forward spiking layer of up to 1024 (padded) neurons, a multiple of 64, on rounded
-// weights runs as ONE launch, product and scan (lif_layer_forward_kernel): I is not stored.
-// A workgroup owns a sample and 64 or 128 neurons; 32-bit
-// byte offsets into the spikes below and V; a threshold the scan's compare-free spike
+// A feed-forward spiking layer of up to 1024 (padded) neurons runs as ONE launch, product and scan
+// (lif_layer_forward_kernel): I is not stored.  A workgroup owns a sample and 64 or 128 neurons;
+// 32-bit byte offsets into the spikes below and V; a threshold the scan's compare-free spike
 // decision is exact for.
 // Width limit (SNN_OPT_LAYER_MAX_NEURONS): the parts of a sample each pass its spike rows below
 // through their CU, which the I round trip saved outweighs up to 1024 neurons (product + scan
 // 228 -> 169 us at 700-512-512-20, 982 -> 781 us at 700-1024-1024-20, 256 steps) and no longer
 // at 2048 (1433 -> 1455 us, 512 steps, 128 samples); the same limit holds for the fan-in.
 // SNN_OPT_LAYER_FORWARD: 0 never, 1 all but the last spiking layer, 2 every such layer, 3 the last
-// one also forms the readout's currents when it has exactly 128 padded neurons, 4 (default) and
+// one also forms the readout's currents when it has at most 128 padded neurons, 4 (default) and
 // runs the readout scan, the loss and the readout's current gradients;
 // SNN_OPT_LAYER_MIN_BATCH: samples from which it is used (default: any number up to 256 steps, 64
 // for longer rasters: at the headline widths it wins from 4 samples on, having fewer launches,
@@ -960,53 +959,68 @@ bool layer_forward_fusable(snn_ctx *c, int l) {
   const Layer &y = c->layers[l];
   const int min_b = layer_min_batch(c);                  // a workgroup walks a sample's blocks of 128 steps one after the other
   const SpikeSrc s = spikes_below(c, l);
-  return c->nplanes == 1 && y.spiking && !y.recurrent && !y.adaptive && y.ld % 64 == 0 && y.ld <= layer_max_neurons(c) && c->B >= min_b &&
+  return y.spiking && !y.recurrent && !y.adaptive && y.ld <= layer_max_neurons(c) && c->B >= min_b &&
          s.ld % 4 == 0 && s.ld <= layer_max_neurons(c) && (size_t)c->M * s.ld < ((size_t)1 << 31) && (size_t)c->M * y.ld * 4 < ((size_t)1 << 31) &&
-         y.qf_plane >= (long long)y.ld * y.ldqf && c->theta >= 0x1p-60f && c->theta <= 0x1p26f;
+         c->theta >= 0x1p-60f && c->theta <= 0x1p26f;
 }
 
 // What the launch of the last spiking layer takes over from the readout: 0 nothing, 1 its
-// currents J, 2 also the LI scan, the loss and dJ (what readout_loss_kernel does).
+// currents J (rounded weights only), 2 also the LI scan, the loss and dJ (what readout_loss_kernel does).
 int layer_forward_takes_readout(snn_ctx *c) {
   const Layer &ro = c->layers[c->L - 1];
   const int mode = layer_fuse_mode(c);
-  const bool ok = c->L >= 2 && mode >= 3 && layer_forward_fusable(c, c->L - 2) && c->layers[c->L - 2].ld == 128 &&
-                  c->opt[SNN_OPT_LAYER_NEURONS] == 128 && c->ldC <= 32 && ro.qf_plane >= 32ll * ro.ldqf && ro.ldqf >= 128;
-  return !ok ? 0 : mode >= 4 && c->hl ? 2 : 1;
+  const bool ok = c->L >= 2 && mode >= 3 && layer_forward_fusable(c, c->L - 2) && c->layers[c->L - 2].ld <= 128 &&
+                  c->opt[SNN_OPT_LAYER_NEURONS] == 128 && c->ldC <= 32 && ro.qf_plane >= 32ll * ro.ldqf;
+  return !ok ? 0 : mode >= 4 ? 2 : c->nplanes == 1 ? 1 : 0;
 }
 
-// Layers l .. l + nl - 1 in one launch (nl = 2: both of exactly 128 padded neurons, a workgroup
+// Neurons per workgroup of a launch whose widest layer has ld: whichever pads less (SNN_OPT_LAYER_NEURONS =
+// 64: 64, but a launch that holds whole layers has one part).  128 at equal padding: 108.0 us per step at
+// 700-128-128-20, 64: 109.7.
+int layer_workgroup_neurons(const snn_ctx *c, int ld, bool whole) {
+  return rup(ld, 64) < rup(ld, 128) || (c->opt[SNN_OPT_LAYER_NEURONS] == 64 && !whole) ? 64 : 128;
+}
+
+// Layers l .. l + nl - 1 in one launch (nl = 2: both of at most 128 padded neurons, a workgroup
 // takes its sample through both); with_readout refers to the last of them.
 int launch_layer_forward(snn_ctx *c, int l, int nl, int with_readout, const int32_t *labels) {
-  Layer &y = c->layers[l];
   LayerForwardArgs a;
   memset(&a, 0, sizeof a);
-  const bool packed = l == 0 && c->x_direct;           // the bottom layer reads the raster packed along time
+  LayerForwardVariant v;
+  memset(&v, 0, sizeof v);
+  v.packed = l == 0 && c->x_direct;                    // the bottom layer reads the raster packed along time
+  v.planes = c->nplanes;
+  v.layers = nl;
+  int widest = 0;
   for (int i = 0; i < nl; ++i) {
     Layer &yi = c->layers[l + i];
     SpikeSrc s = spikes_below(c, l + i);
-    if (packed && i == 0) s = {c->x_packed, c->sizes[0], c->sizes[0], (unsigned)((long long)((c->T + 7) / 8) * c->B * c->sizes[0])};
+    if (v.packed && i == 0) s = {c->x_packed, c->sizes[0], c->sizes[0], (unsigned)((long long)((c->T + 7) / 8) * c->B * c->sizes[0])};
     if (!s.p) return fail(c, SNN_ERR_NULL, "input raster is NULL");
     LayerForwardOp &op = a.op[i];
     op.P = s.p; op.ldp = s.ld; op.kc = s.valid; op.p_bytes = s.bytes;
-    op.Q = yi.Qf; op.ldq = yi.ldqf; op.q_bytes = (unsigned)(yi.qf_plane * 2);
-    op.V = yi.V; op.S = yi.S; op.beta_v = yi.beta_v;
+    op.Q = yi.Qf; op.ldq = yi.ldqf; op.q_bytes = (unsigned)(c->nplanes * yi.qf_plane * 2); op.q_plane = (unsigned)(yi.qf_plane * 2);
+    op.V = yi.V; op.S = yi.S; op.beta_v = yi.beta_v; op.ld = yi.ld;
     yi.i_ready = false;
+    widest = std::max(widest, yi.ld);
   }
   a.theta = c->theta;
-  a.T = c->T; a.B = c->B; a.ld = y.ld;
-  a.nt_store = streams_past_cache(c, c->M * y.ld * 4);
+  a.T = c->T; a.B = c->B;
+  a.nt_store = streams_past_cache(c, c->M * widest * 4);
   a.err = c->err_flag;
-  const int bn = y.ld % 128 ? 64 : c->opt[SNN_OPT_LAYER_NEURONS];   // 128: 108.0 us per step at 700-128-128-20, 64: 109.7
+  v.neurons = layer_workgroup_neurons(c, widest, nl > 1 || with_readout);
+  a.parts = (widest + v.neurons - 1) / v.neurons;
+  v.full = true;
+  for (int i = 0; i < nl; ++i) v.full = v.full && a.op[i].ld == a.parts * v.neurons;
   // Two workgroups per sample, taking its blocks of 64 steps in turn (SNN_OPT_LAYER_TIME_SPLIT, on
   // request: 29.3 us against 28.8 at 700-128-128-20, T = 128, B = 256): from two blocks on, and while a
   // block count fits the flags' 10 bits.
-  const bool split = c->opt[SNN_OPT_LAYER_TIME_SPLIT] && bn == 128 && c->T > 64 && c->T <= 64 * 1000;
+  v.time_split = c->opt[SNN_OPT_LAYER_TIME_SPLIT] && v.neurons == 128 && v.full && v.planes == 1 && c->T > 64 && c->T <= 64 * 1000;
   // A pair of layers on two workgroups per sample (SNN_OPT_LAYER_PAIR = 2, on request: 32.9 us against
   // 27.7 at 700-128-128-20, T = 128, B = 256): the upper layer's workgroup follows the lower layer's,
   // 64 steps at a time.
-  const bool lsplit = nl == 2 && c->opt[SNN_OPT_LAYER_PAIR] == 2 && !split && c->T <= 64 * 1000;
-  if (split || lsplit) {
+  v.layer_split = nl == 2 && c->opt[SNN_OPT_LAYER_PAIR] == 2 && !v.time_split && v.neurons == 128 && v.full && v.planes == 1 && c->T <= 64 * 1000;
+  if (v.time_split || v.layer_split) {
     if (++c->fwd_epoch >= (1 << 21)) {                // long before the flags' counter wraps: start over
       HIPCHK(c, fill_zero(c->stream, c->hand, rup(c->B, 8) * c->hand_parts * SNN_HAND_BYTES));
       c->fwd_epoch = 1;
@@ -1015,37 +1029,22 @@ int launch_layer_forward(snn_ctx *c, int l, int nl, int with_readout, const int3
     a.epoch = c->fwd_epoch;
   }
   Bracket br(c, SNN_K_LIF_FORWARD, l + 1);
-  const dim3 grid((unsigned)(rup(c->B, 8) * (y.ld / bn) * (split || lsplit ? 2 : 1)));
-#define SNN_LFWD3(RO, PK, TS_)                                                                                   \
-  do {                                                                                                           \
-    if (lsplit) hipLaunchKernelGGL((lif_layer_forward_kernel<2, 3, RO, 2, PK, 1, 2>), grid, dim3(256), 0, c->stream, a); \
-    else if (nl == 2) hipLaunchKernelGGL((lif_layer_forward_kernel<2, 3, RO, 2, PK, TS_>), grid, dim3(256), 0, c->stream, a); \
-    else hipLaunchKernelGGL((lif_layer_forward_kernel<2, 3, RO, 1, PK, TS_>), grid, dim3(256), 0, c->stream, a); \
-  } while (0)
-#define SNN_LFWD2(RO, PK) do { if (split) SNN_LFWD3(RO, PK, 2); else SNN_LFWD3(RO, PK, 1); } while (0)
-#define SNN_LFWD(RO) do { if (packed) SNN_LFWD2(RO, true); else SNN_LFWD2(RO, false); } while (0)
   if (with_readout) {
     Layer &ro = c->layers[c->L - 1];
-    a.J = ro.I; a.ldj = c->ldC; a.Qr = ro.Qf; a.ldqr = ro.ldqf; a.qr_bytes = (unsigned)(ro.qf_plane * 2);
+    a.J = ro.I; a.ldj = c->ldC; a.Qr = ro.Qf; a.ldqr = ro.ldqf;
+    a.qr_bytes = (unsigned)(c->nplanes * ro.qf_plane * 2); a.qr_plane = (unsigned)(ro.qf_plane * 2);
+    v.readout = 1;
     if (with_readout == 2) {
       if (!labels) return fail(c, SNN_ERR_NULL, "labels are NULL");
       a.Y = ro.V; a.z = c->z; a.tstar = c->tstar; a.labels = labels; a.loss_b = c->loss_b; a.dz = c->dz;
       a.dJ = ro.dI; a.beta_r = ro.beta_v; a.C = c->C;
-      if (c->integral) SNN_LFWD(3); else SNN_LFWD(2);
+      v.readout = c->integral ? 3 : 2;
       c->dj_ready = true;
       c->loss_ready = false;
-    } else {
-      SNN_LFWD(1);
     }
     ro.i_ready = true;
-  } else if (bn == 64) {
-    if (packed) hipLaunchKernelGGL((lif_layer_forward_kernel<1, 3, 0, 1, true>), grid, dim3(256), 0, c->stream, a);
-    else hipLaunchKernelGGL((lif_layer_forward_kernel<1, 3>), grid, dim3(256), 0, c->stream, a);
-  } else SNN_LFWD(0);
-#undef SNN_LFWD
-#undef SNN_LFWD2
-#undef SNN_LFWD3
-  HIPCHK(c, hipGetLastError());
+  }
+  HIPCHK(c, layer_forward(c->stream, a, v));
   return SNN_OK;
 }
 
@@ -1416,10 +1415,10 @@ static int32_t forward_layers(snn_ctx *c, const int32_t *labels_dev, float *loss
   const bool fuse_top = !whole_top && top_forward_fusable(c);   // the last spiking layer's scan forms the readout's currents
   for (int l = 0; l < c->L; ++l) {
     if (whole >= 1 && (l < c->L - 2 || whole_top) && layer_forward_fusable(c, l)) {
-      // this layer and the next in one launch when both hold exactly 128 padded neurons
+      // this layer and the next in one launch when both hold at most 128 padded neurons
       // (SNN_OPT_LAYER_PAIR = 0: one launch each)
-      const bool pair = c->opt[SNN_OPT_LAYER_PAIR] && c->opt[SNN_OPT_LAYER_NEURONS] == 128 && c->layers[l].ld == 128 && l + 1 <= c->L - 2 &&
-                        (l + 1 < c->L - 2 || whole_top) && layer_forward_fusable(c, l + 1) && c->layers[l + 1].ld == 128;
+      const bool pair = c->opt[SNN_OPT_LAYER_PAIR] && c->opt[SNN_OPT_LAYER_NEURONS] == 128 && c->layers[l].ld <= 128 && l + 1 <= c->L - 2 &&
+                        (l + 1 < c->L - 2 || whole_top) && layer_forward_fusable(c, l + 1) && c->layers[l + 1].ld <= 128;
       const int nl = pair ? 2 : 1;
       if ((rc = launch_layer_forward(c, l, nl, l + nl - 1 == c->L - 2 ? with_readout : 0, labels_dev))) return rc;
       l += nl - 1;
