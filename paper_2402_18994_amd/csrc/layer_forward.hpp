@@ -188,7 +188,7 @@ __device__ __forceinline__ void lif_layer_forward_body(const LayerForwardArgs &a
     const LayerForwardOp &op = a.op[li + LI0];
     const int nk = (op.kc + KS - 1) / KS;
     const u32x4 rp = raw_rsrc(op.P, op.p_bytes), rq = raw_rsrc(op.Q, op.q_bytes);
-    const int ld = FULL ? a.parts * BN : op.ld;
+    const int ld = !FULL ? op.ld : NL == 2 || READOUT || ROLE ? BN : a.parts * BN;   // (those hold whole layers)
     const rsrc_t rV = make_rsrc(op.V, (unsigned)a.T * a.B * ld * 4u), rS = make_rsrc(op.S, (unsigned)a.T * a.B * ld);
     int qv[QI];
 #pragma unroll
@@ -323,14 +323,12 @@ __device__ __forceinline__ void lif_layer_forward_body(const LayerForwardArgs &a
               x[q] = (f[0] > theta ? 1u : 0u) | (f[1] > theta ? 0x100u : 0u) | (f[2] > theta ? 0x10000u : 0u) |
                      (f[3] > theta ? 0x1000000u : 0u);
             }
-            const bool live = t0 + row < a.T;
-            const int at = ((t0 + row) * a.B + b) * ld + n0 + col;
-            const int so = live && (FULL || n0 + col + 16 <= ld) ? at : OOB;
+            const int so = t0 + row < a.T && (FULL || n0 + col + 16 <= ld) ? ((t0 + row) * a.B + b) * ld + n0 + col : OOB;
             if (a.nt_store) __builtin_amdgcn_raw_buffer_store_b128(x, rS, so, 0, NT);
             else __builtin_amdgcn_raw_buffer_store_b128(x, rS, so, 0, 0);
             if (!FULL && (ld & 8)) {                  // the row's last eight neurons are half a piece
               const u32x2 x8 = {x.x, x.y};
-              st_b64(rS, live && n0 + col + 8 == ld ? at : OOB, 0, x8);
+              st_b64(rS, t0 + row < a.T && n0 + col + 8 == ld ? ((t0 + row) * a.B + b) * ld + n0 + col : OOB, 0, x8);
             }
           }
         }

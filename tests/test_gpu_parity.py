@@ -189,6 +189,33 @@ def test_layer_forward_in_one_launch(T, sizes, nt, bn):
     assert rep["spike_rate"][0] > 0.005
 
 
+@pytest.mark.parametrize("precision", ["bf16", "fp32"])
+@pytest.mark.parametrize("T,sizes,loss,packed", [(1, (4, 1, 2), "max", False), (37, (65, 8, 63, 10), "max", False),
+                                                  (129, (64, 72, 121, 32), "integral", False), (260, (12, 130, 200, 20), "max", False),
+                                                  (128, (128, 64, 128, 20), "max", True), (70, (132, 56, 40, 33), "max", True),
+                                                  (50, (90, 40, 300, 104, 10), "integral", True)],
+                         ids=["one-neuron", "one-part-of-64", "part-of-128-two-blocks", "several-parts-three-blocks",
+                              "whole-parts-packed", "no-readout-packed", "pair-and-wide-packed"])
+def test_layer_forward_in_one_launch_any_width(T, sizes, loss, packed, precision):
+    """Feed-forward layers whose width is no multiple of 64, and all of them with fp32 products (three
+    planes of the weights per stage), as one launch: one and several parts of 64 or 128 neurons, rows whose
+    last piece of spikes is half one, pairs of layers of unlike width, the readout inside the launch and,
+    above 32 classes, behind it, one to three blocks of steps, both input formats."""
+    L = len(sizes) - 1
+    wl = workloads.Workload(name="layer-launch-any", index=18, T=T, B=5, sizes=sizes, recurrent=(False,) * (L - 1),
+                            beta=(0.9, 0.93, 0.95, 0.9)[:L], theta=1.0, surrogate="superspike", slope=10.0,
+                            precision=precision, rate_lo=0.05, rate_hi=0.2, loss=loss)
+    # (no step with the integral loss: its gradients of size 1e5 leave weights whose logits are sums of terms
+    # up to 1e6, and 2^-24 of those is 0.06)
+    full_step_parity(wl, w_gain=2.5, options={"layer_min_batch": 1}, check_sgd=loss == "max")
+    if packed:
+        inp = workloads.generate(wl, w_gain=2.5)
+        snn = make(wl, inp, {"layer_min_batch": 1})
+        rep = {}
+        parity.compare_forward(net_of(wl), inp, snn, snn.forward_packed(np.packbits(inp.X, axis=0), inp.labels), rep)
+        snn.destroy()
+
+
 @pytest.mark.parametrize("T,sizes,loss,packed", [(70, (150, 192, 256, 20), "max", False), (150, (203, 128, 128, 20), "max", False),
                                                   (260, (90, 128, 128, 10), "integral", False), (200, (64, 128, 10), "max", True),
                                                   (128, (700, 128, 128, 20), "max", True)],
