@@ -19,6 +19,7 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
 # multiples of 1 KiB, 64.1 / 77.2 of 4 KiB, 64.0 / 77.1 of 64 KiB.)
 UNITS = {"snn_api.hip": ["-Xarch_device", "-falign-functions=1024"],
          "layer_forward.hip": ["-Xarch_device", "-falign-functions=1024"],
+         "layer_reverse.hip": ["-Xarch_device", "-falign-functions=1024"],
          "rlif_wide.hip": [],
          # results of MFMAs in ordinary vector registers (the time loops read them at once)
          "rlif_tile.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
@@ -39,7 +40,7 @@ def _run(cmd, verbose: bool) -> None:
 def build(verbose: bool = False) -> str:
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     extra = os.environ.get("SNN_EXTRA_FLAGS", "").split()
-    with tempfile.TemporaryDirectory() as tmp, concurrent.futures.ThreadPoolExecutor(4) as pool:
+    with tempfile.TemporaryDirectory() as tmp, concurrent.futures.ThreadPoolExecutor(len(UNITS)) as pool:
         objs = {u: os.path.join(tmp, u + ".o") for u in UNITS}
         jobs = [pool.submit(_run, [hipcc] + FLAGS + UNITS[u] + extra + ["-c", "-o", objs[u], os.path.join(CSRC, u)], verbose)
                 for u in UNITS]

@@ -1,7 +1,8 @@
 // Reverse pass of a whole feed-forward LIF layer below a narrow layer in one launch: the
 // spike gradients dS = dX W^T from the current gradients dX of the layer above (at most 128
 // columns: the readout or a narrow spiking layer), the surrogate, the reverse scan
-// g_t -> dI_t (Eq. 1-2 differentiated; see lif_reverse_kernel), dI stored as hi/lo words.
+// g_t -> dI_t (Eq. 1-2 differentiated; see lif_reverse_kernel), dI stored as hi/lo words (F32:
+// fp32 products; dX and dI are fp32, both operands of dS enter in three bfloat16 pieces).
 //
 // lif_reverse_top_kernel does the same with one wavefront per 64 chains, each lane walking
 // its chain through global memory: per step a load, a store and a share of the dX fetches,
@@ -21,6 +22,8 @@
 //   4. scan: BN/64 wavefronts, one neuron per lane, 64 steps of one fused multiply-add each on
 //      LDS (coefficients read 8 steps ahead, g written back in place of c2);
 //   5. store: all wavefronts pack g into hi/lo words and write whole rows, 16 bytes per lane.
+// A layer whose width is no multiple of 64 (not FULL) has columns without neurons in its last part: they
+// read zeros, stay zero and are not stored.
 // g (and the decay gradient's partial sum) stay in the scanning lanes' registers from block
 // to block.  Rows past T read as zero: c2 = 0 there and g, zero at the start, stays zero.
 //
@@ -30,7 +33,7 @@
 // stages of 32 columns, the hi/lo words of dX are split into their two bfloat16 planes after the
 // fragment read, and dS still never reaches memory.  The workgroup then owns 128 neurons.
 #pragma once
-#include "scan.hpp"
+#include "surrogate.hpp"
 #include "gemm_stream.hpp"
 #include <type_traits>
 
@@ -156,24 +159,26 @@ struct WordTile {
 };
 
 struct LayerReverseArgs {
-  const uint32_t *dX;      // current gradients of the layer above [T*B][ldc], hi/lo words
+  const uint32_t *dX;      // current gradients of the layer above [T*B][ldc], hi/lo words (F32: fp32)
   int ldc;                 // its padded columns (multiple of 8, at most 128)
-  const uint16_t *Wq;      // rounded W[n][c] bfloat16, row n = neuron of this layer, zero beyond the valid columns
+  const uint16_t *Wq;      // W[n][c] bfloat16 planes, row n = neuron of this layer, zero beyond the valid columns
   int ldq;
-  unsigned wq_bytes;
+  unsigned wq_bytes, wq_plane;   // all planes; bytes between planes
   const float *V;          // [T*B][ld]
   uint32_t *dI;            // [T*B][ld] hi/lo words
   const float *beta_v;     // [ld]
   float theta, slope;
   float *db_part;          // [B][ld] per-sample parts of the decay gradient, or NULL
-  int T, B, ld;            // ld: a multiple of the workgroup's neurons
+  int T, B, ld;
   int nt_store;            // dI streams past the caches
 };
+// Columns above at most 128 (workgroups of 64 neurons), or any number on request (wide; hi/lo words, ld a multiple of 128).
+hipError_t layer_reverse(hipStream_t st, const LayerReverseArgs &a, int surrogate, bool f32, bool wide);
 
-template <int KS, int SURR, int BN, bool WIDE = false>
+template <int KS, int SURR, int BN, bool WIDE = false, bool F32 = false, bool FULL = true>
 __global__ __launch_bounds__(256, BN == 64 ? 2 : 1) void lif_layer_reverse_kernel(const LayerReverseArgs a) {
   static_assert(BN == 64 || BN == 128, "neurons per workgroup");
-  static_assert(!WIDE || (BN == 128 && KS == 1), "the streamed product takes 128 neurons; KS has no meaning there");
+  static_assert(!WIDE || (BN == 128 && KS == 1 && !F32 && FULL), "the streamed product takes 128 neurons; KS has no meaning there");
   typedef WordTile<2, 4> Wide;
   constexpr int BM = 64;
   constexpr int NJ = BN / 64;                         // 32-neuron MFMA tiles per wavefront
@@ -191,7 +196,7 @@ __global__ __launch_bounds__(256, BN == 64 ? 2 : 1) void lif_layer_reverse_kerne
   char *const Vt = lds, *const C1 = lds + TILE, *const C2 = lds + 2 * TILE, *const Xt = C1;
 
   // Workgroup ids are dealt round-robin to the 8 XCDs: the parts of a sample take ids 8 apart.
-  const int parts = a.ld / BN;
+  const int parts = FULL ? a.ld / BN : (a.ld + BN - 1) / BN;
   const int part = (blockIdx.x >> 3) % parts;
   const int b = (blockIdx.x >> 3) / parts * 8 + (blockIdx.x & 7);
   if (b >= a.B) return;
@@ -202,7 +207,7 @@ __global__ __launch_bounds__(256, BN == 64 ? 2 : 1) void lif_layer_reverse_kerne
   const unsigned vbytes = (unsigned)a.T * a.B * a.ld * 4u;
   const rsrc_t rV = make_rsrc(a.V, vbytes), rdI = make_rsrc(a.dI, vbytes);
   const rsrc_t rX = make_rsrc(a.dX, (unsigned)a.T * a.B * a.ldc * 4u), rW = make_rsrc(a.Wq, a.wq_bytes);
-  if (tid < BN) betas[tid] = a.beta_v[n0 + tid];
+  if (tid < BN) betas[tid] = FULL || n0 + tid < a.ld ? a.beta_v[n0 + tid] : 0.f;
 
   // A block's global loads: V as 8 x 16 bytes per thread (row = 8 k + tid / 32), dX as KK x 16
   // bytes per thread over rows of 8 KS chunks (chunks beyond ldc read as zero).
@@ -211,7 +216,7 @@ __global__ __launch_bounds__(256, BN == 64 ? 2 : 1) void lif_layer_reverse_kerne
 #pragma unroll
     for (int k = 0; k < NV; ++k) {
       const int t = t0 + (256 / LPR) * k + tid / LPR, col = (tid % LPR) * 4;
-      xv[k] = ld_b128(rV, t0 >= 0 && t < a.T ? ((t * a.B + b) * a.ld + n0 + col) * 4 : OOB, 0);
+      xv[k] = ld_b128(rV, t0 >= 0 && t < a.T && (FULL || n0 + col < a.ld) ? ((t * a.B + b) * a.ld + n0 + col) * 4 : OOB, 0);
     }
     if (!WIDE) {
 #pragma unroll
@@ -238,15 +243,18 @@ __global__ __launch_bounds__(256, BN == 64 ? 2 : 1) void lif_layer_reverse_kerne
 
   // First MFMA operand: W[n][c], lane -> neuron (lane & 31) of the 32-neuron tile, columns
   // 16 kk + 8 h .. +7.  Resident for the whole kernel.
-  bf16x8 wf[NJ][KK];
+  constexpr int NP = F32 ? 3 : 1;
+  bf16x8 wf[NP][NJ][KK];
   if (!WIDE) {
 #pragma unroll
-    for (int j = 0; j < NJ; ++j)
+    for (int pl = 0; pl < NP; ++pl)
 #pragma unroll
-      for (int kk = 0; kk < KK; ++kk) {
-        const int n = n0 + 32 * NJ * wn + 32 * j + (lane & 31), c = 16 * kk + 8 * h;
-        wf[j][kk] = __builtin_bit_cast(bf16x8, ld_b128(rW, c + 7 < a.ldq ? (n * a.ldq + c) * 2 : OOB, 0));
-      }
+      for (int j = 0; j < NJ; ++j)
+#pragma unroll
+        for (int kk = 0; kk < KK; ++kk) {
+          const int n = n0 + 32 * NJ * wn + 32 * j + (lane & 31), c = 16 * kk + 8 * h;
+          wf[pl][j][kk] = __builtin_bit_cast(bf16x8, ld_b128(rW, c + 7 < a.ldq ? (n * a.ldq + c) * 2 : OOB, pl * (int)a.wq_plane));
+        }
   }
   // WIDE: global side of the streamed loads.  Q rows are this workgroup's neurons; P rows are the
   // block's steps (set per block).
@@ -281,6 +289,31 @@ __global__ __launch_bounds__(256, BN == 64 ? 2 : 1) void lif_layer_reverse_kerne
         pvw[q] = t < a.T ? ((t * a.B + b) * a.ldc) * 4 + Wide::p_unit(row, lane) * 16 : OOB;
       }
       Wide::run(C1, rpw, rqw, pvw, qvw, nkw, wave, lane, acc);
+    } else if constexpr (F32) {
+      // pieces p of dX and q of W with p + q < 3: every product above 2^-24
+      const char *px = Xt + (32 * wm + (lane & 31)) * XP + 32 * h;
+#pragma unroll
+      for (int kk = 0; kk < KK; ++kk) {
+        const f32x4 j0 = *(const f32x4 *)(px + 64 * kk), j1 = *(const f32x4 *)(px + 64 * kk + 16);
+        bf16x8 xp[3];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          float x = e < 4 ? j0[e] : j1[e - 4];
+#pragma unroll
+          for (int pl = 0; pl < 3; ++pl) {
+            const __bf16 piece = (__bf16)x;
+            xp[pl][e] = piece;
+            x -= (float)piece;
+          }
+        }
+#pragma unroll
+        for (int s = 2; s >= 0; --s)
+#pragma unroll
+          for (int pl = 0; pl <= s; ++pl)
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[s - pl][j][kk], xp[pl], acc[j], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);            // (one step's pieces at a time: the weights take most registers)
+      }
     } else {
       bf16x8 hi[KK];
       const char *px = Xt + (32 * wm + (lane & 31)) * XP + 32 * h;
@@ -295,12 +328,12 @@ __global__ __launch_bounds__(256, BN == 64 ? 2 : 1) void lif_layer_reverse_kerne
         hi[kk] = __builtin_bit_cast(bf16x8, hh);
         const bf16x8 lo = __builtin_bit_cast(bf16x8, ll);
 #pragma unroll
-        for (int j = 0; j < NJ; ++j) acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[j][kk], lo, acc[j], 0, 0, 0);
+        for (int j = 0; j < NJ; ++j) acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[0][j][kk], lo, acc[j], 0, 0, 0);
       }
 #pragma unroll
       for (int kk = 0; kk < KK; ++kk)
 #pragma unroll
-        for (int j = 0; j < NJ; ++j) acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[j][kk], hi[kk], acc[j], 0, 0, 0);
+        for (int j = 0; j < NJ; ++j) acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[0][j][kk], hi[kk], acc[j], 0, 0, 0);
     }
     __syncthreads();                                  // every wavefront has read the dX tile: C1 takes its place
 
@@ -366,8 +399,9 @@ __global__ __launch_bounds__(256, BN == 64 ? 2 : 1) void lif_layer_reverse_kerne
       const int row = (256 / LPR) * k + tid / LPR, col = (tid % LPR) * 4, t = t0 + row;
       const f32x4 gq = *(const f32x4 *)(C2 + row * CP + col * 4);
       u32x4 w;
-      w.x = pack_hl(gq[0]); w.y = pack_hl(gq[1]); w.z = pack_hl(gq[2]); w.w = pack_hl(gq[3]);
-      const int vo = t < a.T ? ((t * a.B + b) * a.ld + n0 + col) * 4 : OOB;
+      if (F32) w = __builtin_bit_cast(u32x4, gq);
+      else { w.x = pack_hl(gq[0]); w.y = pack_hl(gq[1]); w.z = pack_hl(gq[2]); w.w = pack_hl(gq[3]); }
+      const int vo = t < a.T && (FULL || n0 + col < a.ld) ? ((t * a.B + b) * a.ld + n0 + col) * 4 : OOB;
       if (a.nt_store) __builtin_amdgcn_raw_buffer_store_b128(w, rdI, vo, 0, NT);
       else __builtin_amdgcn_raw_buffer_store_b128(w, rdI, vo, 0, 0);
     }
@@ -375,7 +409,7 @@ __global__ __launch_bounds__(256, BN == 64 ? 2 : 1) void lif_layer_reverse_kerne
     // longer than a coefficient row, of part of C2, which this store phase is still reading.
     if (XP > CP) __syncthreads();
   }
-  if (a.db_part && tid < BN) a.db_part[b * a.ld + n0 + tid] = db;
+  if (a.db_part && tid < BN && (FULL || n0 + tid < a.ld)) a.db_part[b * a.ld + n0 + tid] = db;
 }
 
 }  // namespace snn

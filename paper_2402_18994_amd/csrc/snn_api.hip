@@ -763,13 +763,12 @@ int launch_lif_reverse(snn_ctx *c, int l) {
   return SNN_OK;
 }
 
-// A spiking layer can take dS = dX W^T from the current gradients dX of the layer above inside
-// its reverse scan (lif_reverse_top_kernel) when it is feed-forward, its rows hold whole
-// wavefronts (ld a multiple of 64), the layer above has at most 128 padded columns (the
-// readout, or a narrow spiking layer) and the products run on rounded weights.  (One chain per
-// lane also at large widths: at 1024 neurons below the readout the fused scan takes 216 us
-// where the four-chains-per-lane scan plus the readout's input-gradient launch took 290 + 100.)
+// Padded columns of the layer above a spiking layer.
 int columns_above(const snn_ctx *c, int l) { return l + 1 == c->L - 1 ? c->ldC : c->layers[l + 1].ld; }
+// Samples from which a layer runs as one launch (SNN_OPT_LAYER_MIN_BATCH).
+int layer_min_batch(const snn_ctx *c) {
+  return c->opt[SNN_OPT_LAYER_MIN_BATCH] > 0 ? c->opt[SNN_OPT_LAYER_MIN_BATCH] : c->T <= 256 ? 1 : 64;
+}
 // Below a WIDER layer (more than 128 columns) the whole reverse layer can run as one launch whose
 // dS product walks the long contraction on the streamed pipeline (lif_layer_reverse_kernel, WIDE):
 // layers that are a multiple of 128 wide, as many samples as the one-launch layers ask for.
@@ -783,21 +782,36 @@ int columns_above(const snn_ctx *c, int l) { return l + 1 == c->L - 1 ? c->ldC :
 bool reverse_wide(const snn_ctx *c, int l) {
   if (c->opt[SNN_OPT_LAYER_REVERSE] != 2 || l < 0 || l > c->L - 2) return false;
   const Layer &y = c->layers[l];
-  const int min_b = c->opt[SNN_OPT_LAYER_MIN_BATCH] > 0 ? c->opt[SNN_OPT_LAYER_MIN_BATCH] : c->T <= 256 ? 1 : 64;
-  return c->hl && y.spiking && !y.recurrent && !y.adaptive && y.ld % 128 == 0 && columns_above(c, l) > 128 && c->B >= min_b;
+  return c->hl && y.spiking && !y.recurrent && !y.adaptive && y.ld % 128 == 0 && columns_above(c, l) > 128 && c->B >= layer_min_batch(c);
+}
+// A feed-forward spiking layer below at most 128 padded columns (the readout, or a narrow spiking
+// layer) takes dS = dX W^T from the current gradients dX of the layer above inside its reverse pass.
+// Two kernels do that: a workgroup per sample and 64 neurons on LDS (lif_layer_reverse_kernel), and, for
+// rounded weights and layers of whole wavefronts (ld a multiple of 64), a wavefront per 64 chains
+// (lif_reverse_top_kernel).  The second is faster above 256 neurons (121 against 129 us at 512, 466
+// against 492 at 1024); one chain per lane also there: at 1024 neurons below the readout it takes 216 us
+// where the four-chains-per-lane scan plus the readout's input-gradient launch took 290 + 100.
+// SNN_OPT_LAYER_REVERSE = 0 switches the first off, SNN_OPT_TOP_SCANS = 0 both.
+bool reverse_takes_product(const snn_ctx *c, int l) {
+  const Layer &y = c->layers[l];
+  return c->opt[SNN_OPT_TOP_SCANS] && y.spiking && !y.recurrent && !y.adaptive && columns_above(c, l) <= 128;
+}
+bool reverse_on_wavefronts(const snn_ctx *c, int l) { return c->hl && c->layers[l].ld % 64 == 0; }
+bool layer_reverse_whole(const snn_ctx *c, int l) {
+  const Layer &y = c->layers[l];
+  return c->opt[SNN_OPT_LAYER_REVERSE] && reverse_takes_product(c, l) && !reverse_wide(c, l) &&
+         y.ld <= (reverse_on_wavefronts(c, l) ? 256 : 1024) && c->B >= layer_min_batch(c) &&
+         (size_t)c->M * y.ld * 4 < ((size_t)1 << 31) && (size_t)c->M * columns_above(c, l) * 4 < ((size_t)1 << 31);
 }
 bool reverse_fusable(const snn_ctx *c, int l) {
   if (l < 0 || l > c->L - 2) return false;
-  if (reverse_wide(c, l)) return true;
-  if (!c->opt[SNN_OPT_TOP_SCANS]) return false;
-  const Layer &y = c->layers[l];
-  return c->hl && y.spiking && !y.recurrent && !y.adaptive && y.ld % 64 == 0 && columns_above(c, l) <= 128;
+  return reverse_wide(c, l) || layer_reverse_whole(c, l) || (reverse_takes_product(c, l) && reverse_on_wavefronts(c, l));
 }
 
 // Forward counterpart: the last spiking layer's scan also forms the readout's currents
 // (lif_forward_top_kernel), one workgroup per sample.
 bool top_forward_fusable(const snn_ctx *c) {
-  if (c->L < 2 || !reverse_fusable(c, c->L - 2)) return false;
+  if (c->L < 2 || !reverse_takes_product(c, c->L - 2) || !c->hl) return false;
   const int ld = c->layers[c->L - 2].ld;
   return c->nplanes == 1 && c->ldC <= 32 && (ld == 64 || ld == 128 || ld == 256);
 }
@@ -827,81 +841,24 @@ int launch_lif_forward_top(snn_ctx *c) {
   return SNN_OK;
 }
 
-// The same reverse pass as one workgroup per sample and 64 neurons on LDS
-// (lif_layer_reverse_kernel): layers of 64 to 256 neurons (wider, the scan with a wavefront per
-// 64 chains is faster: 121 against 129 us at 512 neurons, 466 against 492 at 1024), 32-bit byte
-// offsets.  SNN_OPT_LAYER_REVERSE = 0 switches it off; SNN_OPT_LAYER_MIN_BATCH as for the forward pass.
-int layer_min_batch(const snn_ctx *c) {
-  return c->opt[SNN_OPT_LAYER_MIN_BATCH] > 0 ? c->opt[SNN_OPT_LAYER_MIN_BATCH] : c->T <= 256 ? 1 : 64;
-}
-bool layer_reverse_whole(snn_ctx *c, int l) {
-  if (!c->opt[SNN_OPT_LAYER_REVERSE]) return false;
-  const Layer &y = c->layers[l];
-  const int min_b = layer_min_batch(c);
-  return reverse_fusable(c, l) && !reverse_wide(c, l) && y.ld <= 256 && c->B >= min_b &&
-         (size_t)c->M * y.ld * 4 < ((size_t)1 << 31) && (size_t)c->M * columns_above(c, l) * 4 < ((size_t)1 << 31);
-}
-
-int launch_layer_reverse(snn_ctx *c, int l) {
+int launch_layer_reverse(snn_ctx *c, int l, bool wide) {
   Layer &y = c->layers[l];
   Layer &up = c->layers[l + 1];
   LayerReverseArgs a;
   memset(&a, 0, sizeof a);
   a.dX = up.dI; a.ldc = columns_above(c, l);
-  a.Wq = up.Qb; a.ldq = up.ldqb; a.wq_bytes = (unsigned)(up.qb_plane * 2);
+  a.Wq = up.Qb; a.ldq = up.ldqb; a.wq_bytes = (unsigned)(c->nplanes * up.qb_plane * 2); a.wq_plane = (unsigned)(up.qb_plane * 2);
   a.V = y.V; a.dI = y.dI; a.beta_v = y.beta_v; a.theta = c->theta; a.slope = c->slope; a.db_part = y.part_b;
   a.T = c->T; a.B = c->B; a.ld = y.ld;
   a.nt_store = streams_past_cache(c, c->M * y.ld * 4);
   Bracket br(c, SNN_K_LIF_REVERSE, l + 1);
-  // 64 neurons per workgroup (two or three workgroups share a compute unit and overlap each
-  // other's phases): 99.8 us per step at 700-128-128-20 against 104.8 with 128 neurons.
-  const dim3 grid((unsigned)(rup(c->B, 8) * (y.ld / 64))), block(256);
-#define SNN_LREV(SU)                                                                                             \
-  do {                                                                                                           \
-    if (a.ldc <= 32) hipLaunchKernelGGL((lif_layer_reverse_kernel<1, SU, 64>), grid, block, 0, c->stream, a);    \
-    else if (a.ldc <= 64) hipLaunchKernelGGL((lif_layer_reverse_kernel<2, SU, 64>), grid, block, 0, c->stream, a); \
-    else hipLaunchKernelGGL((lif_layer_reverse_kernel<4, SU, 64>), grid, block, 0, c->stream, a);                \
-  } while (0)
-  switch (c->surrogate) {
-    case 0: SNN_LREV(0); break;
-    case 1: SNN_LREV(1); break;
-    case 2: SNN_LREV(2); break;
-    case 3: SNN_LREV(3); break;
-    case 4: SNN_LREV(4); break;
-    default: SNN_LREV(5); break;
-  }
-#undef SNN_LREV
-  HIPCHK(c, hipGetLastError());
-  return SNN_OK;
-}
-
-int launch_layer_reverse_wide(snn_ctx *c, int l) {
-  Layer &y = c->layers[l];
-  Layer &up = c->layers[l + 1];
-  LayerReverseArgs a;
-  memset(&a, 0, sizeof a);
-  a.dX = up.dI; a.ldc = columns_above(c, l);
-  a.Wq = up.Qb; a.ldq = up.ldqb; a.wq_bytes = (unsigned)(up.qb_plane * 2);
-  a.V = y.V; a.dI = y.dI; a.beta_v = y.beta_v; a.theta = c->theta; a.slope = c->slope; a.db_part = y.part_b;
-  a.T = c->T; a.B = c->B; a.ld = y.ld;
-  a.nt_store = streams_past_cache(c, c->M * y.ld * 4);
-  Bracket br(c, SNN_K_LIF_REVERSE, l + 1);
-  const dim3 grid((unsigned)(rup(c->B, 8) * (y.ld / 128))), block(256);
-  switch (c->surrogate) {
-    case 0: hipLaunchKernelGGL((lif_layer_reverse_kernel<1, 0, 128, true>), grid, block, 0, c->stream, a); break;
-    case 1: hipLaunchKernelGGL((lif_layer_reverse_kernel<1, 1, 128, true>), grid, block, 0, c->stream, a); break;
-    case 2: hipLaunchKernelGGL((lif_layer_reverse_kernel<1, 2, 128, true>), grid, block, 0, c->stream, a); break;
-    case 3: hipLaunchKernelGGL((lif_layer_reverse_kernel<1, 3, 128, true>), grid, block, 0, c->stream, a); break;
-    case 4: hipLaunchKernelGGL((lif_layer_reverse_kernel<1, 4, 128, true>), grid, block, 0, c->stream, a); break;
-    default: hipLaunchKernelGGL((lif_layer_reverse_kernel<1, 5, 128, true>), grid, block, 0, c->stream, a); break;
-  }
-  HIPCHK(c, hipGetLastError());
+  HIPCHK(c, layer_reverse(c->stream, a, c->surrogate, !c->hl, wide));
   return SNN_OK;
 }
 
 int launch_lif_reverse_fused(snn_ctx *c, int l) {
-  if (reverse_wide(c, l)) return launch_layer_reverse_wide(c, l);
-  if (layer_reverse_whole(c, l)) return launch_layer_reverse(c, l);
+  if (reverse_wide(c, l)) return launch_layer_reverse(c, l, true);
+  if (layer_reverse_whole(c, l)) return launch_layer_reverse(c, l, false);
   Layer &y = c->layers[l];
   Layer &up = c->layers[l + 1];
   Bracket br(c, SNN_K_LIF_REVERSE, l + 1);

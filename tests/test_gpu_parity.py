@@ -730,6 +730,23 @@ def test_layer_reverse_below_a_wide_layer_same_as_separate_launches():
     beta_step_parity(wl, w_gain=2.0, options={"layer_min_batch": 1, "layer_reverse": 2})
 
 
+@pytest.mark.parametrize("precision", ["bf16", "fp32"])
+@pytest.mark.parametrize("T,sizes,surrogate,slope", [(1, (5, 1, 1, 2), "superspike", 10.0), (63, (30, 8, 40, 10), "arctan", 2.0),
+                                                      (64, (30, 72, 128, 33), "sigmoid", 4.0), (65, (30, 200, 121, 64), "triangular", 1.0),
+                                                      (130, (30, 257, 96, 20), "superspike", 10.0), (37, (30, 129, 1020, 10), "boxcar", 1.0)],
+                         ids=["one-neuron", "below-40", "below-128", "below-121", "257-neurons", "1020-neurons-below-the-readout"])
+def test_layer_reverse_in_one_launch_any_width(T, sizes, surrogate, slope, precision):
+    """Reverse layers whose width is no multiple of 64, and all of them with fp32 products (three pieces of
+    both operands of dS), below 8 to 128 columns, in one launch: one and several blocks of 64 steps,
+    a last part of 1 to 64 neurons; the decay gradients' partial sums on the same rows."""
+    wl = workloads.Workload(name="layer-reverse-any", index=24, T=T, B=6, sizes=sizes, recurrent=(False, False),
+                            beta=(0.9, 0.93, 0.95), theta=1.0, surrogate=surrogate, slope=slope, precision=precision,
+                            rate_lo=0.05, rate_hi=0.2)
+    full_step_parity(wl, w_gain=2.5, options={"layer_min_batch": 1})
+    if surrogate == "superspike" and T > 1:
+        beta_step_parity(wl, w_gain=2.5, options={"layer_min_batch": 1})
+
+
 def test_layer_reverse_in_one_launch_with_trainable_decays():
     """The same path with the decay gradients' partial sums taken inside the scan."""
     beta_step_parity(workloads.CONFIGS["shd_ff128"].scaled(T=100, B=12), w_gain=3.0, options={"layer_min_batch": 1})
