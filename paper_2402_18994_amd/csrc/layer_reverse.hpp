@@ -186,12 +186,14 @@ __global__ __launch_bounds__(256, BN == 64 ? 2 : 1) void lif_layer_reverse_kerne
   constexpr int LPR = BN / 4;                         // lanes per row in those accesses
   constexpr int CP = BN * 4 + 16;                     // bytes between time rows of the fp32 tiles
   constexpr int PITCH = CP / 4;
-  constexpr int XP = KS * 128 + 16;                   // bytes between time rows of the dX tile (32 KS words)
+  constexpr int XP = F32 ? KS * 64 + 16 : KS * 128 + 16;   // bytes between time rows of the dX tile (32 KS words; F32: 32 KS bfloat16 per plane)
+  constexpr int XPL = BM * XP, XT = F32 ? 3 * XPL : XPL;   // F32: bytes between planes; bytes of the tile
   constexpr int TILE = BM * CP;
   constexpr int KK = 2 * KS;                          // 16-wide MFMA steps over the columns above
-  static_assert(BM * XP <= 2 * TILE, "the dX tile shares the space of the coefficient tiles");
+  constexpr int LDS_BYTES = TILE + (XT > 2 * TILE ? XT : 2 * TILE);   // the dX tile shares the space of the coefficient tiles
+  static_assert(BN == 128 || LDS_BYTES <= 80 * 1024, "two workgroups per compute unit");
   static_assert(!WIDE || (4 * Wide::ST <= 2 * TILE && TILE % 1024 == 0), "the stages share the space of the coefficient tiles");
-  __shared__ __attribute__((aligned(16))) char lds[3 * TILE];
+  __shared__ __attribute__((aligned(16))) char lds[LDS_BYTES];
   __shared__ __attribute__((aligned(16))) float betas[BN];
   char *const Vt = lds, *const C1 = lds + TILE, *const C2 = lds + 2 * TILE, *const Xt = C1;
 
@@ -233,7 +235,24 @@ __global__ __launch_bounds__(256, BN == 64 ? 2 : 1) void lif_layer_reverse_kerne
 #pragma unroll
       for (int k = 0; k < KK; ++k) {
         const int idx = k * 256 + tid, row = idx / (8 * KS), ch = idx % (8 * KS);
-        *(u32x4 *)(Xt + row * XP + ch * 16) = xd[k];
+        if constexpr (F32) {
+          // split here, once per word; in the product every word would be split by the wavefronts of both
+          // neuron halves, one step behind the other (700-128-128-20, T = 500, B = 4: 5 us per block)
+          typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
+          bf16x4 xp[3];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            float x = __uint_as_float(xd[k][e]);
+#pragma unroll
+            for (int pl = 0; pl < 3; ++pl) {
+              const __bf16 piece = (__bf16)x;
+              xp[pl][e] = piece;
+              x -= (float)piece;
+            }
+          }
+#pragma unroll
+          for (int pl = 0; pl < 3; ++pl) *(bf16x4 *)(Xt + pl * XPL + row * XP + ch * 8) = xp[pl];
+        } else *(u32x4 *)(Xt + row * XP + ch * 16) = xd[k];
       }
     }
   };
@@ -243,18 +262,22 @@ __global__ __launch_bounds__(256, BN == 64 ? 2 : 1) void lif_layer_reverse_kerne
 
   // First MFMA operand: W[n][c], lane -> neuron (lane & 31) of the 32-neuron tile, columns
   // 16 kk + 8 h .. +7.  Resident for the whole kernel.
-  constexpr int NP = F32 ? 3 : 1;
+  // (F32 with 128 columns: the third plane, one of the six products, is fetched per block; resident it makes
+  // registers spill, and each spill's reload waits for the next block's loads in flight)
+  constexpr int NP = F32 ? 3 : 1, NRES = F32 && KS == 4 ? 2 : NP;
   bf16x8 wf[NP][NJ][KK];
+  auto weights = [&](int pl) {
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
+#pragma unroll
+      for (int kk = 0; kk < KK; ++kk) {
+        const int n = n0 + 32 * NJ * wn + 32 * j + (lane & 31), c = 16 * kk + 8 * h;
+        wf[pl][j][kk] = __builtin_bit_cast(bf16x8, ld_b128(rW, c + 7 < a.ldq ? (n * a.ldq + c) * 2 : OOB, pl * (int)a.wq_plane));
+      }
+  };
   if (!WIDE) {
 #pragma unroll
-    for (int pl = 0; pl < NP; ++pl)
-#pragma unroll
-      for (int j = 0; j < NJ; ++j)
-#pragma unroll
-        for (int kk = 0; kk < KK; ++kk) {
-          const int n = n0 + 32 * NJ * wn + 32 * j + (lane & 31), c = 16 * kk + 8 * h;
-          wf[pl][j][kk] = __builtin_bit_cast(bf16x8, ld_b128(rW, c + 7 < a.ldq ? (n * a.ldq + c) * 2 : OOB, pl * (int)a.wq_plane));
-        }
+    for (int pl = 0; pl < NRES; ++pl) weights(pl);
   }
   // WIDE: global side of the streamed loads.  Q rows are this workgroup's neurons; P rows are the
   // block's steps (set per block).
@@ -271,6 +294,7 @@ __global__ __launch_bounds__(256, BN == 64 ? 2 : 1) void lif_layer_reverse_kerne
 
   for (int blk = 0; t0 >= 0; t0 -= BM, ++blk) {
     fill();
+    if (NRES < NP) weights(NRES);
     __syncthreads();
     fetch(t0 - BM);
 
@@ -291,28 +315,27 @@ __global__ __launch_bounds__(256, BN == 64 ? 2 : 1) void lif_layer_reverse_kerne
       Wide::run(C1, rpw, rqw, pvw, qvw, nkw, wave, lane, acc);
     } else if constexpr (F32) {
       // pieces p of dX and q of W with p + q < 3: every product above 2^-24
-      const char *px = Xt + (32 * wm + (lane & 31)) * XP + 32 * h;
+      const char *px = Xt + (32 * wm + (lane & 31)) * XP + 16 * h;
 #pragma unroll
       for (int kk = 0; kk < KK; ++kk) {
-        const f32x4 j0 = *(const f32x4 *)(px + 64 * kk), j1 = *(const f32x4 *)(px + 64 * kk + 16);
         bf16x8 xp[3];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          float x = e < 4 ? j0[e] : j1[e - 4];
-#pragma unroll
-          for (int pl = 0; pl < 3; ++pl) {
-            const __bf16 piece = (__bf16)x;
-            xp[pl][e] = piece;
-            x -= (float)piece;
-          }
-        }
+        for (int pl = 0; pl < 3; ++pl) xp[pl] = *(const bf16x8 *)(px + pl * XPL + 32 * kk);
 #pragma unroll
         for (int s = 2; s >= 0; --s)
 #pragma unroll
           for (int pl = 0; pl <= s; ++pl)
 #pragma unroll
-            for (int j = 0; j < NJ; ++j) acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[s - pl][j][kk], xp[pl], acc[j], 0, 0, 0);
-        __builtin_amdgcn_sched_barrier(0);            // (one step's pieces at a time: the weights take most registers)
+            for (int j = 0; j < NJ; ++j)
+              if (s - pl < NRES) acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[s - pl][j][kk], xp[pl], acc[j], 0, 0, 0);
+      }
+      if constexpr (NRES < NP) {
+#pragma unroll
+        for (int kk = 0; kk < KK; ++kk) {
+          const bf16x8 xp = *(const bf16x8 *)(px + 32 * kk);
+#pragma unroll
+          for (int j = 0; j < NJ; ++j) acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[NRES][j][kk], xp, acc[j], 0, 0, 0);
+        }
       }
     } else {
       bf16x8 hi[KK];
@@ -363,7 +386,7 @@ __global__ __launch_bounds__(256, BN == 64 ? 2 : 1) void lif_layer_reverse_kerne
       float *p2 = (float *)(C2 + tid * 4);
       auto scan = [&](auto DB) {
         constexpr bool with_db = decltype(DB)::value;
-        constexpr int U = 8;
+        constexpr int U = F32 && KS == 4 ? 4 : 8;
         float n1[U], n2[U], nv[U];
         auto read = [&](int s0) {
 #pragma unroll
@@ -405,9 +428,9 @@ __global__ __launch_bounds__(256, BN == 64 ? 2 : 1) void lif_layer_reverse_kerne
       if (a.nt_store) __builtin_amdgcn_raw_buffer_store_b128(w, rdI, vo, 0, NT);
       else __builtin_amdgcn_raw_buffer_store_b128(w, rdI, vo, 0, 0);
     }
-    // The next block's fill writes V and dX, which takes the place of C1 and, when its rows are
-    // longer than a coefficient row, of part of C2, which this store phase is still reading.
-    if (XP > CP) __syncthreads();
+    // The next block's fill writes V and dX, which takes the place of C1 and, when it is larger than
+    // C1, of part of C2, which this store phase is still reading.
+    if (XT > TILE) __syncthreads();
   }
   if (a.db_part && tid < BN && (FULL || n0 + tid < a.ld)) a.db_part[b * a.ld + n0 + tid] = db;
 }

@@ -765,9 +765,22 @@ int launch_lif_reverse(snn_ctx *c, int l) {
 
 // Padded columns of the layer above a spiking layer.
 int columns_above(const snn_ctx *c, int l) { return l + 1 == c->L - 1 ? c->ldC : c->layers[l + 1].ld; }
-// Samples from which a layer runs as one launch (SNN_OPT_LAYER_MIN_BATCH).
-int layer_min_batch(const snn_ctx *c) {
-  return c->opt[SNN_OPT_LAYER_MIN_BATCH] > 0 ? c->opt[SNN_OPT_LAYER_MIN_BATCH] : c->T <= 256 ? 1 : 64;
+// Samples from which a layer runs as one launch: SNN_OPT_LAYER_MIN_BATCH, or any number.
+// Forward, with three planes of the weights, a workgroup walks up to three times the stages, and with few
+// samples the separate product spreads them over more workgroups: 64 samples where a sample's product is
+// more than sixteen rounds of 128 steps x 64 inputs.  (us saved by one launch over two, fp32, 4 / 32 / 64
+// samples: 700-128-128-20 at T = 300 -15 / -14 / -3, T = 500 -22 / -20 / 0, T = 256 4 / 1 / 8; 200-60-10 at
+// T = 500, sixteen rounds, 9 / 8 / 8; rounded weights, 700-128-128-20: T = 300 8 / 9 / 13, T = 500 17 / 19 / 27.)
+int layer_min_batch(const snn_ctx *c) { return std::max(1, c->opt[SNN_OPT_LAYER_MIN_BATCH]); }
+int layer_forward_min_batch(const snn_ctx *c, int l) {
+  const bool long_product = c->nplanes == 3 && (c->T + 127) / 128 * ((c->layers[l].K + 63) / 64) > 16;
+  return c->opt[SNN_OPT_LAYER_MIN_BATCH] == 0 && long_product ? 64 : layer_min_batch(c);
+}
+// Reverse, the six products of fp32 operands below more than 64 columns are the long part of a block: 32
+// samples above 256 steps (us saved, 700-128-128-20, 4 / 64 samples: T = 256 2 / 4, T = 300 0 / 4, T = 500 -3 / 10).
+int layer_reverse_min_batch(const snn_ctx *c, int l) {
+  const bool long_product = c->nplanes == 3 && columns_above(c, l) > 64 && c->T > 256;
+  return c->opt[SNN_OPT_LAYER_MIN_BATCH] == 0 && long_product ? 32 : layer_min_batch(c);
 }
 // Below a WIDER layer (more than 128 columns) the whole reverse layer can run as one launch whose
 // dS product walks the long contraction on the streamed pipeline (lif_layer_reverse_kernel, WIDE):
@@ -800,7 +813,7 @@ bool reverse_on_wavefronts(const snn_ctx *c, int l) { return c->hl && c->layers[
 bool layer_reverse_whole(const snn_ctx *c, int l) {
   const Layer &y = c->layers[l];
   return c->opt[SNN_OPT_LAYER_REVERSE] && reverse_takes_product(c, l) && !reverse_wide(c, l) &&
-         y.ld <= (reverse_on_wavefronts(c, l) ? 256 : 1024) && c->B >= layer_min_batch(c) &&
+         y.ld <= (reverse_on_wavefronts(c, l) ? 256 : 1024) && c->B >= layer_reverse_min_batch(c, l) &&
          (size_t)c->M * y.ld * 4 < ((size_t)1 << 31) && (size_t)c->M * columns_above(c, l) * 4 < ((size_t)1 << 31);
 }
 bool reverse_fusable(const snn_ctx *c, int l) {
@@ -905,18 +918,15 @@ int launch_lif_reverse_fused(snn_ctx *c, int l) {
 // SNN_OPT_LAYER_FORWARD: 0 never, 1 all but the last spiking layer, 2 every such layer, 3 the last
 // one also forms the readout's currents when it has at most 128 padded neurons, 4 (default) and
 // runs the readout scan, the loss and the readout's current gradients;
-// SNN_OPT_LAYER_MIN_BATCH: samples from which it is used (default: any number up to 256 steps, 64
-// for longer rasters: at the headline widths it wins from 4 samples on, having fewer launches,
-// but a workgroup walks its sample's blocks of 128 steps serially); SNN_OPT_LAYER_NEURONS: 64 or
-// 128 neurons per workgroup.
+// SNN_OPT_LAYER_MIN_BATCH: samples from which it is used (0: layer_forward_min_batch);
+// SNN_OPT_LAYER_NEURONS: 64 or 128 neurons per workgroup.
 int layer_fuse_mode(const snn_ctx *c) { return c->opt[SNN_OPT_LAYER_FORWARD]; }
 static int layer_max_neurons(const snn_ctx *c) { return c->opt[SNN_OPT_LAYER_MAX_NEURONS]; }
 bool layer_forward_fusable(snn_ctx *c, int l) {
   if (l < 0 || l > c->L - 2) return false;
   const Layer &y = c->layers[l];
-  const int min_b = layer_min_batch(c);                  // a workgroup walks a sample's blocks of 128 steps one after the other
   const SpikeSrc s = spikes_below(c, l);
-  return y.spiking && !y.recurrent && !y.adaptive && y.ld <= layer_max_neurons(c) && c->B >= min_b &&
+  return y.spiking && !y.recurrent && !y.adaptive && y.ld <= layer_max_neurons(c) && c->B >= layer_forward_min_batch(c, l) &&
          s.ld % 4 == 0 && s.ld <= layer_max_neurons(c) && (size_t)c->M * s.ld < ((size_t)1 << 31) && (size_t)c->M * y.ld * 4 < ((size_t)1 << 31) &&
          c->theta >= 0x1p-60f && c->theta <= 0x1p26f;
 }
