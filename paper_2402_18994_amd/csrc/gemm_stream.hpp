@@ -70,13 +70,20 @@ __device__ __forceinline__ void static_for(F &&f) {
 
 // P operand packed along time (the storage format of Section 2.1.4: eight consecutive steps of one
 // channel in a byte, first step in the most significant bit), for tiles whose 128 rows are
-// consecutive time steps of one sample: the 16 packed rows of the block.
+// consecutive time steps of one sample, or slots of 16 to 64 steps of consecutive samples: the 16
+// packed rows of the block.
 struct PackedRows {
   rsrc_t rsrc;         // the packed raster
-  int base;            // byte offset of the block's first packed row for this sample
-  int row_stride;      // bytes between packed rows of the sample (B x row length)
+  int base;            // byte offset of the block's first packed row for the first sample
+  int row_stride;      // bytes between packed rows of a sample (B x row length)
   int rows;            // packed rows that exist from there on (others read as zero)
   int kbytes;          // row length in bytes (= fan-in), at most 1024, a multiple of 4
+  int slot_log2 = 4;   // packed rows per sample
+  int samples = 1;     // samples that exist
+  __device__ __forceinline__ int offset(int r, int c) const {     // byte c of packed row r of the block
+    const int s = r >> slot_log2, tp = r & ((1 << slot_log2) - 1);
+    return tp < rows && s < samples && c < kbytes ? tp * row_stride + s * kbytes + c : OOB;
+  }
 };
 
 // Geometry and main loop of one tile, shared by the kernels built on this pipeline.  `run`
@@ -159,7 +166,7 @@ struct SpikeTile {
 #pragma unroll
       for (int j = 0; j < PKN; ++j) {
         const int piece = tid + 256 * j, r = piece >> 6, c = (piece & 63) * 16;
-        pkx[j] = ld_b128(pk->rsrc, r < pk->rows && c < pk->kbytes ? r * pk->row_stride + c : OOB, pk->base);
+        pkx[j] = ld_b128(pk->rsrc, pk->offset(r, c), pk->base);
       }
     }
     // Stage kt into buffer `buf`.  Beyond the contraction range the descriptors get size 0:
@@ -399,7 +406,7 @@ struct SpikeTile {
 #pragma unroll
       for (int j = 0; j < PKN; ++j) {
         const int piece = tid + 256 * j, r = piece >> 6, c = (piece & 63) * 16;
-        pkx[j] = ld_b128(pk->rsrc, r < pk->rows && c < pk->kbytes ? r * pk->row_stride + c : OOB, pk->base);
+        pkx[j] = ld_b128(pk->rsrc, pk->offset(r, c), pk->base);
       }
     }
     // Load n of plane pl of round kt (P first, with plane 0).  Beyond the last round the descriptors get

@@ -1,5 +1,5 @@
 // Launches of the one-launch forward layers (layer_forward.hpp): which variant of the kernel runs.
-#include "layer_forward.hpp"
+#include "layer_forward_short.hpp"
 
 namespace snn {
 
@@ -36,7 +36,31 @@ static hipError_t launch_packed(hipStream_t st, const LayerForwardArgs &a, const
   }
 }
 
+template <int TN, bool READOUT, int NL, bool PK>
+static hipError_t launch_slots(hipStream_t st, const LayerForwardArgs &a, const LayerForwardVariant &v, unsigned grid) {
+  if (v.planes == 3) hipLaunchKernelGGL((lif_layer_forward_short_kernel<TN, READOUT, NL, PK, 3>), dim3(grid), dim3(256), 0, st, a);
+  else hipLaunchKernelGGL((lif_layer_forward_short_kernel<TN, READOUT, NL, PK, 1>), dim3(grid), dim3(256), 0, st, a);
+  return hipGetLastError();
+}
+template <int TN>
+static hipError_t launch_short(hipStream_t st, const LayerForwardArgs &a, const LayerForwardVariant &v) {
+  const int groups = (a.B + (128 >> a.slot_log2) - 1) >> (7 - a.slot_log2);
+  const unsigned grid = (unsigned)((groups + 7) / 8 * 8 * a.parts);
+  const int which = (v.readout ? 4 : 0) + (v.layers == 2 ? 2 : 0) + (v.packed ? 1 : 0);
+  switch (which) {
+    case 0: return launch_slots<TN, false, 1, false>(st, a, v, grid);
+    case 1: return launch_slots<TN, false, 1, true>(st, a, v, grid);
+    case 2: return launch_slots<TN, false, 2, false>(st, a, v, grid);
+    case 3: return launch_slots<TN, false, 2, true>(st, a, v, grid);
+    case 4: return launch_slots<TN, true, 1, false>(st, a, v, grid);
+    case 5: return launch_slots<TN, true, 1, true>(st, a, v, grid);
+    case 6: return launch_slots<TN, true, 2, false>(st, a, v, grid);
+    default: return launch_slots<TN, true, 2, true>(st, a, v, grid);
+  }
+}
+
 hipError_t layer_forward(hipStream_t st, const LayerForwardArgs &a, const LayerForwardVariant &v) {
+  if (v.slots) return v.neurons == 64 ? launch_short<1>(st, a, v) : launch_short<2>(st, a, v);
   const unsigned grid = (unsigned)((a.B + 7) / 8 * 8 * a.parts * (v.time_split || v.layer_split ? 2 : 1));
   if (v.neurons == 64) return v.packed ? launch_packed<1, true>(st, a, v, grid) : launch_packed<1, false>(st, a, v, grid);
   return v.packed ? launch_packed<2, true>(st, a, v, grid) : launch_packed<2, false>(st, a, v, grid);

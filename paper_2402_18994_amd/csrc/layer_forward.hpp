@@ -101,6 +101,8 @@ struct LayerForwardArgs {
   // thread).  `epoch` grows with every launch, so flags never have to be cleared.
   uint32_t *hand;
   int epoch;
+  // Rasters of at most 64 steps (layer_forward_short.hpp): log2 of the steps in a sample's slot, and which loss.
+  int slot_log2, integral;
 };
 // Which variant of the kernel a launch is (layer_forward.hip).
 struct LayerForwardVariant {
@@ -110,6 +112,7 @@ struct LayerForwardVariant {
   int planes;              // of the weights: 1 or 3
   bool full;               // every layer fills its column blocks
   bool packed, time_split, layer_split;
+  bool slots;              // several samples to a workgroup (layer_forward_short.hpp)
 };
 hipError_t layer_forward(hipStream_t st, const LayerForwardArgs &a, const LayerForwardVariant &v);
 
@@ -260,22 +263,18 @@ __device__ __forceinline__ void lif_layer_forward_body(const LayerForwardArgs &a
     // has finished, 16 steps behind it: after every 16 steps a barrier, behind which they read the
     // 16 rows of potentials back from the tile and write V (BN/4 pieces of 16 bytes per row) and S
     // (BN/16 pieces of 16 neurons per row, decided from V as in the scan) while the scan goes on
-    // with the next rows.  (Steps past T run on zero currents; nothing of them is stored, and v is
-    // not used after the last block.)
+    // with the next rows.  (Steps past T in the last pair of groups run on zero currents; nothing of them is
+    // stored, and v is not used after the last block.)
     constexpr int U = 16;
+    const int end = ROLE ? BM : min(BM, (a.T - t0 + 2 * U - 1) / (2 * U) * (2 * U));
     if (wave < BN / 64) {
       if (TS == 2 && blk > 0) v[li] = __uint_as_float(hand_load(hand + HAND_V + (li * 2 + ((blk - 1) & 1)) * 128 + tid));
       float *cell = (float *)(lds + tid * 4);
-      float nxt[U];
-#pragma unroll
-      for (int u = 0; u < U; ++u) nxt[u] = cell[u * (CP / 4)];
-      for (int s0 = 0; s0 < BM; s0 += U) {
-        // The currents of the next 16 steps are read before the 16 steps at hand are taken
-        // (the empty asm keeps the reads here, not next to their use).
-        float cur[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) cur[u] = nxt[u];
-        if (s0 + U < BM) {
+      float ga[U], gb[U];                             // the group at hand and the next, in turn
+      // The currents of the next 16 steps are read before the 16 steps at hand are taken
+      // (the empty asm keeps the reads here, not next to their use).
+      auto group = [&](float (&cur)[U], float (&nxt)[U], int s0) {
+        if (s0 + U < end) {
 #pragma unroll
           for (int u = 0; u < U; ++u) nxt[u] = cell[(s0 + U + u) * (CP / 4)];
         }
@@ -292,6 +291,12 @@ __device__ __forceinline__ void lif_layer_forward_body(const LayerForwardArgs &a
         // (the storing wavefronts pass this barrier after the rows before s0 and, at the end of a
         // 64-step chunk, after the acknowledgement of their stores)
         if (ROLE == 1 && s0 > 0 && s0 % 64 == 0 && tid == 0) hand_store(hand + HAND_PAIR, hand_base + (t0 + s0) / 64);
+      };
+#pragma unroll
+      for (int u = 0; u < U; ++u) ga[u] = cell[u * (CP / 4)];
+      for (int s0 = 0; s0 < end; s0 += 2 * U) {
+        group(ga, gb, s0);
+        group(gb, ga, s0 + U);
       }
       if (TS == 2 && blk + 1 < nblocks) {             // hand the potentials on to the workgroup of the next block
         hand_store(hand + HAND_V + (li * 2 + (blk & 1)) * 128 + tid, __float_as_uint(v[li]));
@@ -300,7 +305,7 @@ __device__ __forceinline__ void lif_layer_forward_body(const LayerForwardArgs &a
     } else {
       constexpr int NT_ = 256 - BN, VL = BN / 4, SL = BN / 16;   // storing threads; pieces per row of V and of S
       const int st = tid - BN;
-      for (int s0 = 0; s0 < BM; s0 += U) {
+      for (int s0 = 0; s0 < end; s0 += U) {
         __syncthreads();
 #pragma unroll
         for (int p0 = 0; p0 < U * VL; p0 += NT_) {

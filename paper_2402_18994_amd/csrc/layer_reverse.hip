@@ -3,10 +3,11 @@
 
 namespace snn {
 
-template <int KS, int SURR, int BN, bool WIDE, bool F32, bool FULL>
+template <int KS, int SURR, int BN, bool WIDE, bool F32, bool FULL, bool SLOTS = false>
 static hipError_t launch(hipStream_t st, const LayerReverseArgs &a) {
-  const int grid = (a.B + 7) / 8 * 8 * ((a.ld + BN - 1) / BN);
-  hipLaunchKernelGGL((lif_layer_reverse_kernel<KS, SURR, BN, WIDE, F32, FULL>), dim3((unsigned)grid), dim3(256), 0, st, a);
+  const int groups = SLOTS ? (a.B + (64 >> a.slot_log2) - 1) >> (6 - a.slot_log2) : a.B;
+  const int grid = (groups + 7) / 8 * 8 * ((a.ld + BN - 1) / BN);
+  hipLaunchKernelGGL((lif_layer_reverse_kernel<KS, SURR, BN, WIDE, F32, FULL, SLOTS>), dim3((unsigned)grid), dim3(256), 0, st, a);
   return hipGetLastError();
 }
 
@@ -14,6 +15,7 @@ static hipError_t launch(hipStream_t st, const LayerReverseArgs &a) {
 // phases): 99.8 us per step at 700-128-128-20 against 104.8 with 128 neurons.
 template <int KS, int SURR>
 static hipError_t launch_columns(hipStream_t st, const LayerReverseArgs &a, bool f32) {
+  if (a.slot_log2 < 6) return f32 ? launch<KS, SURR, 64, false, true, false, true>(st, a) : launch<KS, SURR, 64, false, false, false, true>(st, a);
   const bool full = a.ld % 64 == 0;
   if (f32) return full ? launch<KS, SURR, 64, false, true, true>(st, a) : launch<KS, SURR, 64, false, true, false>(st, a);
   return full ? launch<KS, SURR, 64, false, false, true>(st, a) : launch<KS, SURR, 64, false, false, false>(st, a);

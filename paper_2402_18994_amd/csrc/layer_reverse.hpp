@@ -22,6 +22,8 @@
 //   4. scan: BN/64 wavefronts, one neuron per lane, 64 steps of one fused multiply-add each on
 //      LDS (coefficients read 8 steps ahead, g written back in place of c2);
 //   5. store: all wavefronts pack g into hi/lo words and write whole rows, 16 bytes per lane.
+// SLOTS (at most 32 steps, one block): the block's rows are 64 / SL samples in slots of SL = 16 or 32 steps, a
+// wavefront scans a slot; 16 steps in a block of their own leave three of four rows to zeros.
 // A layer whose width is no multiple of 64 (not FULL) has columns without neurons in its last part: they
 // read zeros, stay zero and are not stored.
 // g (and the decay gradient's partial sum) stay in the scanning lanes' registers from block
@@ -171,11 +173,12 @@ struct LayerReverseArgs {
   float *db_part;          // [B][ld] per-sample parts of the decay gradient, or NULL
   int T, B, ld;
   int nt_store;            // dI streams past the caches
+  int slot_log2;           // 6: a block of 64 steps is one sample's; 4 or 5: slots of 16 or 32 steps
 };
 // Columns above at most 128 (workgroups of 64 neurons), or any number on request (wide; hi/lo words, ld a multiple of 128).
 hipError_t layer_reverse(hipStream_t st, const LayerReverseArgs &a, int surrogate, bool f32, bool wide);
 
-template <int KS, int SURR, int BN, bool WIDE = false, bool F32 = false, bool FULL = true>
+template <int KS, int SURR, int BN, bool WIDE = false, bool F32 = false, bool FULL = true, bool SLOTS = false>
 __global__ __launch_bounds__(256, BN == 64 ? 2 : 1) void lif_layer_reverse_kernel(const LayerReverseArgs a) {
   static_assert(BN == 64 || BN == 128, "neurons per workgroup");
   static_assert(!WIDE || (BN == 128 && KS == 1 && !F32 && FULL), "the streamed product takes 128 neurons; KS has no meaning there");
@@ -200,9 +203,15 @@ __global__ __launch_bounds__(256, BN == 64 ? 2 : 1) void lif_layer_reverse_kerne
   // Workgroup ids are dealt round-robin to the 8 XCDs: the parts of a sample take ids 8 apart.
   const int parts = FULL ? a.ld / BN : (a.ld + BN - 1) / BN;
   const int part = (blockIdx.x >> 3) % parts;
-  const int b = (blockIdx.x >> 3) / parts * 8 + (blockIdx.x & 7);
+  const int sl2 = SLOTS ? a.slot_log2 : 6;
+  const int b = ((blockIdx.x >> 3) / parts * 8 + (blockIdx.x & 7)) << (6 - sl2);   // the first sample
   if (b >= a.B) return;
+  static_assert(!SLOTS || (BN == 64 && !WIDE && !FULL), "slots: one block of 64 rows");
   const int n0 = part * BN;
+  // row of the block at t0: its step and sample, and whether they exist
+  auto step = [&](int t0, int row) { return SLOTS ? row & ((1 << sl2) - 1) : t0 + row; };
+  auto sample = [&](int row) { return SLOTS ? b + (row >> sl2) : b; };
+  auto exists = [&](int t, int s) { return t < a.T && (!SLOTS || s < a.B); };
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave >> 1, wn = wave & 1, h = lane >> 5;
   const float theta = a.theta, slope = a.slope;
@@ -217,14 +226,14 @@ __global__ __launch_bounds__(256, BN == 64 ? 2 : 1) void lif_layer_reverse_kerne
   auto fetch = [&](int t0) {                          // t0 < 0: nothing is read
 #pragma unroll
     for (int k = 0; k < NV; ++k) {
-      const int t = t0 + (256 / LPR) * k + tid / LPR, col = (tid % LPR) * 4;
-      xv[k] = ld_b128(rV, t0 >= 0 && t < a.T && (FULL || n0 + col < a.ld) ? ((t * a.B + b) * a.ld + n0 + col) * 4 : OOB, 0);
+      const int row = (256 / LPR) * k + tid / LPR, t = step(t0, row), s = sample(row), col = (tid % LPR) * 4;
+      xv[k] = ld_b128(rV, t0 >= 0 && exists(t, s) && (FULL || n0 + col < a.ld) ? ((t * a.B + s) * a.ld + n0 + col) * 4 : OOB, 0);
     }
     if (!WIDE) {
 #pragma unroll
       for (int k = 0; k < KK; ++k) {
-        const int idx = k * 256 + tid, row = idx / (8 * KS), ch = idx % (8 * KS), t = t0 + row;
-        xd[k] = ld_b128(rX, t0 >= 0 && t < a.T && ch * 4 + 3 < a.ldc ? ((t * a.B + b) * a.ldc + ch * 4) * 4 : OOB, 0);
+        const int idx = k * 256 + tid, row = idx / (8 * KS), ch = idx % (8 * KS), t = step(t0, row), s = sample(row);
+        xd[k] = ld_b128(rX, t0 >= 0 && exists(t, s) && ch * 4 + 3 < a.ldc ? ((t * a.B + s) * a.ldc + ch * 4) * 4 : OOB, 0);
       }
     }
   };
@@ -381,9 +390,11 @@ __global__ __launch_bounds__(256, BN == 64 ? 2 : 1) void lif_layer_reverse_kerne
     __syncthreads();
 
     // 4. scan, steps t0 + 63 down to t0: dI_t = g, then g <- c1 g + c2 (and db += g V_t)
-    if (wave < BN / 64) {
-      const float *p1 = (const float *)(C1 + tid * 4), *pv = (const float *)(Vt + tid * 4);
-      float *p2 = (float *)(C2 + tid * 4);
+    const int scans = SLOTS ? 64 >> sl2 : BN / 64, slot = SLOTS ? wave : 0, rows = 1 << sl2;   // SLOTS: the wavefront's
+    if (wave < scans) {
+      const int cell = SLOTS ? (slot << sl2) * CP + lane * 4 : tid * 4;
+      const float *p1 = (const float *)(C1 + cell), *pv = (const float *)(Vt + cell);
+      float *p2 = (float *)(C2 + cell);
       auto scan = [&](auto DB) {
         constexpr bool with_db = decltype(DB)::value;
         constexpr int U = F32 && KS == 4 ? 4 : 8;
@@ -396,8 +407,8 @@ __global__ __launch_bounds__(256, BN == 64 ? 2 : 1) void lif_layer_reverse_kerne
             if (with_db) nv[u] = pv[(s0 + u) * PITCH];
           }
         };
-        read(BM - U);
-        for (int s0 = BM - U; s0 >= 0; s0 -= U) {
+        read((SLOTS ? rows : BM) - U);
+        for (int s0 = (SLOTS ? rows : BM) - U; s0 >= 0; s0 -= U) {
           float c1[U], c2[U], vv[U];
 #pragma unroll
           for (int u = 0; u < U; ++u) { c1[u] = n1[u]; c2[u] = n2[u]; vv[u] = with_db ? nv[u] : 0.f; }
@@ -419,12 +430,12 @@ __global__ __launch_bounds__(256, BN == 64 ? 2 : 1) void lif_layer_reverse_kerne
     // 5. store: BN/4 lanes x 16 bytes per row
 #pragma unroll
     for (int k = 0; k < NV; ++k) {
-      const int row = (256 / LPR) * k + tid / LPR, col = (tid % LPR) * 4, t = t0 + row;
+      const int row = (256 / LPR) * k + tid / LPR, col = (tid % LPR) * 4, t = step(t0, row), s = sample(row);
       const f32x4 gq = *(const f32x4 *)(C2 + row * CP + col * 4);
       u32x4 w;
       if (F32) w = __builtin_bit_cast(u32x4, gq);
       else { w.x = pack_hl(gq[0]); w.y = pack_hl(gq[1]); w.z = pack_hl(gq[2]); w.w = pack_hl(gq[3]); }
-      const int vo = t < a.T && (FULL || n0 + col < a.ld) ? ((t * a.B + b) * a.ld + n0 + col) * 4 : OOB;
+      const int vo = exists(t, s) && (FULL || n0 + col < a.ld) ? ((t * a.B + s) * a.ld + n0 + col) * 4 : OOB;
       if (a.nt_store) __builtin_amdgcn_raw_buffer_store_b128(w, rdI, vo, 0, NT);
       else __builtin_amdgcn_raw_buffer_store_b128(w, rdI, vo, 0, 0);
     }
@@ -432,7 +443,10 @@ __global__ __launch_bounds__(256, BN == 64 ? 2 : 1) void lif_layer_reverse_kerne
     // C1, of part of C2, which this store phase is still reading.
     if (XT > TILE) __syncthreads();
   }
-  if (a.db_part && tid < BN && (FULL || n0 + tid < a.ld)) a.db_part[b * a.ld + n0 + tid] = db;
+  if (SLOTS) {
+    const int s = b + wave;
+    if (a.db_part && wave < (64 >> sl2) && s < a.B && n0 + lane < a.ld) a.db_part[s * a.ld + n0 + lane] = db;
+  } else if (a.db_part && tid < BN && (FULL || n0 + tid < a.ld)) a.db_part[b * a.ld + n0 + tid] = db;
 }
 
 }  // namespace snn

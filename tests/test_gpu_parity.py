@@ -731,6 +731,34 @@ def test_layer_reverse_below_a_wide_layer_same_as_separate_launches():
 
 
 @pytest.mark.parametrize("precision", ["bf16", "fp32"])
+@pytest.mark.parametrize("T,B,sizes,loss,packed", [(16, 1027, (12, 40, 8, 5), "max", False), (2, 1025, (20, 121, 10), "max", False),
+                                                    (17, 515, (24, 72, 128, 33), "max", False), (32, 517, (12, 128, 64, 10), "integral", True),
+                                                    (33, 259, (20, 121, 40, 32), "max", False), (64, 261, (132, 64, 20), "integral", True),
+                                                    (16, 344, (40, 200, 20), "max", True)],
+                         ids=["eight-samples", "two-steps", "four-samples-no-readout", "four-samples-packed-integral", "two-samples",
+                              "two-samples-packed-integral", "three-parts-packed"])
+def test_short_rasters_several_samples_to_a_tile(T, B, sizes, loss, packed, precision):
+    """At most 64 steps and many samples: the one-launch layers give a workgroup two, four or eight
+    samples, forward, and two or four, reverse (at most 32 steps): a last workgroup that is not full, slots
+    that are, steps that are no multiple of eight, the readout inside the launch and behind it."""
+    L = len(sizes) - 1
+    wl = workloads.Workload(name="short-rasters", index=24, T=T, B=B, sizes=sizes, recurrent=(False,) * (L - 1),
+                            beta=(0.9, 0.93, 0.95)[:L], theta=1.0, surrogate="superspike", slope=10.0, precision=precision,
+                            rate_lo=0.1, rate_hi=0.3, loss=loss)
+    # integral loss: no step, as above; z adds up 32 or 64 steps, and 2^-24 of their sizes' sum passes 1e-5 from
+    # a sum of 168 on (at gain 2.5 logits reach 400: 1.35e-5 seen), which gain 1 stays below
+    gain = 2.5 if loss == "max" else 1.0
+    full_step_parity(wl, w_gain=gain, check_sgd=loss == "max")
+    if loss == "max" and not packed:
+        beta_step_parity(wl, w_gain=gain)
+    if packed:
+        inp = workloads.generate(wl, w_gain=gain)
+        snn = make(wl, inp)
+        parity.compare_forward(net_of(wl), inp, snn, snn.forward_packed(np.packbits(inp.X, axis=0), inp.labels), {})
+        snn.destroy()
+
+
+@pytest.mark.parametrize("precision", ["bf16", "fp32"])
 @pytest.mark.parametrize("T,sizes,surrogate,slope", [(1, (5, 1, 1, 2), "superspike", 10.0), (63, (30, 8, 40, 10), "arctan", 2.0),
                                                       (64, (30, 72, 128, 33), "sigmoid", 4.0), (65, (30, 200, 121, 64), "triangular", 1.0),
                                                       (130, (30, 257, 96, 20), "superspike", 10.0), (37, (30, 129, 1020, 10), "boxcar", 1.0)],
