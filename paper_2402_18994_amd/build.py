@@ -22,6 +22,7 @@ UNITS = {"snn_api.hip": ["-Xarch_device", "-falign-functions=1024"],
          "layer_reverse.hip": ["-Xarch_device", "-falign-functions=1024"],
          "rlif_wide.hip": [],
          # results of MFMAs in ordinary vector registers (the time loops read them at once)
+         "rlif_pair.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
          "rlif_tile.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
 
 

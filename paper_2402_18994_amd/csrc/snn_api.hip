@@ -21,6 +21,7 @@
 #include "layer_reverse.hpp"
 #include "rlif.hpp"
 #include "rlif_wide.hpp"
+#include "rlif_pair.hpp"
 #include "splits.hpp"
 
 using namespace snn;
@@ -703,6 +704,49 @@ int launch_lif_forward(snn_ctx *c, int l) {
   else if (chains >= (1 << 17)) e = lif_fwd_launch<2, 16>(c, y);
   else e = lif_fwd_launch<1, 16>(c, y);
   HIPCHK(c, e);
+  return SNN_OK;
+}
+
+// Layers l and l + 1 run as a pair, one launch per direction (rlif_pair.hpp): both recurrent and
+// narrow, on rounded weights.  (SNN_OPT_LAYER_PAIR = 0: a launch each.)  Pairs are taken from the bottom up.
+// A feed-forward layer above does not join: its one launch per direction, with the readout or its dS, is
+// faster than a place in the loop (700-64(rec)-128-20, T = 200, B = 64: 159 us per step, 191 paired).
+bool rlif_pair_lower(const snn_ctx *c, int l) {
+  if (l < 0 || l + 1 > c->L - 2 || !c->opt[SNN_OPT_LAYER_PAIR] || c->nplanes != 1) return false;
+  const Layer &y = c->layers[l], &up = c->layers[l + 1];
+  return y.recurrent && up.recurrent && rlif_pair_fits(y.ld, up.ld) && c->B <= 2048 && !rlif_pair_lower(c, l - 1);
+}
+RlifPairArgs rlif_pair_args(snn_ctx *c, int l) {
+  RlifPairArgs a;
+  memset(&a, 0, sizeof a);
+  a.T = c->T; a.B = c->B; a.theta = c->theta; a.slope = c->slope; a.surrogate = c->surrogate;
+  for (int i = 0; i < 2; ++i) {
+    Layer &y = c->layers[l + i];
+    RlifPairArgs::Layer &p = i ? a.up : a.lo;
+    p.V = y.V; p.S = y.S; p.dI = y.dI; p.beta_v = y.beta_v; p.db_part = y.part_b; p.ld = y.ld;
+    p.ldr = y.ldqr; p.r_plane = y.qr_plane;
+  }
+  return a;
+}
+int launch_rlif_pair_forward(snn_ctx *c, int l) {
+  Layer &y = c->layers[l], &up = c->layers[l + 1];
+  RlifPairArgs a = rlif_pair_args(c, l);
+  a.lo.X = y.I; a.lo.R = y.QRf; a.up.R = up.QRf;
+  a.W = up.Qf; a.ldw = up.ldqf; a.w_plane = up.qf_plane;
+  Bracket br(c, SNN_K_RLIF_FORWARD, l + 1);
+  HIPCHK(c, rlif_pair_forward(c->stream, a));
+  up.i_ready = false;
+  return SNN_OK;
+}
+int launch_rlif_pair_reverse(snn_ctx *c, int l) {
+  Layer &y = c->layers[l], &up = c->layers[l + 1];
+  RlifPairArgs a = rlif_pair_args(c, l);
+  a.up.X = up.dS; a.lo.R = y.QRb; a.up.R = up.QRb;
+  a.W = up.Qb; a.ldw = up.ldqb; a.w_plane = up.qb_plane;
+  Bracket br(c, SNN_K_RLIF_REVERSE, l + 1);
+  HIPCHK(c, rlif_pair_reverse(c->stream, a));
+  y.ds_ready = false;
+  up.ds_ready = true;
   return SNN_OK;
 }
 
@@ -1406,6 +1450,11 @@ static int32_t forward_layers(snn_ctx *c, const int32_t *labels_dev, float *loss
       continue;
     }
     if (!(fuse_top && l == c->L - 1) && (rc = launch_current_gemm(c, l))) return rc;
+    if (rlif_pair_lower(c, l)) {
+      if ((rc = launch_rlif_pair_forward(c, l))) return rc;
+      ++l;
+      continue;
+    }
     if (c->layers[l].spiking) {
       if ((rc = fuse_top && l == c->L - 2 ? launch_lif_forward_top(c) : launch_lif_forward(c, l))) return rc;
     } else {
@@ -1462,7 +1511,9 @@ int32_t snn_backward(snn_ctx *c) {
   if (!c->dj_ready && (rc = launch_readout_reverse(c))) return rc;
   for (int l = c->L - 1; l >= 0; --l) {
     const bool fused = reverse_fusable(c, l);           // this layer's scan forms its own dS
-    if (c->layers[l].spiking) {
+    if (rlif_pair_lower(c, l - 1)) {                    // this layer and the next one down
+      if ((rc = launch_rlif_pair_reverse(c, l - 1))) return rc;
+    } else if (c->layers[l].spiking && !rlif_pair_lower(c, l)) {
       c->layers[l].ds_ready = !fused;
       if ((rc = fused ? launch_lif_reverse_fused(c, l) : launch_lif_reverse(c, l))) return rc;
     }
@@ -1474,7 +1525,7 @@ int32_t snn_backward(snn_ctx *c) {
       HIPCHK(c, hipGetLastError());
     }
     if ((rc = queue_weight_grad(c, l, wj, jobs))) return rc;
-    if (l > 0 && !reverse_fusable(c, l - 1) && (rc = launch_input_grad(c, l))) return rc;
+    if (l > 0 && !rlif_pair_lower(c, l - 1) && !reverse_fusable(c, l - 1) && (rc = launch_input_grad(c, l))) return rc;
   }
   if (c->learn_beta) {
     // per-sample parts of dL/dbeta: written by the reverse scans for the spiking layers, by a
