@@ -8,7 +8,8 @@
 // is taken by wavefronts of its own from the exchange tile that the one layer writes for its own recurrence
 // and handed to the other through LDS, in time for that layer's same step an iteration later: no product
 // launch, no currents or spike gradients through memory, and no step's chain is longer than its own layer's.
-// (With that product on the other layer's wavefronts, 700-128-128-20, T = 128, B = 256: PAIRA.)
+// 700-128-128-20, T = 128, B = 256, both layers: forward 69 us in two launches and 6.5 for the product between
+// them, 51 so (56 with that product on the upper layer's wavefronts); reverse 96 and 8, 64 so (83).
 //
 // Exchange, 32-neuron wavefronts, planes of g in the MFMA's columns: as in rlif_tile.hpp.
 #pragma once
@@ -81,12 +82,11 @@ __global__ __launch_bounds__(1024) void rlif_pair_forward_kernel(const RlifPairA
   __syncthreads();
   const PairRole role(a.lo.ld, a.up.ld);
   const RlifPairArgs::Layer &y = role.lower() ? a.lo : a.up;
-  const RlifLane L(role.thread());
+  const RlifLaneMasks L(role.thread());
   const int w = L.n >> 5, ld = y.ld, b = blockIdx.x * CS + L.smp, row4 = B * ld * 4;
   const int f1o = L.smp * X1 + 16 * L.q, f2o = L.smp * X2 + 16 * L.q, io = L.smp * IP + L.n;
   auto mine = [&](const f32x4 (&acc)[2], int e) {         // of the sums, those of the lane's own neuron
-    const float h0 = L.e0 ? acc[0][2 + e] : acc[0][e], h1 = L.e0 ? acc[1][2 + e] : acc[1][e];
-    return L.ti ? h1 : h0;
+    return pick(L.mt, pick(L.me, acc[1][2 + e], acc[1][e]), pick(L.me, acc[0][2 + e], acc[0][e]));
   };
   if (role.between()) {
     RlifWeights<1, K1> W;                                 // rows: upper neurons
@@ -96,6 +96,7 @@ __global__ __launch_bounds__(1024) void rlif_pair_forward_kernel(const RlifPairA
       lds_barrier();                                      // the lower layer's spikes of step t
       bf16x8 f[K1];
       pair_fragments<K1>(f, xs1[t & 1] + f1o);
+      __builtin_amdgcn_sched_barrier(0);                  // (all reads first)
       pair_product<K1>(acc, W, f);
       *(u32x2 *)(between[t & 1] + io) = u32x2{__float_as_uint(mine(acc, 0)), __float_as_uint(mine(acc, 1))};
     }
@@ -114,7 +115,7 @@ __global__ __launch_bounds__(1024) void rlif_pair_forward_kernel(const RlifPairA
   auto spikes = [&](char *x) {
     s0 = v[0] > theta ? 1u : 0u;
     s1 = v[1] > theta ? 1u : 0u;
-    *(uint32_t *)x = (s0 | (s1 << 16)) * 0x3F80u;
+    *(uint32_t *)x = (v[0] > theta ? 0x3F80u : 0u) | (v[1] > theta ? 0x3F800000u : 0u);
   };
   auto store = [&](int t) {
     st_b64(rV, vo4, t * row4, u32x2{__float_as_uint(v[0]), __float_as_uint(v[1])});
@@ -140,6 +141,7 @@ __global__ __launch_bounds__(1024) void rlif_pair_forward_kernel(const RlifPairA
       lds_barrier();
       bf16x8 f[K1];
       pair_fragments<K1>(f, xs1[t & 1] + f1o);
+      __builtin_amdgcn_sched_barrier(0);
       pair_product<K1>(acc, R, f);
       store(t);
       update(acc, in);
@@ -166,6 +168,7 @@ __global__ __launch_bounds__(1024) void rlif_pair_forward_kernel(const RlifPairA
       bf16x8 f[K2];
       pair_fragments<K2>(f, xs2[t & 1] + f2o);
       const u32x2 in = *(const u32x2 *)(between[t & 1] + io);
+      __builtin_amdgcn_sched_barrier(0);
       pair_product<K2>(acc, R, f);
       store(t);
       update(acc, in);
@@ -189,12 +192,12 @@ __global__ __launch_bounds__(1024) void rlif_pair_reverse_kernel(const RlifPairA
   __syncthreads();
   const PairRole role(a.lo.ld, a.lo.ld);
   const RlifPairArgs::Layer &y = role.lower() || role.between() ? a.lo : a.up;
-  const RlifLane L(role.thread());
+  const RlifLaneMasks L(role.thread());
   const int w = L.n >> 5, ld = y.ld, b = blockIdx.x * CS + L.smp, row4 = B * ld * 4, pl = L.c >> 3;
   const int f1o = pl * B1 + L.smp * X1 + 16 * L.q, f2o = pl * B2 + L.smp * X2 + 16 * L.q, io = L.smp * IP + L.n;
   auto mine = [&](const f32x4 (&acc)[2], int e) {         // the lane's column, and the one that holds the sample's other plane
-    const float h0 = L.e0 ? acc[0][2 + e] : acc[0][e], h1 = L.e0 ? acc[1][2 + e] : acc[1][e];
-    return (L.ti ? h1 : h0) + row_ror<8>(L.ti ? h0 : h1);
+    const float h0 = pick(L.me, acc[0][2 + e], acc[0][e]), h1 = pick(L.me, acc[1][2 + e], acc[1][e]);
+    return pick(L.mt, h1, h0) + row_ror<8>(pick(L.mt, h0, h1));
   };
   if (role.between()) {
     RlifWeights<1, K2> W;                                 // rows: lower neurons
@@ -204,6 +207,7 @@ __global__ __launch_bounds__(1024) void rlif_pair_reverse_kernel(const RlifPairA
       lds_barrier();                                      // the upper layer's g of step t
       bf16x8 f[K2];
       pair_fragments<K2>(f, xs2[t & 1][0] + f2o);
+      __builtin_amdgcn_sched_barrier(0);
       pair_product<K2>(acc, W, f);
       *(u32x2 *)(between[t & 1] + io) = u32x2{__float_as_uint(mine(acc, 0)), __float_as_uint(mine(acc, 1))};
     }
@@ -254,6 +258,7 @@ __global__ __launch_bounds__(1024) void rlif_pair_reverse_kernel(const RlifPairA
       bf16x8 f[K1];
       pair_fragments<K1>(f, xs1[t & 1][0] + f1o);
       const u32x2 ds = *(const u32x2 *)(between[t & 1] + io);
+      __builtin_amdgcn_sched_barrier(0);
       pair_product<K1>(acc, R, f);
       st_b64(rdI, vo4, t * row4, o);
       surrogates(vv);
@@ -282,6 +287,7 @@ __global__ __launch_bounds__(1024) void rlif_pair_reverse_kernel(const RlifPairA
       lds_barrier();
       bf16x8 f[K2];
       pair_fragments<K2>(f, xs2[t & 1][0] + f2o);
+      __builtin_amdgcn_sched_barrier(0);
       pair_product<K2>(acc, R, f);
       st_b64(rdI, vo4, t * row4, o);
       surrogates(vv);

@@ -14,7 +14,8 @@
 //     MFMA and one fragment read serve all planes, and a rotation within the row of 16 lanes adds them;
 //   * operands and results go straight between registers and memory, PF steps ahead.
 // 700-128-128-20, T = 128, B = 256, per layer: forward 55.8 -> 35.2 us (0.28 us per step), reverse 78.4
-// -> 48.2 us; sixteen samples and 16 neurons per wavefront, the form before, is the left figure.  Eight
+// -> 48.2 us; sixteen samples and 16 neurons per wavefront, the form before, is the left figure.  (Two such
+// layers above each other on rounded weights run as a pair, rlif_pair.hpp.)  Eight
 // samples: 38.4 and 54.1 us; 64 neurons per wavefront: 57 and 83 us.  At 256 neurons 67 and 90 us
 // where a launch per step took 128 x 4.1 and 128 x 4.8 us and the host's time to launch them.  With no
 // memory access at all the steps take 0.27 and 0.29 us.
@@ -29,6 +30,13 @@ namespace snn {
 // x of the lane N columns further in its row of 16 lanes.
 template <int N> __device__ __forceinline__ float row_ror(float x) {
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x120 + N, 0xF, 0xF, false));
+}
+// a where mask is all ones, b where it is zero: one v_bfi_b32.  (A choice between elements of an MFMA result
+// written with ?: can become an indexed extraction, three selects and their compares.  Reverse kernel, T = 200,
+// B = 64, 60 / 128 / 136 / 256 neurons: 49.7 / 70.6 / 107 / 125 us with ?:, 44.0 / 62.7 / 81.4 / 106 so; the forward
+// kernel is the same either way.)
+__device__ __forceinline__ float pick(uint32_t mask, float a, float b) {
+  return __uint_as_float((mask & __float_as_uint(a)) | (~mask & __float_as_uint(b)));
 }
 // Two values rounded to bfloat16, the first in the low half.
 __device__ __forceinline__ uint32_t pk_bf16(float a, float b) {
@@ -66,6 +74,13 @@ struct RlifLane {
   int c, q, smp, ti, e0, n;                              // column, row group, sample, tile, first row in the group, neuron
   __device__ __forceinline__ explicit RlifLane(int tid)
       : c(tid & 15), q((tid >> 4) & 3), smp(c & 3), ti(c >> 3), e0(2 * ((c >> 2) & 1)), n(32 * (tid >> 6) + 16 * ti + 4 * q + e0) {}
+};
+
+struct RlifLaneMasks : RlifLane {
+  uint32_t mt, me;                                        // masks: ti, e0
+  __device__ __forceinline__ explicit RlifLaneMasks(int tid) : RlifLane(tid), mt(ti ? ~0u : 0u), me(e0 ? ~0u : 0u) {
+    asm("" : "+v"(mt), "+v"(me));                         // (values, not conditions)
+  }
 };
 
 template <int NP, int KS>
@@ -141,7 +156,7 @@ __global__ __launch_bounds__(KS * 64) void rlif_tile_reverse_kernel(const float 
   constexpr int GP = NP == 1 ? 2 : 3;                     // planes of g; column c holds plane c/8, or c/4 (the fourth: zeros)
   constexpr int XB = G::CS * G::XP;
   __shared__ __align__(16) char xs[2][GP][XB];
-  const RlifLane L(threadIdx.x);
+  const RlifLaneMasks L(threadIdx.x);
   const int b = blockIdx.x * G::CS + L.smp, row4 = B * ld * 4;
   const unsigned bytes = (unsigned)T * B * ld * 4u;
   const rsrc_t rdS = make_rsrc(dS, bytes), rV = make_rsrc(V, bytes), rdI = make_rsrc(dI, bytes);
@@ -204,10 +219,11 @@ __global__ __launch_bounds__(KS * 64) void rlif_tile_reverse_kernel(const float 
 #pragma unroll
     for (int e = 0; e < 2; ++e) {
       // the sums of the lane's own neuron: its column, and the columns that hold the sample's other planes
-      float h0 = L.e0 ? acc[0][2 + e] : acc[0][e], h1 = L.e0 ? acc[1][2 + e] : acc[1][e];
-      float sum;
+      float h0, h1, sum;
       if (NP == 1) {
-        sum = (L.ti ? h1 : h0) + row_ror<8>(L.ti ? h0 : h1);
+        h0 = pick(L.me, acc[0][2 + e], acc[0][e]);
+        h1 = pick(L.me, acc[1][2 + e], acc[1][e]);
+        sum = pick(L.mt, h1, h0) + row_ror<8>(pick(L.mt, h0, h1));
       } else {
         // four planes in columns c, c + 4, c + 8, c + 12: every one of them adds the same four
         auto planes = [](float y) { y += row_ror<8>(y); return y + row_ror<4>(y); };

@@ -1080,6 +1080,26 @@ def test_recurrent_layers_on_a_workgroup_of_four_samples(precision, T, B, widths
     assert rep["spike_rate"][0] > 0
 
 
+@pytest.mark.parametrize("T,B,widths,surrogate", [(1, 1, (5, 3), "superspike"), (2, 5, (64, 64), "boxcar"), (7, 3, (65, 32), "arctan"),
+                                                  (8, 9, (128, 121), "superspike"), (9, 6, (192, 120), "sigmoid"), (5, 4, (40, 184), "ste"),
+                                                  (13, 2, (130, 70), "triangular"), (6, 7, (30, 60, 90), "superspike"), (6, 5, (24, 96, 16, 130), "arctan")],
+                         ids=lambda v: "-".join(map(str, v)) if isinstance(v, tuple) else str(v))
+def test_pairs_of_recurrent_layers_in_one_launch(T, B, widths, surrogate):
+    """Two recurrent layers of up to 192 neurons side by side on one workgroup, the product between them on
+    wavefronts of its own, against the oracle and against a launch per layer: every combination of the
+    compiled widths, one step, odd and even numbers of them around the prefetch distance, a last
+    workgroup that is not full, a third layer that stays alone and two pairs above each other; with the
+    decay gradients."""
+    L = len(widths) + 1
+    slope = {"superspike": 10.0, "arctan": 2.0, "sigmoid": 4.0}.get(surrogate, 1.0)
+    wl = workloads.Workload(name="rec-pair", index=25, T=T, B=B, sizes=(30,) + widths + (10,), recurrent=(True,) * (L - 1),
+                            beta=(0.9, 0.93, 0.95, 0.9, 0.92)[:L], theta=1.0, surrogate=surrogate, slope=slope, precision="bf16",
+                            rate_lo=0.1, rate_hi=0.3)
+    for pair in (1, 0):
+        full_step_parity(wl, w_gain=2.0, options={"layer_pair": pair})
+        beta_step_parity(wl, w_gain=2.0, options={"layer_pair": pair})
+
+
 @pytest.mark.parametrize("precision", ["fp32", "bf16"])
 @pytest.mark.parametrize("T,B,width,surrogate", [(6, 2309, 121, "superspike"), (3, 2049, 72, "boxcar"), (2, 4610, 64, "arctan"),
                                                   (9, 6145, 20, "sigmoid"), (1, 2051, 128, "ste")])
