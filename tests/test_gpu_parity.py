@@ -1283,6 +1283,35 @@ def test_tensors_read_back_as_set(precision, T, B, N):
     snn.destroy()
 
 
+@pytest.mark.parametrize("precision", ["fp32", "bf16"])
+@pytest.mark.parametrize("B", [1, 16, 256, 257])
+def test_small_tensors_are_announced(B, precision):
+    """Tensors of up to 16384 elements come back through workgroups of 256 whose last one tells the host: one
+    element, one workgroup, the most and one more (which takes the other way), several times in a row, with the
+    loss between them, padding columns left out, hi/lo words as their sums."""
+    T, sizes = 4, (20, 24, 16)
+    wl = workloads.Workload(name="announced", index=26, T=T, B=B, sizes=sizes, recurrent=(False,), beta=(0.9, 0.95), theta=1.0,
+                            surrogate="superspike", slope=10.0, precision=precision, rate_lo=0.2, rate_hi=0.4)
+    inp = workloads.generate(wl, w_gain=3.0)
+    snn = make(wl, inp)
+    rng = np.random.default_rng(B)
+    for _ in range(3):
+        loss = snn.forward(inp.X, inp.labels)
+        per = snn.get_tensor("loss_per_sample").reshape(-1)
+        assert per.size == B and abs(loss - per.astype(np.float64).mean()) <= 1e-6 * max(1.0, abs(loss))
+        g = rng.standard_normal((T, B, 16)).astype(np.float32)
+        snn.set_tensor("d_readout_current", 0, g)
+        got = snn.get_tensor("d_readout_current")
+        if precision == "fp32":
+            assert np.array_equal(got, g)
+        else:
+            assert np.abs(got - g).max() <= 2.0 ** -16 * np.abs(g).max()      # (hi + lo)
+        z = rng.standard_normal((B, 16)).astype(np.float32)
+        snn.set_tensor("d_logits", 0, z)
+        assert np.array_equal(snn.get_tensor("d_logits"), z)
+    snn.destroy()
+
+
 def test_several_threads_read_one_context():
     """Threads that read different tensors of one context at once (ctypes releases the interpreter lock)
     each get their own tensor: tensors of the same size, of several chunks of the read-back space, and
