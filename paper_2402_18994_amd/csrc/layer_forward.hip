@@ -59,7 +59,19 @@ static hipError_t launch_short(hipStream_t st, const LayerForwardArgs &a, const 
   }
 }
 
+template <bool PK, int NP>
+static hipError_t launch_adaptive(hipStream_t st, const LayerForwardArgs &a) {
+  const int groups = (a.B + (128 >> a.slot_log2) - 1) >> (7 - a.slot_log2);
+  const unsigned grid = (unsigned)((groups + 7) / 8 * 8 * a.parts);
+  hipLaunchKernelGGL((lif_layer_forward_short_kernel<1, false, 1, PK, NP, true>), dim3(grid), dim3(256), 0, st, a);
+  return hipGetLastError();
+}
+
 hipError_t layer_forward(hipStream_t st, const LayerForwardArgs &a, const LayerForwardVariant &v) {
+  if (v.adaptive) {
+    if (v.packed) return v.planes == 3 ? launch_adaptive<true, 3>(st, a) : launch_adaptive<true, 1>(st, a);
+    return v.planes == 3 ? launch_adaptive<false, 3>(st, a) : launch_adaptive<false, 1>(st, a);
+  }
   if (v.slots) return v.neurons == 64 ? launch_short<1>(st, a, v) : launch_short<2>(st, a, v);
   const unsigned grid = (unsigned)((a.B + 7) / 8 * 8 * a.parts * (v.time_split || v.layer_split ? 2 : 1));
   if (v.neurons == 64) return v.packed ? launch_packed<1, true>(st, a, v, grid) : launch_packed<1, false>(st, a, v, grid);

@@ -65,6 +65,8 @@ struct LayerForwardOp {
   float *V;                // [T*B][ld]
   uint8_t *S;              // [T*B][ld]
   const float *beta_v;     // [ld]
+  float *A;                // adaptive thresholds: adaptation in force at each step [T*B][ld], its decay and its rise per spike
+  float gamma, kappa;
 };
 
 struct LayerForwardArgs {
@@ -113,6 +115,7 @@ struct LayerForwardVariant {
   bool full;               // every layer fills its column blocks
   bool packed, time_split, layer_split;
   bool slots;              // several samples to a workgroup (layer_forward_short.hpp)
+  bool adaptive;           // adaptive firing threshold: slots, 64 neurons, one layer, no readout
 };
 hipError_t layer_forward(hipStream_t st, const LayerForwardArgs &a, const LayerForwardVariant &v);
 

@@ -14,18 +14,26 @@
 //      entry state from the segments before it in the same slot.
 // 700-200-150-20 fp32, T = 30, B = 500: 150.6 us per step with product and scan apart, 121 so; 700-157-157-20,
 // T = 20, B = 209 (forward, loss and logits): 63.8 apart, 66.6 with a sample to a tile, 58 so.
+//
+// ADAPT: layers with adaptive firing thresholds (see lif_forward_kernel), at any number of steps: the second
+// state A needs a tile of its own beside V, which fits for 64 neurons, and the kernel above hands finished rows to
+// storing wavefronts that would have to know it.  Rasters of more than 64 steps take SL = 128, a block
+// after the other, the two states in the scanning thread's registers.  What bounds it is the chain of a step,
+// four dependent operations (decision, adaptation, threshold, distance) where the plain neuron has two.
+// 700-256-256-20, T = B = 128, per step: 131 us with product and scan apart, 122 so; 700-40-40-20, T = 128, B = 64: 88 and 77.
 #pragma once
 #include "layer_forward.hpp"
 
 namespace snn {
 
-template <int TN, bool READOUT, int NL, bool PACKED, int NP>
+template <int TN, bool READOUT, int NL, bool PACKED, int NP, bool ADAPT = false>
 __global__ __launch_bounds__(256, 2) void lif_layer_forward_short_kernel(const LayerForwardArgs a) {
   typedef SpikeTile<2, 2, 2, TN, 3> Tile;
   constexpr int BM = Tile::BM, BN = Tile::BN, PI = Tile::PI, QI = Tile::QI, KS = Tile::KSTAGE;
   constexpr int TM = 2, CP = BN * 4 + 16, JP = 36;
   constexpr int STAGES = Tile::lds_bytes(false, NP) > Tile::lds_bytes(PACKED, NP) ? Tile::lds_bytes(false, NP) : Tile::lds_bytes(PACKED, NP);
-  constexpr int LDS_BYTES = STAGES > BM * CP ? STAGES : BM * CP;
+  constexpr int TILES = (ADAPT ? 2 : 1) * BM * CP, LDS_BYTES = STAGES > TILES ? STAGES : TILES;
+  static_assert(!ADAPT || (TN == 1 && !READOUT && NL == 1), "adaptive layers: 64 neurons, alone in their launch");
   static_assert(BM == 128 && LDS_BYTES <= 80 * 1024, "two workgroups per compute unit");
   __shared__ __attribute__((aligned(16))) char lds[LDS_BYTES];
   __shared__ float x_e[8][32], x_best[8][32];
@@ -42,11 +50,14 @@ __global__ __launch_bounds__(256, 2) void lif_layer_forward_short_kernel(const L
   const float theta = a.theta;
   const float big = 0x1p100f, mtheta_big = -theta * 0x1p100f, mtheta = -theta;
   // element (t, b) of row r of the tile, or -1
+  int t0 = 0;                                         // (only ADAPT has more than one block)
   auto pos = [&](int r) {
-    const int t = r & (SL - 1), b = b0 + (r >> sl2);
+    const int t = t0 + (r & (SL - 1)), b = b0 + (r >> sl2);
     return t < a.T && b < a.B ? t * a.B + b : -1;
   };
-  const int steps = (a.T + 15) & ~15;                 // whole groups of 16 (at most SL)
+  float v_in = 0.f, ad_in = 0.f;                      // ADAPT: the states entering a block of 128 steps
+  do {
+  const int steps = min(SL, (a.T - t0 + 15) & ~15);   // whole groups of 16
 
   static_for<NL>([&](auto LI) {
     constexpr int li = decltype(LI)::value;
@@ -71,9 +82,9 @@ __global__ __launch_bounds__(256, 2) void lif_layer_forward_short_kernel(const L
     if constexpr (PACKED && li == 0) {
       PackedRows pk;
       pk.rsrc = make_rsrc(op.P, op.p_bytes);
-      pk.base = b0 * op.ldp;
+      pk.base = ((t0 >> 3) * a.B + b0) * op.ldp;
       pk.row_stride = a.B * op.ldp;
-      pk.rows = (a.T + 7) >> 3;
+      pk.rows = ((a.T + 7) >> 3) - (t0 >> 3);
       pk.kbytes = op.ldp;
       pk.slot_log2 = sl2 - 3;
       pk.samples = a.B - b0;
@@ -114,7 +125,7 @@ __global__ __launch_bounds__(256, 2) void lif_layer_forward_short_kernel(const L
     for (int q = tid; q < SPT * BN; q += 256) {       // (256 is a multiple of BN: the same neuron each time)
       constexpr int U = 16;
       float *cell = (float *)(lds + (q / BN << sl2) * CP + (q % BN) * 4);
-      float v = 0.f, nxt[U];
+      float v = ADAPT ? v_in : 0.f, ad = ADAPT ? ad_in : 0.f, nxt[U];
 #pragma unroll
       for (int u = 0; u < U; ++u) nxt[u] = cell[u * (CP / 4)];
       for (int s0 = 0; s0 < steps; s0 += U) {
@@ -131,10 +142,19 @@ __global__ __launch_bounds__(256, 2) void lif_layer_forward_short_kernel(const L
         for (int u = 0; u < U; ++u) {
           cell[(s0 + u) * (CP / 4)] = v;
           float s;
+          if constexpr (ADAPT) {
+            cell[(BM + s0 + u) * (CP / 4)] = ad;
+            const float thr = theta + ad;
+            asm("v_mul_f32 %0, %1, %2 clamp" : "=v"(s) : "v"(v - thr), "v"(big));
+            v = __builtin_fmaf(-thr, s, __builtin_fmaf(beta, v, cur[u]));
+            ad = __builtin_fmaf(op.gamma, ad, op.kappa * s);
+            continue;
+          }
           asm("v_fma_f32 %0, %1, %2, %3 clamp" : "=v"(s) : "v"(v), "v"(big), "v"(mtheta_big));
           v = __builtin_fmaf(mtheta, s, __builtin_fmaf(beta, v, cur[u]));
         }
       }
+      if (ADAPT && SL == BM) { v_in = v; ad_in = ad; }
     }
     __syncthreads();
 
@@ -147,6 +167,12 @@ __global__ __launch_bounds__(256, 2) void lif_layer_forward_short_kernel(const L
       const int vo = e >= 0 && n0 + col < ld ? (e * ld + n0 + col) * 4 : OOB;
       if (a.nt_store) __builtin_amdgcn_raw_buffer_store_b128(x, rV, vo, 0, NT);
       else __builtin_amdgcn_raw_buffer_store_b128(x, rV, vo, 0, 0);
+      if constexpr (ADAPT) {
+        const u32x4 xa = *(const u32x4 *)(lds + (BM + row) * CP + col * 4);
+        const rsrc_t rA = make_rsrc(op.A, (unsigned)a.T * a.B * ld * 4u);
+        if (a.nt_store) __builtin_amdgcn_raw_buffer_store_b128(xa, rA, vo, 0, NT);
+        else __builtin_amdgcn_raw_buffer_store_b128(xa, rA, vo, 0, 0);
+      }
     }
 #pragma unroll
     for (int p0 = 0; p0 < BM * SLC; p0 += 256) {
@@ -154,7 +180,12 @@ __global__ __launch_bounds__(256, 2) void lif_layer_forward_short_kernel(const L
       u32x4 x;
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        const f32x4 f = *(const f32x4 *)(lds + row * CP + (col + 4 * q) * 4);
+        f32x4 f = *(const f32x4 *)(lds + row * CP + (col + 4 * q) * 4);
+        if constexpr (ADAPT) {                        // (the same difference as in the scan, against zero)
+          const f32x4 fa = *(const f32x4 *)(lds + (BM + row) * CP + (col + 4 * q) * 4);
+#pragma unroll
+          for (int e4 = 0; e4 < 4; ++e4) f[e4] = f[e4] - (theta + fa[e4]) > 0.f ? INFINITY : -INFINITY;
+        }
         x[q] = (f[0] > theta ? 1u : 0u) | (f[1] > theta ? 0x100u : 0u) | (f[2] > theta ? 0x10000u : 0u) |
                (f[3] > theta ? 0x1000000u : 0u);
       }
@@ -297,6 +328,9 @@ __global__ __launch_bounds__(256, 2) void lif_layer_forward_short_kernel(const L
       __syncthreads();
     }
   });
+  t0 += SL;
+  if (ADAPT) __syncthreads();                         // the next product's stages overwrite the tiles
+  } while (ADAPT && t0 < a.T);
 }
 
 }  // namespace snn

@@ -971,13 +971,21 @@ int launch_lif_reverse_fused(snn_ctx *c, int l) {
 // runs the readout scan, the loss and the readout's current gradients;
 // SNN_OPT_LAYER_MIN_BATCH: samples from which it is used (0: layer_forward_min_batch);
 // SNN_OPT_LAYER_NEURONS: 64 or 128 neurons per workgroup.
+// Layers with adaptive thresholds (adaptive_in_one_launch): their workgroups scan with one wavefront of four, four
+// dependent operations a step, so up to 256 steps (T = 400, B = 8, 700-256-256-20: 162 us with product and scan apart,
+// 168 in one), and from a short fan-in, where there is less of a product to hide it, where the rows of the tile are
+// used (200-100-20: T = 16, B = 64 37.3 and 38.6, T = 128 56.8 and 54.2, T = 200, B = 400 112 and 117, T = 256 153 and 134).
+bool adaptive_in_one_launch(const snn_ctx *c, int l) {
+  if (c->layers[l].K > 256) return c->T <= 256;
+  return c->T > 40 && c->T <= 256 && (c->T <= 64 || c->T * 5 >= (c->T + 127) / 128 * 128 * 4);
+}
 int layer_fuse_mode(const snn_ctx *c) { return c->opt[SNN_OPT_LAYER_FORWARD]; }
 static int layer_max_neurons(const snn_ctx *c) { return c->opt[SNN_OPT_LAYER_MAX_NEURONS]; }
 bool layer_forward_fusable(snn_ctx *c, int l) {
   if (l < 0 || l > c->L - 2) return false;
   const Layer &y = c->layers[l];
   const SpikeSrc s = spikes_below(c, l);
-  return y.spiking && !y.recurrent && !y.adaptive && y.ld <= layer_max_neurons(c) && c->B >= layer_forward_min_batch(c, l) &&
+  return y.spiking && !y.recurrent && (!y.adaptive || adaptive_in_one_launch(c, l)) && y.ld <= layer_max_neurons(c) && c->B >= layer_forward_min_batch(c, l) &&
          s.ld % 4 == 0 && s.ld <= layer_max_neurons(c) && (size_t)c->M * s.ld < ((size_t)1 << 31) && (size_t)c->M * y.ld * 4 < ((size_t)1 << 31) &&
          c->theta >= 0x1p-60f && c->theta <= 0x1p26f;
 }
@@ -987,7 +995,7 @@ bool layer_forward_fusable(snn_ctx *c, int l) {
 int layer_forward_takes_readout(snn_ctx *c) {
   const Layer &ro = c->layers[c->L - 1];
   const int mode = layer_fuse_mode(c);
-  const bool ok = c->L >= 2 && mode >= 3 && layer_forward_fusable(c, c->L - 2) && c->layers[c->L - 2].ld <= 128 &&
+  const bool ok = c->L >= 2 && mode >= 3 && layer_forward_fusable(c, c->L - 2) && c->layers[c->L - 2].ld <= 128 && !c->layers[c->L - 2].adaptive &&
                   c->opt[SNN_OPT_LAYER_NEURONS] == 128 && c->ldC <= 32 && ro.qf_plane >= 32ll * ro.ldqf;
   return !ok ? 0 : mode >= 4 ? 2 : c->nplanes == 1 ? 1 : 0;
 }
@@ -1019,6 +1027,8 @@ int launch_layer_forward(snn_ctx *c, int l, int nl, int with_readout, const int3
     op.P = s.p; op.ldp = s.ld; op.kc = s.valid; op.p_bytes = s.bytes;
     op.Q = yi.Qf; op.ldq = yi.ldqf; op.q_bytes = (unsigned)(c->nplanes * yi.qf_plane * 2); op.q_plane = (unsigned)(yi.qf_plane * 2);
     op.V = yi.V; op.S = yi.S; op.beta_v = yi.beta_v; op.ld = yi.ld;
+    op.A = yi.A; op.gamma = yi.gamma; op.kappa = yi.kappa;
+    v.adaptive = yi.adaptive;                            // (alone in its launch)
     yi.i_ready = false;
     widest = std::max(widest, yi.ld);
   }
@@ -1026,14 +1036,14 @@ int launch_layer_forward(snn_ctx *c, int l, int nl, int with_readout, const int3
   a.T = c->T; a.B = c->B;
   a.nt_store = streams_past_cache(c, c->M * widest * 4);
   a.err = c->err_flag;
-  v.neurons = layer_workgroup_neurons(c, widest, nl > 1 || with_readout);
+  v.neurons = v.adaptive ? 64 : layer_workgroup_neurons(c, widest, nl > 1 || with_readout);
   a.parts = (widest + v.neurons - 1) / v.neurons;
   v.full = true;
   for (int i = 0; i < nl; ++i) v.full = v.full && a.op[i].ld == a.parts * v.neurons;
   // Two workgroups per sample, taking its blocks of 64 steps in turn (SNN_OPT_LAYER_TIME_SPLIT, on
   // request: 29.3 us against 28.8 at 700-128-128-20, T = 128, B = 256): from two blocks on, and while a
   // block count fits the flags' 10 bits.
-  v.time_split = c->opt[SNN_OPT_LAYER_TIME_SPLIT] && v.neurons == 128 && v.full && v.planes == 1 && c->T > 64 && c->T <= 64 * 1000;
+  v.time_split = c->opt[SNN_OPT_LAYER_TIME_SPLIT] && v.neurons == 128 && v.full && v.planes == 1 && !v.adaptive && c->T > 64 && c->T <= 64 * 1000;
   // A pair of layers on two workgroups per sample (SNN_OPT_LAYER_PAIR = 2, on request: 32.9 us against
   // 27.7 at 700-128-128-20, T = 128, B = 256): the upper layer's workgroup follows the lower layer's,
   // 64 steps at a time.
@@ -1067,7 +1077,8 @@ int launch_layer_forward(snn_ctx *c, int l, int nl, int with_readout, const int3
   // 75.1 with four, 82.4 with two).
   a.slot_log2 = c->T <= 16 ? 4 : c->T <= 32 ? 5 : 6;
   while (a.slot_log2 < 7 && ((long long)c->B * a.parts << a.slot_log2) < 128ll * 128) ++a.slot_log2;
-  v.slots = a.slot_log2 < 7 && c->T <= 64 && !v.layer_split && v.readout != 1;
+  if (c->T > 64) a.slot_log2 = 7;
+  v.slots = a.slot_log2 < 7 && !v.layer_split && v.readout != 1;
   a.integral = c->integral;
   HIPCHK(c, layer_forward(c->stream, a, v));
   return SNN_OK;
@@ -1469,6 +1480,7 @@ static int32_t forward_layers(snn_ctx *c, const int32_t *labels_dev, float *loss
       // this layer and the next in one launch when both hold at most 128 padded neurons
       // (SNN_OPT_LAYER_PAIR = 0: one launch each)
       const bool pair = c->opt[SNN_OPT_LAYER_PAIR] && c->opt[SNN_OPT_LAYER_NEURONS] == 128 && c->layers[l].ld <= 128 && l + 1 <= c->L - 2 &&
+                        !c->layers[l].adaptive && !c->layers[l + 1].adaptive &&
                         (l + 1 < c->L - 2 || whole_top) && layer_forward_fusable(c, l + 1) && c->layers[l + 1].ld <= 128;
       const int nl = pair ? 2 : 1;
       if ((rc = launch_layer_forward(c, l, nl, l + nl - 1 == c->L - 2 ? with_readout : 0, labels_dev))) return rc;

@@ -1566,6 +1566,27 @@ def test_adaptive_threshold_vector_scans(B, nt):
     assert rep["spike_rate"][0] > 0.01
 
 
+@pytest.mark.parametrize("precision", ["bf16", "fp32"])
+@pytest.mark.parametrize("T,B,sizes,packed", [(1, 3, (300, 1, 2), False), (16, 1030, (300, 40, 10), False), (41, 5, (90, 72, 121, 10), True),
+                                              (64, 261, (40, 64, 20), True), (104, 4, (300, 130, 20), True), (129, 5, (300, 200, 96, 10), True),
+                                              (256, 3, (132, 63, 10), False)],
+                         ids=["one-neuron", "eight-samples", "two-layers-packed", "two-samples-packed", "three-parts", "two-blocks-packed",
+                              "two-full-blocks"])
+def test_adaptive_layers_in_one_launch(T, B, sizes, packed, precision):
+    """Layers with adaptive thresholds, product and scan in one launch: slots of several samples, one and two
+    blocks of 128 steps with the two states carried over, parts of 64 neurons, both input formats."""
+    L = len(sizes) - 1
+    wl = workloads.Workload(name="adaptive-launch", index=27, T=T, B=B, sizes=sizes, recurrent=(False,) * (L - 1),
+                            beta=(0.9, 0.93, 0.95)[:L], theta=1.0, surrogate="superspike", slope=10.0, precision=precision,
+                            rate_lo=0.1, rate_hi=0.3, adapt_decay=(0.9, 0.8)[:L - 1], adapt_step=(0.3, 0.2)[:L - 1])
+    full_step_parity(wl, w_gain=2.5, options={"layer_min_batch": 1})
+    if packed:
+        inp = workloads.generate(wl, w_gain=2.5)
+        snn = make(wl, inp, {"layer_min_batch": 1})
+        parity.compare_forward(net_of(wl), inp, snn, snn.forward_packed(np.packbits(inp.X, axis=0), inp.labels), {})
+        snn.destroy()
+
+
 def test_adaptive_threshold_with_trained_decays_and_integral_loss():
     wl = workloads.Workload(name="adaptive_beta", index=32, T=33, B=9, sizes=(50, 40, 24, 5), recurrent=(False, False),
                             beta=(0.9, 0.9, 0.9), theta=1.0, surrogate="sigmoid", slope=4.0, precision="fp32",
