@@ -190,22 +190,26 @@ typedef enum {
 /* Kernel-selection options of a context (snn_set_option).  Every choice computes the same step
  * of the path; results differ only in the order floating-point sums are taken.  The defaults
  * are the measured best; the tests use the options to reach each kernel on small shapes.
- *   LAYER_FORWARD     feed-forward spiking layers of 64..LAYER_MAX_NEURONS padded neurons on
- *                     rounded weights run product and scan as ONE launch (Eq. 1-2 with the
- *                     preceding Linear layer): 0 never; 1 all but the last spiking layer;
- *                     2 every such layer; 3 the last one also forms the readout's currents
- *                     (128 padded neurons, at most 32 padded classes); 4 (default) and runs the
- *                     readout scan, the loss and the readout's current gradients
- *   LAYER_PAIR        1 (default): two consecutive one-launch layers of exactly 128 padded
- *                     neurons share a launch; 0: one launch each; 2: they share a launch with a
+ *   LAYER_FORWARD     feed-forward spiking layers of up to LAYER_MAX_NEURONS padded neurons run
+ *                     product and scan as ONE launch (Eq. 1-2 with the preceding Linear layer;
+ *                     adaptive layers: rasters of up to 256 steps): 0 never; 1 all but the last
+ *                     spiking layer; 2 every such layer; 3 the last one also forms the readout's
+ *                     currents (rounded weights, at most 128 padded neurons and 32 padded classes);
+ *                     4 (default) and runs the readout scan, the loss and the readout's current
+ *                     gradients (fp32 products too)
+ *   LAYER_PAIR        1 (default): two consecutive one-launch layers of at most 128 padded
+ *                     neurons share a launch, and so do two consecutive recurrent layers of at
+ *                     most 192 on rounded weights; 0: one launch each; 2: one-launch layers of
+ *                     exactly 128 padded neurons share a launch with a
  *                     workgroup per layer and sample, the upper layer's following the lower
  *                     layer's through memory 64 steps at a time (measured slower: 32.9 against
  *                     27.7 us at 700-128-128-20, T = 128, B = 256; the upper layer's chain per 64
  *                     steps is longer than the lower layer's scan of them, and starts only once the
  *                     lower layer's whole product is done)
- *   LAYER_REVERSE     1 (default): the reverse pass of a layer of 64..256 neurons below a layer of
- *                     at most 128 columns runs as one launch (dS product, surrogate, scan; dS is
- *                     not stored); 2: so does that of a layer that is a multiple of 128 wide below a
+ *   LAYER_REVERSE     1 (default): the reverse pass of a layer below a layer of at most 128 columns
+ *                     runs as one launch (dS product, surrogate, scan; dS is not stored): up to 1024
+ *                     neurons, or 256 where TOP_SCANS has a kernel for it (rounded weights, a
+ *                     multiple of 64 neurons); 2: so does that of a layer that is a multiple of 128 wide below a
  *                     wider layer (measured slower than product + scan, hence not the default);
  *                     0: off
  *   TOP_SCANS         1 (default): the scans of a layer below at most 128 columns form the
@@ -302,8 +306,8 @@ int32_t snn_forward(snn_ctx *ctx, const uint8_t *x_dev, const int32_t *labels_de
  *   x_packed_dev  device, uint8 [ceil(T/8)][B][N_0]; bit 7-(t%8) of byte [t/8][b][n] is
  *                 the spike at step t (the first step in the most significant bit; bits
  *                 of steps >= T are ignored)
- * Where layer 1 runs as one launch (feed-forward, a multiple of 64 neurons wide, rounded
- * weights, at most 1024 input channels in rows of a multiple of 4 bytes) that launch reads the
+ * Where layer 1 runs as one launch (feed-forward, at most 1024 neurons and as many input
+ * channels, in rows of a multiple of 4 bytes) that launch reads the
  * packed raster itself and unpacks between its LDS read and the MFMA, and so does the weight-
  * gradient product of layer 1 in snn_backward when B is a multiple of 8; nothing is unpacked in
  * memory then.  Other shapes are unpacked into the workspace by a pre-pass.  x_packed_dev must
