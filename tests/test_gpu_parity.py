@@ -377,6 +377,25 @@ def test_weight_gradients_of_fp32_and_narrow_layers_through_transposing_reads(T,
     assert (np.abs(grads[0][0] - ref) <= T * B * 2.0 ** -24 * mag + 1e-30).all()
 
 
+@pytest.mark.parametrize("T,B,sizes", [(62, 8464, (132, 7, 4)), (50, 24, (300, 257, 20)), (50, 21, (140, 48, 10))],
+                         ids=["long-narrow", "wide", "batch-no-multiple-of-eight"])
+def test_fp32_weight_gradients_from_the_packed_raster(T, B, sizes):
+    """fp32 products on a raster packed along time: layer 1 runs as one launch that reads the bits, and so does its
+    weight gradient (narrow tiles, wide tiles; unpacked first where the batch is no multiple of eight)."""
+    wl = workloads.Workload(name="wgrad-packed-32", index=28, T=T, B=B, sizes=sizes, recurrent=(False,), beta=(0.9, 0.95),
+                            theta=1.0, surrogate="superspike", slope=10.0, precision="fp32", rate_lo=0.05, rate_hi=0.15)
+    inp = workloads.generate(wl, w_gain=3.0)
+    snn = make(wl, inp, {"layer_min_batch": 1})
+    snn.forward_packed(np.packbits(inp.X, axis=0), inp.labels)
+    snn.backward()
+    dW, G = snn.get_tensor("grad_w", 1), snn.get_tensor("d_current", 1).reshape(T * B, -1).astype(np.float64)
+    snn.destroy()
+    X = inp.X.reshape(T * B, -1).astype(np.float64)
+    # exact products; T B additions of 2^-24 of the sum of the terms' sizes
+    assert (np.abs(dW - X.T @ G) <= T * B * 2.0 ** -24 * (X.T @ np.abs(G)) + 1e-30).all()
+    assert np.abs(dW).max() > 0
+
+
 @pytest.mark.parametrize("T,B,sizes,rec", [(37, 40, (50, 320, 10), (True,)),
                                             (20, 33, (64, 512, 250, 10), (True, True)),
                                             (2, 5, (30, 264, 10), (True,)),
