@@ -492,7 +492,7 @@ struct SpikeTile {
         asm volatile("" : "+v"(d));
         af[sp][i] = __builtin_bit_cast(bf16x8, d);
       };
-      // what the next stage but one needs: plane pl + 2 of this round, or of the next
+      // what the next stage but one needs: plane pl + 2 of these elements, or of the next
       constexpr int npl = (pl + 2) % 3, np = npl == 0 ? PIK : 0, nl = np + QI;
       IssueRegs ir;
       static_for<SLOTS>([&](auto K) {
