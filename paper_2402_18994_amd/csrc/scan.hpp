@@ -816,31 +816,14 @@ __device__ __forceinline__ void loss_mean_block(const float *__restrict__ loss_b
   if (threadIdx.x == 0) loss[0] = part[0] / (float)B;
 }
 
-// Pinned memory: what the grid has written there (and to device memory) is the host's to read once word 2 holds
-// the number of this read-back.  The last of several workgroups says so (ticket: a device word that is 0
-// between launches).
-__device__ __forceinline__ void announce(int *host, int number, int *ticket = nullptr) {
-  __threadfence_system();
-  __syncthreads();
-  if (threadIdx.x) return;
-  if (ticket && gridDim.x > 1) {
-    if (atomicAdd(ticket, 1) != (int)gridDim.x - 1) return;
-    *ticket = 0;
-  }
-  __hip_atomic_store(host + 2, number, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
-}
-
 // host (optional): pinned memory that receives the error word and the loss.
 __global__ __launch_bounds__(256) void loss_mean_kernel(const float *__restrict__ loss_b, float *__restrict__ loss, int B,
-                                                        const int *__restrict__ err, int *__restrict__ host, int number) {
+                                                        const int *__restrict__ err, int *__restrict__ host) {
   __shared__ float part[256];
   loss_mean_block(loss_b, loss, B, part);
-  if (host) {
-    if (threadIdx.x == 0) {
-      host[0] = *err;
-      host[1] = __float_as_int(part[0] / (float)B);
-    }
-    announce(host, number);
+  if (host && threadIdx.x == 0) {
+    host[0] = *err;
+    host[1] = __float_as_int(part[0] / (float)B);
   }
 }
 
@@ -867,22 +850,6 @@ __global__ __launch_bounds__(256) void pack_rows_kernel(const void *__restrict__
     }
     ((uint32_t *)dst)[i] = v;
   }
-}
-
-// The same for a small tensor of 4-byte elements, announced.  (5120 logits by one workgroup of 1024 threads: 8.2 us.)
-template <bool HL>
-__global__ __launch_bounds__(256) void pack_small_kernel(const uint32_t *__restrict__ src, uint32_t *__restrict__ dst,
-                                                         int count, int cols, int ld, const int *__restrict__ err,
-                                                         int *__restrict__ host, int number, int *__restrict__ ticket) {
-  const int e = blockIdx.x * 256 + threadIdx.x;
-  if (e == 0) host[0] = *err;
-  if (e < count) {
-    const int r = e / cols;
-    uint32_t v = src[(size_t)r * ld + (e - r * cols)];
-    if (HL) v = __float_as_uint(bf16_value(v & 0xFFFFu) + bf16_value(v >> 16));
-    dst[e] = v;
-  }
-  announce(host, number, ticket);
 }
 
 // One workgroup beyond the last job (only launched when loss_b != NULL) takes the mean loss.

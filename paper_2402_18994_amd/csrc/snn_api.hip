@@ -5,7 +5,6 @@
 
 #include <hip/hip_runtime.h>
 
-#include <chrono>
 #include <cstdarg>
 #include <cstdio>
 #include <cstdlib>
@@ -37,10 +36,8 @@ namespace {
 
 inline size_t rup(size_t x, size_t m) { return (x + m - 1) / m * m; }
 
-// Read-back space of a context: word 0 the error word, word 1 the loss, word 2 the number of the last read-back
-// that its kernel has announced, then two chunks.
+// Read-back space of a context: word 0 the error word, word 1 the loss, then two chunks.
 constexpr size_t SNN_PIN_HEAD = 256, SNN_PIN_CHUNK = 512 << 10;
-constexpr size_t SNN_PIN_SMALL = 16384;  // elements of a tensor that is announced
 
 struct Layer {
   int K = 0, N = 0;        // fan-in, fan-out
@@ -119,7 +116,6 @@ struct snn_ctx {
   int opt[SNN_OPT_COUNT] = {4, 1, 1, 1, 1, 0, 128, 1024, 128, 1, 0, 0, 1, 1, 18, 0};   // snn_option values, in the enum's order
   char *pin = nullptr;            // pinned host memory the read-back kernels write: SNN_PIN_HEAD bytes, then two chunks
   hipEvent_t pin_ev[2] = {nullptr, nullptr};
-  int pin_number = 0;             // read-backs announced so far
   std::mutex pin_mutex;           // held from a read-back's launch until the host has taken the values out
   uint32_t *hand = nullptr;       // hand-over space of the forward launches that give a sample to two workgroups
   int hand_parts = 1;             // hand-over regions per sample (one per column block of a layer)
@@ -588,7 +584,7 @@ int launch_reduce(snn_ctx *c, const ReduceJobs &jobs, bool with_loss) {
 
 int ensure_loss(snn_ctx *c) {
   if (c->loss_ready) return SNN_OK;
-  hipLaunchKernelGGL(loss_mean_kernel, dim3(1), dim3(256), 0, c->stream, c->loss_b, c->loss, c->B, nullptr, nullptr, 0);
+  hipLaunchKernelGGL(loss_mean_kernel, dim3(1), dim3(256), 0, c->stream, c->loss_b, c->loss, c->B, nullptr, nullptr);
   HIPCHK(c, hipGetLastError());
   c->loss_ready = true;
   return SNN_OK;
@@ -1215,20 +1211,6 @@ int check_err_word(snn_ctx *c) {
   return SNN_OK;
 }
 
-// Waits for the read-back of the given number.  The kernel's own word in pinned memory is seen a few microseconds
-// before the stream counts as finished (loss and logits of 700-128-128-20, T = B = 256: 78 us with two stream
-// waits, 71 with two of these); after 2 ms, and wherever the kernel does not run, it is the stream wait.
-hipError_t wait_announced(snn_ctx *c, int number) {
-  const int *word = (const int *)c->pin + 2;
-  const auto t0 = std::chrono::steady_clock::now();
-  for (unsigned i = 1;; ++i) {
-    if (__atomic_load_n(word, __ATOMIC_ACQUIRE) == number) return hipSuccess;
-    if (i % 256 == 0 && std::chrono::steady_clock::now() - t0 > std::chrono::milliseconds(2)) break;
-    __builtin_ia32_pause();
-  }
-  return hipStreamSynchronize(c->stream);
-}
-
 // Describes where a tensor lives: rows x cols elements, leading dimension, element size;
 // `hl`: held on the device in hi/lo form, fp32 on the host side.
 struct TensorView { void *p; size_t rows, cols, ld, esz; bool hl; };
@@ -1246,17 +1228,6 @@ int read_back(snn_ctx *c, const TensorView &v, void *dst) {
     HIPCHK(c, hipMemcpyAsync(dst, v.p, n * v.esz, hipMemcpyDeviceToHost, c->stream));
     HIPCHK(c, hipMemcpyAsync(c->pin, c->err_flag, sizeof(int), hipMemcpyDeviceToHost, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
-    return SNN_OK;
-  }
-  if (v.esz == 4 && n <= SNN_PIN_SMALL) {
-    uint32_t *const to = (uint32_t *)(c->pin + SNN_PIN_HEAD);
-    const int number = ++c->pin_number;
-    const dim3 grid((unsigned)((n + 255) / 256));
-    if (v.hl) hipLaunchKernelGGL(pack_small_kernel<true>, grid, dim3(256), 0, c->stream, (const uint32_t *)v.p, to, (int)n, (int)v.cols, (int)v.ld, c->err_flag, (int *)c->pin, number, c->err_flag + 32);
-    else hipLaunchKernelGGL(pack_small_kernel<false>, grid, dim3(256), 0, c->stream, (const uint32_t *)v.p, to, (int)n, (int)v.cols, (int)v.ld, c->err_flag, (int *)c->pin, number, c->err_flag + 32);
-    HIPCHK(c, hipGetLastError());
-    HIPCHK(c, wait_announced(c, number));
-    memcpy(out, to, n * v.esz);
     return SNN_OK;
   }
   const size_t chunks = (n + per - 1) / per;
@@ -1439,7 +1410,6 @@ int32_t snn_init(const snn_config *cfg, void *workspace_dev, size_t workspace_by
     if ((e = static_scratch(&unused)) != hipSuccess) return bail(e, "hipGetSymbolAddress(scratch)");
   }
   if ((e = hipHostMalloc((void **)&c->pin, SNN_PIN_HEAD + 2 * SNN_PIN_CHUNK, hipHostMallocDefault)) != hipSuccess) return bail(e, "hipHostMalloc");
-  memset(c->pin, 0, SNN_PIN_HEAD);
   for (hipEvent_t &ev : c->pin_ev)
     if ((e = hipEventCreateWithFlags(&ev, hipEventDisableTiming)) != hipSuccess) return bail(e, "hipEventCreate");
   if ((e = hipMemsetAsync(c->ws, 0, c->ws_bytes, c->stream)) != hipSuccess) return bail(e, "hipMemsetAsync(workspace)");
@@ -1507,11 +1477,10 @@ static int32_t forward_layers(snn_ctx *c, const int32_t *labels_dev, float *loss
   if (loss_host) {
     // the loss and the error word go straight to pinned memory: one launch, one wait
     std::lock_guard<std::mutex> lock(c->pin_mutex);
-    const int number = ++c->pin_number;
-    hipLaunchKernelGGL(loss_mean_kernel, dim3(1), dim3(256), 0, c->stream, c->loss_b, c->loss, c->B, c->err_flag, (int *)c->pin, number);
+    hipLaunchKernelGGL(loss_mean_kernel, dim3(1), dim3(256), 0, c->stream, c->loss_b, c->loss, c->B, c->err_flag, (int *)c->pin);
     HIPCHK(c, hipGetLastError());
     c->loss_ready = true;
-    HIPCHK(c, wait_announced(c, number));
+    HIPCHK(c, hipStreamSynchronize(c->stream));
     *loss_host = ((volatile float *)c->pin)[1];
     if ((rc = check_err_word(c))) return rc;
   }

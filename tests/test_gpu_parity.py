@@ -1304,12 +1304,11 @@ def test_tensors_read_back_as_set(precision, T, B, N):
 
 @pytest.mark.parametrize("precision", ["fp32", "bf16"])
 @pytest.mark.parametrize("B", [1, 16, 256, 257])
-def test_small_tensors_are_announced(B, precision):
-    """Tensors of up to 16384 elements come back through workgroups of 256 whose last one tells the host: one
-    element, one workgroup, the most and one more (which takes the other way), several times in a row, with the
-    loss between them, padding columns left out, hi/lo words as their sums."""
+def test_small_tensors_read_back_beside_the_loss(B, precision):
+    """Small tensors several times in a row, with the loss between them: one element, one workgroup, many; padding
+    columns left out, hi/lo words as their sums."""
     T, sizes = 4, (20, 24, 16)
-    wl = workloads.Workload(name="announced", index=26, T=T, B=B, sizes=sizes, recurrent=(False,), beta=(0.9, 0.95), theta=1.0,
+    wl = workloads.Workload(name="read-back", index=26, T=T, B=B, sizes=sizes, recurrent=(False,), beta=(0.9, 0.95), theta=1.0,
                             surrogate="superspike", slope=10.0, precision=precision, rate_lo=0.2, rate_hi=0.4)
     inp = workloads.generate(wl, w_gain=3.0)
     snn = make(wl, inp)
@@ -1329,6 +1328,27 @@ def test_small_tensors_are_announced(B, precision):
         snn.set_tensor("d_logits", 0, z)
         assert np.array_equal(snn.get_tensor("d_logits"), z)
     snn.destroy()
+
+
+def test_calls_with_host_results_wait_for_the_stream():
+    """snn_forward with a loss and snn_get_tensor return when the stream is idle, whatever the tensor's size
+    and type: a stream or an event that is asked right after the call has finished."""
+    import torch
+    wl = workloads.CONFIGS["shd_ff128"].scaled(T=32, B=64)
+    inp = workloads.generate(wl, w_gain=3.0)
+    snn = make(wl, inp)
+    x, y = torch.from_numpy(inp.X).cuda(), torch.from_numpy(inp.labels).cuda()
+    busy = []
+    for i in range(200):
+        snn.forward(x, y)
+        if not snn.stream.query():
+            busy.append(("loss", i))
+        for name, layer in (("logits", 0), ("argmax_t", 0), ("spikes", 1), ("membrane", 1)):
+            snn.get_tensor(name, layer)
+            if not snn.stream.query():
+                busy.append((name, i))
+    snn.destroy()
+    assert not busy, (len(busy), busy[:5])
 
 
 def test_several_threads_read_one_context():
