@@ -971,7 +971,10 @@ int launch_lif_reverse_fused(snn_ctx *c, int l) {
 // dependent operations a step, so up to 256 steps (T = 400, B = 8, 700-256-256-20: 162 us with product and scan apart,
 // 168 in one), and from a short fan-in, where there is less of a product to hide it, where the rows of the tile are
 // used (200-100-20: T = 16, B = 64 37.3 and 38.6, T = 128 56.8 and 54.2, T = 200, B = 400 112 and 117, T = 256 153 and 134).
+// Their scan multiplies the threshold and its rise by the spike (0 or 1), which is no choice between values once they
+// are infinite: only where no adaptation (at most kappa a step) leaves the thresholds that the spike decision is exact for.
 bool adaptive_in_one_launch(const snn_ctx *c, int l) {
+  if (!(c->theta + c->layers[l].kappa * (float)c->T <= 0x1p26f)) return false;
   if (c->layers[l].K > 256) return c->T <= 256;
   return c->T > 40 && c->T <= 256 && (c->T <= 64 || c->T * 5 >= (c->T + 127) / 128 * 128 * 4);
 }

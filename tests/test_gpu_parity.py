@@ -1626,6 +1626,32 @@ def test_adaptive_layers_in_one_launch(T, B, sizes, packed, precision):
         snn.destroy()
 
 
+@pytest.mark.parametrize("rise", [float("inf"), 3e38])
+@pytest.mark.parametrize("precision", ["bf16", "fp32"])
+def test_adaptive_thresholds_out_of_reach(precision, rise):
+    """A rise so large that a neuron fires at most once, up to infinity (a network of first spikes): the layer's states
+    are those of any other rise that no potential reaches, bit for bit in spikes and potentials, and those of the
+    oracle (which takes 1e30: infinity times no spike has no value there)."""
+    wl = workloads.Workload(name="first-spikes", index=29, T=40, B=6, sizes=(300, 72, 10), recurrent=(False,), beta=(0.9, 0.95),
+                            theta=1.0, surrogate="superspike", slope=10.0, precision=precision, rate_lo=0.1, rate_hi=0.3,
+                            adapt_decay=(1.0,), adapt_step=(1e30,))
+    inp = workloads.generate(wl, w_gain=2.5)
+    out = []
+    for step in (1e30, rise):
+        snn = make(wl.scaled(adapt_step=(step,)), inp)
+        loss = snn.forward(inp.X, inp.labels)
+        if step == 1e30:
+            rep = {}
+            tr = parity.compare_forward(net_of(wl), inp, snn, loss, rep)
+            assert tr.S[0].sum(axis=0).mean() > 0.1 and tr.S[0].sum(axis=0).max() == 1
+        S, V = snn.get_tensor("spikes", 1), snn.get_tensor("membrane", 1)
+        out.append((S, V, loss))
+        snn.destroy()
+    assert np.array_equal(out[0][0], out[1][0])
+    assert np.array_equal(out[0][1], out[1][1])
+    assert out[0][2] == out[1][2]
+
+
 def test_adaptive_threshold_with_trained_decays_and_integral_loss():
     wl = workloads.Workload(name="adaptive_beta", index=32, T=33, B=9, sizes=(50, 40, 24, 5), recurrent=(False, False),
                             beta=(0.9, 0.9, 0.9), theta=1.0, surrogate="sigmoid", slope=4.0, precision="fp32",
