@@ -164,6 +164,7 @@ class SNN:
         self._chk(rc, None)
         self.ctx = ctx
         self._x = None
+        self._x_packed = False           # self._x is a raster packed along time
         self._labels = None
         for name, value in (options or {}).items():
             self.set_option(name, value)
@@ -215,6 +216,7 @@ class SNN:
     def forward(self, x, labels, want_loss: bool = True):
         """snn_forward.  x: uint8 [T,B,N0] (numpy or cuda tensor), labels: int32 [B]."""
         self._x, self._labels = self._dev_u8(x), self._dev_i32(labels)
+        self._x_packed = False
         assert tuple(self._x.shape) == (self.T, self.B, self.sizes[0]), tuple(self._x.shape)
         assert tuple(self._labels.shape) == (self.B,)
         loss = C.c_float(0.0)
@@ -226,6 +228,7 @@ class SNN:
     def forward_packed(self, x_packed, labels, want_loss: bool = True):
         """snn_forward_packed.  x_packed: uint8 [ceil(T/8),B,N0] = numpy.packbits(x, axis=0)."""
         self._x, self._labels = self._dev_u8(x_packed), self._dev_i32(labels)
+        self._x_packed = True
         assert tuple(self._x.shape) == ((self.T + 7) // 8, self.B, self.sizes[0]), tuple(self._x.shape)
         assert tuple(self._labels.shape) == (self.B,)
         loss = C.c_float(0.0)
@@ -254,10 +257,11 @@ class SNN:
 
     def run_step(self, step: str, layer: int, x=None, labels=None):
         if x is not None:
-            self._x = self._dev_u8(x)
+            self._x, self._x_packed = self._dev_u8(x), False
         if labels is not None:
             self._labels = self._dev_i32(labels)
-        xp = self._x.data_ptr() if self._x is not None else None
+        # (x_dev is a raster of bytes; one packed along time stays where snn_forward_packed found it)
+        xp = self._x.data_ptr() if self._x is not None and not self._x_packed else None
         lp = self._labels.data_ptr() if self._labels is not None else None
         self._chk(self.lib.snn_run_step(self.ctx, STEPS[step], layer, xp, lp), self.ctx)
 

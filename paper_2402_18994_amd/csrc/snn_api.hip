@@ -492,8 +492,13 @@ int launch_input_grad(snn_ctx *c, int l) {
     else e = gemm_launch<P_HL, Q_BF16, EPI_STORE, 1, 4, 1, 1, 1, 1>(a, 1, c->stream);
   }
   HIPCHK(c, e);
+  below.ds_ready = true;
   return SNN_OK;
 }
+
+// I and dS of a layer whose last launch formed them on the fly: into memory, for a reader or a single step.
+int ensure_current(snn_ctx *c, int l) { return c->layers[l].i_ready ? SNN_OK : launch_current_gemm(c, l); }
+int ensure_spike_grads(snn_ctx *c, int l) { return c->layers[l].ds_ready ? SNN_OK : launch_input_grad(c, l + 1); }
 
 // part[split][rows x cols] (or out directly when there is one split) = Sp^T G over one
 // slice of the T*B rows per split.
@@ -1599,13 +1604,8 @@ int32_t snn_get_tensor(snn_ctx *c, int32_t tensor, int32_t layer, void *dst, siz
   std::lock_guard<std::mutex> lock(c->pin_mutex);
   if ((rc = flush_reduce(c))) return rc;
   if (tensor == SNN_T_LOSS && (rc = ensure_loss(c))) return rc;
-  if (tensor == SNN_T_CURRENT && layer >= 1 && layer <= c->L - 1 && !c->layers[layer - 1].i_ready) {
-    if ((rc = launch_current_gemm(c, layer - 1))) return rc;   // the layer ran as one launch: materialise I now
-  }
-  if (tensor == SNN_T_D_SPIKES && layer >= 1 && layer <= c->L - 1 && !c->layers[layer - 1].ds_ready) {
-    if ((rc = launch_input_grad(c, layer))) return rc;   // formed on the fly in snn_backward: materialise it now
-    c->layers[layer - 1].ds_ready = true;
-  }
+  if (tensor == SNN_T_CURRENT && (rc = ensure_current(c, layer - 1))) return rc;
+  if (tensor == SNN_T_D_SPIKES && (rc = ensure_spike_grads(c, layer - 1))) return rc;
   if ((rc = read_back(c, v, dst))) return rc;
   return check_err_word(c);
 }
@@ -1667,11 +1667,13 @@ int32_t snn_run_step(snn_ctx *c, int32_t step, int32_t layer, const uint8_t *x_d
     case SNN_STEP_CURRENT_GEMM: return launch_current_gemm(c, l);
     case SNN_STEP_LIF_FORWARD:
       if (!spiking) return fail(c, SNN_ERR_ARG, "layer %d is not spiking", layer);
+      if (int rc = ensure_current(c, l)) return rc;
       return launch_lif_forward(c, l);
     case SNN_STEP_READOUT_FORWARD: return launch_readout_forward(c, labels_dev);
     case SNN_STEP_READOUT_REVERSE: return launch_readout_reverse(c);
     case SNN_STEP_LIF_REVERSE:
       if (!spiking) return fail(c, SNN_ERR_ARG, "layer %d is not spiking", layer);
+      if (int rc = ensure_spike_grads(c, l)) return rc;
       return launch_lif_reverse(c, l);
     case SNN_STEP_WEIGHT_GRAD: {
       ReduceJobs jobs;

@@ -1245,6 +1245,44 @@ def test_single_steps_on_oracle_tensors():
     snn.destroy()
 
 
+UNSTORED = [("fp32", (70, 150, 66, 10), (False, False), False), ("bf16", (72, 130, 66, 10), (False, False), True),
+            ("bf16", (70, 72, 121, 10), (True, True), False), ("bf16", (300, 96, 40, 10), (False, False), "adaptive")]
+
+
+def unstored_workload(precision, sizes, recurrent, kind):
+    """A network whose passes leave currents or spike gradients of some layers out of memory, and whether its raster
+    comes packed along time."""
+    adaptive = dict(adapt_decay=(0.9, 0.8), adapt_step=(0.3, 0.2)) if kind == "adaptive" else {}
+    wl = workloads.Workload(name="unstored", index=30, T=37, B=8, sizes=sizes, recurrent=recurrent, beta=(0.9, 0.93, 0.95),
+                            theta=1.0, surrogate="superspike", slope=10.0, precision=precision, rate_lo=0.1, rate_hi=0.3, **adaptive)
+    return wl, kind is True
+
+
+@pytest.mark.parametrize("precision,sizes,recurrent,kind", UNSTORED, ids=["fp32", "ragged-packed", "recurrent-pair", "adaptive"])
+def test_single_steps_after_a_pass_that_stored_nothing_between(precision, sizes, recurrent, kind):
+    """The scans alone, right after passes whose launches kept currents and spike gradients to themselves:
+    a step finds its inputs as if they had been stored, and gives the states and gradients of the pass again."""
+    wl, packed = unstored_workload(precision, sizes, recurrent, kind)
+    inp = workloads.generate(wl, w_gain=2.0)
+    snn = make(wl, inp)
+    if packed:
+        snn.forward_packed(np.packbits(inp.X, axis=0), inp.labels)
+    else:
+        snn.forward(inp.X, inp.labels)
+    snn.backward()
+    for l in (2, 1):
+        V, S, dI = (snn.get_tensor(n, l) for n in ("membrane", "spikes", "d_current"))
+        assert S.any() and dI.any()
+        snn.set_tensor("membrane", l, np.zeros_like(V))
+        snn.run_step("lif_forward", l)
+        assert np.array_equal(snn.get_tensor("spikes", l), S)
+        parity.close_state("V%d" % l, snn.get_tensor("membrane", l), V)
+        snn.set_tensor("membrane", l, V)
+        snn.run_step("lif_reverse", l)
+        parity.close_grad("dI%d" % l, snn.get_tensor("d_current", l), dI)
+    snn.destroy()
+
+
 # ---------------------------------------------------------------- invariants, errors, repeatability
 def test_silent_network_and_invariants():
     wl = workloads.CONFIGS["tiny_ff"]
