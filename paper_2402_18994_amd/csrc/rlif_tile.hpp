@@ -155,6 +155,11 @@ __global__ __launch_bounds__(KS * 64) void rlif_tile_reverse_kernel(const float 
   constexpr int PF = NP == 1 ? 6 : 4;                     // steps of dS and V in flight (one plane: 4: 51.5 us, 8: 47.8)
   constexpr int GP = NP == 1 ? 2 : 3;                     // planes of g; column c holds plane c/8, or c/4 (the fourth: zeros)
   constexpr int XB = G::CS * G::XP;
+  // The sigmoid's two exponentials and reciprocals come last in the step where the compiler is free, behind the
+  // products; at 129 to 192 neurons they stand under the fragment reads instead (T = 200, B = 64, 130 / 144 / 160 / 192
+  // neurons: 90.3 / 91.1 / 94.5 / 99.4 us behind, 89.2 / 89.5 / 90.3 / 91.6 so; at 60 and 250 neurons behind is
+  // faster, 49.5 against 55.2 and 113 against 117).
+  constexpr bool EARLY = NP == 1 && SURR == 2 && KS == 6;
   __shared__ __align__(16) char xs[2][GP][XB];
   const RlifLaneMasks L(threadIdx.x);
   const int b = blockIdx.x * G::CS + L.smp, row4 = B * ld * 4;
@@ -195,10 +200,28 @@ __global__ __launch_bounds__(KS * 64) void rlif_tile_reverse_kernel(const float 
       for (int k = 0; k < GP; ++k) *(uint32_t *)(x + k * XB + xo) = bf16_piece(gv[0], k) | (bf16_piece(gv[1], k) << 16);
     }
     f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+    float sg[2], u[2];
+    auto surrogates = [&] {
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        const float vt = __uint_as_float(vv[e]);
+        sg[e] = surr_rcp<SURR>(slope, vt - theta);
+        u[e] = __uint_as_float(ds[e]) - theta * gv[e];
+        db[e] += gv[e] * vt;
+      }
+    };
     lds_barrier();
+    bf16x8 early[EARLY ? KS : 1];
+    if constexpr (EARLY) {
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) early[ks] = *(const bf16x8 *)(x + fo + 64 * ks);
+      __builtin_amdgcn_sched_barrier(0);
+      surrogates();
+      __builtin_amdgcn_sched_barrier(0);
+    }
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
-      bf16x8 gf = *(const bf16x8 *)(x + fo + 64 * ks);
+      bf16x8 gf = EARLY ? early[EARLY ? ks : 0] : *(const bf16x8 *)(x + fo + 64 * ks);
       if (GP == 3 && pl == 3) gf = bf16x8{};
 #pragma unroll
       for (int p = NP - 1; p >= 0; --p)
@@ -206,14 +229,7 @@ __global__ __launch_bounds__(KS * 64) void rlif_tile_reverse_kernel(const float 
         for (int i = 0; i < 2; ++i) acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(W.f[p][i][ks], gf, acc[i], 0, 0, 0);
     }
     st_b64(rdI, vo4, t * row4, o);
-    float sg[2], u[2];
-#pragma unroll
-    for (int e = 0; e < 2; ++e) {
-      const float vt = __uint_as_float(vv[e]);
-      sg[e] = surr_rcp<SURR>(slope, vt - theta);
-      u[e] = __uint_as_float(ds[e]) - theta * gv[e];
-      db[e] += gv[e] * vt;
-    }
+    if (!EARLY) surrogates();
     ds = ld_b64(rdS, vo4, max(t - PF, 0) * row4);
     vv = ld_b64(rV, vo4, max(t - PF, 0) * row4);
 #pragma unroll
