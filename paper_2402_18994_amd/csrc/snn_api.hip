@@ -814,17 +814,8 @@ int launch_lif_reverse(snn_ctx *c, int l) {
 
 // Padded columns of the layer above a spiking layer.
 int columns_above(const snn_ctx *c, int l) { return l + 1 == c->L - 1 ? c->ldC : c->layers[l + 1].ld; }
-// Samples from which a layer runs as one launch: SNN_OPT_LAYER_MIN_BATCH, or any number.
-// Forward, with three planes of the weights, a workgroup walks up to three times the stages, and with few
-// samples the separate product spreads them over more workgroups: 64 samples where a sample's product is
-// more than sixteen rounds of 128 steps x 64 inputs.  (us saved by one launch over two, fp32, 4 / 32 / 64
-// samples: 700-128-128-20 at T = 300 -15 / -14 / -3, T = 500 -22 / -20 / 0, T = 256 4 / 1 / 8; 200-60-10 at
-// T = 500, sixteen rounds, 9 / 8 / 8; rounded weights, 700-128-128-20: T = 300 8 / 9 / 13, T = 500 17 / 19 / 27.)
+// Samples from which a layer runs as one launch: SNN_OPT_LAYER_MIN_BATCH, or by the rules here and below.
 int layer_min_batch(const snn_ctx *c) { return std::max(1, c->opt[SNN_OPT_LAYER_MIN_BATCH]); }
-int layer_forward_min_batch(const snn_ctx *c, int l) {
-  const bool long_product = c->nplanes == 3 && (c->T + 127) / 128 * ((c->layers[l].K + 63) / 64) > 16;
-  return c->opt[SNN_OPT_LAYER_MIN_BATCH] == 0 && long_product ? 64 : layer_min_batch(c);
-}
 // Reverse, the six products of fp32 operands below more than 64 columns are the long part of a block: 32
 // samples above 256 steps (us saved, 700-128-128-20, 4 / 64 samples: T = 256 2 / 4, T = 300 0 / 4, T = 500 -3 / 10).
 int layer_reverse_min_batch(const snn_ctx *c, int l) {
@@ -970,18 +961,85 @@ int launch_lif_reverse_fused(snn_ctx *c, int l) {
 // SNN_OPT_LAYER_FORWARD: 0 never, 1 all but the last spiking layer, 2 every such layer, 3 the last
 // one also forms the readout's currents when it has at most 128 padded neurons, 4 (default) and
 // runs the readout scan, the loss and the readout's current gradients;
-// SNN_OPT_LAYER_MIN_BATCH: samples from which it is used (0: layer_forward_min_batch);
+// SNN_OPT_LAYER_MIN_BATCH: samples from which it is used (0: layer_forward_pays);
 // SNN_OPT_LAYER_NEURONS: 64 or 128 neurons per workgroup.
 // Layers with adaptive thresholds (adaptive_in_one_launch): their workgroups scan with one wavefront of four, four
 // dependent operations a step, so up to 256 steps (T = 400, B = 8, 700-256-256-20: 162 us with product and scan apart,
 // 168 in one), and from a short fan-in, where there is less of a product to hide it, where the rows of the tile are
 // used (200-100-20: T = 16, B = 64 37.3 and 38.6, T = 128 56.8 and 54.2, T = 200, B = 400 112 and 117, T = 256 153 and 134).
+// A second block of 128 steps that is nearly empty costs as much as a full one: not up to 159 steps where few workgroups
+// have nothing to hide it behind, nor up to 175 where so many keep the chip busy all the time (700-N-20, T = 129, us
+// apart and in one: N = 256, B = 32, 128 workgroups, 66.4 and 67.8, B = 128, 512 of them, 88.6 and 87.6; N = 768, B = 256,
+// 3072, 370 and 383; N = 1000, fp32, B = 256, 4096, 594 and 646; T = 170: 300-100-20, B = 4 58.4 and 56.7, N = 768, B = 256
+// 448 and 458).  Rows of more than 768 neurons that are no multiple of 64 lose on a busy chip at any such T, rounded
+// weights (N = 1000, B = 256, T = 200 / 256: 602 / 772 and 633 / 811; B = 128: 388 / 465 and 360 / 440; N = 960, B = 256:
+// 587 / 746 and 565 / 705; fp32, T = 256: 984 and 973).
 // Their scan multiplies the threshold and its rise by the spike (0 or 1), which is no choice between values once they
 // are infinite: only where no adaptation (at most kappa a step) leaves the thresholds that the spike decision is exact for.
 bool adaptive_in_one_launch(const snn_ctx *c, int l) {
-  if (!(c->theta + c->layers[l].kappa * (float)c->T <= 0x1p26f)) return false;
-  if (c->layers[l].K > 256) return c->T <= 256;
+  const Layer &y = c->layers[l];
+  if (!(c->theta + y.kappa * (float)c->T <= 0x1p26f)) return false;
+  if (c->T > 128 && c->opt[SNN_OPT_LAYER_MIN_BATCH] == 0) {
+    const long long groups = (long long)c->B * ((y.ld + 63) / 64);
+    if (c->T < (groups > 1536 ? 176 : groups < 256 ? 160 : 0)) return false;
+    if (c->nplanes == 1 && groups > 1536 && y.ld > 768 && y.ld % 64) return false;
+  }
+  if (y.K > 256) return c->T <= 256;
   return c->T > 40 && c->T <= 256 && (c->T <= 64 || c->T * 5 >= (c->T + 127) / 128 * 128 * 4);
+}
+// Neurons per workgroup of a launch whose widest layer has ld: whichever pads less (SNN_OPT_LAYER_NEURONS =
+// 64: 64, but a launch that holds whole layers has one part).  128 at equal padding: 108.0 us per step at
+// 700-128-128-20, 64: 109.7.
+int layer_workgroup_neurons(const snn_ctx *c, int ld, bool whole) {
+  return rup(ld, 64) < rup(ld, 128) || (c->opt[SNN_OPT_LAYER_NEURONS] == 64 && !whole) ? 64 : 128;
+}
+// A layer of at most 128 neurons whose launch holds more than the layer (the readout, or a second such layer): the
+// widest of the layers that can be in it; else 0.
+int narrow_in_company(const snn_ctx *c, int l) {
+  auto narrow = [&](int i) {
+    const bool is = i >= 0 && i <= c->L - 2 && c->layers[i].ld <= 128 && !c->layers[i].recurrent && !c->layers[i].adaptive;
+    return is ? c->layers[i].ld : 0;
+  };
+  if (!narrow(l) || !((l == c->L - 2 && c->ldC <= 32) || narrow(l - 1) || narrow(l + 1))) return 0;
+  return std::max(narrow(l), std::max(narrow(l - 1), narrow(l + 1)));
+}
+// Whether there are workgroups enough: each walks its sample's blocks of 128 steps one after the other, in rounds of
+// 64 inputs, where the product apart spreads over the chip.  All figures: % saved by one launch.
+//   Rounded weights.  Any number where the alternative is lif_forward_top_kernel (700-128-128-20, 4 / 16 samples: T = 300
+// 22 / 21, T = 2000 22 / 23; 700-256-20, T = 260 to 1500, 1 to 32 samples 0 to 12) and where a launch in company takes
+// 64 neurons (700-60-20, T = 300 to 2000, 1 to 100 samples: 24 to 30); up to 256 steps, 384 in company or with 64 neurons to
+// a workgroup (700-100-20, T = 300, 1 / 32 / 64: -2 / 0 / 4; 700-264-20, 20 workgroups, 3); beyond, by workgroups.
+// (700-N-20, T = 400 / 700 / 1500: N = 512 with 32 of them -6 / -6 / -8, with 64 0 / -2 / -3, with 128 5 / 7 / 12; N = 1024,
+// 32 -6 / -5 / -8, 64 0 / -2 / -3, 128 4 / 6 / 9; N = 640, T = 500, 20 -6, 80 3; N = 100, T = 500 / 1000 / 2000: 8 -4 / -16 / -23,
+// 64 3 / -4 / -3, 100 9 / 6 / -5; 700-100-100-20 the same within 3; 100-120-20, T = 1000, 16 rounds, 8 1, 32 2, T = 2000, 32
+// rounds, 8 -4, 64 3.)
+//   Three planes (fp32) make a round three stages.  One block of 128 steps: any; beyond, by rounds and workgroups.  (In
+// company, 100-128-20, 1 / 8 / 32 samples: T = 256, 4 rounds, 6 / 9 / 12, T = 300, 6 rounds, 2 samples 0, 32 6, T = 400, 8
+// rounds, -6 / -4 / 0, T = 1000, 16 rounds, -15 / -10 / -7, 64 / 128 samples -2 / 5; with 64 neurons to a workgroup 200-60-10,
+// T = 400, 16 rounds, 9 to 11, 100-60-60-20, T = 1000, 16 rounds, 2 / 32 samples 13 / 11; 700-128-128-20, 32 / 64 / 96 / 128 / 256:
+// T = 256, 22 rounds, -3 / 7 / 13 / 13 / 20, T = 500, 44 rounds, -10 / 0 / 6 / 11 / 15, T = 1000, 88 rounds, -15 / -8 / -8 / -4 /
+// 15.  Others, K-N-20: 8 rounds, 4 workgroups 0; 10 rounds, 300-200-200-20, 4 / 32 -2 / -3; 14 rounds, 64 neurons to a
+// workgroup, 10 6; 16 rounds, 32 -8, 64 2; 22 rounds, 64 -1, 128 4 to 5; 32 rounds, 64 -3, 128 -1 to 1, 256 16; 44 rounds,
+// 64 -4, 128 2 to 4; 88 rounds, 128 -8, 256 13.)
+bool layer_forward_pays(const snn_ctx *c, int l) {
+  if (c->opt[SNN_OPT_LAYER_MIN_BATCH]) return c->B >= c->opt[SNN_OPT_LAYER_MIN_BATCH];
+  const Layer &y = c->layers[l];
+  const int rounds = (c->T + 127) / 128 * ((y.K + 63) / 64);
+  if (y.adaptive) return c->nplanes == 1 || rounds <= 16 || c->B >= 64;
+  const int company = narrow_in_company(c, l);
+  const int n = company ? (company <= 64 ? 64 : 128) : layer_workgroup_neurons(c, y.ld, false);
+  const long long groups = (long long)c->B * ((y.ld + n - 1) / n);
+  if (c->nplanes == 1) {
+    if (c->T <= (company || n == 64 ? 384 : 256) || (company && n == 64) || (c->T <= 512 && rounds <= 16)) return true;
+    if (top_forward_fusable(c) && (l == c->L - 2 || (l == c->L - 3 && company && narrow_in_company(c, l + 1)))) return true;
+    return groups >= (rounds <= 16 ? 32 : rounds <= 32 || c->T <= 512 ? 64 : c->T <= 1024 ? 80 : 128);
+  }
+  if (c->T <= 128 || (c->T <= 256 && rounds <= (company ? 16 : 8))) return true;
+  if (rounds <= 16) {
+    if (company ? n == 64 || c->T <= 384 : n == 64 && c->T <= 512) return true;
+    return groups >= (company && c->T <= 512 ? 32 : c->T <= 768 ? 64 : 128);
+  }
+  return groups >= (rounds > 64 ? 192 : company && (n == 64 || c->T <= 768) ? 64 : 128);
 }
 int layer_fuse_mode(const snn_ctx *c) { return c->opt[SNN_OPT_LAYER_FORWARD]; }
 static int layer_max_neurons(const snn_ctx *c) { return c->opt[SNN_OPT_LAYER_MAX_NEURONS]; }
@@ -989,7 +1047,7 @@ bool layer_forward_fusable(snn_ctx *c, int l) {
   if (l < 0 || l > c->L - 2) return false;
   const Layer &y = c->layers[l];
   const SpikeSrc s = spikes_below(c, l);
-  return y.spiking && !y.recurrent && (!y.adaptive || adaptive_in_one_launch(c, l)) && y.ld <= layer_max_neurons(c) && c->B >= layer_forward_min_batch(c, l) &&
+  return y.spiking && !y.recurrent && (!y.adaptive || adaptive_in_one_launch(c, l)) && y.ld <= layer_max_neurons(c) && layer_forward_pays(c, l) &&
          s.ld % 4 == 0 && s.ld <= layer_max_neurons(c) && (size_t)c->M * s.ld < ((size_t)1 << 31) && (size_t)c->M * y.ld * 4 < ((size_t)1 << 31) &&
          c->theta >= 0x1p-60f && c->theta <= 0x1p26f;
 }
@@ -1002,13 +1060,6 @@ int layer_forward_takes_readout(snn_ctx *c) {
   const bool ok = c->L >= 2 && mode >= 3 && layer_forward_fusable(c, c->L - 2) && c->layers[c->L - 2].ld <= 128 && !c->layers[c->L - 2].adaptive &&
                   c->opt[SNN_OPT_LAYER_NEURONS] == 128 && c->ldC <= 32 && ro.qf_plane >= 32ll * ro.ldqf;
   return !ok ? 0 : mode >= 4 ? 2 : c->nplanes == 1 ? 1 : 0;
-}
-
-// Neurons per workgroup of a launch whose widest layer has ld: whichever pads less (SNN_OPT_LAYER_NEURONS =
-// 64: 64, but a launch that holds whole layers has one part).  128 at equal padding: 108.0 us per step at
-// 700-128-128-20, 64: 109.7.
-int layer_workgroup_neurons(const snn_ctx *c, int ld, bool whole) {
-  return rup(ld, 64) < rup(ld, 128) || (c->opt[SNN_OPT_LAYER_NEURONS] == 64 && !whole) ? 64 : 128;
 }
 
 // Layers l .. l + nl - 1 in one launch (nl = 2: both of at most 128 padded neurons, a workgroup

@@ -23,6 +23,18 @@ def make(wl, inp, options=None):
     return from_workload(wl, inp, options=options)
 
 
+def launches(snn, x, labels, *wanted):
+    """How often a forward and backward pass launches each (kernel class, layer) of `wanted`."""
+    out = []
+    for kernel, layer in wanted:
+        snn.profile_select(kernel, layer)
+        snn.forward(x, labels, want_loss=False)
+        snn.backward()
+        out.append(snn.profile_read()[1])
+    snn.profile_select("none")
+    return out
+
+
 def full_step_parity(wl, w_gain=1.0, lr=0.1, seed=None, grad_tol=parity.TOL_GRAD, check_sgd=True, options=None,
                      say=lambda text: None):
     """`say`: progress lines of a long case (a run that stays silent for minutes is taken for hung)."""
@@ -69,6 +81,58 @@ def full_step_parity(wl, w_gain=1.0, lr=0.1, seed=None, grad_tol=parity.TOL_GRAD
             f.write(json.dumps(rep) + "\n")
     snn.destroy()
     return rep
+
+
+# ---------------------------------------------------------------- the rules of the one-launch layers
+# precision, T, B, fan-in, neurons, adaptive, classes (above 32: neurons of a layer above), one launch: both sides of every line
+RULES = [("bf16", 300, 16, 384, 512, False, 10, True), ("bf16", 300, 15, 384, 512, False, 10, False),
+         ("bf16", 512, 1, 256, 512, False, 10, True), ("bf16", 513, 8, 64, 512, False, 10, True),
+         ("bf16", 513, 7, 64, 512, False, 10, False), ("bf16", 513, 16, 256, 512, False, 10, True),
+         ("bf16", 513, 15, 256, 512, False, 10, False), ("bf16", 513, 20, 512, 512, False, 10, True),
+         ("bf16", 513, 19, 512, 512, False, 10, False), ("bf16", 1025, 32, 256, 512, False, 10, True),
+         ("bf16", 1025, 31, 256, 512, False, 10, False), ("bf16", 385, 1, 300, 264, False, 10, False),
+         ("bf16", 384, 1, 700, 264, False, 10, True), ("bf16", 256, 1, 700, 512, False, 10, True),
+         ("bf16", 600, 1, 300, 128, False, 10, True), ("bf16", 600, 1, 300, 128, False, 128, True),
+         ("bf16", 600, 1, 300, 128, False, 120, False), ("bf16", 600, 1, 300, 100, False, 10, False),
+         ("bf16", 384, 1, 700, 100, False, 10, True), ("bf16", 600, 1, 300, 60, False, 10, True),
+         ("bf16", 300, 1, 400, 128, False, 256, False), ("bf16", 300, 1, 400, 256, False, 10, True),
+         ("bf16", 300, 1, 400, 256, False, 256, False),
+         ("fp32", 128, 1, 700, 512, False, 10, True), ("fp32", 256, 1, 256, 512, False, 10, True),
+         ("fp32", 256, 16, 260, 512, False, 10, True), ("fp32", 256, 15, 260, 512, False, 10, False),
+         ("fp32", 512, 1, 256, 264, False, 10, True), ("fp32", 513, 1, 64, 264, False, 10, False),
+         ("fp32", 257, 32, 384, 512, False, 10, True), ("fp32", 257, 31, 384, 512, False, 10, False),
+         ("fp32", 1280, 48, 448, 512, False, 10, True), ("fp32", 1280, 47, 448, 512, False, 10, False),
+         ("fp32", 256, 1, 512, 128, False, 10, True), ("fp32", 384, 1, 320, 128, False, 10, True),
+         ("fp32", 385, 32, 64, 128, False, 10, True), ("fp32", 385, 31, 64, 128, False, 10, False),
+         ("fp32", 513, 64, 64, 128, False, 10, True), ("fp32", 513, 63, 64, 128, False, 10, False),
+         ("fp32", 769, 128, 64, 128, False, 10, True), ("fp32", 769, 127, 64, 128, False, 10, False),
+         ("fp32", 257, 64, 384, 128, False, 10, True), ("fp32", 257, 63, 384, 128, False, 10, False),
+         ("fp32", 1280, 1, 64, 32, False, 10, True), ("fp32", 769, 64, 192, 32, False, 10, True),
+         ("fp32", 769, 63, 192, 32, False, 10, False), ("fp32", 1280, 192, 448, 32, False, 10, True),
+         ("fp32", 1280, 191, 448, 32, False, 10, False),
+         ("bf16", 129, 64, 300, 256, True, 10, True), ("bf16", 129, 63, 300, 256, True, 10, False),
+         ("bf16", 128, 1, 300, 256, True, 10, True), ("bf16", 160, 1, 300, 256, True, 10, True),
+         ("bf16", 159, 1, 300, 256, True, 10, False), ("bf16", 175, 384, 300, 256, True, 10, True),
+         ("bf16", 175, 385, 300, 256, True, 10, False), ("bf16", 176, 385, 300, 256, True, 10, True),
+         ("bf16", 200, 96, 300, 1000, True, 10, True), ("bf16", 200, 97, 300, 1000, True, 10, False),
+         ("bf16", 200, 97, 300, 1024, True, 10, True), ("fp32", 200, 97, 300, 1000, True, 10, True),
+         ("bf16", 257, 64, 300, 256, True, 10, False)]
+
+
+@pytest.mark.parametrize("precision,T,B,K,N,adaptive,above,whole", RULES, ids=["-".join(map(str, r[:7])) for r in RULES])
+def test_which_layers_run_as_one_launch(precision, T, B, K, N, adaptive, above, whole):
+    """The default rules, by what is launched: a layer that runs as one launch has no product launch of its own."""
+    import torch
+    from paper_2402_18994_amd.binding import SNN
+    sizes = (K, N, above) + ((10,) if above > 32 else ())
+    L = len(sizes) - 1
+    W = [np.zeros((a, b), np.float32) for a, b in zip(sizes, sizes[1:])]
+    adapt = dict(adapt_decay=(0.9,) * (L - 1), adapt_step=(0.2,) * (L - 1)) if adaptive else {}
+    snn = SNN(T, B, sizes, (False,) * (L - 1), (0.9,) * L, 1.0, "superspike", 10.0, precision, W, **adapt)
+    x, y = torch.zeros((T, B, K), dtype=torch.uint8, device="cuda"), torch.zeros(B, dtype=torch.int32, device="cuda")
+    n = launches(snn, x, y, ("current_gemm", 1))
+    snn.destroy()
+    assert n == [0 if whole else 1]
 
 
 # ---------------------------------------------------------------- feed-forward, fp32 products
