@@ -1506,11 +1506,17 @@ static int32_t forward_layers(snn_ctx *c, const int32_t *labels_dev, float *loss
   const bool fuse_top = !whole_top && top_forward_fusable(c);   // the last spiking layer's scan forms the readout's currents
   for (int l = 0; l < c->L; ++l) {
     if (whole >= 1 && (l < c->L - 2 || whole_top) && layer_forward_fusable(c, l)) {
-      // this layer and the next in one launch when both hold at most 128 padded neurons
-      // (SNN_OPT_LAYER_PAIR = 0: one launch each)
-      const bool pair = c->opt[SNN_OPT_LAYER_PAIR] && c->opt[SNN_OPT_LAYER_NEURONS] == 128 && c->layers[l].ld <= 128 && l + 1 <= c->L - 2 &&
-                        !c->layers[l].adaptive && !c->layers[l + 1].adaptive &&
-                        (l + 1 < c->L - 2 || whole_top) && layer_forward_fusable(c, l + 1) && c->layers[l + 1].ld <= 128;
+      // this layer and the next in one launch when both hold at most 128 padded neurons (SNN_OPT_LAYER_PAIR = 0: one
+      // launch each), but not one of at most 64 with a wider one that can be paired with the layer above it: the
+      // launch would hold 128 columns of both (700-64-128-128-20, B = 100, T = 500 / 1000: 210 / 413 us so, 203 / 393
+      // with the two equal ones together)
+      auto wide = [&](int i) { return c->layers[i].ld > 64; };
+      auto pairs = [&](int i) {
+        return c->opt[SNN_OPT_LAYER_PAIR] && c->opt[SNN_OPT_LAYER_NEURONS] == 128 && i + 1 <= c->L - 2 && c->layers[i].ld <= 128 &&
+               c->layers[i + 1].ld <= 128 && !c->layers[i].adaptive && !c->layers[i + 1].adaptive &&
+               (i + 1 < c->L - 2 || whole_top) && layer_forward_fusable(c, i) && layer_forward_fusable(c, i + 1);
+      };
+      const bool pair = pairs(l) && !(wide(l) != wide(l + 1) && pairs(l + 1) && wide(l + 1) == wide(l + 2));
       const int nl = pair ? 2 : 1;
       if ((rc = launch_layer_forward(c, l, nl, l + nl - 1 == c->L - 2 ? with_readout : 0, labels_dev))) return rc;
       l += nl - 1;

@@ -994,6 +994,22 @@ def test_sgd_step_straight_after_backward_headline_shape():
     assert all(np.abs(g).max() > 0 for g in out[0][4:])
 
 
+@pytest.mark.parametrize("sizes,counts", [((70, 64, 128, 128, 20), (1, 1, 0)), ((70, 128, 40, 56, 20), (1, 1, 0)),
+                                          ((70, 64, 128, 56, 20), (1, 0, 1)), ((70, 40, 128, 20), (1, 0)), ((70, 64, 40, 128, 20), (1, 0, 1))])
+def test_narrow_layers_share_launches_with_their_like(sizes, counts):
+    """Of three narrow layers the two that take workgroups of the same width run together; two of unlike width do
+    where neither has another partner."""
+    L = len(sizes) - 1
+    wl = workloads.Workload(name="partners", index=31, T=70, B=5, sizes=sizes, recurrent=(False,) * (L - 1), beta=(0.9,) * L,
+                            theta=1.0, surrogate="superspike", slope=10.0, precision="bf16", rate_lo=0.1, rate_hi=0.3)
+    full_step_parity(wl, w_gain=2.5)
+    inp = workloads.generate(wl)
+    snn = make(wl, inp)
+    got = launches(snn, inp.X, inp.labels, *[("lif_forward", l) for l in range(1, L)])
+    snn.destroy()
+    assert tuple(got) == counts
+
+
 @pytest.mark.parametrize("T,sizes", [(150, (90, 128, 128, 128, 10)), (40, (50, 128, 128, 64, 128, 128, 12))])
 def test_two_layers_per_forward_launch(T, sizes):
     """Consecutive one-launch layers of exactly 128 neurons share a launch in pairs: a workgroup
