@@ -1012,7 +1012,7 @@ int narrow_in_company(const snn_ctx *c, int l) {
 // (700-N-20, T = 400 / 700 / 1500: N = 512 with 32 of them -6 / -6 / -8, with 64 0 / -2 / -3, with 128 5 / 7 / 12; N = 1024,
 // 32 -6 / -5 / -8, 64 0 / -2 / -3, 128 4 / 6 / 9; N = 640, T = 500, 20 -6, 80 3; N = 100, T = 500 / 1000 / 2000: 8 -4 / -16 / -23,
 // 64 3 / -4 / -3, 100 9 / 6 / -5; 700-100-100-20 the same within 3; 100-120-20, T = 1000, 16 rounds, 8 1, 32 2, T = 2000, 32
-// rounds, 8 -4, 64 3.)
+// rounds, 8 -4, 64 3; two layers of exactly 128 that fill their launch, 700-128-128-64-20, T = 500 / 1000: 4 4 / -1, 64 0 / 5.)
 //   Three planes (fp32) make a round three stages.  One block of 128 steps: any; beyond, by rounds and workgroups.  (In
 // company, 100-128-20, 1 / 8 / 32 samples: T = 256, 4 rounds, 6 / 9 / 12, T = 300, 6 rounds, 2 samples 0, 32 6, T = 400, 8
 // rounds, -6 / -4 / 0, T = 1000, 16 rounds, -15 / -10 / -7, 64 / 128 samples -2 / 5; with 64 neurons to a workgroup 200-60-10,
@@ -1032,6 +1032,8 @@ bool layer_forward_pays(const snn_ctx *c, int l) {
   if (c->nplanes == 1) {
     if (c->T <= (company || n == 64 ? 384 : 256) || (company && n == 64) || (c->T <= 512 && rounds <= 16)) return true;
     if (top_forward_fusable(c) && (l == c->L - 2 || (l == c->L - 3 && company && narrow_in_company(c, l + 1)))) return true;
+    auto full = [&](int i) { return i >= 0 && i <= c->L - 2 && c->layers[i].ld == 128 && narrow_in_company(c, i); };
+    if (full(l) && (full(l - 1) || full(l + 1))) return c->T <= 512 || groups >= (c->T <= 1024 ? 32 : 80);
     return groups >= (rounds <= 16 ? 32 : rounds <= 32 || c->T <= 512 ? 64 : c->T <= 1024 ? 80 : 128);
   }
   if (c->T <= 128 || (c->T <= 256 && rounds <= (company ? 16 : 8))) return true;

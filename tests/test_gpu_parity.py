@@ -84,7 +84,8 @@ def full_step_parity(wl, w_gain=1.0, lr=0.1, seed=None, grad_tol=parity.TOL_GRAD
 
 
 # ---------------------------------------------------------------- the rules of the one-launch layers
-# precision, T, B, fan-in, neurons, adaptive, classes (above 32: neurons of a layer above), one launch: both sides of every line
+# precision, T, B, fan-in, neurons, adaptive, classes (above 32, or several: neurons of the layers above), one launch: both
+# sides of every line
 RULES = [("bf16", 300, 16, 384, 512, False, 10, True), ("bf16", 300, 15, 384, 512, False, 10, False),
          ("bf16", 512, 1, 256, 512, False, 10, True), ("bf16", 513, 8, 64, 512, False, 10, True),
          ("bf16", 513, 7, 64, 512, False, 10, False), ("bf16", 513, 16, 256, 512, False, 10, True),
@@ -96,7 +97,9 @@ RULES = [("bf16", 300, 16, 384, 512, False, 10, True), ("bf16", 300, 15, 384, 51
          ("bf16", 600, 1, 300, 128, False, 120, False), ("bf16", 600, 1, 300, 100, False, 10, False),
          ("bf16", 384, 1, 700, 100, False, 10, True), ("bf16", 600, 1, 300, 60, False, 10, True),
          ("bf16", 300, 1, 400, 128, False, 256, False), ("bf16", 300, 1, 400, 256, False, 10, True),
-         ("bf16", 300, 1, 400, 256, False, 256, False),
+         ("bf16", 300, 1, 400, 256, False, 256, False), ("bf16", 512, 1, 300, 128, False, (128, 64), True),
+         ("bf16", 513, 32, 400, 128, False, (128, 64), True), ("bf16", 513, 31, 400, 128, False, (128, 64), False),
+         ("bf16", 1025, 80, 300, 128, False, (128, 64), True), ("bf16", 1025, 79, 300, 128, False, (128, 64), False),
          ("fp32", 128, 1, 700, 512, False, 10, True), ("fp32", 256, 1, 256, 512, False, 10, True),
          ("fp32", 256, 16, 260, 512, False, 10, True), ("fp32", 256, 15, 260, 512, False, 10, False),
          ("fp32", 512, 1, 256, 264, False, 10, True), ("fp32", 513, 1, 64, 264, False, 10, False),
@@ -124,7 +127,8 @@ def test_which_layers_run_as_one_launch(precision, T, B, K, N, adaptive, above, 
     """The default rules, by what is launched: a layer that runs as one launch has no product launch of its own."""
     import torch
     from paper_2402_18994_amd.binding import SNN
-    sizes = (K, N, above) + ((10,) if above > 32 else ())
+    above = above if isinstance(above, tuple) else (above,)
+    sizes = (K, N) + above + ((10,) if above[-1] > 32 else ())
     L = len(sizes) - 1
     W = [np.zeros((a, b), np.float32) for a, b in zip(sizes, sizes[1:])]
     adapt = dict(adapt_decay=(0.9,) * (L - 1), adapt_step=(0.2,) * (L - 1)) if adaptive else {}
