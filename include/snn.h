@@ -132,7 +132,12 @@ typedef struct {
 
 /* Tensors that snn_get_tensor / snn_set_tensor move.  `layer` is 1-based as in the text:
  * weights 1..L, spiking-layer tensors 1..L-1, readout tensors ignore it.  Element type on
- * the host side is float unless noted; shapes are dense (no padding). */
+ * the host side is float unless noted; shapes are dense (no padding).
+ * Launches that hold whole layers (snn_option) do not store CURRENT and D_SPIKES.  snn_get_tensor and
+ * snn_run_step form such a tensor again when they need it, from the spikes below (layer 1: from the
+ * caller's raster, which must then still be there, unchanged) or the current gradients above, and the
+ * weights of that pass - after snn_sgd_step recovered from the present ones and their gradients, to the
+ * rounding of that sum; after snn_set_tensor of a weight, those set. */
 typedef enum {
   SNN_T_WEIGHT = 0,      /* [N_{l-1}][N_l]  fp32 master weights (settable)                 */
   SNN_T_RWEIGHT = 1,     /* [N_l][N_l] (from,to), recurrent layers only (settable)         */

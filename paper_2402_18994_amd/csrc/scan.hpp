@@ -929,7 +929,7 @@ struct ParamJobs {
   long long qf_plane[SNN_MAX_JOBS], qb_plane[SNN_MAX_JOBS];
 };
 
-__global__ __launch_bounds__(256) void param_update_kernel(const ParamJobs jobs, float lr, int nplanes) {
+__global__ __launch_bounds__(256) void param_update_kernel(const ParamJobs jobs, float lr, int nplanes, int store) {
   __shared__ uint16_t tile[3][32][33];
   int j = 0;
   while (j + 1 < jobs.njobs && (int)blockIdx.x >= jobs.first_block[j + 1]) ++j;
@@ -949,7 +949,8 @@ __global__ __launch_bounds__(256) void param_update_kernel(const ParamJobs jobs,
     float w = 0.f;
     if (k < K && n < N) {
       w = W[(size_t)k * N + n];
-      if (dW) { w -= lr * dW[(size_t)k * N + n]; W[(size_t)k * N + n] = w; }
+      if (dW) w -= lr * dW[(size_t)k * N + n];
+      if (dW && store) W[(size_t)k * N + n] = w;
     }
     for (int p = 0; p < nplanes; ++p) {
       const uint16_t bits = (uint16_t)bf16_piece(w, p);

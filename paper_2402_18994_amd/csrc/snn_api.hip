@@ -65,6 +65,7 @@ struct Layer {
   void *rp_space = nullptr;                           // exchange space of the one-launch forward loop of a wide recurrent layer
   bool i_ready = true;     // I is in memory (false: the last forward pass ran the layer in one launch and never stored it)
   bool ds_ready = true;    // dS is in memory (false: the layer's reverse scan formed it itself in the last backward pass)
+  bool moved = false;      // the weights are one snn_sgd_step past those of the last pass
   int splits_w = 1, splits_r = 1;                     // contraction splits of dW and dR
   long long per_w = 0, per_r = 0;                     // rows per split
   float *part_w = nullptr, *part_r = nullptr;         // per-split partial results
@@ -102,6 +103,7 @@ struct snn_ctx {
   bool wg_tall = false;           // weight-gradient products use 256 x 128 tiles
   bool wg_narrow = false;         // weight gradients: no product of more than 32 columns, and a long one
   bool integral = false;          // integral cross-entropy instead of max over time
+  float last_lr = 0.f;            // of the last snn_sgd_step
   bool learn_beta = false;        // decays are trained: dbeta in snn_backward, clipped update in snn_sgd_step
   const uint8_t *x_eff = nullptr;  // raster the products read: the caller's, or x_buf
   uint8_t *x_buf = nullptr;        // [T*B][ldx]: zero-padded copy (N_0 not a multiple of 4) or unpacked input
@@ -495,10 +497,6 @@ int launch_input_grad(snn_ctx *c, int l) {
   below.ds_ready = true;
   return SNN_OK;
 }
-
-// I and dS of a layer whose last launch formed them on the fly: into memory, for a reader or a single step.
-int ensure_current(snn_ctx *c, int l) { return c->layers[l].i_ready ? SNN_OK : launch_current_gemm(c, l); }
-int ensure_spike_grads(snn_ctx *c, int l) { return c->layers[l].ds_ready ? SNN_OK : launch_input_grad(c, l + 1); }
 
 // part[split][rows x cols] (or out directly when there is one split) = Sp^T G over one
 // slice of the T*B rows per split.
@@ -1201,8 +1199,9 @@ void add_param_job(ParamJobs &jobs, float *W, const float *dW, int K, int N, uin
   jobs.first_block[j + 1] = jobs.first_block[j] + jobs.blocks_x[j] * ((K + 31) / 32);
 }
 
-// SGD (when with_grad) and refresh of the bfloat16 operand planes for layers [l0, l1).
-int update_layers(snn_ctx *c, int l0, int l1, bool with_grad, float lr) {
+// SGD (when with_grad) and refresh of the bfloat16 operand planes for layers [l0, l1); not `store`: the planes alone,
+// the masters stay.
+int update_layers(snn_ctx *c, int l0, int l1, bool with_grad, float lr, bool store = true) {
   ParamJobs jobs;
   memset(&jobs, 0, sizeof jobs);
   for (int l = l0; l < l1; ++l) {
@@ -1213,10 +1212,24 @@ int update_layers(snn_ctx *c, int l0, int l1, bool with_grad, float lr) {
                     y.qr_plane);
   }
   hipLaunchKernelGGL(param_update_kernel, dim3(jobs.first_block[jobs.njobs]), dim3(256), 0, c->stream, jobs, lr,
-                     c->nplanes);
+                     c->nplanes, store ? 1 : 0);
   HIPCHK(c, hipGetLastError());
   return SNN_OK;
 }
+
+// I of layer l and dS of the layer below it (W^l enters both), where the last pass kept them to itself: into memory,
+// for a reader or a single step, on the weights of that pass.  After snn_sgd_step those are W + lr dW, to the rounding
+// of that sum: their planes take the place of the present ones for the product.
+int form_again(snn_ctx *c, int l, int (*product)(snn_ctx *, int)) {
+  const bool moved = c->layers[l].moved;
+  int rc, back = SNN_OK;
+  if (moved && (rc = update_layers(c, l, l + 1, true, -c->last_lr, false))) return rc;
+  rc = product(c, l);
+  if (moved) back = update_layers(c, l, l + 1, false, 0.f);
+  return rc ? rc : back;
+}
+int ensure_current(snn_ctx *c, int l) { return c->layers[l].i_ready ? SNN_OK : form_again(c, l, launch_current_gemm); }
+int ensure_spike_grads(snn_ctx *c, int l) { return c->layers[l].ds_ready ? SNN_OK : form_again(c, l + 1, launch_input_grad); }
 
 // snn_sgd_step right after snn_backward: partial sums -> dW -> W and its operand layouts, one launch.
 int reduce_and_update(snn_ctx *c, float lr) {
@@ -1502,6 +1515,7 @@ static bool first_layer_runs_whole(snn_ctx *c) {
 
 static int32_t forward_layers(snn_ctx *c, const int32_t *labels_dev, float *loss_host) {
   int rc;
+  for (Layer &y : c->layers) y.moved = false;
   const int whole = layer_fuse_mode(c);                 // layers that run as one launch, product and scan
   const bool whole_top = whole >= 2 && layer_forward_fusable(c, c->L - 2);
   const int with_readout = whole_top ? layer_forward_takes_readout(c) : 0;
@@ -1648,6 +1662,8 @@ int32_t snn_sgd_step(snn_ctx *c, float lr) {
     hipLaunchKernelGGL(beta_update_kernel, dim3((bj.first[bj.njobs] + 255) / 256), dim3(256), 0, c->stream, bj, lr);
     HIPCHK(c, hipGetLastError());
   }
+  for (Layer &y : c->layers) y.moved = true;
+  c->last_lr = lr;
   c->state = 0;
   return SNN_OK;
 }
@@ -1701,6 +1717,7 @@ int32_t snn_set_tensor(snn_ctx *c, int32_t tensor, int32_t layer, const void *sr
   if (tensor == SNN_T_CURRENT) c->layers[layer - 1].i_ready = true;     // what the caller imposed is what a reader gets
   if (tensor == SNN_T_D_SPIKES) c->layers[layer - 1].ds_ready = true;
   if (tensor == SNN_T_BETA) c->state = 0;                               // a forward pass on other decays is stale
+  if (tensor == SNN_T_WEIGHT) c->layers[layer - 1].moved = false;
   if (tensor == SNN_T_WEIGHT || tensor == SNN_T_RWEIGHT) {
     if ((rc = update_layers(c, layer - 1, layer, false, 0.f))) return rc;
     HIPCHK(c, hipStreamSynchronize(c->stream));
@@ -1735,6 +1752,7 @@ int32_t snn_run_step(snn_ctx *c, int32_t step, int32_t layer, const uint8_t *x_d
       if (int rc = ensure_spike_grads(c, l)) return rc;
       return launch_lif_reverse(c, l);
     case SNN_STEP_WEIGHT_GRAD: {
+      c->layers[l].moved = false;                         // (the gradient of the update is overwritten)
       ReduceJobs jobs;
       memset(&jobs, 0, sizeof jobs);
       WgradJobs wj;

@@ -1367,6 +1367,43 @@ def test_single_steps_after_a_pass_that_stored_nothing_between(precision, sizes,
     snn.destroy()
 
 
+@pytest.mark.parametrize("precision,sizes,recurrent,kind", UNSTORED, ids=["fp32", "ragged-packed", "recurrent-pair", "adaptive"])
+@pytest.mark.parametrize("defer", [1, 0])
+def test_tensors_of_a_pass_read_after_the_update(precision, sizes, recurrent, kind, defer):
+    """Currents and spike gradients that the launches kept to themselves, asked for after snn_sgd_step: those of the
+    pass, not of the updated weights; and reading them leaves weights and the next pass as they are."""
+    wl, packed = unstored_workload(precision, sizes, recurrent, kind)
+    inp = workloads.generate(wl, w_gain=2.0)
+    names = [(n, l) for n in ("current", "d_spikes") for l in (1, 2)]
+    out, after = [], []
+    for read in ("before", "after", "after", "never"):
+        snn = make(wl, inp, {"defer_reduce": defer})
+        step = lambda: snn.forward_packed(np.packbits(inp.X, axis=0), inp.labels) if packed else snn.forward(inp.X, inp.labels)
+        step()
+        snn.backward()
+        grads = [np.abs(snn.get_tensor("grad_w", l)).max() for l in (1, 2, 3)]
+        if read == "before":
+            out.append([snn.get_tensor(*k) for k in names])
+        snn.sgd_step(float(0.5 / max(grads)))
+        if read == "after":
+            out.append([snn.get_tensor(*k) for k in names])
+        after.append([snn.get_tensor("weight", l) for l in (1, 2, 3)] + [np.float32(step())])
+        snn.backward()
+        after[-1] += [snn.get_tensor("grad_w", l) for l in (1, 2, 3)]
+        snn.destroy()
+    for other in after[1:]:
+        assert all(np.array_equal(a, b) for a, b in zip(after[0], other))
+    moved = max(np.abs(a - w).max() / np.abs(w).max() for a, w in zip(after[0], inp.W))
+    assert moved > 0.05
+    for (n, l), ref, got, again in zip(names, out[0], out[1], out[2]):
+        assert np.array_equal(got, again)
+        # W + lr dW is off by an ulp of the larger of the two, at most 2^-23 of the largest weight each for the update
+        # and its recovery; a rounded weight that lies that close to a tie moves by 2^-8 of itself (one in 2^14)
+        d, r = (got - ref).astype(np.float64), ref.astype(np.float64)
+        assert np.linalg.norm(d) <= (2e-6 if precision == "fp32" else 1e-3) * np.linalg.norm(r), (n, l)
+        assert np.abs(d).max() <= (2e-5 if precision == "fp32" else 2.0 ** -6) * np.abs(r).max(), (n, l)
+
+
 # ---------------------------------------------------------------- invariants, errors, repeatability
 def test_silent_network_and_invariants():
     wl = workloads.CONFIGS["tiny_ff"]
