@@ -35,6 +35,15 @@ def launches(snn, x, labels, *wanted):
     return out
 
 
+def assert_launches(wl, options, wanted):
+    """`wanted`: number of launches by (kernel class, layer) in a forward and backward pass of the workload."""
+    inp = workloads.generate(wl)
+    snn = make(wl, inp, options)
+    got = dict(zip(wanted, launches(snn, inp.X, inp.labels, *wanted)))
+    snn.destroy()
+    assert got == wanted
+
+
 def full_step_parity(wl, w_gain=1.0, lr=0.1, seed=None, grad_tol=parity.TOL_GRAD, check_sgd=True, options=None,
                      say=lambda text: None):
     """`say`: progress lines of a long case (a run that stays silent for minutes is taken for hung)."""
@@ -276,6 +285,7 @@ def test_layer_forward_in_one_launch_any_width(T, sizes, loss, packed, precision
     # (no step with the integral loss: its gradients of size 1e5 leave weights whose logits are sums of terms
     # up to 1e6, and 2^-24 of those is 0.06)
     full_step_parity(wl, w_gain=2.5, options={"layer_min_batch": 1}, check_sgd=loss == "max")
+    assert_launches(wl, {"layer_min_batch": 1}, {("current_gemm", l): 0 for l in range(1, L)})
     if packed:
         inp = workloads.generate(wl, w_gain=2.5)
         snn = make(wl, inp, {"layer_min_batch": 1})
@@ -836,6 +846,7 @@ def test_short_rasters_several_samples_to_a_tile(T, B, sizes, loss, packed, prec
     # a sum of 168 on (at gain 2.5 logits reach 400: 1.35e-5 seen), which gain 1 stays below
     gain = 2.5 if loss == "max" else 1.0
     full_step_parity(wl, w_gain=gain, check_sgd=loss == "max")
+    assert_launches(wl, None, {(k, l + (k == "input_grad")): 0 for k in ("current_gemm", "input_grad") for l in range(1, L)})
     if loss == "max" and not packed:
         beta_step_parity(wl, w_gain=gain)
     if packed:
@@ -858,6 +869,7 @@ def test_layer_reverse_in_one_launch_any_width(T, sizes, surrogate, slope, preci
                             beta=(0.9, 0.93, 0.95), theta=1.0, surrogate=surrogate, slope=slope, precision=precision,
                             rate_lo=0.05, rate_hi=0.2)
     full_step_parity(wl, w_gain=2.5, options={"layer_min_batch": 1})
+    assert_launches(wl, {"layer_min_batch": 1}, {("input_grad", l + 1): int(sizes[l + 1] > 128) for l in (1, 2)})
     if surrogate == "superspike" and T > 1:
         beta_step_parity(wl, w_gain=2.5, options={"layer_min_batch": 1})
 
@@ -1185,14 +1197,16 @@ def test_recurrent_layers_on_a_workgroup_of_four_samples(precision, T, B, widths
 
 @pytest.mark.parametrize("T,B,widths,surrogate", [(1, 1, (5, 3), "superspike"), (2, 5, (64, 64), "boxcar"), (7, 3, (65, 32), "arctan"),
                                                   (8, 9, (128, 121), "superspike"), (9, 6, (192, 120), "sigmoid"), (5, 4, (40, 184), "ste"),
-                                                  (13, 2, (130, 70), "triangular"), (6, 7, (30, 60, 90), "superspike"), (6, 5, (24, 96, 16, 130), "arctan")],
+                                                  (13, 2, (130, 70), "triangular"), (6, 7, (30, 60, 90), "superspike"), (6, 5, (24, 96, 16, 130), "arctan"),
+                                                  (14, 6, (128, 192), "superspike"), (15, 5, (136, 40), "arctan"), (17, 7, (160, 160), "sigmoid"),
+                                                  (6, 3, (168, 168), "superspike"), (5, 3, (136, 192), "boxcar")],
                          ids=lambda v: "-".join(map(str, v)) if isinstance(v, tuple) else str(v))
 def test_pairs_of_recurrent_layers_in_one_launch(T, B, widths, surrogate):
     """Two recurrent layers of up to 192 neurons side by side on one workgroup, the product between them on
     wavefronts of its own, against the oracle and against a launch per layer: every combination of the
     compiled widths, one step, odd and even numbers of them around the prefetch distance, a last
-    workgroup that is not full, a third layer that stays alone and two pairs above each other; with the
-    decay gradients."""
+    workgroup that is not full, a third layer that stays alone and two pairs above each other, widths whose
+    wavefronts would be more than sixteen and which stay alone; with the decay gradients."""
     L = len(widths) + 1
     slope = {"superspike": 10.0, "arctan": 2.0, "sigmoid": 4.0}.get(surrogate, 1.0)
     wl = workloads.Workload(name="rec-pair", index=25, T=T, B=B, sizes=(30,) + widths + (10,), recurrent=(True,) * (L - 1),
@@ -1201,6 +1215,13 @@ def test_pairs_of_recurrent_layers_in_one_launch(T, B, widths, surrogate):
     for pair in (1, 0):
         full_step_parity(wl, w_gain=2.0, options={"layer_pair": pair})
         beta_step_parity(wl, w_gain=2.0, options={"layer_pair": pair})
+        wanted, lower = {}, False
+        for l in range(1, L):
+            waves = [-(-n // 32) for n in widths[l - 2:l]]
+            lower = bool(pair) and l > 1 and not lower and sum(waves) + max(waves) <= 16   # the layer below l shares its launches
+            wanted.update({("rlif_forward", l): int(not lower), ("rlif_reverse", l): int(not lower),
+                           ("current_gemm", l): int(not lower)})
+        assert_launches(wl, {"layer_pair": pair}, wanted)
 
 
 @pytest.mark.parametrize("precision", ["fp32", "bf16"])
@@ -1778,6 +1799,8 @@ def test_adaptive_layers_in_one_launch(T, B, sizes, packed, precision):
                             beta=(0.9, 0.93, 0.95)[:L], theta=1.0, surrogate="superspike", slope=10.0, precision=precision,
                             rate_lo=0.1, rate_hi=0.3, adapt_decay=(0.9, 0.8)[:L - 1], adapt_step=(0.3, 0.2)[:L - 1])
     full_step_parity(wl, w_gain=2.5, options={"layer_min_batch": 1})
+    # (the second layer of "two-blocks-packed", of a fan-in of 200, runs as product and scan)
+    assert_launches(wl, {"layer_min_batch": 1}, {("current_gemm", l): int(l == 2 and T == 129) for l in range(1, L)})
     if packed:
         inp = workloads.generate(wl, w_gain=2.5)
         snn = make(wl, inp, {"layer_min_batch": 1})
