@@ -41,31 +41,119 @@ def pad8(n):
     return (n + 7) // 8 * 8
 
 
+def adaptive(wl, layer):
+    return bool(wl.adapt_step) and wl.adapt_step[layer - 1] > 0
+
+
+def runs_whole(wl, l):
+    """Whether text layer l runs product and scan as one forward launch (the library's default rule)."""
+    L = len(wl.sizes) - 1
+    if not (1 <= l < L) or wl.recurrent[l - 1]:
+        return False
+    n = pad8(wl.sizes[l])
+    k = wl.sizes[0] if l == 1 and wl.sizes[0] % 4 == 0 else pad8(wl.sizes[l - 1])
+    if n > 1024 or k > 1024:
+        return False
+    T, B, bf, fan_in = wl.T, wl.B, wl.precision == "bf16", wl.sizes[l - 1]
+    blocks = -(-T // 128)
+    rounds = blocks * -(-fan_in // 64)
+    if adaptive(wl, l):
+        groups = B * -(-n // 64)
+        if T > 256 or wl.theta + wl.adapt_step[l - 1] * T > 2.0 ** 26:
+            return False
+        if 128 < T < (176 if groups > 1536 else 160 if groups < 256 else 0):
+            return False
+        if T > 128 and bf and groups > 1536 and n > 768 and n % 64:
+            return False
+        if fan_in <= 256 and not (T > 40 and (T <= 64 or T * 5 >= blocks * 128 * 4)):
+            return False
+        return bf or rounds <= 16 or B >= 64
+    company = narrow_in_company(wl, l)
+    per = (64 if company <= 64 else 128) if company else 64 if -(-n // 64) * 64 < -(-n // 128) * 128 else 128
+    groups = B * -(-n // per)
+    if bf:
+        if T <= (384 if company or per == 64 else 256) or (company and per == 64) or (T <= 512 and rounds <= 16):
+            return True
+        if top_scan_forms_currents(wl, L - 1) and (l == L - 1 or l == L - 2 and company and narrow_in_company(wl, L - 1)):
+            return True
+
+        def full(i):
+            return 1 <= i < L and pad8(wl.sizes[i]) == 128 and narrow_in_company(wl, i)
+        if full(l) and (full(l - 1) or full(l + 1)):
+            return T <= 512 or groups >= (32 if T <= 1024 else 80)
+        return groups >= (32 if rounds <= 16 else 64 if rounds <= 32 or T <= 512 else 80 if T <= 1024 else 128)
+    if T <= 128 or (T <= 256 and rounds <= (16 if company else 8)):
+        return True
+    if rounds <= 16:
+        if (per == 64 or T <= 384) if company else (per == 64 and T <= 512):
+            return True
+        return groups >= (32 if company and T <= 512 else 64 if T <= 768 else 128)
+    return groups >= (192 if rounds > 64 else 64 if company and (per == 64 or T <= 768) else 128)
+
+
+def narrow_in_company(wl, l):
+    """For a layer of at most 128 neurons whose launch holds the readout or a second such layer too: the widest of the
+    layers that can be in it; else 0."""
+    L = len(wl.sizes) - 1
+
+    def narrow(i):
+        is_narrow = 1 <= i < L and pad8(wl.sizes[i]) <= 128 and not wl.recurrent[i - 1] and not adaptive(wl, i)
+        return pad8(wl.sizes[i]) if is_narrow else 0
+    if not narrow(l) or not ((l == L - 1 and pad8(wl.sizes[L]) <= 32) or narrow(l - 1) or narrow(l + 1)):
+        return 0
+    return max(narrow(l), narrow(l - 1), narrow(l + 1))
+
+
+def top_scan_forms_currents(wl, layer):
+    """Whether the scan of the last spiking layer, where it is a launch of its own, forms the readout's currents."""
+    L = len(wl.sizes) - 1
+    return (layer == L - 1 and wl.precision == "bf16" and not wl.recurrent[layer - 1] and not adaptive(wl, layer)
+            and pad8(wl.sizes[layer]) in (64, 128, 256) and pad8(wl.sizes[L]) <= 32)
+
+
 def forward_chain(wl, layer):
     """The spiking layers that the forward launch starting at text layer `layer` covers, and whether it
     runs the readout too; ([], False) if that layer runs as separate product and scan launches."""
     L = len(wl.sizes) - 1
-
-    def whole(l):
-        n, k = pad8(wl.sizes[l]), wl.sizes[l - 1] if l >= 1 else 0
-        return (wl.precision == "bf16" and 1 <= l < L and not wl.recurrent[l - 1] and n % 64 == 0 and n <= 1024
-                and pad8(k) <= 1024 and (wl.T <= 256 or wl.B >= 64))
-    if not whole(layer):
+    if not runs_whole(wl, layer):
         return [], False
+
+    def joins(l):
+        return l < L and pad8(wl.sizes[l]) <= 128 and not adaptive(wl, l)
+
+    def pairs(l):
+        return joins(l) and joins(l + 1) and runs_whole(wl, l) and runs_whole(wl, l + 1)
+
+    def like(l):                     # workgroups of the same width
+        return (pad8(wl.sizes[l]) > 64) == (pad8(wl.sizes[l + 1]) > 64)
     chain = [layer]
-    if pad8(wl.sizes[layer]) == 128 and whole(layer + 1) and pad8(wl.sizes[layer + 1]) == 128:
+    if pairs(layer) and (like(layer) or not (pairs(layer + 1) and like(layer + 1))):
         chain.append(layer + 1)
     top = chain[-1]
-    return chain, top == L - 1 and pad8(wl.sizes[top]) == 128 and pad8(wl.sizes[L]) <= 32
+    return chain, top == L - 1 and joins(top) and pad8(wl.sizes[L]) <= 32
 
 
 def reverse_forms_ds(wl, layer):
-    """Whether the reverse scan of text layer `layer` forms dS from the current gradients above itself
-    (bf16 products, feed-forward, a multiple of 64 wide, at most 128 padded columns above)."""
+    """Whether the reverse launch of text layer `layer` forms dS from the current gradients above itself
+    (feed-forward, at most 128 padded columns above; up to 1024 neurons, or any multiple of 64 on rounded weights)."""
     L = len(wl.sizes) - 1
-    if not (wl.precision == "bf16" and 1 <= layer < L and not wl.recurrent[layer - 1]):
+    if not (1 <= layer < L) or wl.recurrent[layer - 1] or adaptive(wl, layer) or pad8(wl.sizes[layer + 1]) > 128:
         return False
-    return wl.sizes[layer] % 64 == 0 and pad8(wl.sizes[layer + 1]) <= 128
+    n, bf = pad8(wl.sizes[layer]), wl.precision == "bf16"
+    least = 32 if not bf and pad8(wl.sizes[layer + 1]) > 64 and wl.T > 256 else 1
+    return (bf and n % 64 == 0) or (n <= 1024 and wl.B >= least)
+
+
+def recurrent_pair(wl, layer):
+    """Whether text layer `layer` and the one above it share a launch per direction: recurrent, rounded weights,
+    at most 192 neurons each and sixteen wavefronts with those of the product between them, up to 2048 samples;
+    taken from the bottom up."""
+    L = len(wl.sizes) - 1
+    if not (1 <= layer < L - 1) or wl.precision != "bf16" or wl.B > 2048 or not (wl.recurrent[layer - 1] and wl.recurrent[layer]):
+        return False
+    n = [pad8(v) for v in wl.sizes[layer:layer + 2]]
+    waves = [-(-v // 32) for v in n]
+    return max(n) <= 192 and sum(waves) + max(waves) <= 16 and not recurrent_pair(wl, layer - 1)
 
 
 def algorithmic_bytes(wl, kernel, layer, packed=False):
@@ -75,7 +163,8 @@ def algorithmic_bytes(wl, kernel, layer, packed=False):
     M = wl.T * wl.B
     # rows of the raster as the launches of layer 1 read it (they read the bits themselves where layer 1
     # runs as one launch and, for the weight gradient, the batch is a multiple of 8; else a pre-pass unpacks)
-    x_rows = (wl.T + 7) // 8 * wl.B if packed and forward_chain(wl, 1)[0] and wl.B % 8 == 0 else M
+    direct = packed and wl.sizes[0] % 4 == 0 and runs_whole(wl, 1) and (kernel != "weight_grad" or wl.B % 8 == 0)
+    x_rows = (wl.T + 7) // 8 * wl.B if direct else M
     bf = wl.precision == "bf16"
     di = 4                           # current gradients are 4 bytes in memory in both modes
     planes = 1 if bf else 3
@@ -84,22 +173,23 @@ def algorithmic_bytes(wl, kernel, layer, packed=False):
         return sum(algorithmic_bytes(wl, kernel, l, packed) for l in range(1, L + 1))
     n_in, n_out = wl.sizes[layer - 1], wl.sizes[layer]
     fused_rev = reverse_forms_ds(wl, layer)
-    fused_fwd = fused_rev and layer == L - 1 and n_out in (64, 128, 256) and pad8(wl.sizes[L]) <= 32
+    fused_fwd = top_scan_forms_currents(wl, layer)
+    state = 4 if layer < L and adaptive(wl, layer) else 0        # the adaptation, beside V
     chain, with_readout = forward_chain(wl, layer)
     if kernel == "lif_forward" and chain:
-        # the launch that starts at `layer`: spikes below (1 B) and W (2 B) read; V (4) and S (1) written per
-        # layer; with the readout its currents, its trace and its current gradients (4 B each)
+        # the launch that starts at `layer`: spikes below (1 B) and W (2 B a plane) read; V (4) and S (1) written
+        # per layer; with the readout its currents, its trace and its current gradients (4 B each)
         total = (x_rows if layer == 1 else M) * n_in
         for l in chain:
-            total += 2 * wl.sizes[l - 1] * wl.sizes[l] + M * wl.sizes[l] * (4 + 1)
+            total += planes * 2 * wl.sizes[l - 1] * wl.sizes[l] + M * wl.sizes[l] * (4 + 1 + state)
         if with_readout:
-            total += 2 * wl.sizes[chain[-1]] * wl.sizes[L] + 3 * M * pad8(wl.sizes[L]) * 4
+            total += planes * 2 * wl.sizes[chain[-1]] * wl.sizes[L] + 3 * M * pad8(wl.sizes[L]) * 4
         return total
     if kernel == "lif_forward":      # read I (4), write V (4) and S (1 byte) [+ the readout's currents]
-        return M * n_out * (4 + 4 + 1) + (M * pad8(wl.sizes[L]) * 4 if fused_fwd else 0)
+        return M * n_out * (4 + 4 + 1 + state) + (M * pad8(wl.sizes[L]) * 4 if fused_fwd else 0)
     if kernel == "lif_reverse":      # read dS (4) [or the current gradients above] and V (4), write dI (4)
         above = pad8(wl.sizes[layer + 1]) if fused_rev else n_out
-        return M * (above * 4 + n_out * (4 + di))
+        return M * (above * 4 + n_out * (4 + di + state))
     if kernel == "current_gemm":     # read spikes (1 byte) and the weight planes, write I (4)
         return M * n_in + planes * 2 * n_in * n_out + M * n_out * 4
     if kernel == "weight_grad":      # read spikes and dI, write dW (recurrent: own spikes too, and dR)
@@ -125,8 +215,9 @@ def method_flops(wl, kernel, layer):
     if kernel == "lif_forward":
         chain, with_readout = forward_chain(wl, layer)
         f = sum(2 * M * wl.sizes[l - 1] * wl.sizes[l] for l in chain)
-        if with_readout or (not chain and reverse_forms_ds(wl, layer) and layer == L - 1
-                            and n_out in (64, 128, 256) and pad8(wl.sizes[L]) <= 32):
+        if with_readout:
+            f += 2 * M * wl.sizes[chain[-1]] * wl.sizes[L]
+        elif not chain and top_scan_forms_currents(wl, layer):
             f += 2 * M * n_out * wl.sizes[L]
         return f
     if kernel == "lif_reverse":
@@ -136,8 +227,9 @@ def method_flops(wl, kernel, layer):
     if kernel == "weight_grad":
         rec = layer < L and wl.recurrent[layer - 1]
         return 2 * M * n_in * n_out + (2 * M * n_out * n_out if rec else 0)
-    if kernel in ("rlif_forward", "rlif_reverse"):
-        return 2 * M * n_out * n_out
+    if kernel in ("rlif_forward", "rlif_reverse"):       # a pair: both layers' own products and the one between them
+        up = wl.sizes[layer + 1] if recurrent_pair(wl, layer) else 0
+        return 2 * M * (n_out * n_out + n_out * up + up * up)
     return 0
 
 

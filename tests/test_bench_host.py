@@ -37,14 +37,54 @@ def test_scan_and_weight_gradient_bytes_at_the_headline_shape():
 
 
 def test_which_layers_run_as_one_forward_launch():
-    """Mirrors the library's rule: feed-forward layers of a multiple of 64 and at most 1024
-    neurons (fan-in too) on bf16 products; pairs of exactly 128; the readout rides along below
-    128 neurons and at most 32 padded classes."""
-    assert bench.forward_chain(workloads.CONFIGS["table1_ff512"], 1) == ([1], False)
-    assert bench.forward_chain(workloads.CONFIGS["wide_ff1024"], 2) == ([2], False)
-    assert bench.forward_chain(workloads.CONFIGS["deep_rec2048"], 2) == ([], False)
-    assert bench.forward_chain(workloads.CONFIGS["shd_rec128"], 1) == ([], False)
-    assert bench.forward_chain(workloads.CONFIGS["tiny_ff"], 1) == ([], False)     # fp32 products
+    """Mirrors the library's rule: feed-forward layers of at most 1024 neurons (fan-in too); pairs of at
+    most 128; the readout rides along below 128 neurons and at most 32 padded classes."""
+    cfg = workloads.CONFIGS
+    assert bench.forward_chain(cfg["table1_ff512"], 1) == ([1], False)
+    assert bench.forward_chain(cfg["wide_ff1024"], 2) == ([2], False)
+    assert bench.forward_chain(cfg["deep_rec2048"], 2) == ([], False)
+    assert bench.forward_chain(cfg["shd_rec128"], 1) == ([], False)
+    assert bench.forward_chain(cfg["tiny_ff"], 1) == ([1], True)                    # fp32 products
+    assert bench.forward_chain(cfg["shd_ff128"].scaled(precision="fp32"), 1) == ([1, 2], True)
+    assert bench.forward_chain(cfg["shd_ff128"].scaled(sizes=(203, 121, 70, 33)), 1) == ([1, 2], False)
+    five = cfg["shd_ff128"].scaled(sizes=(70, 64, 128, 128, 20), recurrent=(False,) * 3, beta=(0.9,) * 4)
+    assert bench.forward_chain(five, 1) == ([1], False) and bench.forward_chain(five, 2) == ([2, 3], True)
+    long = cfg["table1_ff512"].scaled(T=300, B=16)                                  # few samples of many steps
+    assert bench.runs_whole(long, 1) and not bench.runs_whole(long.scaled(B=15), 1)
+    steep = dict(adapt_decay=(0.9, 0.9), adapt_step=(0.2, 0.2))
+    assert bench.forward_chain(cfg["shd_ff128"].scaled(**steep), 1) == ([1], False)
+    assert bench.forward_chain(cfg["shd_ff128"].scaled(T=257, **steep), 1) == ([], False)
+    assert not bench.runs_whole(cfg["shd_ff128"].scaled(adapt_decay=(0.9, 0.9), adapt_step=(float("inf"),) * 2), 1)
+
+
+def test_reverse_launches_that_form_their_own_spike_gradients():
+    cfg = workloads.CONFIGS
+    assert all(bench.reverse_forms_ds(cfg["shd_ff128"].scaled(precision=p), l) for p in ("bf16", "fp32") for l in (1, 2))
+    assert bench.reverse_forms_ds(cfg["shd_ff128"].scaled(sizes=(203, 130, 70, 11)), 1)
+    assert not bench.reverse_forms_ds(cfg["table1_ff512"], 1) and bench.reverse_forms_ds(cfg["table1_ff512"], 2)
+    few = cfg["shd_ff128"].scaled(precision="fp32", T=300, B=31)                    # six products below 128 columns
+    assert not bench.reverse_forms_ds(few, 1) and bench.reverse_forms_ds(few.scaled(B=32), 1) and bench.reverse_forms_ds(few, 2)
+
+
+def test_operations_of_a_pair_of_recurrent_layers():
+    """Two recurrent layers of few neurons share a launch per direction, which also takes the product between them."""
+    wl = workloads.CONFIGS["shd_rec128"]
+    M = 128 * 256
+    assert bench.recurrent_pair(wl, 1) and not bench.recurrent_pair(wl, 2)
+    for kernel in ("rlif_forward", "rlif_reverse"):
+        assert bench.method_flops(wl, kernel, 1) == 2 * M * 3 * 128 * 128
+        assert bench.method_flops(wl.scaled(precision="fp32"), kernel, 1) == 2 * M * 128 * 128
+        assert bench.method_flops(wl.scaled(sizes=(700, 168, 168, 20)), kernel, 1) == 2 * M * 168 * 168
+
+
+def test_launch_bytes_of_fp32_products():
+    """Three planes of the weights (2 bytes each); everything else as with rounded weights."""
+    wl = workloads.CONFIGS["shd_ff128"].scaled(precision="fp32")
+    M = 128 * 256
+    weights = 700 * 128 + 128 * 128 + 128 * 20
+    assert bench.algorithmic_bytes(wl, "lif_forward", 1) == M * 700 + 6 * weights + 2 * M * 128 * 5 + 3 * M * 24 * 4
+    assert bench.algorithmic_bytes(wl, "lif_forward", 1, packed=True) == M // 8 * 700 + 6 * weights + 2 * M * 128 * 5 + 3 * M * 24 * 4
+    assert bench.method_flops(wl, "lif_forward", 1) == 2 * M * weights
 
 
 def test_more_than_one_gpu_is_refused():

@@ -148,6 +148,31 @@ def test_which_layers_run_as_one_launch(precision, T, B, K, N, adaptive, above, 
     assert n == [0 if whole else 1]
 
 
+@pytest.mark.parametrize("T,B,sizes,recurrent,precision,adaptive",
+                         [(128, 16, (700, 128, 128, 20), (0, 0), "bf16", False), (128, 16, (700, 128, 128, 20), (0, 0), "fp32", False),
+                          (40, 6, (203, 130, 70, 11), (1, 0), "bf16", False), (40, 6, (100, 96, 60, 33), (1, 1), "bf16", False),
+                          (70, 4, (70, 64, 128, 128, 20), (0, 0, 0), "bf16", False), (300, 2, (100, 1030, 512, 10), (0, 0), "bf16", False),
+                          (300, 31, (100, 200, 100, 10), (0, 0), "fp32", False), (150, 8, (300, 256, 100, 10), (0, 0), "bf16", True)])
+def test_bench_describes_what_is_launched(T, B, sizes, recurrent, precision, adaptive):
+    """bench.py's account of which launches hold which layers (its bytes and operations go by it), by what is launched."""
+    import bench
+    L = len(sizes) - 1
+    kw = dict(adapt_decay=(0.9,) * (L - 1), adapt_step=(0.2,) * (L - 1)) if adaptive else {}
+    wl = workloads.Workload(name="account", index=33, T=T, B=B, sizes=sizes, recurrent=tuple(map(bool, recurrent)), beta=(0.9,) * L,
+                            theta=1.0, surrogate="superspike", slope=10.0, precision=precision, rate_lo=0.1, rate_hi=0.2, **kw)
+    wanted, l, readout = {}, 1, False
+    while l < L:
+        chain, with_readout = bench.forward_chain(wl, l)
+        upper = l > 1 and bench.recurrent_pair(wl, l - 1)
+        wanted.update({("current_gemm", i): 0 for i in chain} or {("current_gemm", l): int(not upper)})
+        wanted.update({("lif_forward", i): int(i == l) for i in chain} or {("rlif_forward" if recurrent[l - 1] else "lif_forward", l): int(not upper)})
+        readout = readout or with_readout
+        l = chain[-1] + 1 if chain else l + 1
+    wanted["readout_forward", L] = int(not readout)
+    wanted.update({("input_grad", l + 1): int(not bench.reverse_forms_ds(wl, l) and not bench.recurrent_pair(wl, l)) for l in range(1, L)})
+    assert_launches(wl, None, wanted)
+
+
 # ---------------------------------------------------------------- feed-forward, fp32 products
 @pytest.mark.parametrize("gain", [1.0, 3.0])
 def test_tiny_ff_fp32(gain):
