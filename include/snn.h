@@ -203,8 +203,10 @@ typedef enum {
  *                     4 (default) and runs the readout scan, the loss and the readout's current
  *                     gradients (fp32 products too)
  *   LAYER_PAIR        1 (default): two consecutive one-launch layers of at most 128 padded
- *                     neurons share a launch, and so do two consecutive recurrent layers of at
- *                     most 192 on rounded weights; 0: one launch each; 2: one-launch layers of
+ *                     neurons share a launch (layers of up to 64 with their like where there is a
+ *                     choice), and so do two consecutive recurrent layers of at most 192 on rounded
+ *                     weights, up to 2048 samples, that need at most sixteen wavefronts of 32 neurons
+ *                     with as many as the wider one for the product between them; 0: one launch each; 2: one-launch layers of
  *                     exactly 128 padded neurons share a launch with a
  *                     workgroup per layer and sample, the upper layer's following the lower
  *                     layer's through memory 64 steps at a time (measured slower: 32.9 against
@@ -385,8 +387,8 @@ int32_t snn_weight_grad_static(const uint8_t *S_dev, const float *G_dev, float *
                                int32_t K, int32_t N, void *hip_stream);
 
 /* Event timer.  snn_profile_select(ctx, k, layer) brackets every later launch of kernel
- * class k (layer = 0: all layers, else that layer only) with a pair of HIP events on the
- * library's stream; k = SNN_K_NONE switches it off and clears the totals.
+ * class k (layer = 0: all layers, else that layer only; a launch that holds several layers counts for
+ * the lowest of them) with a pair of HIP events on the library's stream; k = SNN_K_NONE switches it off and clears the totals.
  * snn_profile_read waits for the stream and returns the summed elapsed milliseconds and
  * the number of bracketed launches since the last select. */
 int32_t snn_profile_select(snn_ctx *ctx, int32_t kernel_class, int32_t layer);

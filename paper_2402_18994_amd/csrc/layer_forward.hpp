@@ -5,7 +5,7 @@
 // at 128 neurons that round trip is most of both kernels' traffic, and at 32 768 chains the
 // scan has two wavefronts per compute unit which each issue a load and two stores per step.
 // Here a workgroup owns one sample and BN = 64 or 128 of the layer's neurons (a layer of ld
-// neurons is cut in ld / BN parts; the parts of a sample run on the same XCD and share its
+// neurons is cut in parts of BN, the last one perhaps not full; the parts of a sample run on the same XCD and share its
 // spike rows in that L2).  Per block of 128 steps:
 //   1. product: the 128 rows (t, b) of the spike tensor below times the rounded weights, on
 //      the streamed pipeline of the large current products (operands straight into LDS,
@@ -22,7 +22,7 @@
 //      register); the two fused multiply-adds take 35;
 //   4. store: all four wavefronts write V as whole rows, 16 bytes per lane, and S as 16
 //      neurons per lane, decided again from the stored V (the same exact comparison);
-//   5. (last spiking layer of 128 neurons, at most 32 padded classes) the readout's currents
+//   5. (last spiking layer of at most 128 neurons, at most 32 padded classes) the readout's currents
 //      J = S W_out of the block, eight 32x32x16 MFMAs per wavefront on the spikes in LDS: no
 //      product launch for the readout;
 //   6. (same case) the readout itself: the LI scan of the block in eight segments of 16 steps
@@ -32,9 +32,15 @@
 //      form per segment: no launch for the readout at all.
 // The potential is carried in the scanning lanes' registers from block to block.
 // Rows past T read as zero and are not stored; columns of W past the fan-in are zero.
-// Two consecutive layers of exactly 128 neurons can share the launch (NL = 2): per block the
+// Two consecutive layers of at most 128 neurons can share the launch (NL = 2): per block the
 // workgroup runs steps 1 to 4 for the lower layer, waits until its spike stores are
-// acknowledged, and runs them again for the upper layer on the rows it has just written.
+// acknowledged, and runs them again for the upper layer on the rows it has just written.  Rows of fewer
+// than 128 neurons share their cache lines with the rows of the next samples, and a stage of 64 inputs
+// reads past a row's end into them, so such a line may have been in the compute unit's L1 before the row
+// was written.  What is read is right all the same: stores write through that L1, so a workgroup's loads
+// behind its own acknowledged stores and a barrier see them whatever it held (the wavefronts of a workgroup
+// share a compute unit; nothing has to be invalidated between them), and the neighbours' bytes, which may
+// be old, are 0 or 1 and meet rows of the weights past the fan-in, which are zero.
 // PACKED: the bottom layer of the launch reads the input raster packed along time (eight steps
 // per byte, Section 2.1.4): the 16 packed rows of the sample's block sit in LDS for the whole
 // product and are unpacked between the fragment read and the MFMA; the stages carry W alone.

@@ -714,6 +714,9 @@ int launch_lif_forward(snn_ctx *c, int l) {
 // narrow, on rounded weights.  (SNN_OPT_LAYER_PAIR = 0: a launch each.)  Pairs are taken from the bottom up.
 // A feed-forward layer above does not join: its one launch per direction, with the readout or its dS, is
 // faster than a place in the loop (700-64(rec)-128-20, T = 200, B = 64: 159 us per step, 191 paired).
+// Up to 2048 samples, from where a layer alone takes sixteen samples to a workgroup (100-128-128-20, T = 50, us per step
+// apart and paired: 1024 samples 161 and 118, 2048 286 and 238; beyond, pairs would still be the faster ones, 2560 348 and
+// 295, 4096 491 and 428, the 64 / 64 and 192 / 120 widths alike: the line could go up).
 bool rlif_pair_lower(const snn_ctx *c, int l) {
   if (l < 0 || l + 1 > c->L - 2 || !c->opt[SNN_OPT_LAYER_PAIR] || c->nplanes != 1) return false;
   const Layer &y = c->layers[l], &up = c->layers[l + 1];
@@ -815,7 +818,8 @@ int columns_above(const snn_ctx *c, int l) { return l + 1 == c->L - 1 ? c->ldC :
 // Samples from which a layer runs as one launch: SNN_OPT_LAYER_MIN_BATCH, or by the rules here and below.
 int layer_min_batch(const snn_ctx *c) { return std::max(1, c->opt[SNN_OPT_LAYER_MIN_BATCH]); }
 // Reverse, the six products of fp32 operands below more than 64 columns are the long part of a block: 32
-// samples above 256 steps (us saved, 700-128-128-20, 4 / 64 samples: T = 256 2 / 4, T = 300 0 / 4, T = 500 -3 / 10).
+// samples above 256 steps (us saved, 700-128-128-20, 4 / 64 samples: T = 256 2 / 4, T = 300 0 / 4, T = 500 -3 / 10; 300-200-100-20,
+// 16 / 32 / 64 / 128: T = 200 -2 / 1 / 5 / 8, T = 1000 0 / 2 / 31 / 63).
 int layer_reverse_min_batch(const snn_ctx *c, int l) {
   const bool long_product = c->nplanes == 3 && columns_above(c, l) > 64 && c->T > 256;
   return c->opt[SNN_OPT_LAYER_MIN_BATCH] == 0 && long_product ? 32 : layer_min_batch(c);
@@ -842,6 +846,10 @@ bool reverse_wide(const snn_ctx *c, int l) {
 // (lif_reverse_top_kernel).  The second is faster above 256 neurons (121 against 129 us at 512, 466
 // against 492 at 1024); one chain per lane also there: at 1024 neurons below the readout it takes 216 us
 // where the four-chains-per-lane scan plus the readout's input-gradient launch took 290 + 100.
+// Widths and products that the second does not take run on the first up to 1024 neurons, at any batch (us per step with
+// product and scan apart and in one, 700-N-20: N = 500, T = 260, B = 64 115 and 103, T = 1000, B = 1 176 and 158; N = 1000, T = 64,
+// B = 4 56 and 52, T = 128, B = 512 604 and 546; fp32, N = 256, T = 260, B = 64 119 and 110, N = 512, T = 1000, B = 64 462 and 400,
+// N = 1000, T = 260, B = 1 89 and 86, B = 64 262 and 239).
 // SNN_OPT_LAYER_REVERSE = 0 switches the first off, SNN_OPT_TOP_SCANS = 0 both.
 bool reverse_takes_product(const snn_ctx *c, int l) {
   const Layer &y = c->layers[l];
@@ -903,7 +911,10 @@ int launch_layer_reverse(snn_ctx *c, int l, bool wide) {
   a.T = c->T; a.B = c->B; a.ld = y.ld;
   a.nt_store = streams_past_cache(c, c->M * y.ld * 4);
   Bracket br(c, SNN_K_LIF_REVERSE, l + 1);
-  // Rasters of at most 32 steps: several samples to a block of 64 rows.
+  // Rasters of at most 32 steps: several samples to a block of 64 rows, as many as leave 256 workgroups (us per step with
+  // so many, and with one: 200-60-20, T = 16, B = 1024 35.5 and 39.1, 200-256-20, B = 256 42.4 and 48.0, fp32 45.9 and 52.2,
+  // T = 32, B = 512 54.3 and 58.1; with fewer workgroups than that all are within 1 us, four samples in 128 of them 31.4,
+  // two in 256 32.0, one 32.8 at 200-60-20, T = 16, B = 512).
   a.slot_log2 = c->T <= 16 ? 4 : c->T <= 32 ? 5 : 6;
   while (a.slot_log2 < 6 && ((long long)c->B * ((y.ld + 63) / 64) << a.slot_log2) < 64ll * 256) ++a.slot_log2;
   HIPCHK(c, layer_reverse(c->stream, a, c->surrogate, !c->hl, wide));

@@ -1053,7 +1053,7 @@ def test_narrow_layers_share_launches_with_their_like(sizes, counts):
 
 @pytest.mark.parametrize("T,sizes", [(150, (90, 128, 128, 128, 10)), (40, (50, 128, 128, 64, 128, 128, 12))])
 def test_two_layers_per_forward_launch(T, sizes):
-    """Consecutive one-launch layers of exactly 128 neurons share a launch in pairs: a workgroup
+    """Consecutive one-launch layers of 128 neurons share a launch in pairs: a workgroup
     takes its sample through the lower layer's block, stores its spikes, and reads them back as
     the upper layer's input.  Three hidden layers (a pair, then the last one alone with the
     readout) and five (pair, a 64-wide layer on its own, pair with the readout), two blocks of
@@ -1791,8 +1791,9 @@ def test_adaptive_threshold_ragged_shapes(precision):
 
 @pytest.mark.parametrize("adaptive", [(True, False), (False, True), (True, True)], ids=["lower", "upper", "both"])
 def test_adaptive_threshold_headline_widths(adaptive):
-    """700-128-128-20 on bf16 products with one or both hidden layers adapting: an adapting layer
-    runs as product + scan launches between (or below, or above) layers that run as one launch."""
+    """700-128-128-20 on bf16 products with one or both hidden layers adapting: an adapting layer runs as a launch
+    of its own on the kernel with two states (layer 1, of a long fan-in; layer 2, of 128 inputs, as product and scan
+    at this number of steps), below or above a layer that runs on the one without."""
     wl = workloads.CONFIGS["shd_ff128"].scaled(T=70, B=24, adapt_decay=(0.95, 0.9),
                                                adapt_step=tuple(0.25 if a else 0.0 for a in adaptive))
     rep = full_step_parity(wl, w_gain=3.0)
