@@ -10,6 +10,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <mutex>
+#include <numeric>
 #include <string>
 #include <vector>
 
@@ -100,7 +101,8 @@ struct snn_ctx {
   bool loss_ready = false;        // the mean of loss_b has been taken since the last readout
   int wall_khz = 100000;          // rate of the device's constant clock
   int cus = 0;                    // compute units of the device
-  bool wg_tall = false;           // weight-gradient products use 256 x 128 tiles
+  bool wg_tall = false;           // weight-gradient products use 256 x 128 tiles (general kernel)
+  bool wg_tr_tall = false;        // the same on the kernel of transposing LDS reads
   bool wg_narrow = false;         // weight gradients: no product of more than 32 columns, and a long one
   bool integral = false;          // integral cross-entropy instead of max over time
   float last_lr = 0.f;            // of the last snn_sgd_step
@@ -240,18 +242,20 @@ void carve(snn_ctx &c, Carver &cv) {
   }
   c.wg_narrow = any_long && all_narrow;
   auto narrow = [&](const Layer &y) { return !all_narrow && long_and_narrow(c.M, y.K, y.N, c.precision == SNN_PREC_FP32); };
+  std::vector<int> job_tiles;                             // of each product of the merged launch
   auto count_tiles = [&](bool tall) {
-    int n = 0;
+    job_tiles.clear();
     for (int l = 0; l < c.L; ++l) {
-      if (!narrow(c.layers[l])) n += wgrad_tiles(c.layers[l].K, c.layers[l].N, tall);
-      if (c.layers[l].recurrent) n += wgrad_tiles(c.layers[l].N, c.layers[l].N, tall);
+      if (!narrow(c.layers[l])) job_tiles.push_back(wgrad_tiles(c.layers[l].K, c.layers[l].N, tall));
+      if (c.layers[l].recurrent) job_tiles.push_back(wgrad_tiles(c.layers[l].N, c.layers[l].N, tall));
     }
-    return n;
+    return std::accumulate(job_tiles.begin(), job_tiles.end(), 0);
   };
   c.wg_tall = c.precision != SNN_PREC_FP32 && count_tiles(false) >= 32;
   // (the splits are laid out here, for the kernel that SNN_OPT_WGRAD_TR selects at this point)
   const bool wg_tr = c.opt[SNN_OPT_WGRAD_TR] != 0 && !c.wg_narrow;
-  const int wg_tiles = count_tiles(c.wg_tall && !wg_tr);
+  c.wg_tr_tall = wg_tr && c.precision != SNN_PREC_FP32 && wgrad_tall_pays(c.M, count_tiles(false), count_tiles(true));
+  const int wg_tiles = count_tiles(c.wg_tr_tall || (c.wg_tall && !wg_tr));
   long long wg_weights = 0, wg_row_bytes = 0;             // what the merged launch writes per split / reads per row
   for (int l = 0; l < c.L; ++l) {
     const Layer &y = c.layers[l];
@@ -281,6 +285,7 @@ void carve(snn_ctx &c, Carver &cv) {
     // eight steps, so that the same splits serve a raster packed along time)
     const long long rows_w = l == 0 ? (long long)((c.T + 7) / 8 * 8) * c.B : c.M;
     y.splits_w = narrow(y) ? choose_splits(rows_w, wgrad_tiles(y.K, y.N, false), (long long)K * N, K + 4ll * N, &y.per_w, false)
+                           : c.wg_tr_tall ? choose_splits_tall(rows_w, job_tiles.data(), (int)job_tiles.size(), wg_weights, &y.per_w)
                            : choose_splits(rows_w, wg_tiles, wg_weights, wg_row_bytes, &y.per_w, wg_tr);
     if (y.splits_w > 1) y.part_w = cv.take<float>((size_t)y.splits_w * K * N);
     if (y.recurrent) {
@@ -293,7 +298,8 @@ void carve(snn_ctx &c, Carver &cv) {
       y.g[0] = cv.take<float>((size_t)c.B * y.ld);
       y.g[1] = cv.take<float>((size_t)c.B * y.ld);
       if (c.precision != SNN_PREC_FP32 && rlif_wide_layer(y.ld)) y.rp_space = cv.take<char>(RlifWide::BYTES);
-      y.splits_r = choose_splits(c.M, wg_tiles, wg_weights, wg_row_bytes, &y.per_r, wg_tr);
+      y.splits_r = c.wg_tr_tall ? choose_splits_tall(c.M, job_tiles.data(), (int)job_tiles.size(), wg_weights, &y.per_r)
+                                : choose_splits(c.M, wg_tiles, wg_weights, wg_row_bytes, &y.per_r, wg_tr);
       if (y.splits_r > 1) y.part_r = cv.take<float>((size_t)y.splits_r * N * N);
     }
     y.beta_v = cv.take<float>(y.ld);
@@ -512,6 +518,7 @@ struct WgradJobs {
 // long_and_narrow), else through the general one (256 x 128 tiles when there are many wide ones).
 static bool wgrad_tr(const snn_ctx *c) { return c->opt[SNN_OPT_WGRAD_TR] != 0 && !c->wg_narrow; }
 static bool wgrad_tall(const snn_ctx *c) { return c->wg_tall && !wgrad_tr(c); }
+static bool wgrad_tr_tall(const snn_ctx *c) { return c->wg_tr_tall && wgrad_tr(c); }
 
 int flush_tn(snn_ctx *c, WgradJobs &w, int which) {
   hipError_t e = hipSuccess;
@@ -525,7 +532,7 @@ int flush_tn(snn_ctx *c, WgradJobs &w, int which) {
             : gemm_jobs_launch<P_T_U8, Q_T_HL, EPI_STORE, 2, 2, 2, 1, 2, 1>(w.mid, c->stream);
     memset(&w.mid, 0, sizeof w.mid);
   } else if (which == 2 && w.wide.njobs) {
-    e = wgrad_tr(c) ? wgrad_tr_jobs_launch(w.wide, f32, c->stream)
+    e = wgrad_tr(c) ? wgrad_tr_jobs_launch(w.wide, f32, wgrad_tr_tall(c), c->stream)
             : f32 ? gemm_jobs_launch<P_T_U8, Q_T_F32S, EPI_STORE, 2, 2, 2, 2, 3, 1>(w.wide, c->stream)
             : c->wg_tall ? gemm_jobs_launch<P_T_U8, Q_T_HL, EPI_STORE, 2, 2, 4, 2, 2, 1>(w.wide, c->stream)
                            : gemm_jobs_launch<P_T_U8, Q_T_HL, EPI_STORE, 2, 2, 2, 2, 2, 1>(w.wide, c->stream);
@@ -557,6 +564,7 @@ int queue_tn(snn_ctx *c, WgradJobs &w, SpikeSrc s, int rows, const void *G, int 
   }
   if (which == 0) gemm_jobs_add<4, 1, 1, 1>(list, a, splits);
   else if (which == 1) gemm_jobs_add<2, 2, 2, 1>(list, a, splits);
+  else if (wgrad_tr_tall(c)) wgrad_tr_tall_add(list, a, splits);
   else if (wgrad_tall(c)) gemm_jobs_add<2, 2, 4, 2>(list, a, splits);
   else gemm_jobs_add<2, 2, 2, 2>(list, a, splits);
   return SNN_OK;
@@ -1821,7 +1829,7 @@ int32_t snn_weight_grad_static(const uint8_t *S_dev, const float *G_dev, float *
     e = gemm_jobs_launch<P_T_U8, Q_T_F32S, EPI_STORE, 4, 1, 1, 1, 3, 1>(jobs, st);
   } else {
     gemm_jobs_add<2, 2, 2, 2>(jobs, a, splits);
-    e = wgrad_tr_jobs_launch(jobs, true, st);
+    e = wgrad_tr_jobs_launch(jobs, true, false, st);
   }
   if (e != hipSuccess) return fail(nullptr, SNN_ERR_HIP, "weight-gradient launch failed: %s", hipGetErrorString(e));
   if (splits > 1) {

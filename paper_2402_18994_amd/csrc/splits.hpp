@@ -65,6 +65,37 @@ inline int choose_splits(long long M, int tiles, long long weights, long long ro
   return (int)((M + per - 1) / per);
 }
 
+// Tiles of 256 x 128 on the kernel of transposing LDS reads (rounded weights), one workgroup per compute unit.
+// A row of a 128 x 128 tile's contraction takes about 66 ps of the whole chip, one of a tall tile 95, and a launch of
+// tall tiles about 18 us more: longer to start and end, and twice the partial sums at the same count of workgroups.
+// us per step, 128 x 128 and 256 x 128, by tiles of either kind and rows (T*B): 700-128-128-20, 8 and 5, 32768: 76.3 85.4,
+// 128000: 254 255; 700-256-20, 14 and 7, 32768: 83.7 88.3, 65536: 132.5 133.8, 128000: 301 268; 700-256-256-20, 18 and 9,
+// 32768: 138 144, 65536: 295 273; 700-512-20, 28 and 14, 32768: 127.4 129.6, 128000: 537 471; 700-512-512-20, 44 and 22,
+// 8192: 109.7 110.9, 16384: 158.3 155.6, 32768: 306 280, 65536: 552 525; 300-1024-20 (512 rows for 300), 32 and 20, 32768: 175
+// 191, 65536: 394 383, 128000: 744 703; 100-300-200-20 (512 for 300), 11 and 8, 65536: 275 277.
+inline bool wgrad_tall_pays(long long M, int tiles, int tall_tiles) {
+  return M * (66ll * tiles - 95ll * tall_tiles) >= 18000000;
+}
+
+// Splits of tall tiles: any count, for the workgroups of an XCD (32 compute units; each product's workgroups are dealt
+// evenly over the XCDs) to take the fewest rounds for their length, 18 ns a row and 5 us a round, with the partial
+// sums.  700-512-512-20, T*B = 65536 (the launch alone, us): 8 splits 160, 11 131, 14 190, 16 171, 23 145; 700-1024-1024-20,
+// 131072: 4 splits 665, 8 705, 16 737.
+inline int choose_splits_tall(long long M, const int *tiles, int jobs, long long weights, long long *per_split) {
+  int best = 1;
+  double best_us = 0.;
+  for (int want = 1; want <= 64 && (want == 1 || 256ll * want <= M); ++want) {
+    const long long per = round_up((M + want - 1) / want, 64);
+    const int n = (int)((M + per - 1) / per);
+    long long slots = 0;                                 // workgroups of an XCD
+    for (int j = 0; j < jobs; ++j) slots += ((long long)tiles[j] * n + 7) / 8;
+    const double us = (slots + 31) / 32 * (per * 18e-3 + 5.) + (n > 1 ? n * weights * 1.25e-6 : 0.);
+    if (want == 1 || us < best_us) { best = want; best_us = us; }
+  }
+  *per_split = round_up((M + best - 1) / best, 64);
+  return (int)((M + *per_split - 1) / *per_split);
+}
+
 inline int wgrad_tiles(int rows, int cols, bool tall) {
   int bn = cols <= 32 ? 32 : (cols <= 64 ? 64 : 128);
   const int bm = tall && cols > 64 ? 256 : 128;

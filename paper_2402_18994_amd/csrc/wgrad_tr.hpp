@@ -21,13 +21,19 @@
 //                       the B operand, hence in adjacent lanes of the accumulator: the two sums are
 //                       kept apart over the whole contraction and joined by one cross-lane add at the
 //                       end (smallest terms are never lost in a running sum of the large ones).
-// A workgroup owns 128 rows k x 128 columns n of dW for one slice of the contraction (the splits
+// A workgroup owns 128 (or 256) rows k x 128 columns n of dW for one slice of the contraction (the splits
 // and the order in which partial results are added are those of the general kernel); 2 x 2
 // wavefronts hold 64 x 64 each, as 2 x 4 accumulator tiles (a column tile is 16 neurons x {hi, lo}).
 // Stages of 32 rows m on three buffers: 4 KiB of S (rows of 128 bytes) and 16 KiB of G (rows of 128
 // words) per stage; 16-byte units are placed at slot u ^ f(m) within a row (applied on the global
 // side of the loads) so that the transposed reads, which touch 8 (S) or 4 (G) consecutive rows at
 // the same columns, spread over the banks.
+//
+// Tall tiles, 256 rows k (TI = 4): what bounds large products on 128 x 128 tiles is the ingest of the operands, 20 KiB for
+// 512 cycles of MFMA where the L2 gives a compute unit about 29 bytes a cycle, and the LDS reads, 640 bytes per MFMA.  A
+// wavefront of 128 x 64 (16 accumulator tiles, 256 registers; one workgroup per compute unit) asks for 24 KiB per 1024
+// cycles and reads 384 bytes per MFMA.  The launch of 700-1024-1024-20 at T*B = 131072: 854 -> 665 us (1.4 PFLOP/s with both
+// passes); 700-2048(rec)-2048-2048-20, 65536: 3504 -> 2330; 700-512-512-20, 65536: 155 -> 131.  When: wgrad_tall_pays.
 #pragma once
 #include "gemm_stream.hpp"
 
@@ -39,11 +45,12 @@ typedef __attribute__((address_space(3))) v2i32_t *lds_v2i32_ptr;
 typedef __attribute__((address_space(3))) v4i16_t *lds_v4i16_ptr;
 typedef __attribute__((address_space(3))) char *lds_char_ptr;
 
-template <int NS_>
+// TI: 32-row tiles of a wavefront, 2 (BM = 128) or 4 (BM = 256).
+template <int NS_, int TI_>
 struct WgradTr {
-  static constexpr int BM = 128, BN = 128, MT = 32, NS = NS_;
-  static constexpr int SP = MT * 128, GP = MT * 512, ST = SP + GP;   // bytes of a stage: S part, G part
-  static constexpr int NL = 5;                                       // load instructions per wavefront and stage
+  static constexpr int TI = TI_, BM = 64 * TI, BN = 128, MT = 32, NS = NS_;
+  static constexpr int SP = MT * BM, GP = MT * 512, ST = SP + GP;    // bytes of a stage: S part, G part
+  static constexpr int nl(bool pk) { return (pk ? 1 : TI / 2) + 4; } // load instructions per wavefront and stage
   static constexpr int LDS_BYTES = NS * ST;
 };
 
@@ -52,8 +59,8 @@ template <bool PK, int NS, typename FIssue, typename FPrep, typename FLoad, type
 __device__ __forceinline__ void wgrad_tr_f32_multiply(const GemmArgs &a, char *lds, const int lane, const int wave, const int row0,
                                                       const int col0, const int split, const int nk, FIssue &issue, FPrep &issue_prepare,
                                                       FLoad &issue_load, FConv &convert) {
-  typedef WgradTr<NS> G;
-  constexpr int SP = G::SP, ST = G::ST, NL = G::NL;
+  typedef WgradTr<NS, 2> G;
+  constexpr int SP = G::SP, ST = G::ST, NL = G::nl(PK);
   typedef const __attribute__((address_space(3))) uint32_t *lds_u32_ptr;
   // A (tr_b8), step s, row tile i: as for HL words, row tiles 0..3 at bytes 32 i of a stage row.
   // B, step s: stage rows 16 s + 8 (lane / 32) + e, e = 0..7, word 32 wave + lane % 32; the place of a
@@ -194,16 +201,23 @@ __device__ __forceinline__ void wgrad_tr_f32_multiply(const GemmArgs &a, char *l
 // conversion between them (general kernel: every word split by rounding in software, about 40 instructions
 // per word pair, behind register transposes).  700-128, T*B = 32768, with
 // the reduction: 47.6 -> 25.6 us.
-template <bool PK, bool F32, int NS>
+template <bool PK, bool F32, int NS, int TI>
 __device__ __forceinline__ void wgrad_tr_body(const GemmArgs &a, const int block, char *lds) {
-  typedef WgradTr<NS> G;
+  static_assert(TI == 2 || (TI == 4 && !F32), "fp32 words: 128 rows");
+  typedef WgradTr<NS, TI> G;
   constexpr int BM = G::BM, BN = G::BN, MT = G::MT;
-  constexpr int SP = G::SP, ST = G::ST, NL = G::NL;
+  constexpr int SP = G::SP, ST = G::ST, NL = G::nl(PK);
+  constexpr int SL = NL - 4;                           // load instructions of S
   // tile and split of this workgroup: as gemm_body
   const int ntiles = a.tiles_m * a.tiles_n;
   const int xcd = block & 7, slot = block >> 3;
   int tile, split;
-  if (a.splits == 1) {
+  if constexpr (TI == 4) {                             // any number of splits, as many workgroups on each XCD
+    const int flat = xcd * ((ntiles * a.splits + 7) >> 3) + slot;
+    split = flat / ntiles;
+    tile = flat - split * ntiles;
+    if (slot >= (ntiles * a.splits + 7) >> 3) return;
+  } else if (a.splits == 1) {
     tile = xcd * ((ntiles + 7) >> 3) + slot;
     split = 0;
   } else {
@@ -233,20 +247,29 @@ __device__ __forceinline__ void wgrad_tr_body(const GemmArgs &a, const int block
   // 2 (4 q + wave), + 1, lane -> row lane / 32, slot lane % 32 holding unit slot ^ 4 (row % 4).
   // PK: S rows are the stage's four samples (lanes 0..31 of wavefront 0 fetch them, natural order);
   // stage row rr of G is sample rr / 8 of the four at step rr % 8 of the eight: B rows apart per step.
-  int pv, qv[4];
+  int pv[SL], qv[4];
   int pk_tp = 0, pk_rem = 0;                           // PK: the next stage to issue starts at packed row pk_tp B + pk_rem
   if constexpr (PK) {
     pk_tp = (kbeg >> 3) / a.pk_B;
     pk_rem = (kbeg >> 3) - pk_tp * a.pk_B;
-    pv = wave == 0 && lane < 32 ? (lane >> 3) * a.ldp + row0 + 16 * (lane & 7) : OOB;
+    pv[0] = TI == 4 ? (wave == 0 ? (lane >> 4) * a.ldp + row0 + 16 * (lane & 15) : OOB)
+                    : wave == 0 && lane < 32 ? (lane >> 3) * a.ldp + row0 + 16 * (lane & 7) : OOB;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const int rr = 2 * (4 * q + wave) + (lane >> 5), uu = (lane & 31) ^ (4 * (rr & 3));
       qv[q] = (((rr & 7) * a.pk_B + (rr >> 3)) * a.ldq + col0 + 4 * uu) * 4;
     }
   } else {
-    const int r = 8 * wave + (lane >> 3), u = (lane & 7) ^ (r & 7);
-    pv = (kbeg + r) * a.ldp + row0 + 16 * u;
+    if constexpr (TI == 4) {
+#pragma unroll
+      for (int q = 0; q < SL; ++q) {
+        const int r = 4 * (4 * q + wave) + (lane >> 4), u = (lane & 15) ^ (2 * (r & 7));
+        pv[q] = (kbeg + r) * a.ldp + row0 + 16 * u;
+      }
+    } else {
+      const int r = 8 * wave + (lane >> 3), u = (lane & 7) ^ (r & 7);
+      pv[0] = (kbeg + r) * a.ldp + row0 + 16 * u;
+    }
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const int rr = 2 * (4 * q + wave) + (lane >> 5), uu = (lane & 31) ^ (4 * (rr & 3));
@@ -277,14 +300,14 @@ __device__ __forceinline__ void wgrad_tr_body(const GemmArgs &a, const int block
   auto issue_load = [&](const Issue &r, auto N) {
     constexpr int n = decltype(N)::value;
     if constexpr (PK) {
-      if constexpr (n == 0) load_to_lds_b128(r.p, r.dst, pv == OOB ? OOB : pv + r.pbase, 0);
+      if constexpr (n == 0) load_to_lds_b128(r.p, r.dst, pv[0] == OOB ? OOB : pv[0] + r.pbase, 0);
       else load_to_lds_b128(r.q, r.dst + SP + 4096 * (n - 1), qv[n - 1] + r.qbase, 0);
-    } else if constexpr (n == 0) {
-      load_to_lds_b128(r.p, r.dst, pv, 0);
-      pv += pstep;
+    } else if constexpr (n < SL) {
+      load_to_lds_b128(r.p, r.dst + 4096 * n, pv[n], 0);
+      pv[n] += pstep;
     } else {
-      load_to_lds_b128(r.q, r.dst + SP + 4096 * (n - 1), qv[n - 1], 0);
-      qv[n - 1] += qstep;
+      load_to_lds_b128(r.q, r.dst + SP + 4096 * (n - SL), qv[n - SL], 0);
+      qv[n - SL] += qstep;
     }
   };
   auto issue = [&](int kt_any, int buf) {
@@ -314,10 +337,6 @@ __device__ __forceinline__ void wgrad_tr_body(const GemmArgs &a, const int block
   };
   typedef std::integral_constant<int, 0> I0;
   typedef std::integral_constant<int, 1> I1;
-  typedef std::integral_constant<int, 2> I2;
-  typedef std::integral_constant<int, 3> I3;
-  typedef std::integral_constant<int, 4> I4;
-#define SNN_SLOT_END __builtin_amdgcn_sched_barrier(0)
 
   if constexpr (F32) {
     wgrad_tr_f32_multiply<PK, NS>(a, lds, lane, wave, row0, col0, split, nk, issue, issue_prepare, issue_load, convert);
@@ -332,22 +351,22 @@ __device__ __forceinline__ void wgrad_tr_body(const GemmArgs &a, const int block
   // Step, half and stage only add constants to the address (they leave row % 8 and row % 4 alone).
   // PK, A: the byte of sample 2 s + lane / 32 of the stage's four and channel 64 wm + 32 i + lane % 32.
   const int g = lane >> 4, j = lane & 15;
-  lds_char_ptr fa[2], fb[4];
+  lds_char_ptr fa[TI], fb[4];
   {
     lds_char_ptr base = (lds_char_ptr)lds;
     const int ra = 8 * (g >> 1) + (j >> 1), rb = 8 * (g >> 1) + (j >> 2);
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
-      fa[i] = PK ? base + (lane >> 5) * 128 + 64 * wm + 32 * i + (lane & 31)
-                 : base + ra * 128 + (((4 * wm + 2 * i + (g & 1)) ^ (ra & 7)) << 4) + 8 * (j & 1);
+    for (int i = 0; i < TI; ++i)
+      fa[i] = PK ? base + (lane >> 5) * BM + 32 * TI * wm + 32 * i + (lane & 31)
+                 : base + ra * BM + (((2 * TI * wm + 2 * i + (g & 1)) ^ ((TI / 2) * (ra & 7))) << 4) + 8 * (j & 1);
 #pragma unroll
     for (int t = 0; t < 4; ++t)
       fb[t] = base + SP + rb * 512 + ((16 * wn + 4 * (t ^ (rb & 3)) + 2 * (g & 1) + ((j >> 1) & 1)) << 4) + 8 * (j & 1);
   }
 
-  f32x16 acc[2][4];
+  f32x16 acc[TI][4];
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < TI; ++i)
 #pragma unroll
     for (int t = 0; t < 4; ++t)
 #pragma unroll
@@ -364,18 +383,15 @@ __device__ __forceinline__ void wgrad_tr_body(const GemmArgs &a, const int block
   // registers (slots 0..7), so that the fragment reads of the first step, issued in slots 0..3, are
   // back before their use in slot 8; the reads of the second step follow in slots 8..11.
   struct Pending {
-    bf16x8 af[2], bq[4];
+    bf16x8 af[TI], bq[4];
   };
-  auto read_a = [&](auto U, auto S, v2i32_t (&ar)[2]) {
-    constexpr int off = decltype(U)::value * ST + decltype(S)::value * (PK ? 256 : 2048);
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      if constexpr (PK) {
-        ar[i].x = *(const __attribute__((address_space(3))) unsigned char *)(fa[i] + off);
-        ar[i].y = 0;
-      } else {
-        ar[i] = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i32_ptr)(fa[i] + off));
-      }
+  auto read_a = [&](auto U, auto S, int i, v2i32_t &ar) {
+    constexpr int off = decltype(U)::value * ST + decltype(S)::value * (PK ? 2 * BM : 16 * BM);
+    if constexpr (PK) {
+      ar.x = *(const __attribute__((address_space(3))) unsigned char *)(fa[i] + off);
+      ar.y = 0;
+    } else {
+      ar = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i32_ptr)(fa[i] + off));
     }
   };
   auto read_b = [&](auto U, auto S, int t, bf16x8 &bq) {
@@ -393,34 +409,35 @@ __device__ __forceinline__ void wgrad_tr_body(const GemmArgs &a, const int block
 #pragma unroll
     for (int t = 0; t < 4; ++t)
 #pragma unroll
-      for (int i = 0; i < 2; ++i) mfma(x, t, i);
+      for (int i = 0; i < TI; ++i) mfma(x, t, i);
+  };
+  // The MFMAs of x with what the next step needs behind them: fragment reads of step S first, conversions last.
+  auto half = [&](auto U, auto S, const Pending &x, Pending &next, auto fetch) {
+    v2i32_t ar[TI];
+    static_for<4 * TI>([&](auto N) {
+      constexpr int n = decltype(N)::value;
+      mfma(x, n / TI, n % TI);
+      if constexpr (TI == 2 && n == 0) { read_a(U, S, 0, ar[0]); read_a(U, S, 1, ar[1]); }
+      if constexpr (TI == 4 && n < 4) read_a(U, S, n, ar[n]);
+      if constexpr (n < 4) read_b(U, S, n, next.bq[n]);
+      fetch(N);
+      if constexpr (n >= 3 * TI) next.af[n - 3 * TI] = convert(ar[n - 3 * TI]);
+      __builtin_amdgcn_sched_barrier(0);
+    });
   };
   auto stage = [&](auto U, int kt, Pending &pend) {
     constexpr int u = decltype(U)::value;
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NS - 2) * NL) : "memory");
     lds_barrier();
-    SNN_SLOT_END;
+    __builtin_amdgcn_sched_barrier(0);
     Pending now;
-    v2i32_t ar0[2], ar1[2];
-    const Issue ld = issue_prepare(kt + NS - 1, (u + NS - 1) % NS);
-    mfma(pend, 0, 0); read_a(U, I0(), ar0); read_b(U, I0(), 0, now.bq[0]); SNN_SLOT_END;
-    mfma(pend, 0, 1); read_b(U, I0(), 1, now.bq[1]); issue_load(ld, I0()); SNN_SLOT_END;
-    mfma(pend, 1, 0); read_b(U, I0(), 2, now.bq[2]); issue_load(ld, I1()); SNN_SLOT_END;
-    mfma(pend, 1, 1); read_b(U, I0(), 3, now.bq[3]); issue_load(ld, I2()); SNN_SLOT_END;
-    mfma(pend, 2, 0); issue_load(ld, I3()); SNN_SLOT_END;
-    mfma(pend, 2, 1); issue_load(ld, I4()); SNN_SLOT_END;
-    mfma(pend, 3, 0); now.af[0] = convert(ar0[0]); SNN_SLOT_END;
-    mfma(pend, 3, 1); now.af[1] = convert(ar0[1]); SNN_SLOT_END;
-    mfma(now, 0, 0); read_a(U, I1(), ar1); read_b(U, I1(), 0, pend.bq[0]); SNN_SLOT_END;
-    mfma(now, 0, 1); read_b(U, I1(), 1, pend.bq[1]); SNN_SLOT_END;
-    mfma(now, 1, 0); read_b(U, I1(), 2, pend.bq[2]); SNN_SLOT_END;
-    mfma(now, 1, 1); read_b(U, I1(), 3, pend.bq[3]); SNN_SLOT_END;
-    mfma(now, 2, 0); SNN_SLOT_END;
-    mfma(now, 2, 1); SNN_SLOT_END;
-    mfma(now, 3, 0); pend.af[0] = convert(ar1[0]); SNN_SLOT_END;
-    mfma(now, 3, 1); pend.af[1] = convert(ar1[1]); SNN_SLOT_END;
+    const auto ld = issue_prepare(kt + NS - 1, (u + NS - 1) % NS);
+    constexpr int F0 = TI == 2 ? 1 : 4;                 // the slot of the first load
+    half(U, I0(), pend, now, [&](auto N) {
+      if constexpr (decltype(N)::value >= F0 && decltype(N)::value < F0 + NL) issue_load(ld, std::integral_constant<int, decltype(N)::value - F0>());
+    });
+    half(U, I1(), now, pend, [](auto) {});
   };
-#undef SNN_SLOT_END
 
 #pragma unroll
   for (int t = 0; t < NS - 1; ++t) issue(t, t);
@@ -428,7 +445,7 @@ __device__ __forceinline__ void wgrad_tr_body(const GemmArgs &a, const int block
   {
     const u32x4 z = {0u, 0u, 0u, 0u};
 #pragma unroll
-    for (int i = 0; i < 2; ++i) pend.af[i] = __builtin_bit_cast(bf16x8, z);
+    for (int i = 0; i < TI; ++i) pend.af[i] = __builtin_bit_cast(bf16x8, z);
 #pragma unroll
     for (int t = 0; t < 4; ++t) pend.bq[t] = __builtin_bit_cast(bf16x8, z);
   }
@@ -449,7 +466,7 @@ __device__ __forceinline__ void wgrad_tr_body(const GemmArgs &a, const int block
   // column tile t + 1 (both lanes of a pair hold both sums).  The spikes entered as 2.0: halved here.
   float *C = a.C + (size_t)split * a.c_split_stride;
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < TI; ++i)
 #pragma unroll
     for (int tp = 0; tp < 4; tp += 2)
 #pragma unroll
@@ -457,7 +474,7 @@ __device__ __forceinline__ void wgrad_tr_body(const GemmArgs &a, const int block
         const float x0 = acc[i][tp][r], x1 = acc[i][tp + 1][r];
         const float s0 = x0 + __shfl_xor(x0, 1), s1 = x1 + __shfl_xor(x1, 1);
         const float v = 0.5f * ((lane & 1) ? s1 : s0);
-        const int row = row0 + 64 * wm + 32 * i + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+        const int row = row0 + 32 * TI * wm + 32 * i + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
         const int col = col0 + 64 * wn + 16 * (tp + (lane & 1)) + ((lane & 31) >> 1);
         if (row < a.rows && col < a.cols) {
           const size_t o = (size_t)row * a.ldc + col;
@@ -470,22 +487,32 @@ __device__ __forceinline__ void wgrad_tr_body(const GemmArgs &a, const int block
 // The weight-gradient jobs; a job's S may be the raster packed along time.
 // NS: stages in flight.  3 (60 KiB) lets two workgroups share a compute unit.  More do not help, not even
 // a launch of one workgroup per compute unit (700-128-128-20, T*B = 32768, 256 workgroups: 18.1 us with
-// 3, 18.3 with 4, 19.6 with 6): the latency of the loads is covered.
-template <bool F32, int NS>
-__global__ __launch_bounds__(256, 2) void wgrad_tr_jobs_kernel(const GemmJobs jobs) {
-  static_assert(WgradTr<NS>::LDS_BYTES <= 163840, "LDS of a compute unit");
-  __shared__ __attribute__((aligned(16))) char lds[WgradTr<NS>::LDS_BYTES];
+// 3, 18.3 with 4, 19.6 with 6): the latency of the loads is covered.  Nor tall tiles (3, 4, 5, 6 stages: 700-1024-1024-20,
+// T*B = 131072 665, 677, 682, 690).
+template <bool F32, int NS, int TI>
+__global__ __launch_bounds__(256, TI == 2 ? 2 : 1) void wgrad_tr_jobs_kernel(const GemmJobs jobs) {
+  static_assert(WgradTr<NS, TI>::LDS_BYTES <= 163840, "LDS of a compute unit");
+  __shared__ __attribute__((aligned(16))) char lds[WgradTr<NS, TI>::LDS_BYTES];
   int j = 0;
   while (j + 1 < jobs.njobs && (int)blockIdx.x >= jobs.first_block[j + 1]) ++j;
-  if (jobs.job[j].packed) wgrad_tr_body<true, F32, NS>(jobs.job[j], blockIdx.x - jobs.first_block[j], lds);
-  else wgrad_tr_body<false, F32, NS>(jobs.job[j], blockIdx.x - jobs.first_block[j], lds);
+  if (jobs.job[j].packed) wgrad_tr_body<true, F32, NS, TI>(jobs.job[j], blockIdx.x - jobs.first_block[j], lds);
+  else wgrad_tr_body<false, F32, NS, TI>(jobs.job[j], blockIdx.x - jobs.first_block[j], lds);
 }
 
-static hipError_t wgrad_tr_jobs_launch(const GemmJobs &jobs, bool f32, hipStream_t st) {
+// Adds a job of tall tiles: as many workgroups on each XCD, for any number of splits.
+static void wgrad_tr_tall_add(GemmJobs &jobs, GemmArgs a, int splits) {
+  const int j = jobs.njobs++;
+  gemm_prepare<2, 2, 4, 2>(a, splits);
+  jobs.job[j] = a;
+  jobs.first_block[j + 1] = jobs.first_block[j] + (a.tiles_m * a.tiles_n * splits + 7) / 8 * 8;
+}
+
+static hipError_t wgrad_tr_jobs_launch(const GemmJobs &jobs, bool f32, bool tall, hipStream_t st) {
   if (jobs.njobs == 0) return hipSuccess;
   dim3 grid(jobs.first_block[jobs.njobs], 1, 1);
-  if (f32) hipLaunchKernelGGL((wgrad_tr_jobs_kernel<true, 3>), grid, dim3(256), 0, st, jobs);
-  else hipLaunchKernelGGL((wgrad_tr_jobs_kernel<false, 3>), grid, dim3(256), 0, st, jobs);
+  if (f32) hipLaunchKernelGGL((wgrad_tr_jobs_kernel<true, 3, 2>), grid, dim3(256), 0, st, jobs);
+  else if (tall) hipLaunchKernelGGL((wgrad_tr_jobs_kernel<false, 3, 4>), grid, dim3(256), 0, st, jobs);
+  else hipLaunchKernelGGL((wgrad_tr_jobs_kernel<false, 3, 2>), grid, dim3(256), 0, st, jobs);
   return hipGetLastError();
 }
 

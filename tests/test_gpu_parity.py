@@ -436,6 +436,49 @@ def test_weight_gradients_through_transposing_reads(T, B, sizes, rec, packed):
         assert np.abs(a - b).max() <= 1e-5 * np.abs(b).max() + 1e-30
 
 
+@pytest.mark.parametrize("T,B,sizes,rec,packed", [(130, 130, (700, 1024, 1000, 20), (False, False), False),
+                                                   (125, 136, (513, 768, 1030, 40), (False, False), True),
+                                                   (128, 129, (260, 1000, 10), (True,), False),
+                                                   (250, 264, (700, 512, 512, 20), (False, False), False)],
+                         ids=["several-splits", "packed-ragged", "recurrent", "eleven-splits"])
+def test_weight_gradients_on_tall_tiles(T, B, sizes, rec, packed):
+    """Products large enough for tiles of 256 x 128 (wgrad_tall_pays): rows, columns and contraction tails that fill no
+    tile, split counts that are no multiple of eight, a packed layer-1 job, dR beside dW.  On the device's own spikes and
+    current gradients, in 64 bits."""
+    import torch
+    L = len(sizes) - 1
+    wl = workloads.Workload(name="wgrad-tall", index=29, T=T, B=B, sizes=sizes, recurrent=rec,
+                            beta=(0.9, 0.93, 0.95)[:L], theta=1.0, surrogate="superspike", slope=10.0, precision="bf16",
+                            rate_lo=0.03, rate_hi=0.12, loss="max")
+    inp = workloads.generate(wl, w_gain=1.5 if any(rec) else 3.0)
+    snn = make(wl, inp, {})
+    if packed:
+        snn.forward_packed(np.packbits(inp.X, axis=0), inp.labels)
+    else:
+        snn.forward(inp.X, inp.labels)
+    snn.backward()
+    M = T * B
+
+    def check(S, G, dW):
+        S, G = (torch.from_numpy(np.ascontiguousarray(a)).cuda().reshape(M, -1).double() for a in (S, G))
+        ref, mag = S.T @ G, S.T @ G.abs()
+        err = torch.from_numpy(dW).cuda().double() - ref
+        # exact products (a word is hi + lo); M additions of 2^-24 of the sum of the terms' sizes at most, and of the
+        # root of their number where the roundings are independent (a tenth of 66000 rows: 5e-6)
+        assert (err.abs() <= M * 2.0 ** -24 * mag + 1e-30).all()
+        assert err.norm() <= 1e-5 * ref.norm()
+        assert ref.abs().max() > 0
+    below = inp.X
+    for l in range(L):
+        G = snn.get_tensor("d_current", l + 1) if l < L - 1 else snn.get_tensor("d_readout_current")
+        check(below, G, snn.get_tensor("grad_w", l + 1))
+        if l < L - 1:
+            below = snn.get_tensor("spikes", l + 1)
+            if rec[l]:
+                check(below, G, snn.get_tensor("grad_r", l + 1))
+    snn.destroy()
+
+
 @pytest.mark.parametrize("T,B,sizes,precision,packed", [(32, 16, (100, 64, 10), "fp32", False),
                                                           (5, 3, (12, 40, 3), "fp32", False),
                                                           (33, 5, (203, 130, 70, 11), "fp32", False),
