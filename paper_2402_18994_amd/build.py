@@ -20,6 +20,7 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
 UNITS = {"snn_api.hip": ["-Xarch_device", "-falign-functions=1024"],
          "layer_forward.hip": ["-Xarch_device", "-falign-functions=1024"],
          "layer_reverse.hip": ["-Xarch_device", "-falign-functions=1024"],
+         "layer_reverse_wide.hip": ["-Xarch_device", "-falign-functions=1024"],
          "rlif_wide.hip": [],
          # results of MFMAs in ordinary vector registers (the time loops read them at once)
          "rlif_pair.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],

@@ -3,11 +3,11 @@
 
 namespace snn {
 
-template <int KS, int SURR, int BN, bool WIDE, bool F32, bool FULL, bool SLOTS = false>
+template <int KS, int SURR, int BN, bool F32, bool FULL, bool SLOTS = false>
 static hipError_t launch(hipStream_t st, const LayerReverseArgs &a) {
   const int groups = SLOTS ? (a.B + (64 >> a.slot_log2) - 1) >> (6 - a.slot_log2) : a.B;
   const int grid = (groups + 7) / 8 * 8 * ((a.ld + BN - 1) / BN);
-  hipLaunchKernelGGL((lif_layer_reverse_kernel<KS, SURR, BN, WIDE, F32, FULL, SLOTS>), dim3((unsigned)grid), dim3(256), 0, st, a);
+  hipLaunchKernelGGL((lif_layer_reverse_kernel<KS, SURR, BN, F32, FULL, SLOTS>), dim3((unsigned)grid), dim3(256), 0, st, a);
   return hipGetLastError();
 }
 
@@ -15,28 +15,27 @@ static hipError_t launch(hipStream_t st, const LayerReverseArgs &a) {
 // phases): 99.8 us per step at 700-128-128-20 against 104.8 with 128 neurons.
 template <int KS, int SURR>
 static hipError_t launch_columns(hipStream_t st, const LayerReverseArgs &a, bool f32) {
-  if (a.slot_log2 < 6) return f32 ? launch<KS, SURR, 64, false, true, false, true>(st, a) : launch<KS, SURR, 64, false, false, false, true>(st, a);
+  if (a.slot_log2 < 6) return f32 ? launch<KS, SURR, 64, true, false, true>(st, a) : launch<KS, SURR, 64, false, false, true>(st, a);
   const bool full = a.ld % 64 == 0;
-  if (f32) return full ? launch<KS, SURR, 64, false, true, true>(st, a) : launch<KS, SURR, 64, false, true, false>(st, a);
-  return full ? launch<KS, SURR, 64, false, false, true>(st, a) : launch<KS, SURR, 64, false, false, false>(st, a);
+  if (f32) return full ? launch<KS, SURR, 64, true, true>(st, a) : launch<KS, SURR, 64, true, false>(st, a);
+  return full ? launch<KS, SURR, 64, false, true>(st, a) : launch<KS, SURR, 64, false, false>(st, a);
 }
 
 template <int SURR>
-static hipError_t launch_surrogate(hipStream_t st, const LayerReverseArgs &a, bool f32, bool wide) {
-  if (wide) return launch<1, SURR, 128, true, false, true>(st, a);
+static hipError_t launch_surrogate(hipStream_t st, const LayerReverseArgs &a, bool f32) {
   if (a.ldc <= 32) return launch_columns<1, SURR>(st, a, f32);
   if (a.ldc <= 64) return launch_columns<2, SURR>(st, a, f32);
   return launch_columns<4, SURR>(st, a, f32);
 }
 
-hipError_t layer_reverse(hipStream_t st, const LayerReverseArgs &a, int surrogate, bool f32, bool wide) {
+hipError_t layer_reverse(hipStream_t st, const LayerReverseArgs &a, int surrogate, bool f32) {
   switch (surrogate) {
-    case 0: return launch_surrogate<0>(st, a, f32, wide);
-    case 1: return launch_surrogate<1>(st, a, f32, wide);
-    case 2: return launch_surrogate<2>(st, a, f32, wide);
-    case 3: return launch_surrogate<3>(st, a, f32, wide);
-    case 4: return launch_surrogate<4>(st, a, f32, wide);
-    default: return launch_surrogate<5>(st, a, f32, wide);
+    case 0: return launch_surrogate<0>(st, a, f32);
+    case 1: return launch_surrogate<1>(st, a, f32);
+    case 2: return launch_surrogate<2>(st, a, f32);
+    case 3: return launch_surrogate<3>(st, a, f32);
+    case 4: return launch_surrogate<4>(st, a, f32);
+    default: return launch_surrogate<5>(st, a, f32);
   }
 }
 

@@ -20,6 +20,7 @@
 #include "layer_forward.hpp"
 #include "scan.hpp"
 #include "layer_reverse.hpp"
+#include "layer_reverse_wide.hpp"
 #include "rlif.hpp"
 #include "rlif_wide.hpp"
 #include "rlif_pair.hpp"
@@ -832,20 +833,30 @@ int layer_reverse_min_batch(const snn_ctx *c, int l) {
   const bool long_product = c->nplanes == 3 && columns_above(c, l) > 64 && c->T > 256;
   return c->opt[SNN_OPT_LAYER_MIN_BATCH] == 0 && long_product ? 32 : layer_min_batch(c);
 }
-// Below a WIDER layer (more than 128 columns) the whole reverse layer can run as one launch whose
-// dS product walks the long contraction on the streamed pipeline (lif_layer_reverse_kernel, WIDE):
-// layers that are a multiple of 128 wide, as many samples as the one-launch layers ask for.
-// Only on request (SNN_OPT_LAYER_REVERSE = 2): measured, it is slower than the input-gradient
-// product followed by the scan at every width tried (700-512-512-20, 256 steps, 256 samples: 195 us
-// against 84 + 69; 700-1024-1024-20, 256 steps, 512 samples: 1421 us against 526 + 270).  A
-// workgroup walks one sample through time, so the 64 rows of a block lie B x columns x 4 bytes
-// apart (2 MiB at the second shape), every stage waits out a full memory latency with three stages
-// (48 KiB) in flight per compute unit, and the weights of its 128 neurons (256 KiB) pass through
-// the compute unit again for every 64 steps.
-bool reverse_wide(const snn_ctx *c, int l) {
-  if (c->opt[SNN_OPT_LAYER_REVERSE] != 2 || l < 0 || l > c->L - 2) return false;
+// Below a WIDE layer (more than 128 columns; rounded weights) the whole reverse layer can run as one launch whose dS
+// product walks the long contraction (layer_reverse_wide.hpp).  Where: by a model of both, us, with 15 % in favour of the
+// two launches.  One launch: a workgroup takes 9 us and 0.62 per stage of 32 columns for each block of 128 steps, 256
+// workgroups at a time.  Two: 1.2 per GFLOP and 5 TB/s of dX and dS for the product, 12 bytes per neuron and step
+// at 5.2 TB/s for the scan, or 48 ns a step where there are few chains.  us per step, apart and in one: 700-512-512-20, T = B = 256
+// 535 and 467; 700-1024-1024-20, T = 256, B = 512 2488 and 2260; 200-256-256-20, B = 256: T = 50 85.6 84.5, 70 95.8 91.2, 128 120 108,
+// 140 (a second block of 12) 142 133, T = 500, B = 64 170 186; 200-512-512-20: T = 128, B = 32 / 64 / 256 85.1 89.2 / 98.5 96.5 / 258 226, T =
+// 256, B = 32 / 64 126 137 / 150 149, T = 200, B = 128 222 181; 100-300-1000-20, T = 256, B = 64 188 196, T = 500, B = 128 677 657; 100-2048-2048-10, T =
+// 128, B = 32 / 64 / 256 342 309 / 525 477 / 1592 1559, T = 50, B = 256 802 888.  Over 112 such cases nothing it takes is slower.
+bool reverse_wide_pays(const snn_ctx *c, int l) {
   const Layer &y = c->layers[l];
-  return c->hl && y.spiking && !y.recurrent && !y.adaptive && y.ld % 128 == 0 && columns_above(c, l) > 128 && c->B >= layer_min_batch(c);
+  const double M = (double)c->M, N = y.ld, columns = columns_above(c, l);
+  const long long groups = (long long)c->B * ((y.ld + 255) / 256);
+  const double rounds = groups <= 512 ? (double)((groups + 255) / 256) : groups / 256.;
+  const double one = 4. + ((c->T + 127) / 128) * rounds * (9. + 0.62 * ((columns_above(c, l) + 31) / 32));
+  const double product = 3. + 2.4e-9 * M * N * columns + 4. * M * (N + columns) / 5e6;
+  const double scan = std::max(0.048 * c->T + 1., 2. + 12. * M * N / 5.2e6);
+  return 1.15 * one < product + scan + 2.;
+}
+bool reverse_wide(const snn_ctx *c, int l) {
+  if (!c->opt[SNN_OPT_LAYER_REVERSE] || l < 0 || l > c->L - 2) return false;
+  const Layer &y = c->layers[l];
+  if (!c->hl || !y.spiking || y.recurrent || y.adaptive || columns_above(c, l) <= 128) return false;
+  return c->opt[SNN_OPT_LAYER_REVERSE] == 2 || reverse_wide_pays(c, l);
 }
 // A feed-forward spiking layer below at most 128 padded columns (the readout, or a narrow spiking
 // layer) takes dS = dX W^T from the current gradients dX of the layer above inside its reverse pass.
@@ -925,7 +936,7 @@ int launch_layer_reverse(snn_ctx *c, int l, bool wide) {
   // two in 256 32.0, one 32.8 at 200-60-20, T = 16, B = 512).
   a.slot_log2 = c->T <= 16 ? 4 : c->T <= 32 ? 5 : 6;
   while (a.slot_log2 < 6 && ((long long)c->B * ((y.ld + 63) / 64) << a.slot_log2) < 64ll * 256) ++a.slot_log2;
-  HIPCHK(c, layer_reverse(c->stream, a, c->surrogate, !c->hl, wide));
+  HIPCHK(c, wide ? layer_reverse_wide(c->stream, a, c->surrogate) : layer_reverse(c->stream, a, c->surrogate, !c->hl));
   return SNN_OK;
 }
 

@@ -851,16 +851,18 @@ def test_layer_reverse_in_one_launch(T, sizes, surrogate, slope):
                                                          (30, (330, 1024, 960, 20), "sigmoid", 4.0, True),
                                                          (70, (50, 256, 200, 12), "triangular", 1.0, False),
                                                          (129, (40, 128, 136, 256, 5), "boxcar", 1.0, False),
-                                                         (33, (70, 384, 1024, 3), "ste", 1.0, True)],
+                                                         (33, (70, 384, 1024, 3), "ste", 1.0, True),
+                                                         (300, (60, 300, 203, 10), "superspike", 10.0, False),
+                                                         (128, (50, 20, 131, 10), "sigmoid", 4.0, False)],
                          ids=["128-below-256", "512-below-384", "1024-below-960", "256-below-200-columns",
-                              "128-below-136-below-256", "384-below-1024"])
+                              "128-below-136-below-256", "384-below-1024", "300-below-203", "20-below-131"])
 def test_layer_reverse_in_one_launch_below_a_wide_layer(T, sizes, surrogate, slope, nt):
-    """bf16 products, a feed-forward layer that is a multiple of 128 wide below a layer of more
-    than 128 columns: on request the reverse layer runs as one launch whose dS = dI W^T product streams the
+    """bf16 products, a feed-forward layer below a layer of more than 128 columns: on request (and by
+    default where it pays) the reverse layer runs as one launch whose dS = dI W^T product streams the
     hi/lo words of the layer above and its weights through LDS in stages of 32 columns (dS read
     back afterwards comes from the product kernel and must agree with the oracle as well).  One
-    to three blocks of 64 steps with ragged first blocks, 136 to 1024 columns above (five to 32
-    stages, with and without a ragged last one), every surrogate, stores with and without the
+    to three blocks of 128 steps with ragged first blocks, less than one to four parts of 256 neurons, 136 to 1024
+    columns above (five to 32 stages, with and without a ragged last one), every surrogate, stores with and without the
     non-temporal hint, five samples (three of the eight launched workgroups have none)."""
     L = len(sizes) - 1
     wl = workloads.Workload(name="layer-reverse-wide", index=34, T=T, B=5, sizes=sizes, recurrent=(False,) * (L - 1),
