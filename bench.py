@@ -133,9 +133,27 @@ def forward_chain(wl, layer):
     return chain, top == L - 1 and joins(top) and pad8(wl.sizes[L]) <= 32
 
 
+def reverse_wide(wl, layer):
+    """Whether the reverse pass of text layer `layer`, feed-forward on rounded weights and below more than 128 columns or
+    adaptive, runs as one launch: the library's estimate of its time (us) against that of product and scan."""
+    if not (1 <= layer < len(wl.sizes) - 1):
+        return False
+    n, above, rows = pad8(wl.sizes[layer]), pad8(wl.sizes[layer + 1]), wl.T * wl.B
+    a = adaptive(wl, layer)
+    if wl.precision != "bf16" or wl.recurrent[layer - 1] or (above <= 128 and not a):
+        return False
+    groups = wl.B * -(-n // 256)
+    rounds = -(-groups // 256) if groups <= 512 else groups / 256
+    one = 4 + -(-wl.T // 128) * rounds * ((12 if a else 9) + 0.62 * -(-above // 32))
+    product = 3 + 2.4e-9 * rows * n * above + 4 * rows * (n + above) / 5e6
+    scan = max(0.062 * wl.T + 2, 2 + 16 * rows * n / 5.2e6) if a else max(0.048 * wl.T + 1, 2 + 12 * rows * n / 5.2e6)
+    return 1.15 * one < product + scan + 2
+
+
 def reverse_forms_ds(wl, layer):
     """Whether the reverse launch of text layer `layer` forms dS from the current gradients above itself
-    (feed-forward, at most 128 padded columns above; up to 1024 neurons, or any multiple of 64 on rounded weights)."""
+    (feed-forward, at most 128 padded columns above; up to 1024 neurons, or any multiple of 64 on rounded weights).
+    Below wider layers, and with adaptive thresholds: reverse_wide."""
     L = len(wl.sizes) - 1
     if not (1 <= layer < L) or wl.recurrent[layer - 1] or adaptive(wl, layer) or pad8(wl.sizes[layer + 1]) > 128:
         return False
@@ -172,7 +190,7 @@ def algorithmic_bytes(wl, kernel, layer, packed=False):
     if kernel == "weight_grad" and layer == 0:   # the merged launch: every layer's spikes below, dI and dW (+ dR)
         return sum(algorithmic_bytes(wl, kernel, l, packed) for l in range(1, L + 1))
     n_in, n_out = wl.sizes[layer - 1], wl.sizes[layer]
-    fused_rev = reverse_forms_ds(wl, layer)
+    fused_rev = reverse_forms_ds(wl, layer) or reverse_wide(wl, layer)
     fused_fwd = top_scan_forms_currents(wl, layer)
     state = 4 if layer < L and adaptive(wl, layer) else 0        # the adaptation, beside V
     chain, with_readout = forward_chain(wl, layer)
@@ -221,7 +239,7 @@ def method_flops(wl, kernel, layer):
             f += 2 * M * n_out * wl.sizes[L]
         return f
     if kernel == "lif_reverse":
-        return 2 * M * n_out * wl.sizes[layer + 1] if reverse_forms_ds(wl, layer) else 0
+        return 2 * M * n_out * wl.sizes[layer + 1] if reverse_forms_ds(wl, layer) or reverse_wide(wl, layer) else 0
     if kernel in ("current_gemm", "input_grad"):
         return 2 * M * n_in * n_out
     if kernel == "weight_grad":

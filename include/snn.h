@@ -216,8 +216,9 @@ typedef enum {
  *   LAYER_REVERSE     1 (default): the reverse pass of a layer below a layer of at most 128 columns
  *                     runs as one launch (dS product, surrogate, scan; dS is not stored): up to 1024
  *                     neurons, or 256 where TOP_SCANS has a kernel for it (rounded weights, a
- *                     multiple of 64 neurons); below a wider layer (rounded weights) where it is the
- *                     faster form by a rule on the sizes; 2: there always; 0: off
+ *                     multiple of 64 neurons); below a wider layer, or of a layer with adaptive thresholds
+ *                     (rounded weights), where it is the faster form by a rule on the sizes; 2: there
+ *                     always; 0: off
  *   TOP_SCANS         1 (default): the scans of a layer below at most 128 columns form the
  *                     narrow products themselves (readout currents forward, dS reverse); 0: off
  *   DEFER_REDUCE      1 (default): snn_backward leaves the per-split partial sums of the weight

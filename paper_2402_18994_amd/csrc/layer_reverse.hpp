@@ -49,6 +49,8 @@ struct LayerReverseArgs {
   int T, B, ld;
   int nt_store;            // dI streams past the caches
   int slot_log2;           // 6: a block of 64 steps is one sample's; 4 or 5: slots of 16 or 32 steps
+  const float *A;          // layer_reverse_wide: adaptation in force at each step [T*B][ld], its decay and its rise per spike, or NULL
+  float gamma, kappa;
 };
 hipError_t layer_reverse(hipStream_t st, const LayerReverseArgs &a, int surrogate, bool f32);
 

@@ -5,9 +5,11 @@ namespace snn {
 
 template <int SURR>
 static hipError_t launch(hipStream_t st, const LayerReverseArgs &a) {
-  const int grid = (a.B + 7) / 8 * 8 * ((a.ld + ReverseWide::BN - 1) / ReverseWide::BN);
-  if (a.nt_store) hipLaunchKernelGGL((lif_layer_reverse_wide_kernel<SURR, NT>), dim3((unsigned)grid), dim3(256), 0, st, a);
-  else hipLaunchKernelGGL((lif_layer_reverse_wide_kernel<SURR, 0>), dim3((unsigned)grid), dim3(256), 0, st, a);
+  const dim3 grid((unsigned)((a.B + 7) / 8 * 8 * ((a.ld + ReverseWide::BN - 1) / ReverseWide::BN)));
+#define SNN_LRW(POL, AD) hipLaunchKernelGGL((lif_layer_reverse_wide_kernel<SURR, POL, AD>), grid, dim3(256), 0, st, a)
+  if (a.A) { if (a.nt_store) SNN_LRW(NT, true); else SNN_LRW(0, true); }
+  else { if (a.nt_store) SNN_LRW(NT, false); else SNN_LRW(0, false); }
+#undef SNN_LRW
   return hipGetLastError();
 }
 

@@ -1,6 +1,6 @@
 // Reverse pass of a feed-forward LIF layer below a WIDE layer (more than 128 columns) in one launch: the spike gradients
 // dS = dX W^T, the surrogate, the reverse scan, dI stored as hi/lo words (rounded weights; see layer_reverse.hpp for
-// narrow layers above).  dS never reaches memory.
+// narrow layers above).  dS never reaches memory.  ADAPT: a layer with adaptive thresholds, below any layer.
 //
 // As two launches the product writes dS and the scan reads it back, 8 bytes per neuron and step, where the pass cannot do
 // without 12 (dX, V, dI).  A workgroup owns one sample and 256 neurons; per block of 128 steps, last block first:
@@ -33,7 +33,7 @@ struct ReverseWide {
   static_assert(LDS_BYTES == 81920 && 64 * PITCH * 4 <= LDS_BYTES, "two workgroups per compute unit");
 };
 
-template <int SURR, int POL>
+template <int SURR, int POL, bool ADAPT>
 __global__ __launch_bounds__(256, 2) void lif_layer_reverse_wide_kernel(const LayerReverseArgs a) {
   typedef ReverseWide G;
   constexpr int BM = G::BM, BN = G::BN, PB = G::PB, QB = G::QB;
@@ -138,9 +138,10 @@ __global__ __launch_bounds__(256, 2) void lif_layer_reverse_wide_kernel(const La
   // State of neuron n0 + tid.
   const bool mine = n0 + tid < a.ld;
   const float beta = mine ? a.beta_v[n0 + tid] : 0.f, theta = a.theta, slope = a.slope;
-  float g = 0.f, db = 0.f;
+  float g = 0.f, ga = 0.f, db = 0.f;                   // (ga: gradient of the adaptation, see lif_reverse_kernel)
   const unsigned vbytes = (unsigned)a.T * a.B * a.ld * 4u;
   const rsrc_t rV = make_rsrc(a.V, vbytes), rdI = make_rsrc(a.dI, vbytes);
+  const rsrc_t rA = make_rsrc(a.A, ADAPT ? vbytes : 0u);
   const int row4 = a.B * a.ld * 4, vo = mine ? (b * a.ld + n0 + tid) * 4 : OOB;
   const float *const cell = (const float *)lds + tid;
 
@@ -174,16 +175,21 @@ __global__ __launch_bounds__(256, 2) void lif_layer_reverse_wide_kernel(const La
     static_for<5>([&](auto U) {
       if (kt + decltype(U)::value < nk) stage(U, kt + decltype(U)::value, pend);
     });
-    // The potentials of the first 32 steps are asked for under the last MFMAs, and those 32 steps on as steps are taken.
-    float v[2][16];
-    auto fetch = [&](float (&v)[16], int t) {          // steps t .. t + 15 (past T: zeros)
+    // The potentials of the first 32 steps (16, with their adaptation) are asked for under the last MFMAs, and those as many
+    // steps on as steps are taken.
+    constexpr int U = ADAPT ? 8 : 16;
+    struct Rows { float v[U], a[ADAPT ? U : 1]; } rows[2];
+    auto fetch = [&](Rows &x, int t) {                 // steps t .. t + U - 1 (past T: zeros)
 #pragma unroll
-      for (int s = 0; s < 16; ++s)
-        v[s] = __uint_as_float(ld_b32<POL>(rV, t >= 0 && t + s < a.T ? vo : OOB, min(max(t + s, 0), a.T - 1) * row4));
+      for (int s = 0; s < U; ++s) {
+        const int off = t >= 0 && t + s < a.T ? vo : OOB, so = min(max(t + s, 0), a.T - 1) * row4;
+        x.v[s] = __uint_as_float(ld_b32<POL>(rV, off, so));
+        if (ADAPT) x.a[ADAPT ? s : 0] = __uint_as_float(ld_b32<POL>(rA, off, so));
+      }
     };
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // (the stage loads beyond the range have written their zeros)
 #pragma unroll
-    for (int k = 1; k >= 0; --k) fetch(v[k], t0 + BM - 32 + 16 * k);
+    for (int k = 1; k >= 0; --k) fetch(rows[k], t0 + BM - 2 * U + U * k);
 #pragma unroll
     for (int n = 0; n < 16; ++n)
       acc[(n & 7) >> 1][n & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
@@ -206,24 +212,31 @@ __global__ __launch_bounds__(256, 2) void lif_layer_reverse_wide_kernel(const La
             }
       }
       lds_barrier();
-      auto steps = [&](const float (&v)[16], int s0) { // steps s0 + 15 .. s0 of the half
+      auto steps = [&](const Rows &x, int s0) {        // steps s0 + U - 1 .. s0 of the half
         const int t = t0 + 64 * hf + s0;
         if (t >= a.T) return;
-        float ds[16];
+        float ds[U];
 #pragma unroll
-        for (int s = 0; s < 16; ++s) ds[s] = cell[(s0 + s) * G::PITCH];
+        for (int s = 0; s < U; ++s) ds[s] = cell[(s0 + s) * G::PITCH];
 #pragma unroll
-        for (int s = 15; s >= 0; --s) {
+        for (int s = U - 1; s >= 0; --s) {
           __builtin_amdgcn_raw_buffer_store_b32(pack_hl(g), rdI, t + s < a.T ? vo : OOB, min(t + s, a.T - 1) * row4, POL);
-          db = __builtin_fmaf(g, v[s], db);
-          g = beta * g + surr_rcp<SURR>(slope, v[s] - theta) * (ds[s] - theta * g);
+          db = __builtin_fmaf(g, x.v[s], db);
+          if constexpr (ADAPT) {
+            const float thr = theta + x.a[s], y = x.v[s] - thr;
+            const float sq = surr_rcp<SURR>(slope, y) * (ds[s] - thr * g + a.kappa * ga);
+            ga = a.gamma * ga - (y > 0.f ? g : 0.f) - sq;
+            g = beta * g + sq;
+          } else {
+            g = beta * g + surr_rcp<SURR>(slope, x.v[s] - theta) * (ds[s] - theta * g);
+          }
         }
       };
       const int t = t0 + 64 * hf;
 #pragma unroll
-      for (int k = 3; k >= 0; --k) {
-        steps(v[k & 1], 16 * k);
-        if (hf || k >= 2) fetch(v[k & 1], t - 32 + 16 * k);
+      for (int k = 64 / U - 1; k >= 0; --k) {
+        steps(rows[k & 1], U * k);
+        if (hf || k >= 2) fetch(rows[k & 1], t + U * (k - 2));
       }
       lds_barrier();                                   // the rows are read before the next ones, or the next block's stages, land
     });

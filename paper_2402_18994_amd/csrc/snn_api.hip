@@ -842,20 +842,24 @@ int layer_reverse_min_batch(const snn_ctx *c, int l) {
 // 140 (a second block of 12) 142 133, T = 500, B = 64 170 186; 200-512-512-20: T = 128, B = 32 / 64 / 256 85.1 89.2 / 98.5 96.5 / 258 226, T =
 // 256, B = 32 / 64 126 137 / 150 149, T = 200, B = 128 222 181; 100-300-1000-20, T = 256, B = 64 188 196, T = 500, B = 128 677 657; 100-2048-2048-10, T =
 // 128, B = 32 / 64 / 256 342 309 / 525 477 / 1592 1559, T = 50, B = 256 802 888.  Over 112 such cases nothing it takes is slower.
+// Adaptive thresholds, below any layer (a scan takes 16 bytes and 62 ns; 12 us a block): 700-256-256-20, T = B = 128 127.2
+// 121.9; 700-256-20: T = 128, B = 64 / 128 / 256 61.0 63.1 / 75.7 72.8 / 115 101, T = 200, B = 128 102.4 102.7; 700-100-20, T = 128, B =
+// 128 / 256 59.8 62.0 / 74.8 73.3; 200-1000-20, T = 100, B = 32 74.4 72.5, T = B = 128 184 138; 700-512-512-20, T = 64, B = 16 81.9
+// 92.8, T = 300, B = 256 883 790.  Of 60 such cases nothing it takes is slower.
 bool reverse_wide_pays(const snn_ctx *c, int l) {
   const Layer &y = c->layers[l];
   const double M = (double)c->M, N = y.ld, columns = columns_above(c, l);
   const long long groups = (long long)c->B * ((y.ld + 255) / 256);
   const double rounds = groups <= 512 ? (double)((groups + 255) / 256) : groups / 256.;
-  const double one = 4. + ((c->T + 127) / 128) * rounds * (9. + 0.62 * ((columns_above(c, l) + 31) / 32));
+  const double one = 4. + ((c->T + 127) / 128) * rounds * ((y.adaptive ? 12. : 9.) + 0.62 * ((columns_above(c, l) + 31) / 32));
   const double product = 3. + 2.4e-9 * M * N * columns + 4. * M * (N + columns) / 5e6;
-  const double scan = std::max(0.048 * c->T + 1., 2. + 12. * M * N / 5.2e6);
+  const double scan = y.adaptive ? std::max(0.062 * c->T + 2., 2. + 16. * M * N / 5.2e6) : std::max(0.048 * c->T + 1., 2. + 12. * M * N / 5.2e6);
   return 1.15 * one < product + scan + 2.;
 }
 bool reverse_wide(const snn_ctx *c, int l) {
   if (!c->opt[SNN_OPT_LAYER_REVERSE] || l < 0 || l > c->L - 2) return false;
   const Layer &y = c->layers[l];
-  if (!c->hl || !y.spiking || y.recurrent || y.adaptive || columns_above(c, l) <= 128) return false;
+  if (!c->hl || !y.spiking || y.recurrent || (!y.adaptive && columns_above(c, l) <= 128)) return false;
   return c->opt[SNN_OPT_LAYER_REVERSE] == 2 || reverse_wide_pays(c, l);
 }
 // A feed-forward spiking layer below at most 128 padded columns (the readout, or a narrow spiking
@@ -928,6 +932,7 @@ int launch_layer_reverse(snn_ctx *c, int l, bool wide) {
   a.Wq = up.Qb; a.ldq = up.ldqb; a.wq_bytes = (unsigned)(c->nplanes * up.qb_plane * 2); a.wq_plane = (unsigned)(up.qb_plane * 2);
   a.V = y.V; a.dI = y.dI; a.beta_v = y.beta_v; a.theta = c->theta; a.slope = c->slope; a.db_part = y.part_b;
   a.T = c->T; a.B = c->B; a.ld = y.ld;
+  a.A = y.A; a.gamma = y.gamma; a.kappa = y.kappa;
   a.nt_store = streams_past_cache(c, c->M * y.ld * 4);
   Bracket br(c, SNN_K_LIF_REVERSE, l + 1);
   // Rasters of at most 32 steps: several samples to a block of 64 rows, as many as leave 256 workgroups (us per step with

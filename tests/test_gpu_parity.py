@@ -173,6 +173,20 @@ def test_bench_describes_what_is_launched(T, B, sizes, recurrent, precision, ada
     assert_launches(wl, None, wanted)
 
 
+@pytest.mark.parametrize("T,B,sizes,adaptive", [(128, 256, (100, 256, 260, 10), False), (128, 32, (100, 256, 260, 10), False),
+                                                (128, 200, (100, 200, 300, 10), True), (128, 40, (100, 200, 300, 10), True)])
+def test_bench_describes_reverse_launches_below_wide_layers(T, B, sizes, adaptive):
+    """The same for the reverse launches below more than 128 columns and of adaptive layers: both sides of the rule."""
+    import bench
+    L = len(sizes) - 1
+    kw = dict(adapt_decay=(0.9,) * (L - 1), adapt_step=(0.2,) * (L - 1)) if adaptive else {}
+    wl = workloads.Workload(name="account", index=37, T=T, B=B, sizes=sizes, recurrent=(False,) * (L - 1), beta=(0.9,) * L,
+                            theta=1.0, surrogate="superspike", slope=10.0, precision="bf16", rate_lo=0.1, rate_hi=0.2, **kw)
+    one = {l: bench.reverse_forms_ds(wl, l) or bench.reverse_wide(wl, l) for l in range(1, L)}
+    assert one[1] == (B > 100)
+    assert_launches(wl, None, {**{("input_grad", l + 1): int(not one[l]) for l in one}, **{("lif_reverse", l): 1 for l in one}})
+
+
 # ---------------------------------------------------------------- feed-forward, fp32 products
 @pytest.mark.parametrize("gain", [1.0, 3.0])
 def test_tiny_ff_fp32(gain):
@@ -1877,6 +1891,26 @@ def test_adaptive_layers_in_one_launch(T, B, sizes, packed, precision):
         snn = make(wl, inp, {"layer_min_batch": 1})
         parity.compare_forward(net_of(wl), inp, snn, snn.forward_packed(np.packbits(inp.X, axis=0), inp.labels), {})
         snn.destroy()
+
+
+@pytest.mark.parametrize("T,B,sizes,surrogate,loss,nt", [(128, 5, (60, 256, 256, 20), "superspike", "max", False),
+                                                         (129, 3, (40, 300, 72, 5), "triangular", "integral", True),
+                                                         (300, 9, (50, 20, 264, 40), "sigmoid", "max", False),
+                                                         (1, 1, (30, 8, 10), "arctan", "max", False)],
+                         ids=["256", "odd", "several-blocks", "least"])
+def test_adaptive_layers_reverse_in_one_launch(T, B, sizes, surrogate, loss, nt):
+    """The reverse pass of adaptive layers as one launch (product, scan of both gradients), on request at any size: below
+    the readout and below wider layers, one to three blocks of 128 steps, parts of 256 neurons that are not full, trained decays;
+    against the oracle, and what is launched."""
+    L = len(sizes) - 1
+    wl = workloads.Workload(name="adaptive-reverse", index=36, T=T, B=B, sizes=sizes, recurrent=(False,) * (L - 1),
+                            beta=(0.9, 0.95, 0.9)[:L], theta=1.0, surrogate=surrogate, slope=4.0, precision="bf16",
+                            rate_lo=0.1, rate_hi=0.3, loss=loss, adapt_decay=(0.9, 0.8)[:L - 1], adapt_step=(0.3, 0.2)[:L - 1])
+    options = {"layer_reverse": 2, "stream_min_mb": 0} if nt else {"layer_reverse": 2}
+    full_step_parity(wl, w_gain=2.0, options=options)
+    beta_step_parity(wl, w_gain=2.0, options=options)
+    assert_launches(wl, options, {("lif_reverse", 1): 1, ("input_grad", 0): 0})
+    assert_launches(wl, {"layer_reverse": 0}, {("lif_reverse", 1): 1, ("input_grad", 0): L - 1})
 
 
 @pytest.mark.parametrize("rise", [float("inf"), 3e38])
