@@ -111,6 +111,25 @@ def top_scan_forms_currents(wl, layer):
             and pad8(wl.sizes[layer]) in (64, 128, 256) and pad8(wl.sizes[L]) <= 32)
 
 
+def forward_wide(wl, layer):
+    """Whether text layer `layer` runs on the kernel for wide layers (two samples and 128 neurons to a workgroup): more
+    than 128 neurons, rounded weights, where there are workgroups enough, or by the library's estimate (us) against product
+    and scan apart."""
+    L = len(wl.sizes) - 1
+    if not (1 <= layer < L) or wl.precision != "bf16" or wl.recurrent[layer - 1] or adaptive(wl, layer) or pad8(wl.sizes[layer]) <= 128:
+        return False
+    n, fan_in, rows = pad8(wl.sizes[layer]), wl.sizes[layer - 1], wl.T * wl.B
+    parts = -(-n // 128)
+    if runs_whole(wl, layer):
+        return wl.T > 64 and -(-n // 64) * 64 == parts * 128 and wl.B * parts >= 768
+    if top_scan_forms_currents(wl, layer):
+        return False
+    rounds = max(1, (wl.B + 1) // 2 * parts / 256)
+    one = 4 + -(-wl.T // 128) * rounds * (10.5 + 0.5 * -(-fan_in // 64))
+    product = 3 + (1.5e-9 if rows * n * 4 >= 128 << 20 else 2.5e-9) * rows * n * fan_in + 4 * rows * n / 5e6
+    return 1.1 * one < product + max(0.043 * wl.T + 2, 2 + 9 * rows * n / 6e6)
+
+
 def forward_chain(wl, layer):
     """The spiking layers that the forward launch starting at text layer `layer` covers, and whether it
     runs the readout too; ([], False) if that layer runs as separate product and scan launches."""
@@ -131,6 +150,11 @@ def forward_chain(wl, layer):
         chain.append(layer + 1)
     top = chain[-1]
     return chain, top == L - 1 and joins(top) and pad8(wl.sizes[L]) <= 32
+
+
+def forward_launch(wl, layer):
+    """forward_chain, with the layers that run on the kernel for wide layers."""
+    return ([layer], False) if forward_wide(wl, layer) else forward_chain(wl, layer)
 
 
 def reverse_wide(wl, layer):
@@ -193,7 +217,7 @@ def algorithmic_bytes(wl, kernel, layer, packed=False):
     fused_rev = reverse_forms_ds(wl, layer) or reverse_wide(wl, layer)
     fused_fwd = top_scan_forms_currents(wl, layer)
     state = 4 if layer < L and adaptive(wl, layer) else 0        # the adaptation, beside V
-    chain, with_readout = forward_chain(wl, layer)
+    chain, with_readout = forward_launch(wl, layer)
     if kernel == "lif_forward" and chain:
         # the launch that starts at `layer`: spikes below (1 B) and W (2 B a plane) read; V (4) and S (1) written
         # per layer; with the readout its currents, its trace and its current gradients (4 B each)
@@ -231,7 +255,7 @@ def method_flops(wl, kernel, layer):
         return sum(method_flops(wl, kernel, l) for l in range(1, L + 1))
     n_in, n_out = wl.sizes[layer - 1], wl.sizes[layer]
     if kernel == "lif_forward":
-        chain, with_readout = forward_chain(wl, layer)
+        chain, with_readout = forward_launch(wl, layer)
         f = sum(2 * M * wl.sizes[l - 1] * wl.sizes[l] for l in chain)
         if with_readout:
             f += 2 * M * wl.sizes[chain[-1]] * wl.sizes[L]
@@ -414,7 +438,7 @@ def main():
     if args.dominant is None:
         # the launch with the largest share of the step: where the forward pass of all spiking layers and the
         # readout is one launch, that one; else the merged weight-gradient launch
-        chain, with_readout = forward_chain(wl, 1)
+        chain, with_readout = forward_launch(wl, 1)
         args.dominant = "lif_forward:1" if with_readout and len(chain) == L - 1 else "weight_grad:0"
     kname, klayer = args.dominant.split(":")
     klayer = int(klayer)

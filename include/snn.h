@@ -201,7 +201,9 @@ typedef enum {
  *                     spiking layer; 2 every such layer; 3 the last one also forms the readout's
  *                     currents (rounded weights, at most 128 padded neurons and 32 padded classes);
  *                     4 (default) and runs the readout scan, the loss and the readout's current
- *                     gradients (fp32 products too)
+ *                     gradients (fp32 products too); layers of more than 128 neurons on rounded
+ *                     weights, of any width, then also run on workgroups of two samples and 128
+ *                     neurons where a rule on the sizes says so (LAYER_MAX_NEURONS = 1024)
  *   LAYER_PAIR        1 (default): two consecutive one-launch layers of at most 128 padded
  *                     neurons share a launch (layers of up to 64 with their like where there is a
  *                     choice), and so do two consecutive recurrent layers of at most 192 on rounded

@@ -19,6 +19,7 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
 # multiples of 1 KiB, 64.1 / 77.2 of 4 KiB, 64.0 / 77.1 of 64 KiB.)
 UNITS = {"snn_api.hip": ["-Xarch_device", "-falign-functions=1024"],
          "layer_forward.hip": ["-Xarch_device", "-falign-functions=1024"],
+         "layer_forward_wide.hip": ["-Xarch_device", "-falign-functions=1024"],
          "layer_reverse.hip": ["-Xarch_device", "-falign-functions=1024"],
          "layer_reverse_wide.hip": ["-Xarch_device", "-falign-functions=1024"],
          "rlif_wide.hip": [],

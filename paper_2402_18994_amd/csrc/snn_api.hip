@@ -18,6 +18,7 @@
 #include "gemm_stream.hpp"
 #include "wgrad_tr.hpp"
 #include "layer_forward.hpp"
+#include "layer_forward_wide.hpp"
 #include "scan.hpp"
 #include "layer_reverse.hpp"
 #include "layer_reverse_wide.hpp"
@@ -1174,6 +1175,56 @@ int launch_layer_forward(snn_ctx *c, int l, int nl, int with_readout, const int3
   return SNN_OK;
 }
 
+// A feed-forward layer of more than 128 neurons on rounded weights can run on the kernel for wide layers
+// (layer_forward_wide.hpp): workgroups of two samples and 128 neurons.
+// Against one launch of workgroups of one sample and 128 neurons (layer_forward.hpp), where those are so many that both
+// fill the chip more than once, beyond 64 steps, and the last part is not half empty (us per step, before and so; workgroups
+// before: 700-512-512-20: T = 128, B = 64, 256: 111.6 120.4, T = 200, B = 128, 512: 241.4 245.2, T = 100 140.3 138.6, T = 128, B = 255,
+// 1020: 266 256, T = B = 256, 1024: 480 442, T = 50 148.6 154.9, T = 70 177.8 169.1; 700-1024-1024-20: B = 64, 512: T = 128 194.9 194.0,
+// T = 500 590 595, T = 256, B = 512, 4096: 2267 2169; 700-256-256-20: T = 140, B = 256, 512: 177.1 177.6, T = 300, B = 200, 400: 282 287).
+// Against product and scan apart (above 1024 neurons or inputs) by a model of both, us, with 10 % in favour of those: 10.5
+// and half a us per 64 inputs for each block of 128 steps, 256 workgroups at a time; 1.25 per GFLOP (0.75 where the currents
+// stream past the caches) and 5 TB/s of currents for the product, 9 bytes at 6 TB/s or 43 ns a step for the scan.  700-2048-2048-10:
+// T = 128, B = 32 / 64 / 255 362 280 / 566 474 / 1764 1525, T = 500, B = 128 3658 3092, T = 500, B = 16 621 614, T = 1000, B = 8 701 804.
+bool forward_wide_pays(snn_ctx *c, int l) {
+  const Layer &y = c->layers[l];
+  const long long parts = (y.ld + 127) / 128;
+  if (layer_forward_fusable(c, l)) return c->T > 64 && rup(y.ld, 64) == rup(y.ld, 128) && c->B * parts >= 768;
+  if (l == c->L - 2 && top_forward_fusable(c)) return false;
+  const double M = (double)c->M, N = y.ld, rounds = std::max(1., (c->B + 1) / 2 * parts / 256.);
+  const double one = 4. + ((c->T + 127) / 128) * rounds * (10.5 + 0.5 * ((y.K + 63) / 64));
+  const double product = 3. + (streams_past_cache(c, c->M * y.ld * 4) ? 1.5e-9 : 2.5e-9) * M * N * y.K + 4. * M * N / 5e6;
+  const double scan = std::max(0.043 * c->T + 2., 2. + 9. * M * N / 6e6);
+  return 1.1 * one < product + scan;
+}
+bool forward_wide(snn_ctx *c, int l) {
+  if (l < 0 || l > c->L - 2 || layer_fuse_mode(c) < 4 || c->opt[SNN_OPT_LAYER_MAX_NEURONS] < 1024) return false;
+  const Layer &y = c->layers[l];
+  const SpikeSrc s = spikes_below(c, l);
+  return c->nplanes == 1 && y.spiking && !y.recurrent && !y.adaptive && y.ld > 128 && s.ld % 4 == 0 && !(l == 0 && c->x_direct) &&
+         (size_t)c->M * s.ld < ((size_t)1 << 31) && (size_t)c->M * y.ld * 4 < ((size_t)1 << 31) && c->theta >= 0x1p-60f &&
+         c->theta <= 0x1p26f && forward_wide_pays(c, l);
+}
+int launch_layer_forward_wide(snn_ctx *c, int l) {
+  Layer &y = c->layers[l];
+  const SpikeSrc s = spikes_below(c, l);
+  if (!s.p) return fail(c, SNN_ERR_NULL, "input raster is NULL");
+  LayerForwardArgs a;
+  memset(&a, 0, sizeof a);
+  LayerForwardOp &op = a.op[0];
+  op.P = s.p; op.ldp = s.ld; op.kc = s.valid; op.p_bytes = s.bytes;
+  op.Q = y.Qf; op.ldq = y.ldqf; op.q_bytes = (unsigned)(y.qf_plane * 2); op.q_plane = op.q_bytes;
+  op.V = y.V; op.S = y.S; op.beta_v = y.beta_v; op.ld = y.ld;
+  a.theta = c->theta;
+  a.T = c->T; a.B = c->B;
+  a.parts = (y.ld + ForwardWide::BN - 1) / ForwardWide::BN;
+  a.nt_store = streams_past_cache(c, c->M * y.ld * 4);
+  Bracket br(c, SNN_K_LIF_FORWARD, l + 1);
+  HIPCHK(c, layer_forward_wide(c->stream, a));
+  y.i_ready = false;
+  return SNN_OK;
+}
+
 int launch_readout_forward(snn_ctx *c, const int32_t *labels) {
   if (!labels) return fail(c, SNN_ERR_NULL, "labels are NULL");
   Layer &y = c->layers[c->L - 1];
@@ -1554,8 +1605,12 @@ static int32_t forward_layers(snn_ctx *c, const int32_t *labels_dev, float *loss
   const int whole = layer_fuse_mode(c);                 // layers that run as one launch, product and scan
   const bool whole_top = whole >= 2 && layer_forward_fusable(c, c->L - 2);
   const int with_readout = whole_top ? layer_forward_takes_readout(c) : 0;
-  const bool fuse_top = !whole_top && top_forward_fusable(c);   // the last spiking layer's scan forms the readout's currents
+  const bool fuse_top = !whole_top && !forward_wide(c, c->L - 2) && top_forward_fusable(c);   // the last spiking layer's scan forms the readout's currents
   for (int l = 0; l < c->L; ++l) {
+    if (forward_wide(c, l)) {
+      if ((rc = launch_layer_forward_wide(c, l))) return rc;
+      continue;
+    }
     if (whole >= 1 && (l < c->L - 2 || whole_top) && layer_forward_fusable(c, l)) {
       // this layer and the next in one launch when both hold at most 128 padded neurons (SNN_OPT_LAYER_PAIR = 0: one
       // launch each), but not one of at most 64 with a wider one that can be paired with the layer above it: the

@@ -1893,6 +1893,25 @@ def test_adaptive_layers_in_one_launch(T, B, sizes, packed, precision):
         snn.destroy()
 
 
+@pytest.mark.parametrize("T,B,sizes,nt", [(70, 97, (60, 1024, 10), False), (130, 96, (203, 1000, 40), True),
+                                          (128, 41, (90, 2056, 10), False), (66, 100, (700, 1024, 1016, 20), False),
+                                          (300, 193, (44, 512, 10), True)],
+                         ids=["odd-batch", "ragged", "above-1024", "long-fan-in", "several-blocks"])
+def test_wide_layers_forward_on_pairs_of_samples(T, B, sizes, nt):
+    """The forward kernel for wide layers, where its rule takes it: a pair with one sample, one to three blocks of 128
+    steps that end anywhere, a last part of neurons that is not full, one stage of inputs to sixteen, stores with and without the
+    non-temporal hint; against the oracle, and what is launched."""
+    import bench
+    L = len(sizes) - 1
+    wl = workloads.Workload(name="forward-wide", index=38, T=T, B=B, sizes=sizes, recurrent=(False,) * (L - 1), beta=(0.9, 0.95, 0.9)[:L],
+                            theta=1.0, surrogate="superspike", slope=10.0, precision="bf16", rate_lo=0.05, rate_hi=0.15)
+    options = {"stream_min_mb": 0} if nt else {}
+    assert all(bench.forward_wide(wl, l) for l in range(1, L))
+    assert_launches(wl, options, {("lif_forward", l): 1 for l in range(1, L)} | {("current_gemm", l): 0 for l in range(1, L)})
+    rep = full_step_parity(wl, w_gain=2.0, options=options)
+    assert min(rep["spike_rate"]) > 0.005
+
+
 @pytest.mark.parametrize("T,B,sizes,surrogate,loss,nt", [(128, 5, (60, 256, 256, 20), "superspike", "max", False),
                                                          (129, 3, (40, 300, 72, 5), "triangular", "integral", True),
                                                          (300, 9, (50, 20, 264, 40), "sigmoid", "max", False),
