@@ -1893,6 +1893,15 @@ def test_adaptive_layers_in_one_launch(T, B, sizes, packed, precision):
         snn.destroy()
 
 
+@pytest.mark.parametrize("precision", ["bf16", "fp32"])
+@pytest.mark.parametrize("N", [8, 32, 33, 65, 96, 97, 129, 160, 161, 193, 224, 225, 256])
+def test_recurrent_layers_of_every_number_of_steps(N, precision):
+    """One recurrent layer at both ends of every number of 32-neuron steps that its loops are compiled for."""
+    wl = workloads.Workload(name="rec-steps", index=39, T=21, B=5, sizes=(60, N, 7), recurrent=(True,), beta=(0.9, 0.95), theta=1.0,
+                            surrogate="sigmoid" if N % 2 else "superspike", slope=5.0, precision=precision, rate_lo=0.1, rate_hi=0.3)
+    full_step_parity(wl, w_gain=2.0)
+
+
 @pytest.mark.parametrize("T,B,sizes,nt", [(70, 97, (60, 1024, 10), False), (130, 96, (203, 1000, 40), True),
                                           (128, 41, (90, 2056, 10), False), (66, 100, (700, 1024, 1016, 20), False),
                                           (300, 193, (44, 512, 10), True)],
