@@ -111,6 +111,7 @@ struct LayerForwardArgs {
   int epoch;
   // Rasters of at most 64 steps (layer_forward_short.hpp): log2 of the steps in a sample's slot, and which loss.
   int slot_log2, integral;
+  u32x2 *host;             // optional: [B] in pinned memory, error bits and loss of every sample (TS = 1 and ROLE = 0)
 };
 // Which variant of the kernel a launch is (layer_forward.hip).
 struct LayerForwardVariant {
@@ -190,6 +191,7 @@ __device__ __forceinline__ void lif_layer_forward_body(const LayerForwardArgs &a
   for (int i = 1; i < SEG; i *= 2) bseg *= bseg;
   float y_in = 0.f, best = -INFINITY, ysum = 0.f;
   int lab = LOSS ? a.labels[b] : 0;                   // (asked for here: the epilogue would wait a memory round trip for it)
+  const uint32_t before = LOSS && a.host ? (uint32_t)*a.err : 0u;   // what earlier launches reported
   int tb = 0, par = 0;
 
   for (int blk = half; blk < nblocks; blk += TS) {
@@ -489,14 +491,19 @@ __device__ __forceinline__ void lif_layer_forward_body(const LayerForwardArgs &a
     float sum = ex;
 #pragma unroll
     for (int o = 16; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
-    if (lab < 0 || lab >= a.C) { if (tid == 0) atomicOr(a.err, 1); lab = 0; }
+    const bool bad = lab < 0 || lab >= a.C;
+    if (bad) { if (tid == 0) atomicOr(a.err, 1); lab = 0; }
     float zl = (live && c == lab) ? best : 0.f;
 #pragma unroll
     for (int o = 16; o > 0; o >>= 1) zl += __shfl_xor(zl, o);
     const float d = live ? (ex / sum - (c == lab ? 1.f : 0.f)) / (float)a.B : 0.f;
     if (g == 0) {
       if (live) a.dz[p] = d;
-      if (c == 0) a.loss_b[b] = m + logf(sum) - zl;
+      if (c == 0) {
+        const float loss = m + logf(sum) - zl;
+        a.loss_b[b] = loss;
+        if (a.host) a.host[b] = u32x2{before | (bad ? 1u : 0u), __float_as_uint(loss)};
+      }
     }
     // dJ_t = h_t with h_t = beta h_{t+1} + dz [t == t*] (integral loss: dz at every step): entered
     // per segment in closed form, the recursion inside it

@@ -504,7 +504,7 @@ __global__ __launch_bounds__(256) void lif_reverse_top_kernel(const uint32_t *__
 // holds columns 4q..4q+3 of row r (r = i / LPR, q = i % LPR, LPR = SPB*ld/4 <= 16 lanes per
 // row); a 1 KB LDS stage per access turns that into the chain arrangement and back.  Lanes
 // without work address beyond the buffers: loads return zero, stores are dropped.
-// Per-sample losses go to loss_b; their mean is taken by a later launch (the partial-sum
+// Per-sample losses go to loss_b (and, with error bits, to pinned memory where the host asked for the loss: `host`); their mean is taken by a later launch (the partial-sum
 // reduction of the backward pass, or loss_mean_kernel when the loss is asked for first), in
 // index order either way.
 template <int CW, bool HL, bool INTEGRAL>
@@ -513,7 +513,7 @@ __global__ __launch_bounds__(512) void readout_loss_kernel(const float *__restri
                                                            const int *__restrict__ labels, float *__restrict__ loss_b,
                                                            float *__restrict__ dz, int *__restrict__ err,
                                                            uint32_t *__restrict__ dJ, int T, int B, int C, int ldc,
-                                                           const float *__restrict__ beta_v) {
+                                                           const float *__restrict__ beta_v, u32x2 *__restrict__ host) {
   constexpr int SPB = 64 / CW;                        // samples per workgroup
   constexpr int NW = 8;                               // wavefronts = time segments per block
   constexpr int G = 4;                                // accesses (of four rows) per segment
@@ -623,14 +623,19 @@ __global__ __launch_bounds__(512) void readout_loss_kernel(const float *__restri
 #pragma unroll
   for (int o = CW / 2; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
   int lab = lab_in;
-  if (lab < 0 || lab >= C) { if (c == 0 && w == 0) atomicOr(err, 1); lab = 0; }
+  const bool bad = lab < 0 || lab >= C;
+  if (bad) { if (c == 0 && w == 0) atomicOr(err, 1); lab = 0; }
   float zl = (live && c == lab) ? best : 0.f;          // z[label], gathered across the group
 #pragma unroll
   for (int o = CW / 2; o > 0; o >>= 1) zl += __shfl_xor(zl, o);
   const float d = live ? (ex / sum - (c == lab ? 1.f : 0.f)) / (float)B : 0.f;
   if (w == 0) {
     if (live) dz[p] = d;
-    if (b < B && c == 0) loss_b[b] = m + logf(sum) - zl;
+    if (b < B && c == 0) {
+      const float loss = m + logf(sum) - zl;
+      loss_b[b] = loss;
+      if (host) host[b] = u32x2{(uint32_t)*err | (bad ? 1u : 0u), __float_as_uint(loss)};
+    }
   }
 
   // dJ

@@ -1594,6 +1594,35 @@ def test_small_tensors_read_back_beside_the_loss(B, precision):
     snn.destroy()
 
 
+@pytest.mark.parametrize("T,B,sizes,rec,integral,options", [
+    (32, 33, (50, 64, 10), False, False, {}),                  # several samples to a tile: mean taken by a launch
+    (128, 40, (50, 64, 10), False, False, {}),                 # the whole readout in the layers' launch
+    (70, 300, (50, 128, 128, 20), False, True, {}),            # sums of more than one value a thread; integral loss
+    (130, 7, (50, 128, 128, 20), False, False, {"layer_pair": 2}),   # pair of layers on two workgroups: a launch
+    (20, 31, (50, 40, 33), True, False, {}),                   # readout's own launch, two samples a wavefront
+    (9, 13, (50, 40, 70), False, False, {}),                   # more than 64 classes: scan, cross-entropy, mean
+    (5, 4096, (20, 24, 16), True, False, {}), (5, 4097, (20, 24, 16), True, False, {}),   # the batches that pinned memory takes
+])
+def test_loss_of_the_forward_call_is_the_loss_of_its_samples(T, B, sizes, rec, integral, options):
+    """The mean that snn_forward returns, whoever sums it, has the bits of the mean taken on the device; a label out of
+    range is reported by the call that returns the loss, once."""
+    wl = workloads.Workload(name="call-loss", index=31, T=T, B=B, sizes=sizes, recurrent=(rec,) * (len(sizes) - 2),
+                            beta=(0.9,) * (len(sizes) - 2) + (0.95,), theta=1.0, surrogate="superspike", slope=10.0, precision="bf16",
+                            rate_lo=0.2, rate_hi=0.4, loss="integral" if integral else "max")
+    inp = workloads.generate(wl, w_gain=3.0)
+    snn = make(wl, inp, options)
+    bad = np.array(inp.labels)
+    bad[B - 1] = sizes[-1]
+    for _ in range(2):
+        loss = snn.forward(inp.X, inp.labels)
+        assert snn.get_tensor("loss")[0] == loss
+        per = snn.get_tensor("loss_per_sample").astype(np.float64)
+        assert abs(loss - per.mean()) <= 1e-6 * abs(loss)         # (fp32 sum in a tree of at most 17 + 8 additions)
+        with pytest.raises(Exception, match="label"):
+            snn.forward(inp.X, bad)
+    snn.destroy()
+
+
 def test_calls_with_host_results_wait_for_the_stream():
     """snn_forward with a loss and snn_get_tensor return when the stream is idle, whatever the tensor's size
     and type: a stream or an event that is asked right after the call has finished."""
