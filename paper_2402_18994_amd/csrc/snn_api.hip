@@ -10,7 +10,6 @@
 #include <cstdlib>
 #include <cstring>
 #include <mutex>
-#include <numeric>
 #include <string>
 #include <vector>
 
@@ -241,39 +240,20 @@ void carve(snn_ctx &c, Carver &cv) {
   // the products are large enough for 256 x 128 tiles, which move 1.7 times fewer operand
   // bytes per flop (measured 2.8 times faster at 1024-wide layers, slower at 128-wide ones).
   // (long products of few columns in the company of wider ones have splits of their own: see long_and_narrow)
-  bool any_long = false, all_narrow = true;
-  for (int l = 0; l < c.L; ++l) {
-    any_long = any_long || long_and_narrow(c.M, c.layers[l].K, c.layers[l].N, c.precision == SNN_PREC_FP32);
-    all_narrow = all_narrow && c.layers[l].N <= 32;
-  }
-  c.wg_narrow = any_long && all_narrow;
-  auto narrow = [&](const Layer &y) { return !all_narrow && long_and_narrow(c.M, y.K, y.N, c.precision == SNN_PREC_FP32); };
-  std::vector<int> job_tiles;                             // of each product of the merged launch
+  std::vector<bool> recurrent;
+  for (const Layer &y : c.layers) recurrent.push_back(y.recurrent);
+  const WgradLaunch wg = wgrad_launch(c.M, c.L, c.sizes.data(), recurrent, c.precision == SNN_PREC_FP32);
+  c.wg_narrow = wg.narrow;
   auto count_tiles = [&](bool tall) {
-    job_tiles.clear();
-    for (int l = 0; l < c.L; ++l) {
-      if (!narrow(c.layers[l])) job_tiles.push_back(wgrad_tiles(c.layers[l].K, c.layers[l].N, tall));
-      if (c.layers[l].recurrent) job_tiles.push_back(wgrad_tiles(c.layers[l].N, c.layers[l].N, tall));
-    }
-    return std::accumulate(job_tiles.begin(), job_tiles.end(), 0);
+    int n = 0;
+    for (const WgradProduct &p : wg.products) n += wgrad_tiles(p.rows, p.cols, tall);
+    return n;
   };
   c.wg_tall = c.precision != SNN_PREC_FP32 && count_tiles(false) >= 32;
   // (the splits are laid out here, for the kernel that SNN_OPT_WGRAD_TR selects at this point)
   const bool wg_tr = c.opt[SNN_OPT_WGRAD_TR] != 0 && !c.wg_narrow;
-  c.wg_tr_tall = wg_tr && c.precision != SNN_PREC_FP32 && wgrad_tall_pays(c.M, count_tiles(false), count_tiles(true));
-  const int wg_tiles = count_tiles(c.wg_tr_tall || (c.wg_tall && !wg_tr));
-  long long wg_weights = 0, wg_row_bytes = 0;             // what the merged launch writes per split / reads per row
-  for (int l = 0; l < c.L; ++l) {
-    const Layer &y = c.layers[l];
-    if (!narrow(y)) {
-      wg_weights += (long long)y.K * y.N;
-      wg_row_bytes += y.K + 4ll * y.N;                           // spike bytes below, 4-byte current gradients
-    }
-    if (y.recurrent) {
-      wg_weights += (long long)y.N * y.N;
-      wg_row_bytes += y.N + (narrow(y) ? 4ll * y.N : 0);
-    }
-  }
+  c.wg_tr_tall = wg_tr && c.precision != SNN_PREC_FP32 && wgrad_tall_pays(c.M, wg);
+  const int wg_tiles = count_tiles(c.wg_tall && !wg_tr);
   for (int l = 0; l < c.L; ++l) {
     Layer &y = c.layers[l];
     const size_t K = y.K, N = y.N;
@@ -290,9 +270,9 @@ void carve(snn_ctx &c, Carver &cv) {
     // (layer 1: from the length of the contraction in packed order, T rounded up to whole bytes of
     // eight steps, so that the same splits serve a raster packed along time)
     const long long rows_w = l == 0 ? (long long)((c.T + 7) / 8 * 8) * c.B : c.M;
-    y.splits_w = narrow(y) ? choose_splits(rows_w, wgrad_tiles(y.K, y.N, false), (long long)K * N, K + 4ll * N, &y.per_w, false)
-                           : c.wg_tr_tall ? choose_splits_tall(rows_w, job_tiles.data(), (int)job_tiles.size(), wg_weights, &y.per_w)
-                           : choose_splits(rows_w, wg_tiles, wg_weights, wg_row_bytes, &y.per_w, wg_tr);
+    y.splits_w = wg.own[l] ? choose_splits(rows_w, wgrad_tiles(y.K, y.N, false), (long long)K * N, K + 4ll * N, &y.per_w, false)
+                           : c.wg_tr_tall ? choose_splits_tall(rows_w, wg, &y.per_w)
+                           : choose_splits(rows_w, wg_tiles, wg.weights, wg.row_bytes, &y.per_w, wg_tr);
     if (y.splits_w > 1) y.part_w = cv.take<float>((size_t)y.splits_w * K * N);
     if (y.recurrent) {
       y.Rm = cv.take<float>(N * N);
@@ -304,8 +284,8 @@ void carve(snn_ctx &c, Carver &cv) {
       y.g[0] = cv.take<float>((size_t)c.B * y.ld);
       y.g[1] = cv.take<float>((size_t)c.B * y.ld);
       if (c.precision != SNN_PREC_FP32 && rlif_wide_layer(y.ld)) y.rp_space = cv.take<char>(RlifWide::BYTES);
-      y.splits_r = c.wg_tr_tall ? choose_splits_tall(c.M, job_tiles.data(), (int)job_tiles.size(), wg_weights, &y.per_r)
-                                : choose_splits(c.M, wg_tiles, wg_weights, wg_row_bytes, &y.per_r, wg_tr);
+      y.splits_r = c.wg_tr_tall ? choose_splits_tall(c.M, wg, &y.per_r)
+                                : choose_splits(c.M, wg_tiles, wg.weights, wg.row_bytes, &y.per_r, wg_tr);
       if (y.splits_r > 1) y.part_r = cv.take<float>((size_t)y.splits_r * N * N);
     }
     y.beta_v = cv.take<float>(y.ld);

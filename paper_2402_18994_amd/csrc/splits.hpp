@@ -1,5 +1,6 @@
 // How the contraction of the weight-gradient products is split over workgroups (host arithmetic only).
 #pragma once
+#include <vector>
 
 namespace snn {
 
@@ -65,43 +66,6 @@ inline int choose_splits(long long M, int tiles, long long weights, long long ro
   return (int)((M + per - 1) / per);
 }
 
-// Tiles of 256 x 128 on the kernel of transposing LDS reads (rounded weights), one workgroup per compute unit.
-// A row of a 128 x 128 tile's contraction takes about 66 ps of the whole chip, one of a tall tile 95, and a launch of
-// tall tiles about 18 us more: longer to start and end, and twice the partial sums at the same count of workgroups.
-// us per step, 128 x 128 and 256 x 128, by tiles of either kind and rows (T*B): 700-128-128-20, 8 and 5, 32768: 76.3 85.4,
-// 128000: 254 255; 700-256-20, 14 and 7, 32768: 83.7 88.3, 65536: 132.5 133.8, 128000: 301 268; 700-256-256-20, 18 and 9,
-// 32768: 138 144, 65536: 295 273; 700-512-20, 28 and 14, 32768: 127.4 129.6, 128000: 537 471; 700-512-512-20, 44 and 22,
-// 8192: 109.7 110.9, 16384: 158.3 155.6, 32768: 306 280, 65536: 552 525; 300-1024-20 (512 rows for 300), 32 and 20, 32768: 175
-// 191, 65536: 394 383, 128000: 744 703; 100-300-200-20 (512 for 300), 11 and 8, 65536: 275 277.
-inline bool wgrad_tall_pays(long long M, int tiles, int tall_tiles) {
-  return M * (66ll * tiles - 95ll * tall_tiles) >= 18000000;
-}
-
-// Splits of tall tiles: any count, for the workgroups of an XCD (32 compute units; each product's workgroups are dealt
-// evenly over the XCDs) to take the fewest rounds for their length, 18 ns a row and 5 us a round, with the partial
-// sums.  700-512-512-20, T*B = 65536 (the launch alone, us): 8 splits 160, 11 131, 14 190, 16 171, 23 145; 700-1024-1024-20,
-// 131072: 4 splits 665, 8 705, 16 737.
-inline int choose_splits_tall(long long M, const int *tiles, int jobs, long long weights, long long *per_split) {
-  int best = 1;
-  double best_us = 0.;
-  for (int want = 1; want <= 64 && (want == 1 || 256ll * want <= M); ++want) {
-    const long long per = round_up((M + want - 1) / want, 64);
-    const int n = (int)((M + per - 1) / per);
-    long long slots = 0;                                 // workgroups of an XCD
-    for (int j = 0; j < jobs; ++j) slots += ((long long)tiles[j] * n + 7) / 8;
-    const double us = (slots + 31) / 32 * (per * 18e-3 + 5.) + (n > 1 ? n * weights * 1.25e-6 : 0.);
-    if (want == 1 || us < best_us) { best = want; best_us = us; }
-  }
-  *per_split = round_up((M + best - 1) / best, 64);
-  return (int)((M + *per_split - 1) / *per_split);
-}
-
-inline int wgrad_tiles(int rows, int cols, bool tall) {
-  int bn = cols <= 32 ? 32 : (cols <= 64 ? 64 : 128);
-  const int bm = tall && cols > 64 ? 256 : 128;
-  return ((rows + bm - 1) / bm) * ((cols + bn - 1) / bn);
-}
-
 // A product of at most 32 columns: three of the four wavefronts of a 128-column tile multiply nothing, which shows
 // once it takes longer than a launch.  Alone it takes tiles of 128 x 32 of the general kernel then: fp32, 512 x 16:
 // T*B = 16384 13.4 us with the wide tile and 14.4 with the narrow one, 32768 18.4 and 16.8, 262144 84.3 and 71.1; 100 x 16,
@@ -113,6 +77,105 @@ inline int wgrad_tiles(int rows, int cols, bool tall) {
 inline bool long_and_narrow(long long M, int rows, int cols, bool fp32) {
   const long long t = (rows + 127) / 128;
   return cols <= 32 && t >= 2 && t * M >= (fp32 ? 1 << 17 : 3 << 18);
+}
+
+// A product of the merged weight-gradient launch: dW or dR, rows x cols.
+struct WgradProduct { int rows, cols; };
+
+// The merged launch of a network: `sizes` of its L + 1 layers, `recurrent` flags of the first L.
+struct WgradLaunch {
+  std::vector<WgradProduct> products;                    // those whose splits are the launch's
+  std::vector<bool> own;                                 // per layer: dW is long and narrow beside wider products, splits of its own
+  bool narrow = false;                                   // every dW is narrow and one is long
+  long long weights = 0, row_bytes = 0;                  // what `products` write per split / read per row
+};
+inline WgradLaunch wgrad_launch(long long M, int L, const int *sizes, const std::vector<bool> &recurrent, bool fp32) {
+  WgradLaunch w;
+  bool any_long = false, all_narrow = true;
+  for (int l = 0; l < L; ++l) {
+    any_long = any_long || long_and_narrow(M, sizes[l], sizes[l + 1], fp32);
+    all_narrow = all_narrow && sizes[l + 1] <= 32;
+  }
+  w.narrow = any_long && all_narrow;
+  for (int l = 0; l < L; ++l) {
+    const int K = sizes[l], N = sizes[l + 1];
+    w.own.push_back(!all_narrow && long_and_narrow(M, K, N, fp32));
+    if (!w.own[l]) {
+      w.products.push_back({K, N});
+      w.weights += (long long)K * N;
+      w.row_bytes += K + 4ll * N;                        // spike bytes below, 4-byte current gradients
+    }
+    if (recurrent[l]) {
+      w.products.push_back({N, N});
+      w.weights += (long long)N * N;
+      w.row_bytes += N + (w.own[l] ? 4ll * N : 0);
+    }
+  }
+  return w;
+}
+
+// Tiles of 256 x 128 on the kernel of transposing LDS reads (rounded weights), one workgroup per compute unit: that kernel
+// has one tile for products of any width.
+inline int wgrad_tall_tiles(const WgradProduct &p) { return ((p.rows + 255) / 256) * ((p.cols + 127) / 128); }
+inline int wgrad_flat_tiles(const WgradProduct &p) { return ((p.rows + 127) / 128) * ((p.cols + 127) / 128); }
+
+// Splits of tall tiles: any count, for the workgroups of an XCD (32 compute units; each product's workgroups are dealt
+// evenly over the XCDs) to take the fewest rounds for their length, 18 ns a row and 5 us a round, with the partial sums.  A long and narrow product beside them has splits of its own (see
+// long_and_narrow) that come to about one workgroup for every compute unit, whatever its height: a round in front of
+// the others', the same for each count.  The launch alone, us, * the choice: 700-512-512-20, T*B = 65536: 8 splits 162, 9 152, 10 143, 11 137*,
+// 12 221, 16 175, 23 144; 700-1024-1024-20, 131072: 4 727, 8 719, 9 698*; 700-256-256-20, 65536: 16 88, 24 69, 26 65, 28 64*,
+// 32 94; 300-1024-20, 65536: 8 153, 10 130, 12 121*, 14 185.
+inline long long tall_slots(const WgradLaunch &w, int splits) {
+  long long slots = 0;                                   // workgroups of an XCD
+  for (const WgradProduct &p : w.products) slots += ((long long)wgrad_tall_tiles(p) * splits + 7) / 8;
+  return slots;
+}
+inline int choose_splits_tall(long long M, const WgradLaunch &w, long long *per_split) {
+  int best = 1;
+  double best_us = 0.;
+  for (int want = 1; want <= 64 && (want == 1 || 256ll * want <= M); ++want) {
+    const long long per = round_up((M + want - 1) / want, 64);
+    const int splits = (int)((M + per - 1) / per);
+    const double us = (tall_slots(w, splits) + 31) / 32 * (per * 18e-3 + 5.) + (splits > 1 ? splits * w.weights * 1.25e-6 : 0.);
+    if (want == 1 || us < best_us) { best = want; best_us = us; }
+  }
+  *per_split = round_up((M + best - 1) / best, 64);
+  return (int)((M + *per_split - 1) / *per_split);
+}
+
+// Whether tall tiles are the faster form: by a model of both launches, us, with 7 in favour of 128 x 128 tiles.  Either
+// launch takes a time for its rows and one for the rounds of its workgroups and writes its partial sums, which the update
+// reads (dW from one split goes straight to its place); 128 x 128 tiles read more of the operands from memory once those do
+// not stay in the caches (`row_bytes`: bytes of all operands per row of the contraction; 120 MB).  The model is within 6 % (tall)
+// and 9 % of 203 launches at 512 to 250000 rows.  Of 165 steps measured where it takes tall tiles four are 1 to 2.1 % slower with
+// them and 136 more than 2 % faster (1.31 times at most); of 102 where it does not, three would be more than 4 % faster.
+// us per step, 128 x 128 and 256 x 128, * the choice: 700-512-512-20, T*B = 10000 126.0* 125.6, 16384 155 152*, 32768 272 260*, 65536
+// 471 456*; 700-256-256-20, 32768 143.1* 143.4, 51200 229 218*, 65536 277 256*; 300-1024-20 (512 rows for 300), 32768 175* 187, 65536
+// 380 366*; 700-512-20, 40960 162* 167, 57344 249 222*; 700-1024-1024-20, 8192 196 191*, 131072 2415 2242*; 700-1472-1472-10, 1536 249
+// 195*; 700-2048-2048-20, 4096 368 348*; 398-1911-1911-1911-10, 3503 559* 590; 700-1542-1542-20, 5300 406* 416; 700-1664-1664-10,
+// 11235 575 543*.
+inline bool wgrad_tall_pays(long long M, const WgradLaunch &w) {
+  long long tiles = 0, tiles_tall = 0, per, per_tall, slots = 0;
+  for (const WgradProduct &p : w.products) {
+    tiles += wgrad_flat_tiles(p);
+    tiles_tall += wgrad_tall_tiles(p);
+  }
+  const int splits = choose_splits(M, (int)tiles, w.weights, w.row_bytes, &per, true), splits_tall = choose_splits_tall(M, w, &per_tall);
+  for (const WgradProduct &p : w.products)               // workgroups of the fullest XCD, splits dealt round-robin
+    slots += splits == 1 ? (wgrad_flat_tiles(p) + 7) / 8 : (long long)wgrad_flat_tiles(p) * ((splits + 7) / 8);
+  const long long rounds = (slots + 31) / 32, rounds_tall = (tall_slots(w, splits_tall) + 31) / 32;
+  const double from_memory = M * w.row_bytes * 1e-6 - 120.;
+  const double flat = 22e-6 * M * tiles + 6.5e-3 * rounds * per + 0.6e-6 * splits * w.weights + (from_memory > 0. ? 0.1 * from_memory : 0.);
+  const double tall = 3. + 27e-6 * M * tiles_tall + 13.3e-3 * rounds_tall * per_tall + 0.72e-6 * splits_tall * w.weights;
+  const double update = 1e-6 * w.weights * (splits_tall - splits + 3 * ((splits_tall > 1) - (splits > 1)));
+  return flat - tall - update >= 7.;
+}
+
+// Tiles of the general kernel.
+inline int wgrad_tiles(int rows, int cols, bool tall) {
+  int bn = cols <= 32 ? 32 : (cols <= 64 ? 64 : 128);
+  const int bm = tall && cols > 64 ? 256 : 128;
+  return ((rows + bm - 1) / bm) * ((cols + bn - 1) / bn);
 }
 
 }  // namespace snn

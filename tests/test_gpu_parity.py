@@ -12,7 +12,7 @@ import pytest
 import workloads
 from oracle import snn_oracle as O
 from tests import parity
-from tests.helpers import net_of
+from tests.helpers import net_of, weight_gradient_form
 
 pytestmark = pytest.mark.gpu
 
@@ -450,24 +450,31 @@ def test_weight_gradients_through_transposing_reads(T, B, sizes, rec, packed):
         assert np.abs(a - b).max() <= 1e-5 * np.abs(b).max() + 1e-30
 
 
-@pytest.mark.parametrize("T,B,sizes,rec,packed", [(130, 130, (700, 1024, 1000, 20), (False, False), False),
-                                                   (125, 136, (513, 768, 1030, 40), (False, False), True),
-                                                   (128, 129, (260, 1000, 10), (True,), False),
-                                                   (250, 264, (700, 512, 512, 20), (False, False), False)],
-                         ids=["several-splits", "packed-ragged", "recurrent", "eleven-splits"])
-def test_weight_gradients_on_tall_tiles(T, B, sizes, rec, packed):
-    """Products large enough for tiles of 256 x 128 (wgrad_tall_pays): rows, columns and contraction tails that fill no
-    tile, split counts that are no multiple of eight, a packed layer-1 job, dR beside dW.  On the device's own spikes and
+@pytest.mark.parametrize("T,B,sizes,rec,packed,splits", [(130, 130, (700, 1024, 1000, 20), (False, False), False, 4),
+                                                          (125, 136, (516, 1020, 1000, 40), (False, False), True, 4),
+                                                          (128, 129, (260, 1000, 600, 10), (True, False), False, 3),
+                                                          (250, 264, (700, 512, 512, 20), (False, False), False, 11),
+                                                          (33, 65, (300, 2040, 1500, 20), (False, False), False, 1),
+                                                          (192, 512, (64, 520, 1024, 20), (False, False), False, 17)],
+                         ids=["several-splits", "packed-ragged", "recurrent", "eleven-splits", "one-split", "long-narrow-beside"])
+def test_weight_gradients_on_tall_tiles(T, B, sizes, rec, packed, splits):
+    """Products large enough for tiles of 256 x 128 (by the library's rule, asked on the host): rows, columns and contraction
+    tails that fill no tile, split counts that are no multiple of eight, one split, a packed layer-1 job (multiples of 4
+    channels and of 8 samples), dR beside dW, a long narrow product with splits of its own.  On the device's own spikes and
     current gradients, in 64 bits."""
     import torch
     L = len(sizes) - 1
+    assert weight_gradient_form(T * B, sizes, rec)[:2] == (True, splits)
     wl = workloads.Workload(name="wgrad-tall", index=29, T=T, B=B, sizes=sizes, recurrent=rec,
                             beta=(0.9, 0.93, 0.95)[:L], theta=1.0, surrogate="superspike", slope=10.0, precision="bf16",
                             rate_lo=0.03, rate_hi=0.12, loss="max")
     inp = workloads.generate(wl, w_gain=1.5 if any(rec) else 3.0)
     snn = make(wl, inp, {})
-    if packed:
+    if packed:                                  # (layer 1 in one launch reads the packed raster itself: no product of its own)
+        snn.profile_select("current_gemm", 1)
         snn.forward_packed(np.packbits(inp.X, axis=0), inp.labels)
+        assert snn.profile_read()[1] == 0 and sizes[0] % 4 == 0 and B % 8 == 0
+        snn.profile_select("none")
     else:
         snn.forward(inp.X, inp.labels)
     snn.backward()

@@ -5,6 +5,8 @@ import subprocess
 
 import pytest
 
+from tests.helpers import weight_gradient_form
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 PROGRAM = r'''
@@ -52,3 +54,26 @@ def test_splits_cover_the_rows_and_their_time_has_no_jump(program, tiles, weight
             return 1e-2 * min(M, (-(-M // count) + 63) // 64 * 64) + 1.25e-6 * weights * count
         best = min(time(c) for c in (1, 2, 4, 8, 16, 32, 64) if c * tiles <= 256 or c == 1)
         assert time(n) <= max(4 / 3 * best, best + 1.0), (M, n, per)
+
+
+# rows, sizes, recurrent layers, tiles of 256 x 128, their splits: where both kinds were timed, the faster one
+TALL = [(65536, (700, 512, 512, 20), (), True, 11), (10000, (700, 512, 512, 20), (), False, 11),
+        (65536, (700, 256, 256, 20), (), True, 28), (32768, (700, 256, 256, 20), (), False, 27),
+        (65536, (300, 1024, 20), (), True, 12), (32768, (300, 1024, 20), (), False, 12),
+        (57344, (700, 512, 20), (), True, 18), (40960, (700, 512, 20), (), False, 18),
+        (131072, (700, 1024, 1024, 20), (), True, 9), (65536, (700, 2048, 2048, 2048, 20), (1, 0, 0), True, 4),
+        (32768, (700, 128, 128, 20), (), False, 47), (3503, (398, 1911, 1911, 1911, 10), (), False, 2),
+        (11235, (700, 1664, 1664, 10), (), True, 3)]
+
+
+@pytest.mark.parametrize("M,sizes,recurrent,tall,splits", TALL, ids=["%d-rows-%s" % (t[0], "-".join(map(str, t[1]))) for t in TALL])
+def test_which_weight_gradients_run_on_tall_tiles(M, sizes, recurrent, tall, splits):
+    """The form, and the splits with the workgroups that are launched: every product has tiles of 256 x 128, also the
+    narrow ones.  Every row belongs to one split, none of them is empty."""
+    rec = tuple(recurrent) + (0,) * (len(sizes) - 2 - len(recurrent))
+    got_tall, n, per, slots = weight_gradient_form(M, sizes, rec)
+    assert (got_tall, n) == (tall, splits)
+    assert per % 64 == 0 and (n - 1) * per < M <= n * per
+    products = [(a, b) for a, b in zip(sizes, sizes[1:]) if not (b <= 32 and a > 128 and -(-a // 128) * M >= 3 << 18)]
+    products += [(b, b) for b, r in zip(sizes[1:], rec) if r]
+    assert slots == sum(-(-(-(-a // 256) * -(-b // 128) * n) // 8) for a, b in products)
