@@ -225,7 +225,7 @@ typedef enum {
  *                     narrow products themselves (readout currents forward, dS reverse); 0: off
  *   DEFER_REDUCE      1 (default): snn_backward leaves the per-split partial sums of the weight
  *                     gradients to snn_sgd_step (or the first reader); 0: it adds them itself
- *   LAYER_MIN_BATCH   smallest batch for the one-launch layers; 0 (default) = by measured rules on steps, fan-in and
+ *   LAYER_MIN_BATCH   smallest batch for the one-launch layers, wide ones too; 0 (default) = by measured rules on steps, fan-in and
  *                     workgroups: any up to 128 steps, more where a sample's walk is long and samples are few
  *   LAYER_NEURONS     neurons per workgroup of the one-launch forward layers: 128 (default) or 64
  *   LAYER_MAX_NEURONS widest layer (and fan-in) that runs as one launch: 64..1024 (default 1024)

@@ -821,7 +821,7 @@ int layer_reverse_min_batch(const snn_ctx *c, int l) {
 }
 // Whether the reverse pass of a layer below a wide one, or with adaptive thresholds, is one launch (wide_rules.hpp).
 bool reverse_wide(const snn_ctx *c, int l) {
-  if (!c->opt[SNN_OPT_LAYER_REVERSE] || l < 0 || l > c->L - 2) return false;
+  if (!c->opt[SNN_OPT_LAYER_REVERSE] || l < 0 || l > c->L - 2 || c->B < layer_min_batch(c)) return false;
   const Layer &y = c->layers[l];
   const int columns = columns_above(c, l);
   if (!c->hl || !y.spiking || y.recurrent || (!y.adaptive && columns <= 128)) return false;
@@ -1146,7 +1146,7 @@ int launch_layer_forward(snn_ctx *c, int l, int nl, int with_readout, const int3
 
 // Whether a layer runs on the kernel for wide layers (wide_rules.hpp).
 bool forward_wide(snn_ctx *c, int l) {
-  if (l < 0 || l > c->L - 2 || layer_fuse_mode(c) < 4 || c->opt[SNN_OPT_LAYER_MAX_NEURONS] < 1024) return false;
+  if (l < 0 || l > c->L - 2 || layer_fuse_mode(c) < 4 || c->opt[SNN_OPT_LAYER_MAX_NEURONS] < 1024 || c->B < layer_min_batch(c)) return false;
   const Layer &y = c->layers[l];
   const SpikeSrc s = spikes_below(c, l);
   return c->nplanes == 1 && y.spiking && !y.recurrent && !y.adaptive && y.ld > 128 && s.ld % 4 == 0 && !(l == 0 && c->x_direct) &&

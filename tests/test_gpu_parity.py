@@ -187,6 +187,21 @@ def test_bench_describes_reverse_launches_below_wide_layers(T, B, sizes, adaptiv
     assert_launches(wl, None, {**{("input_grad", l + 1): int(not one[l]) for l in one}, **{("lif_reverse", l): 1 for l in one}})
 
 
+@pytest.mark.parametrize("T,B,sizes,adaptive,reverse", [(128, 256, (100, 512, 500, 10), False, 1), (100, 128, (100, 1100, 1040, 10), False, 1),
+                                                        (20, 6, (60, 200, 300, 10), False, 2), (128, 200, (100, 200, 300, 10), True, 1),
+                                                        (50, 6, (60, 200, 96, 10), True, 2)],
+                         ids=["512", "1100", "on-request", "adaptive", "adaptive-on-request"])
+def test_smallest_batch_of_the_one_launch_layers_holds_for_wide_ones(T, B, sizes, adaptive, reverse):
+    """LAYER_MIN_BATCH, one launch per layer and direction where the batch reaches it: product and scan apart below."""
+    L = len(sizes) - 1
+    kw = dict(adapt_decay=(0.9,) * (L - 1), adapt_step=(0.2,) * (L - 1)) if adaptive else {}
+    wl = workloads.Workload(name="min-batch", index=38, T=T, B=B, sizes=sizes, recurrent=(False,) * (L - 1), beta=(0.9,) * L,
+                            theta=1.0, surrogate="superspike", slope=10.0, precision="bf16", rate_lo=0.1, rate_hi=0.2, **kw)
+    for least, apart in ((0, 0), (B, 0), (B + 1, 1)):
+        assert_launches(wl, {"layer_min_batch": least, "layer_reverse": reverse},
+                        {("current_gemm", 1): apart, ("current_gemm", 2): apart, ("input_grad", 2): apart})
+
+
 # ---------------------------------------------------------------- feed-forward, fp32 products
 @pytest.mark.parametrize("gain", [1.0, 3.0])
 def test_tiny_ff_fp32(gain):
