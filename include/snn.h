@@ -203,7 +203,8 @@ typedef enum {
  *                     4 (default) and runs the readout scan, the loss and the readout's current
  *                     gradients (fp32 products too); layers of more than 128 neurons on rounded
  *                     weights, of any width, then also run on workgroups of two samples and 128
- *                     neurons where a rule on the sizes says so (LAYER_MAX_NEURONS = 1024)
+ *                     neurons where a rule on the sizes says so (LAYER_MAX_NEURONS = 1024, LAYER_NEURONS = 128,
+ *                     LAYER_TIME_SPLIT = 0)
  *   LAYER_PAIR        1 (default): two consecutive one-launch layers of at most 128 padded
  *                     neurons share a launch (layers of up to 64 with their like where there is a
  *                     choice), and so do two consecutive recurrent layers of at most 192 on rounded

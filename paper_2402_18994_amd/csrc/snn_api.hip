@@ -1146,7 +1146,9 @@ int launch_layer_forward(snn_ctx *c, int l, int nl, int with_readout, const int3
 
 // Whether a layer runs on the kernel for wide layers (wide_rules.hpp).
 bool forward_wide(snn_ctx *c, int l) {
-  if (l < 0 || l > c->L - 2 || layer_fuse_mode(c) < 4 || c->opt[SNN_OPT_LAYER_MAX_NEURONS] < 1024 || c->B < layer_min_batch(c)) return false;
+  if (l < 0 || l > c->L - 2 || c->B < layer_min_batch(c) ||
+      !forward_wide_allowed(layer_fuse_mode(c), layer_max_neurons(c), c->opt[SNN_OPT_LAYER_NEURONS], c->opt[SNN_OPT_LAYER_TIME_SPLIT]))
+    return false;
   const Layer &y = c->layers[l];
   const SpikeSrc s = spikes_below(c, l);
   return c->nplanes == 1 && y.spiking && !y.recurrent && !y.adaptive && y.ld > 128 && s.ld % 4 == 0 && !(l == 0 && c->x_direct) &&

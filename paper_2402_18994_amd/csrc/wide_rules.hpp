@@ -39,6 +39,10 @@ inline bool reverse_wide_pays(int T, int B, int ld, int columns, bool adaptive) 
 // and half a us per 64 inputs for each block of 128 steps, 256 workgroups at a time; 1.25 per GFLOP (0.75 where the currents
 // stream past the caches) and 5 TB/s of currents for the product, 9 bytes at 6 TB/s or 43 ns a step for the scan.  700-2048-2048-10:
 // T = 128, B = 32 / 64 / 255 362 280 / 566 474 / 1764 1525, T = 500, B = 128 3658 3092, T = 500, B = 16 621 614, T = 1000, B = 8 701 804.
+// Whether a context's options leave it a choice: 64 neurons or two workgroups to a sample ask for the kernel that has them.
+inline bool forward_wide_allowed(int layer_forward, int layer_max_neurons, int layer_neurons, int layer_time_split) {
+  return layer_forward >= 4 && layer_max_neurons >= 1024 && layer_neurons == 128 && !layer_time_split;
+}
 // `one_launch`: the layer would run as one launch of that kernel; `top_scan`: as a scan that forms the readout's currents;
 // `streams`: its currents stream past the caches.
 inline bool forward_wide_pays(int T, int B, int ld, int fan_in, bool one_launch, bool top_scan, bool streams) {

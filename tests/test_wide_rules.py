@@ -3,6 +3,8 @@ compiler (no GPU), against bench.py's account of the same."""
 import random
 import subprocess
 
+import pytest
+
 import bench
 import workloads
 from tests.helpers import host_program
@@ -43,3 +45,13 @@ def test_bench_accounts_for_wide_layers_as_the_library_decides():
         assert bench.reverse_wide(wl, l) == (reverse and (above > 128 or adaptive)), (wl, l)
         seen.add((forward, reverse, adaptive))
     assert len(seen) == 8
+
+
+@pytest.mark.parametrize("layer_forward,max_neurons,neurons,time_split", [(4, 1024, 128, 0), (3, 1024, 128, 0), (4, 960, 128, 0), (4, 1024, 64, 0),
+                                                                          (4, 1024, 128, 1)])
+def test_options_that_ask_for_another_forward_kernel_are_heard(layer_forward, max_neurons, neurons, time_split):
+    program = host_program('#include "wide_rules.hpp"\n#include <cstdio>\n#include <cstdlib>\nint main(int, char **v) {'
+                           ' printf("%d", (int)snn::forward_wide_allowed(atoi(v[1]), atoi(v[2]), atoi(v[3]), atoi(v[4]))); }')
+    options = (layer_forward, max_neurons, neurons, time_split)
+    out = subprocess.run([program] + list(map(str, options)), check=True, capture_output=True, text=True).stdout
+    assert out == str(int(options == (4, 1024, 128, 0)))
