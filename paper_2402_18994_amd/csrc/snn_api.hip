@@ -824,7 +824,7 @@ bool reverse_wide(const snn_ctx *c, int l) {
   if (!c->opt[SNN_OPT_LAYER_REVERSE] || l < 0 || l > c->L - 2 || c->B < layer_min_batch(c)) return false;
   const Layer &y = c->layers[l];
   const int columns = columns_above(c, l);
-  if (!c->hl || !y.spiking || y.recurrent || (!y.adaptive && columns <= 128)) return false;
+  if (!c->hl || !y.spiking || y.recurrent || (columns <= 128 && !(y.adaptive && c->opt[SNN_OPT_TOP_SCANS]))) return false;
   return c->opt[SNN_OPT_LAYER_REVERSE] == 2 || reverse_wide_pays(c->T, c->B, y.ld, columns, y.adaptive);
 }
 // A feed-forward spiking layer below at most 128 padded columns (the readout, or a narrow spiking

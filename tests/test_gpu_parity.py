@@ -202,6 +202,16 @@ def test_smallest_batch_of_the_one_launch_layers_holds_for_wide_ones(T, B, sizes
                         {("current_gemm", 1): apart, ("current_gemm", 2): apart, ("input_grad", 2): apart})
 
 
+def test_adaptive_layers_below_few_columns_heed_top_scans():
+    """TOP_SCANS = 0: below at most 128 columns the product that gives dS is a launch of its own, also for adaptive layers."""
+    wl = workloads.Workload(name="top-scans", index=39, T=50, B=6, sizes=(60, 200, 300, 96, 10), recurrent=(False,) * 3, beta=(0.9,) * 4,
+                            theta=1.0, surrogate="superspike", slope=10.0, precision="bf16", rate_lo=0.1, rate_hi=0.2,
+                            adapt_decay=(0.9,) * 3, adapt_step=(0.2,) * 3)
+    for top_scans in (0, 1):
+        assert_launches(wl, {"layer_reverse": 2, "top_scans": top_scans},
+                        {("input_grad", 2): 0, ("input_grad", 3): 1 - top_scans, ("input_grad", 4): 1 - top_scans})
+
+
 # ---------------------------------------------------------------- feed-forward, fp32 products
 @pytest.mark.parametrize("gain", [1.0, 3.0])
 def test_tiny_ff_fp32(gain):
