@@ -1466,26 +1466,44 @@ def test_single_steps_on_oracle_tensors():
     snn.destroy()
 
 
-UNSTORED = [("fp32", (70, 150, 66, 10), (False, False), False), ("bf16", (72, 130, 66, 10), (False, False), True),
-            ("bf16", (70, 72, 121, 10), (True, True), False), ("bf16", (300, 96, 40, 10), (False, False), "adaptive")]
+UNSTORED = [("fp32", (70, 150, 66, 10), (False, False), ""), ("bf16", (72, 130, 66, 10), (False, False), "packed"),
+            ("bf16", (70, 72, 121, 10), (True, True), ""), ("bf16", (300, 96, 40, 10), (False, False), "adaptive"),
+            ("bf16", (70, 150, 200, 10), (False, False), "one reverse launch"),
+            ("bf16", (300, 150, 200, 10), (False, False), "adaptive, one reverse launch"),
+            ("bf16", (60, 1100, 1040, 10), (False, False), "large")]
+UNSTORED_IDS = ["fp32", "ragged-packed", "recurrent-pair", "adaptive", "below-wide", "adaptive-in-one-launch", "pairs-of-samples"]
 
 
 def unstored_workload(precision, sizes, recurrent, kind):
-    """A network whose passes leave currents or spike gradients of some layers out of memory, and whether its raster
-    comes packed along time."""
-    adaptive = dict(adapt_decay=(0.9, 0.8), adapt_step=(0.3, 0.2)) if kind == "adaptive" else {}
-    wl = workloads.Workload(name="unstored", index=30, T=37, B=8, sizes=sizes, recurrent=recurrent, beta=(0.9, 0.93, 0.95),
+    """A network whose passes leave currents or spike gradients of some layers out of memory, its options, and whether its
+    raster comes packed along time.  "large": at 128 samples of 100 steps both layers run in one launch forward, layer 1 in reverse too."""
+    adaptive = dict(adapt_decay=(0.9, 0.8), adapt_step=(0.3, 0.2)) if "adaptive" in kind else {}
+    T, B = (100, 128) if kind == "large" else (37, 8)
+    wl = workloads.Workload(name="unstored", index=30, T=T, B=B, sizes=sizes, recurrent=recurrent, beta=(0.9, 0.93, 0.95),
                             theta=1.0, surrogate="superspike", slope=10.0, precision=precision, rate_lo=0.1, rate_hi=0.3, **adaptive)
-    return wl, kind is True
+    return wl, {"layer_reverse": 2} if "one reverse launch" in kind else {}, kind == "packed"
 
 
-@pytest.mark.parametrize("precision,sizes,recurrent,kind", UNSTORED, ids=["fp32", "ragged-packed", "recurrent-pair", "adaptive"])
+@pytest.mark.parametrize("kind,sizes", [(u[3], u[1]) for u in UNSTORED[4:]], ids=UNSTORED_IDS[4:])
+def test_launches_of_the_wide_passes_that_store_nothing_between(kind, sizes):
+    """The last of UNSTORED take the launches they are there for: dS of layer 1, and of an adaptive layer 2, in the reverse
+    launches; currents of layers above 1024 neurons in the forward ones."""
+    wl, options, _ = unstored_workload("bf16", sizes, (False, False), kind)
+    wanted = {("input_grad", 2): 0}
+    if kind != "one reverse launch":
+        wanted["input_grad", 3] = int(kind == "large")
+    if kind == "large":
+        wanted.update({("current_gemm", 1): 0, ("current_gemm", 2): 0})
+    assert_launches(wl, options, wanted)
+
+
+@pytest.mark.parametrize("precision,sizes,recurrent,kind", UNSTORED, ids=UNSTORED_IDS)
 def test_single_steps_after_a_pass_that_stored_nothing_between(precision, sizes, recurrent, kind):
     """The scans alone, right after passes whose launches kept currents and spike gradients to themselves:
     a step finds its inputs as if they had been stored, and gives the states and gradients of the pass again."""
-    wl, packed = unstored_workload(precision, sizes, recurrent, kind)
+    wl, options, packed = unstored_workload(precision, sizes, recurrent, kind)
     inp = workloads.generate(wl, w_gain=2.0)
-    snn = make(wl, inp)
+    snn = make(wl, inp, options)
     if packed:
         snn.forward_packed(np.packbits(inp.X, axis=0), inp.labels)
     else:
@@ -1504,17 +1522,17 @@ def test_single_steps_after_a_pass_that_stored_nothing_between(precision, sizes,
     snn.destroy()
 
 
-@pytest.mark.parametrize("precision,sizes,recurrent,kind", UNSTORED, ids=["fp32", "ragged-packed", "recurrent-pair", "adaptive"])
+@pytest.mark.parametrize("precision,sizes,recurrent,kind", UNSTORED, ids=UNSTORED_IDS)
 @pytest.mark.parametrize("defer", [1, 0])
 def test_tensors_of_a_pass_read_after_the_update(precision, sizes, recurrent, kind, defer):
     """Currents and spike gradients that the launches kept to themselves, asked for after snn_sgd_step: those of the
     pass, not of the updated weights; and reading them leaves weights and the next pass as they are."""
-    wl, packed = unstored_workload(precision, sizes, recurrent, kind)
+    wl, options, packed = unstored_workload(precision, sizes, recurrent, kind)
     inp = workloads.generate(wl, w_gain=2.0)
     names = [(n, l) for n in ("current", "d_spikes") for l in (1, 2)]
     out, after = [], []
     for read in ("before", "after", "after", "never"):
-        snn = make(wl, inp, {"defer_reduce": defer})
+        snn = make(wl, inp, {**options, "defer_reduce": defer})
         step = lambda: snn.forward_packed(np.packbits(inp.X, axis=0), inp.labels) if packed else snn.forward(inp.X, inp.labels)
         step()
         snn.backward()
