@@ -16,8 +16,9 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
 # translation unit -> flags of its own
 # (The speed of the short launches depends on where their code lies: the feed-forward step runs the same instructions
 # in, us at T = B = 128 / T = 128, B = 256 of 700-128-128-20: 65.1 / 76.9 where the linker puts them, 63.5 / 76.4 at
-# multiples of 1 KiB, 64.1 / 77.2 of 4 KiB, 64.0 / 77.1 of 64 KiB. The reverse launches at multiples of 4 KiB: T = 128, B = 256 77.0 us
-# against 77.7 at 1 KiB, with fp32-exact products 96.8 against 97.7, packed at T = 256 120.7 against 119.9.)
+# multiples of 1 KiB; multiples of 4 and 64 KiB are no better.  The reverse launches at multiples of 4 KiB for the step with
+# fp32-exact products alone: 104.8 us against 105.5 at 1 KiB, both builds in turn, twice; the others differ by no more than
+# two runs of one build, 0.2 %.)
 UNITS = {"snn_api.hip": ["-Xarch_device", "-falign-functions=1024"],
          "layer_forward.hip": ["-Xarch_device", "-falign-functions=1024"],
          "layer_forward_wide.hip": ["-Xarch_device", "-falign-functions=1024"],
