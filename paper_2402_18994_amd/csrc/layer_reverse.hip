@@ -3,22 +3,20 @@
 
 namespace snn {
 
-template <int KS, int SURR, int BN, bool F32, bool FULL, bool SLOTS = false>
+template <int KS, int SURR, bool F32, bool FULL, bool SLOTS = false>
 static hipError_t launch(hipStream_t st, const LayerReverseArgs &a) {
   const int groups = SLOTS ? (a.B + (64 >> a.slot_log2) - 1) >> (6 - a.slot_log2) : a.B;
-  const int grid = (groups + 7) / 8 * 8 * ((a.ld + BN - 1) / BN);
-  hipLaunchKernelGGL((lif_layer_reverse_kernel<KS, SURR, BN, F32, FULL, SLOTS>), dim3((unsigned)grid), dim3(256), 0, st, a);
+  const int grid = (groups + 7) / 8 * 8 * ((a.ld + 63) / 64);
+  hipLaunchKernelGGL((lif_layer_reverse_kernel<KS, SURR, F32, FULL, SLOTS>), dim3((unsigned)grid), dim3(256), 0, st, a);
   return hipGetLastError();
 }
 
-// 64 neurons per workgroup (two or three workgroups share a compute unit and overlap each other's
-// phases): 99.8 us per step at 700-128-128-20 against 104.8 with 128 neurons.
 template <int KS, int SURR>
 static hipError_t launch_columns(hipStream_t st, const LayerReverseArgs &a, bool f32) {
-  if (a.slot_log2 < 6) return f32 ? launch<KS, SURR, 64, true, false, true>(st, a) : launch<KS, SURR, 64, false, false, true>(st, a);
+  if (a.slot_log2 < 6) return f32 ? launch<KS, SURR, true, false, true>(st, a) : launch<KS, SURR, false, false, true>(st, a);
   const bool full = a.ld % 64 == 0;
-  if (f32) return full ? launch<KS, SURR, 64, true, true>(st, a) : launch<KS, SURR, 64, true, false>(st, a);
-  return full ? launch<KS, SURR, 64, false, true>(st, a) : launch<KS, SURR, 64, false, false>(st, a);
+  if (f32) return full ? launch<KS, SURR, true, true>(st, a) : launch<KS, SURR, true, false>(st, a);
+  return full ? launch<KS, SURR, false, true>(st, a) : launch<KS, SURR, false, false>(st, a);
 }
 
 template <int SURR>

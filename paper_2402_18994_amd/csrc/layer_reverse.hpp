@@ -7,19 +7,19 @@
 // lif_reverse_top_kernel does the same with one wavefront per 64 chains, each lane walking
 // its chain through global memory: per step a load, a store and a share of the dX fetches,
 // which is what bounds it (a wavefront issues a memory instruction about every 60 cycles).
-// Here a workgroup owns one sample and BN = 64 neurons (128 also builds; measured slower: one
-// workgroup per compute unit, nothing overlaps its phases), and per block of 64 steps, last
-// block first:
-//   1. V (64 x BN) and dX (64 x ldc words) arrive through 16-byte loads issued one block
+// Here a workgroup owns one sample and 64 neurons (two or three workgroups share a compute unit and
+// overlap each other's phases: 99.8 us per step at 700-128-128-20 against 104.8 with 128 neurons), and
+// per block of 64 steps, last block first:
+//   1. V (64 x 64) and dX (64 x ldc words) arrive through 16-byte loads issued one block
 //      ahead (they land during the previous block's scan) and go to LDS;
-//   2. dS: 32x32x16 bfloat16 MFMAs, the rounded weights of the wavefront's BN/2 neurons resident
+//   2. dS: 32x32x16 bfloat16 MFMAs, the rounded weights of the wavefront's 32 neurons resident
 //      in registers, the hi and lo halves of dX as the second operand, lo first; a wavefront
-//      holds 32 steps x BN/2 neurons of the result;
+//      holds 32 steps x 32 neurons of the result;
 //   3. still in the MFMA layout, every lane turns its elements into the two coefficients of
 //      the step: with s = surr(V - theta), g' = beta g + s (dS - theta g) = c1 g + c2,
 //      c1 = beta - s theta, c2 = s dS.  The surrogate (a division or an exponential) is
 //      computed here by all four wavefronts, not inside the sequential scan;
-//   4. scan: BN/64 wavefronts, one neuron per lane, 64 steps of one fused multiply-add each on
+//   4. scan: one wavefront, a neuron per lane, 64 steps of one fused multiply-add each on
 //      LDS (coefficients read 8 steps ahead, g written back in place of c2);
 //   5. store: all wavefronts pack g into hi/lo words and write whole rows, 16 bytes per lane.
 // SLOTS (at most 32 steps, one block): the block's rows are 64 / SL samples in slots of SL = 16 or 32 steps, a
@@ -54,11 +54,9 @@ struct LayerReverseArgs {
 };
 hipError_t layer_reverse(hipStream_t st, const LayerReverseArgs &a, int surrogate, bool f32);
 
-template <int KS, int SURR, int BN, bool F32 = false, bool FULL = true, bool SLOTS = false>
-__global__ __launch_bounds__(256, BN == 64 ? 2 : 1) void lif_layer_reverse_kernel(const LayerReverseArgs a) {
-  static_assert(BN == 64 || BN == 128, "neurons per workgroup");
-  constexpr int BM = 64;
-  constexpr int NJ = BN / 64;                         // 32-neuron MFMA tiles per wavefront
+template <int KS, int SURR, bool F32 = false, bool FULL = true, bool SLOTS = false>
+__global__ __launch_bounds__(256, 2) void lif_layer_reverse_kernel(const LayerReverseArgs a) {
+  constexpr int BM = 64, BN = 64;                     // steps of a block, neurons
   constexpr int NV = BN / 16;                         // 16-byte accesses per thread to a 64 x BN fp32 tile
   constexpr int LPR = BN / 4;                         // lanes per row in those accesses
   constexpr int CP = BN * 4 + 16;                     // bytes between time rows of the fp32 tiles
@@ -68,7 +66,7 @@ __global__ __launch_bounds__(256, BN == 64 ? 2 : 1) void lif_layer_reverse_kerne
   constexpr int TILE = BM * CP;
   constexpr int KK = 2 * KS;                          // 16-wide MFMA steps over the columns above
   constexpr int LDS_BYTES = TILE + (XT > 2 * TILE ? XT : 2 * TILE);   // the dX tile shares the space of the coefficient tiles
-  static_assert(BN == 128 || LDS_BYTES <= 80 * 1024, "two workgroups per compute unit");
+  static_assert(LDS_BYTES <= 80 * 1024, "two workgroups per compute unit");
   __shared__ __attribute__((aligned(16))) char lds[LDS_BYTES];
   __shared__ __attribute__((aligned(16))) float betas[BN];
   char *const Vt = lds, *const C1 = lds + TILE, *const C2 = lds + 2 * TILE, *const Xt = C1;
@@ -79,7 +77,7 @@ __global__ __launch_bounds__(256, BN == 64 ? 2 : 1) void lif_layer_reverse_kerne
   const int sl2 = SLOTS ? a.slot_log2 : 6;
   const int b = ((blockIdx.x >> 3) / parts * 8 + (blockIdx.x & 7)) << (6 - sl2);   // the first sample
   if (b >= a.B) return;
-  static_assert(!SLOTS || (BN == 64 && !FULL), "slots: one block of 64 rows");
+  static_assert(!SLOTS || !FULL, "slots: any width");
   const int n0 = part * BN;
   // row of the block at t0: its step and sample, and whether they exist
   auto step = [&](int t0, int row) { return SLOTS ? row & ((1 << sl2) - 1) : t0 + row; };
@@ -93,7 +91,7 @@ __global__ __launch_bounds__(256, BN == 64 ? 2 : 1) void lif_layer_reverse_kerne
   const rsrc_t rX = make_rsrc(a.dX, (unsigned)a.T * a.B * a.ldc * 4u), rW = make_rsrc(a.Wq, a.wq_bytes);
   if (tid < BN) betas[tid] = FULL || n0 + tid < a.ld ? a.beta_v[n0 + tid] : 0.f;
 
-  // A block's global loads: V as 8 x 16 bytes per thread (row = 8 k + tid / 32), dX as KK x 16
+  // A block's global loads: V as NV x 16 bytes per thread, dX as KK x 16
   // bytes per thread over rows of 8 KS chunks (chunks beyond ldc read as zero).
   u32x4 xv[NV], xd[KK];
   auto fetch = [&](int t0) {                          // t0 < 0: nothing is read
@@ -143,20 +141,18 @@ __global__ __launch_bounds__(256, BN == 64 ? 2 : 1) void lif_layer_reverse_kerne
   // (F32 with 128 columns: the third plane, one of the six products, is fetched per block; resident it makes
   // registers spill, and each spill's reload waits for the next block's loads in flight)
   constexpr int NP = F32 ? 3 : 1, NRES = F32 && KS == 4 ? 2 : NP;
-  bf16x8 wf[NP][NJ][KK];
+  bf16x8 wf[NP][KK];
   auto weights = [&](int pl) {
 #pragma unroll
-    for (int j = 0; j < NJ; ++j)
-#pragma unroll
-      for (int kk = 0; kk < KK; ++kk) {
-        const int n = n0 + 32 * NJ * wn + 32 * j + (lane & 31), c = 16 * kk + 8 * h;
-        wf[pl][j][kk] = __builtin_bit_cast(bf16x8, ld_b128(rW, c + 7 < a.ldq ? (n * a.ldq + c) * 2 : OOB, pl * (int)a.wq_plane));
-      }
+    for (int kk = 0; kk < KK; ++kk) {
+      const int n = n0 + 32 * wn + (lane & 31), c = 16 * kk + 8 * h;
+      wf[pl][kk] = __builtin_bit_cast(bf16x8, ld_b128(rW, c + 7 < a.ldq ? (n * a.ldq + c) * 2 : OOB, pl * (int)a.wq_plane));
+    }
   };
 #pragma unroll
   for (int pl = 0; pl < NRES; ++pl) weights(pl);
 
-  float g = 0.f, db = 0.f;                            // state of neuron n0 + tid (wavefronts 0 and 1)
+  float g = 0.f, db = 0.f;                            // state of neuron n0 + tid (wavefront 0; SLOTS: n0 + lane)
 
   for (int blk = 0; t0 >= 0; t0 -= BM, ++blk) {
     fill();
@@ -166,11 +162,9 @@ __global__ __launch_bounds__(256, BN == 64 ? 2 : 1) void lif_layer_reverse_kerne
 
     // 2. dS^T tile: rows = neurons, columns = steps; the lane holds step 32 wm + (lane & 31)
     // and register r neuron 8 (r / 4) + 4 h + (r % 4) of its 32-neuron tile.
-    f32x16 acc[NJ];
+    f32x16 acc;
 #pragma unroll
-    for (int j = 0; j < NJ; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[j][r] = 0.f;
+    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
     if constexpr (F32) {
       // pieces p of dX and q of W with p + q < 3: every product above 2^-24
       const char *px = Xt + (32 * wm + (lane & 31)) * XP + 16 * h;
@@ -183,16 +177,13 @@ __global__ __launch_bounds__(256, BN == 64 ? 2 : 1) void lif_layer_reverse_kerne
         for (int s = 2; s >= 0; --s)
 #pragma unroll
           for (int pl = 0; pl <= s; ++pl)
-#pragma unroll
-            for (int j = 0; j < NJ; ++j)
-              if (s - pl < NRES) acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[s - pl][j][kk], xp[pl], acc[j], 0, 0, 0);
+            if (s - pl < NRES) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[s - pl][kk], xp[pl], acc, 0, 0, 0);
       }
       if constexpr (NRES < NP) {
 #pragma unroll
         for (int kk = 0; kk < KK; ++kk) {
           const bf16x8 xp = *(const bf16x8 *)(px + 32 * kk);
-#pragma unroll
-          for (int j = 0; j < NJ; ++j) acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[NRES][j][kk], xp, acc[j], 0, 0, 0);
+          acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[NRES][kk], xp, acc, 0, 0, 0);
         }
       }
     } else {
@@ -208,38 +199,33 @@ __global__ __launch_bounds__(256, BN == 64 ? 2 : 1) void lif_layer_reverse_kerne
         hh.w = __builtin_amdgcn_perm(j1.w, j1.z, 0x05040100u); ll.w = __builtin_amdgcn_perm(j1.w, j1.z, 0x07060302u);
         hi[kk] = __builtin_bit_cast(bf16x8, hh);
         const bf16x8 lo = __builtin_bit_cast(bf16x8, ll);
-#pragma unroll
-        for (int j = 0; j < NJ; ++j) acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[0][j][kk], lo, acc[j], 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[0][kk], lo, acc, 0, 0, 0);
       }
 #pragma unroll
-      for (int kk = 0; kk < KK; ++kk)
-#pragma unroll
-        for (int j = 0; j < NJ; ++j) acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[0][j][kk], hi[kk], acc[j], 0, 0, 0);
+      for (int kk = 0; kk < KK; ++kk) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[0][kk], hi[kk], acc, 0, 0, 0);
     }
     __syncthreads();                                  // every wavefront has read the dX tile: C1 takes its place
 
     // 3. coefficients
 #pragma unroll
-    for (int j = 0; j < NJ; ++j)
+    for (int q = 0; q < 4; ++q) {
+      const int t = 32 * wm + (lane & 31), n = 32 * wn + 8 * q + 4 * h;
+      const f32x4 vv = *(const f32x4 *)(Vt + t * CP + n * 4);
+      const f32x4 bb = *(const f32x4 *)(&betas[n]);
+      f32x4 c1, c2;
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int t = 32 * wm + (lane & 31), n = 32 * NJ * wn + 32 * j + 8 * q + 4 * h;
-        const f32x4 vv = *(const f32x4 *)(Vt + t * CP + n * 4);
-        const f32x4 bb = *(const f32x4 *)(&betas[n]);
-        f32x4 c1, c2;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const float s = surr_rcp<SURR>(slope, vv[e] - theta);
-          c1[e] = bb[e] - s * theta;
-          c2[e] = s * acc[j][4 * q + e];
-        }
-        *(f32x4 *)(C1 + t * CP + n * 4) = c1;
-        *(f32x4 *)(C2 + t * CP + n * 4) = c2;
+      for (int e = 0; e < 4; ++e) {
+        const float s = surr_rcp<SURR>(slope, vv[e] - theta);
+        c1[e] = bb[e] - s * theta;
+        c2[e] = s * acc[4 * q + e];
       }
+      *(f32x4 *)(C1 + t * CP + n * 4) = c1;
+      *(f32x4 *)(C2 + t * CP + n * 4) = c2;
+    }
     __syncthreads();
 
     // 4. scan, steps t0 + 63 down to t0: dI_t = g, then g <- c1 g + c2 (and db += g V_t)
-    const int scans = SLOTS ? 64 >> sl2 : BN / 64, slot = SLOTS ? wave : 0, rows = 1 << sl2;   // SLOTS: the wavefront's
+    const int scans = SLOTS ? 64 >> sl2 : 1, slot = SLOTS ? wave : 0, rows = 1 << sl2;   // SLOTS: the wavefront's
     if (wave < scans) {
       const int cell = SLOTS ? (slot << sl2) * CP + lane * 4 : tid * 4;
       const float *p1 = (const float *)(C1 + cell), *pv = (const float *)(Vt + cell);
@@ -276,7 +262,7 @@ __global__ __launch_bounds__(256, BN == 64 ? 2 : 1) void lif_layer_reverse_kerne
     }
     __syncthreads();
 
-    // 5. store: BN/4 lanes x 16 bytes per row
+    // 5. store: 16 lanes x 16 bytes per row
 #pragma unroll
     for (int k = 0; k < NV; ++k) {
       const int row = (256 / LPR) * k + tid / LPR, col = (tid % LPR) * 4, t = step(t0, row), s = sample(row);

@@ -10,7 +10,8 @@
 //      come from memory: two stages to land), the weights two (they stay in the L2): 80 KiB, so that two workgroups share
 //      a compute unit and one multiplies while the other scans.
 //   2. scan, 64 steps at a time: the wavefronts that hold these steps put them into LDS (the stages are free), and every
-//      thread walks its own neuron: V straight from memory 16 steps ahead, g' = beta g + s (dS - theta g), dI stored.
+//      thread walks its own neuron: V straight from memory 32 steps ahead (16 with its adaptation), g' = beta g + s (dS -
+//      theta g), dI stored.
 // The words are split into their bfloat16 planes after the fragment read, lo first; both meet the same weights.
 //
 // 700-512-512-20, T = B = 256: 84 us (product) + 69 (scan) -> 89, 80 of it what dX, V and dI take at 5 TB/s; 700-1024-1024-20, T = 256,

@@ -15,8 +15,9 @@ static bool sixteen(int B, int ld, bool three_planes_of_g = false) {
 }
 
 // Steps of 32 neurons of the contraction, each compiled: a step that multiplies nothing lies in the chain of every time step
-// all the same (even numbers only before; T = 200, B = 64, forward / reverse: 30 neurons 30.1 / 37.6 us -> 29.6 / 32.2, 90: 43.7 /
-// 57.0 -> 42.6 / 50.5, 130: 68.5 / 79.2 -> 62.5 / 70.0, 200: 87.5 / 99.9 -> 77.5 / 85.5, fp32 130: 137 / 159 -> 119 / 143).
+// all the same (T = 200, B = 64, forward / reverse, us with a step too many and with those it needs: 30 neurons 30.1 / 37.6 and 29.6 /
+// 32.2, 90: 43.7 / 57.0 and 42.6 / 50.5, 130: 68.5 / 79.2 and 62.5 / 70.0, 200: 87.5 / 99.9 and 77.5 / 85.5, fp32 130: 137 / 159 and
+// 119 / 143).
 static int tile_steps(int ld) { return (ld + 31) / 32; }
 
 hipError_t rlif_tile_forward(hipStream_t st, bool fp32, int T, int B, int ld, const float *I, float *V, uint8_t *S,

@@ -159,7 +159,7 @@ __global__ __launch_bounds__(KS * 64) void rlif_tile_reverse_kernel(const float 
   // products; at 129 to 192 neurons they stand under the fragment reads instead (T = 200, B = 64, 130 / 144 / 160 neurons:
   // 76.3 / 76.5 / 83.3 us behind, 77.9 / 78.1 / 78.4 so; 192, six steps of the contraction: 99.4 and 91.6; at 60 and 250
   // neurons behind is faster, 49.5 against 55.2 and 113 against 117).
-    constexpr bool EARLY = NP == 1 && SURR == 2 && (KS == 5 || KS == 6);
+  constexpr bool EARLY = NP == 1 && SURR == 2 && (KS == 5 || KS == 6);
   __shared__ __align__(16) char xs[2][GP][XB];
   const RlifLaneMasks L(threadIdx.x);
   const int b = blockIdx.x * G::CS + L.smp, row4 = B * ld * 4;
