@@ -16,9 +16,10 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
 # translation unit -> flags of its own
 # (The speed of the short launches depends on where their code lies: the feed-forward step runs the same instructions
 # in, us at T = B = 128 / T = 128, B = 256 of 700-128-128-20: 65.1 / 76.9 where the linker puts them, 63.5 / 76.4 at
-# multiples of 1 KiB; multiples of 4 and 64 KiB are no better.  The reverse launches at multiples of 4 KiB for the step with
-# fp32-exact products alone: 104.8 us against 105.5 at 1 KiB, both builds in turn, twice; the others differ by no more than
-# two runs of one build, 0.2 %.)
+# multiples of 1 KiB; multiples of 4 and 64 KiB are no better.  The reverse launches of narrow layers at multiples of 4 KiB against 1 KiB,
+# everything else the same, both builds in turn, twice: T = 128, B = 256 85.4, 85.9 and 85.8, 86.8, with fp32-exact products 104.1,
+# 103.6 and 104.3, 103.8, packed at T = 256 136.1, 136.1 and 138.2, 138.3.  These are properties of a build: a change elsewhere
+# that moves the kernels is worth as much, either way.)
 UNITS = {"snn_api.hip": ["-Xarch_device", "-falign-functions=1024"],
          "layer_forward.hip": ["-Xarch_device", "-falign-functions=1024"],
          "layer_forward_wide.hip": ["-Xarch_device", "-falign-functions=1024"],
