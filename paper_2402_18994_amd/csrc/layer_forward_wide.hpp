@@ -13,9 +13,9 @@
 //      at a time; the spikes of four steps are four compare masks, and lane 16 g + i stores neurons 4 i .. + 3 of step g.
 // The spike decision is the compare-free one of layer_forward.hpp.
 //
-// 700-512-512-20, T = B = 256: 82 + 70 -> 68 + 44 us for the two layers; 700-1024-1024-20, T = 256, B = 512: 300 + 347 -> 256 +
-// 284, the second one's 805 MB in 161 at 5 TB/s; the 2048 x 2048 layers of T = 512, B = 128: 522 (product) + 205 (scan) -> 458.  The
-// product alone takes 157 us of the 284 (1.75 PFLOP/s): what is left is that all compute units write at the same time.
+// 700-512-512-20, T = B = 256: 67 + 66 -> 66 + 44 us for the two layers; 700-1024-1024-20, T = 256, B = 512: 294 + 338 -> 250 +
+// 279, the second one's 805 MB in 161 at 5 TB/s; the 2048 x 2048 layers of T = 512, B = 128: 526 (product) + 210 (scan) -> 445.  The
+// product alone takes 157 us of the 279 (1.75 PFLOP/s): what is left is that all compute units write at the same time.
 #pragma once
 #include "gemm_stream.hpp"
 #include "layer_forward.hpp"

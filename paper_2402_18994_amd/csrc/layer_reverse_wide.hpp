@@ -14,8 +14,8 @@
 //      theta g), dI stored.
 // The words are split into their bfloat16 planes after the fragment read, lo first; both meet the same weights.
 //
-// 700-512-512-20, T = B = 256: 84 us (product) + 69 (scan) -> 89, 80 of it what dX, V and dI take at 5 TB/s; 700-1024-1024-20, T = 256,
-// B = 512: 575 + 270 -> 680, where 128 steps of a sample lie in 128 different pages of 2 MiB (with the rows of a sample side by
+// 700-512-512-20, T = B = 256: 87 us (product) + 65 (scan) -> 90, 80 of it what dX, V and dI take at 5 TB/s; 700-1024-1024-20, T = 256,
+// B = 512: 537 + 267 -> 675, where 128 steps of a sample lie in 128 different pages of 2 MiB (with the rows of a sample side by
 // side the launch takes 557).  Potentials 32 steps ahead of the scan instead of 16: 96 -> 89 and 698 -> 680; 64 steps spill.  No
 // difference: the walk through the contraction starting elsewhere in each sample, priorities or a delay between the two
 // workgroups of a compute unit.

@@ -122,9 +122,9 @@ inline int wgrad_flat_tiles(const WgradProduct &p) { return ((p.rows + 127) / 12
 // Splits of tall tiles: any count, for the workgroups of an XCD (32 compute units; each product's workgroups are dealt
 // evenly over the XCDs) to take the fewest rounds for their length, 18 ns a row and 5 us a round, with the partial sums.  A long and narrow product beside them has splits of its own (see
 // long_and_narrow) that come to about one workgroup for every compute unit, whatever its height: a round in front of
-// the others', the same for each count.  The launch alone, us, * the choice: 700-512-512-20, T*B = 65536: 8 splits 162, 9 152, 10 143, 11 137*,
-// 12 221, 16 175, 23 144; 700-1024-1024-20, 131072: 4 727, 8 719, 9 698*; 700-256-256-20, 65536: 16 88, 24 69, 26 65, 28 64*,
-// 32 94; 300-1024-20, 65536: 8 153, 10 130, 12 121*, 14 185.
+// the others', the same for each count.  The launch alone in one sweep, us, * the choice: 700-512-512-20, T*B = 65536: 8 splits 165, 9 155, 10 146,
+// 11 140*, 12 224, 16 178, 23 147; 700-1024-1024-20, 131072: 4 730, 8 722, 9 701*; 700-256-256-20, 65536: 16 91, 24 72, 26 68, 28
+// 67*, 32 97; 300-1024-20, 65536: 8 156, 10 133, 12 124*, 14 188.
 inline long long tall_slots(const WgradLaunch &w, int splits) {
   long long slots = 0;                                   // workgroups of an XCD
   for (const WgradProduct &p : w.products) slots += ((long long)wgrad_tall_tiles(p) * splits + 7) / 8;

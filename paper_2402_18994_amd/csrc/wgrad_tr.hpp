@@ -32,8 +32,9 @@
 // Tall tiles, 256 rows k (TI = 4): what bounds large products on 128 x 128 tiles is the ingest of the operands, 20 KiB for
 // 512 cycles of MFMA where the L2 gives a compute unit about 29 bytes a cycle, and the LDS reads, 640 bytes per MFMA.  A
 // wavefront of 128 x 64 (16 accumulator tiles, 256 registers; one workgroup per compute unit) asks for 24 KiB per 1024
-// cycles and reads 384 bytes per MFMA.  The launch of 700-1024-1024-20 at T*B = 131072: 854 -> 665 us (1.4 PFLOP/s with both
-// passes); 700-2048(rec)-2048-2048-20, 65536: 3504 -> 2330; 700-512-512-20, 65536: 155 -> 131.  When: wgrad_tall_pays.
+// cycles and reads 384 bytes per MFMA.  The launch of 700-1024-1024-20 at T*B = 131072: 836 -> 623 us (1.5 PFLOP/s with both
+// passes); 700-2048(rec)-2048-2048-20, 65536: 3560 -> 2370, of which the update, now of four splits, takes 84 back; 700-512-512-20,
+// 65536: 159 -> 131.  When: wgrad_tall_pays.
 #pragma once
 #include "gemm_stream.hpp"
 

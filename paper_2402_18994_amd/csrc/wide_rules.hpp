@@ -12,11 +12,13 @@ namespace snn {
 // 535 and 467; 700-1024-1024-20, T = 256, B = 512 2488 and 2260; 200-256-256-20, B = 256: T = 50 85.6 84.5, 70 95.8 91.2, 128 120 108,
 // 140 (a second block of 12) 142 133, T = 500, B = 64 170 186; 200-512-512-20: T = 128, B = 32 / 64 / 256 85.1 89.2 / 98.5 96.5 / 258 226, T =
 // 256, B = 32 / 64 126 137 / 150 149, T = 200, B = 128 222 181; 100-300-1000-20, T = 256, B = 64 188 196, T = 500, B = 128 677 657; 100-2048-2048-10, T =
-// 128, B = 32 / 64 / 256 342 309 / 525 477 / 1592 1559, T = 50, B = 256 802 888.  Over 112 such cases nothing it takes is slower.
+// 128, B = 32 / 64 / 256 342 309 / 525 477 / 1592 1559, T = 50, B = 256 802 888.  Of 70 networks drawn at
+// random where it takes the one launch two are more than 0.6 % slower with it (700-1280-640-20, T = 89, B = 51 165 169, 2.5 %; 1.0 %), the median is 7 %
+// faster.
 // Adaptive thresholds, below any layer (a scan takes 16 bytes and 62 ns; 12 us a block): 700-256-256-20, T = B = 128 127.2
 // 121.9; 700-256-20: T = 128, B = 64 / 128 / 256 61.0 63.1 / 75.7 72.8 / 115 101, T = 200, B = 128 102.4 102.7; 700-100-20, T = 128, B =
 // 128 / 256 59.8 62.0 / 74.8 73.3; 200-1000-20, T = 100, B = 32 74.4 72.5, T = B = 128 184 138; 700-512-512-20, T = 64, B = 16 81.9
-// 92.8, T = 300, B = 256 883 790.  Of 60 such cases nothing it takes is slower.
+// 92.8, T = 300, B = 256 883 790.  Of 70 drawn networks that it takes none is more than 0.5 % slower.
 // `ld`: the layer's padded neurons; `columns`: those of the layer above.
 inline bool reverse_wide_pays(int T, int B, int ld, int columns, bool adaptive) {
   const double M = (double)T * B, N = ld;
@@ -38,7 +40,8 @@ inline bool reverse_wide_pays(int T, int B, int ld, int columns, bool adaptive) 
 // Against product and scan apart (above 1024 neurons or inputs) by a model of both, us, with 10 % in favour of those: 10.5
 // and half a us per 64 inputs for each block of 128 steps, 256 workgroups at a time; 1.25 per GFLOP (0.75 where the currents
 // stream past the caches) and 5 TB/s of currents for the product, 9 bytes at 6 TB/s or 43 ns a step for the scan.  700-2048-2048-10:
-// T = 128, B = 32 / 64 / 255 362 280 / 566 474 / 1764 1525, T = 500, B = 128 3658 3092, T = 500, B = 16 621 614, T = 1000, B = 8 701 804.
+// T = 128, B = 32 / 64 / 255 362 280 / 566 474 / 1764 1525, T = 500, B = 128 3658 3092, T = 500, B = 16 621 614, T = 1000, B = 8 701 804.  Of 70
+// drawn networks that either rule takes one is slower (623-640-640-10, T = 125, B = 254 342 347, 1.5 %).
 // Whether a context's options leave it a choice: 64 neurons or two workgroups to a sample ask for the kernel that has them.
 inline bool forward_wide_allowed(int layer_forward, int layer_max_neurons, int layer_neurons, int layer_time_split) {
   return layer_forward >= 4 && layer_max_neurons >= 1024 && layer_neurons == 128 && !layer_time_split;
