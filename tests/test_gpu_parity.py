@@ -480,8 +480,9 @@ def test_weight_gradients_through_transposing_reads(T, B, sizes, rec, packed):
                                                           (128, 129, (260, 1000, 600, 10), (True, False), False, 3),
                                                           (250, 264, (700, 512, 512, 20), (False, False), False, 11),
                                                           (33, 65, (300, 2040, 1500, 20), (False, False), False, 1),
+                                                          (13, 40, (300, 1400, 1300, 20), (False, False), False, 1),
                                                           (192, 512, (64, 520, 1024, 20), (False, False), False, 17)],
-                         ids=["several-splits", "packed-ragged", "recurrent", "eleven-splits", "one-split", "long-narrow-beside"])
+                         ids=["several-splits", "packed-ragged", "recurrent", "eleven-splits", "one-split", "few-rows", "long-narrow-beside"])
 def test_weight_gradients_on_tall_tiles(T, B, sizes, rec, packed, splits):
     """Products large enough for tiles of 256 x 128 (by the library's rule, asked on the host): rows, columns and contraction
     tails that fill no tile, split counts that are no multiple of eight, one split, a packed layer-1 job (multiples of 4
